@@ -19,7 +19,7 @@
 // always has a non-empty softmax.  Wavefronts whose 32 queries are all padding skip their work:
 // hidden states at padded positions are unspecified by contract.
 //
-// float32 path: plain per-query loops for the validation mode, any head width.
+// float32 path: the validation mode, any head width.
 #include <type_traits>
 
 #include "kernels.h"
@@ -255,7 +255,122 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     }
 }
 
-// float32 validation path.  One workgroup per (problem, sequence, head); each wavefront takes queries
+// float32 validation path, head widths 32 and 64, on the matrix cores (v_mfma_f32_32x32x2_f32: float32 products and sums).  One
+// workgroup per (problem, sequence, head, 32 queries); wavefront w takes the 32-key blocks w, w + 4, ... with an online softmax of
+// its own, and the four are merged at the end.  Operands go straight from global memory to registers (a wavefront uses a key
+// block once).  As in the bf16 kernel the scores are computed transposed: a lane holds, for its query, keys 8 g + 4 half + i, which is
+// the operand layout of the product with the values when MFMA (g, i) takes key 8 g + i from the lower and 8 g + 4 + i from the upper half.
+// A block is 8 us of chained loads and 64-clock instructions at any size; what made the loop over queries and lanes slow (744 us a
+// launch for 8 sequences of up to 128 tokens, now 13) were its serial dot products on 96 workgroups.
+template <int D>
+__global__ __launch_bounds__(256) void attention_f32_mfma_kernel(AttnGroup g, const int32_t* __restrict__ mask,
+                                                                 const int32_t* __restrict__ seq_start,
+                                                                 const int32_t* __restrict__ seq_len, int B, int Smax, int H, float scale)
+{
+    constexpr int DT = D / 32, NE = DT * 16;
+    __shared__ float s_o[4][NE][64];
+    __shared__ float s_m[4][64], s_l[4][64];
+    const int grp = blockIdx.z / B, b = blockIdx.z % B, a = blockIdx.y;
+    const int row0 = seq_start ? seq_start[b] : b * Smax;
+    const int S = seq_len ? min(seq_len[b], Smax) : Smax;
+    const int q0 = blockIdx.x * 32;
+    if (q0 >= S) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+    const size_t ld = (size_t)3 * H;
+    const float* __restrict__ qkv = static_cast<const float*>(g.qkv[grp]) + (size_t)row0 * ld + a * D;
+    const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * Smax : nullptr;
+    f32x4 qf[D / 8];
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) qf[c] = *reinterpret_cast<const f32x4*>(qkv + (size_t)min(q0 + l32, S - 1) * ld + c * 8 + half * 4);
+    f32x16 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    for (int kb = wave * 32; kb < S; kb += 128) {
+        f32x4 kf[D / 8];
+        float vf[DT][16];
+        const float* krow = qkv + (size_t)min(kb + l32, S - 1) * ld + H + half * 4;
+#pragma unroll
+        for (int c = 0; c < D / 8; ++c) kf[c] = *reinterpret_cast<const f32x4*>(krow + c * 8);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float* vrow = qkv + (size_t)min(kb + (e >> 2) * 8 + half * 4 + (e & 3), S - 1) * ld + 2 * H + l32;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) vf[dt][e] = vrow[dt * 32];
+        }
+        f32x16 sc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+        for (int c = 0; c < D / 8; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][i], qf[c][i], sc, 0, 0, 0);
+        float mloc = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int key = kb + (e >> 2) * 8 + half * 4 + (e & 3);
+            float t = sc[e] * scale;
+            if (mrow && key < S && mrow[key] == 0) t += kMaskedScore;
+            t = key < S ? t : -INFINITY;
+            sc[e] = t;
+            mloc = fmaxf(mloc, t);
+        }
+        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));            // finite: the block's first key exists
+        const float m_new = fmaxf(m_run, mloc);
+        const float alpha = expf(m_run - m_new);
+        float lsum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            sc[e] = expf(sc[e] - m_new);
+            lsum += sc[e];
+        }
+        l_run = l_run * alpha + lsum + __shfl_xor(lsum, 32, 64);
+        m_run = m_new;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[dt][e], sc[e], o[dt], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s_o[wave][dt * 16 + e][lane] = o[dt][e];
+    s_m[wave][lane] = m_run;
+    s_l[wave][lane] = l_run;
+    __syncthreads();
+    // wavefront w merges columns NE/4 w .. of the lane's query: quads of four consecutive head columns
+    float m = s_m[0][lane], l = 0.f, f[4];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m = fmaxf(m, s_m[w][lane]);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        f[w] = expf(s_m[w][lane] - m);                           // a wavefront without keys has m = -inf: 0
+        l += f[w] * s_l[w][lane];
+    }
+    const float inv = 1.0f / l;
+    if (q0 + l32 >= S) return;
+    float* out = static_cast<float*>(g.ctx[grp]) + ((size_t)row0 + q0 + l32) * H + a * D + half * 4;
+#pragma unroll
+    for (int k = 0; k < NE / 16; ++k) {
+        const int e0 = (wave * (NE / 16) + k) * 4;
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) t = fmaf(f[w], s_o[w][e0 + i][lane], t);
+            v[i] = t * inv;
+        }
+        *reinterpret_cast<f32x4*>(out + (e0 >> 4) * 32 + ((e0 & 15) >> 2) * 8) = v;
+    }
+}
+
+// Other head widths.  One workgroup per (problem, sequence, head); each wavefront takes queries
 // wave, wave+4, ...; lanes run over keys for the scores and over head columns for the context.
 __global__ __launch_bounds__(256) void attention_f32_kernel(AttnGroup g, const int32_t* __restrict__ mask,
                                                             const int32_t* __restrict__ seq_start,
@@ -523,6 +638,13 @@ hipError_t launch_attention_f32(const AttnGroup& g, int G, const int32_t* mask, 
     if (G > kMaxGroup || (size_t)S * 16 > 64 * 1024) return hipErrorInvalidValue;
     dim3 grid(1, A, B * G), block(256);
     const float scale = 1.0f / sqrtf((float)(H / A));
+    const int d = H / A;
+    if (H % A == 0 && (d == 32 || d == 64)) {
+        dim3 tiles((S + 31) / 32, A, B * G);
+        if (d == 64) hipLaunchKernelGGL(attention_f32_mfma_kernel<64>, tiles, block, 0, stream, g, mask, seq_start, seq_len, B, S, H, scale);
+        else hipLaunchKernelGGL(attention_f32_mfma_kernel<32>, tiles, block, 0, stream, g, mask, seq_start, seq_len, B, S, H, scale);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(attention_f32_kernel, grid, block, (size_t)S * 4 * sizeof(float), stream, g, mask, seq_start, seq_len, B, S, H, A,
                        scale);
     return hipGetLastError();

@@ -65,8 +65,8 @@ hipError_t launch_gemm_skinny_bf16(const GemmGroup& g, const GemmShape& s, hipSt
 // mfma_rate_out_floats(n_cu) floats.  Synchronises on the stream.
 hipError_t run_mfma_rate(int iters, int n_cu, float* d_out, hipStream_t stream, float* tflops);
 int mfma_rate_out_floats(int n_cu);
-// fp32 (A) x {fp32|bf16} (W) on the vector ALUs, any shape.  w_bf16 selects the W element type.
-hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, int w_bf16, hipStream_t stream);
+// float32 operands, products and sums; any shape.
+hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t stream);
 
 // Token rows of a batch in padding-free order: only positions with mask == 1 are kept, sequence after
 // sequence, so every row-wise kernel and every contraction runs on sum_b len_b rows instead of B*S.

@@ -397,11 +397,11 @@ struct Launcher {
         if (first_err == hipSuccess && e != hipSuccess) first_err = e;
     }
 
-    void gemm(int klass, const GemmGroup& g, GemmShape s, bool force_f32_kernel)
+    void gemm(int klass, const GemmGroup& g, const GemmShape& s)
     {
         begin(klass);
-        if (m->bf16 && !force_f32_kernel) check(launch_gemm_bf16(g, s, st));
-        else check(launch_gemm_f32(g, s, m->bf16 ? 1 : 0, st));
+        if (m->bf16) check(launch_gemm_bf16(g, s, st));
+        else check(launch_gemm_f32(g, s, st));
         end();
     }
 };
@@ -470,7 +470,7 @@ void run_layer_group(Launcher& L, const std::vector<LayerIO>& io, const RowMap& 
         L.check(launch_gemm_fp8(g, s, L.st));
         L.end();
     } else {
-        L.gemm(MT_K_GEMM_QKV, g, s, false);
+        L.gemm(MT_K_GEMM_QKV, g, s);
     }
 
     // attention
@@ -523,7 +523,7 @@ void run_layer_group(Launcher& L, const std::vector<LayerIO>& io, const RowMap& 
         L.check(launch_gemm_fp8(g, s, L.st));
         L.end();
     } else {
-        L.gemm(MT_K_GEMM_OUT, g, s, false);
+        L.gemm(MT_K_GEMM_OUT, g, s);
     }
 
     LnGroup lg;
@@ -560,7 +560,7 @@ void run_layer_group(Launcher& L, const std::vector<LayerIO>& io, const RowMap& 
         L.check(launch_gemm_fp8(g, s, L.st));
         L.end();
     } else {
-        L.gemm(MT_K_GEMM_FFN1, g, s, false);
+        L.gemm(MT_K_GEMM_FFN1, g, s);
     }
 
     // FFN2 -> y (fp32 partial products), then LayerNorm(y + bias + residual) -> layer output
@@ -580,7 +580,7 @@ void run_layer_group(Launcher& L, const std::vector<LayerIO>& io, const RowMap& 
         L.check(launch_gemm_fp8(g, s, L.st));
         L.end();
     } else {
-        L.gemm(MT_K_GEMM_FFN2, g, s, false);
+        L.gemm(MT_K_GEMM_FFN2, g, s);
     }
 
     for (int i = 0; i < n; ++i) {
@@ -635,7 +635,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
             g.N[i] = 2 * H;
         }
         s = GemmShape{n, M, 2 * H, H, H, 3 * H, 0, ACT_NONE, bf ? 0 : 1, rm.n_rows, 1, 0};
-        L.gemm(MT_K_GEMM_QKV, g, s, false);
+        L.gemm(MT_K_GEMM_QKV, g, s);
 
     }
 
@@ -659,7 +659,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         g.N[i] = H;
     }
     s = GemmShape{n, B, H, H, H, H, 0, ACT_NONE, bf ? 0 : 1, nullptr, 1, 0};
-    L.gemm(MT_K_GEMM_FIRST, g, s, false);
+    L.gemm(MT_K_GEMM_FIRST, g, s);
 
     if (!kvfree) {
         AttnClsGroup ag;
@@ -694,7 +694,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         s.sub_a = d;
         s.sub_w = d;
         s.sub_c = H;
-        L.gemm(MT_K_GEMM_FIRST, g, s, false);
+        L.gemm(MT_K_GEMM_FIRST, g, s);
 
         for (int i = 0; i < n; ++i) {
             g.A[i] = io[i].in_a;
@@ -707,7 +707,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         s.sub_w = (int64_t)A_pad * H;
         s.d_sub_row0 = rm.seq_start;
         s.d_sub_rows = rm.seq_len;
-        L.gemm(MT_K_GEMM_FIRST, g, s, false);
+        L.gemm(MT_K_GEMM_FIRST, g, s);
 
         PoolGroup pg;
         memset(&pg, 0, sizeof pg);
@@ -733,7 +733,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         s.sub_w = (int64_t)d * H;
         s.sub_c = d;
         s.sub_bias = d;
-        L.gemm(MT_K_GEMM_FIRST, g, s, false);
+        L.gemm(MT_K_GEMM_FIRST, g, s);
     }
 
     // projection (split along K: only B rows, so the weight stream is what has to be spread), LayerNorm
@@ -753,7 +753,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         g.N[i] = H;
     }
     s = GemmShape{n, B, H, H, H, H, 0, ACT_NONE, 1, nullptr, sp_o, MBH};
-    L.gemm(MT_K_GEMM_FIRST, g, s, false);
+    L.gemm(MT_K_GEMM_FIRST, g, s);
 
     LnGroup lg;
     memset(&lg, 0, sizeof lg);
@@ -778,7 +778,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         g.N[i] = F;
     }
     s = GemmShape{n, B, F, H, H, F, 0, gelu_act, bf ? 0 : 1, nullptr, 1, 0};
-    L.gemm(MT_K_GEMM_FIRST, g, s, false);
+    L.gemm(MT_K_GEMM_FIRST, g, s);
 
     const int sp_f = splits_for(F, 4);
     for (int i = 0; i < n; ++i) {
@@ -789,7 +789,7 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
         g.N[i] = H;
     }
     s = GemmShape{n, B, H, F, F, H, 0, ACT_NONE, 1, nullptr, sp_f, MBH};
-    L.gemm(MT_K_GEMM_FIRST, g, s, false);
+    L.gemm(MT_K_GEMM_FIRST, g, s);
 
     for (int i = 0; i < n; ++i) {
         lg.x[i] = (const float*)(ws + io[i].cls->y);
@@ -1366,7 +1366,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         } else {
             L.check(launch_gather_rows(sg, n, HB, H, hrm.seq_start, S, HB * S, L.st));
             GemmShape s{n, HB, H, H, H, H, 0, ACT_TANH, 1, nullptr, 1, 0};
-            L.check(launch_gemm_f32(g, s, 0, L.st));
+            L.check(launch_gemm_f32(g, s, L.st));
         }
         L.check(launch_classifier(cg, n, HB, H, maxC, bf ? 1 : 0, m->C_tot, out_row, L.st));
         L.end();
@@ -1781,7 +1781,7 @@ int mt_op_linear(int32_t precision, const void* d_A, int64_t lda, const void* d_
     g.N[0] = N;
     GemmShape s{1, M, N, K, lda, ldc, ldc, act_kind, (precision == MT_BF16) ? (out_f32 ? 1 : 0) : 1, nullptr, 1, 0};
     hipError_t e = precision == MT_BF16 ? launch_gemm_bf16(g, s, static_cast<hipStream_t>(hip_stream))
-                                        : launch_gemm_f32(g, s, 0, static_cast<hipStream_t>(hip_stream));
+                                        : launch_gemm_f32(g, s, static_cast<hipStream_t>(hip_stream));
     if (e == hipErrorInvalidValue) return MT_ERR_SHAPE;
     return e == hipSuccess ? MT_OK : MT_ERR_HIP;
 }
@@ -1883,7 +1883,7 @@ int mt_op_linear_batched(int32_t precision, int32_t G, const void* d_A, int64_t 
     }
     GemmShape s{G, M, N, K, lda, ldc, ldc, act_kind, of32, nullptr, 1, 0};
     hipError_t e = bf ? launch_gemm_bf16(g, s, static_cast<hipStream_t>(hip_stream))
-                      : launch_gemm_f32(g, s, 0, static_cast<hipStream_t>(hip_stream));
+                      : launch_gemm_f32(g, s, static_cast<hipStream_t>(hip_stream));
     if (e == hipErrorInvalidValue) return MT_ERR_SHAPE;
     return e == hipSuccess ? MT_OK : MT_ERR_HIP;
 }

@@ -1,0 +1,52 @@
+"""Single kernels at the sizes where their tiles, splits and remainders can go wrong, against the oracle."""
+import numpy as np
+import pytest
+
+import mt_synth as ms
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2107_05377_amd as mt  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    mt.lib()
+
+
+def dev(x, dtype=None):
+    t = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    return t if dtype is None else t.to(dtype)
+
+
+# one row, full and one-over row blocks of the few-row kernel, of both tiles of the matrix-core kernel and of its large grid
+@pytest.mark.parametrize("M,N,K", [(1, 4, 64), (32, 100, 192), (33, 68, 64), (65, 64, 128), (31, 32, 832), (2113, 2052, 64)])
+@pytest.mark.parametrize("act", [0, 1])
+def test_gemm_f32_tiles(M, N, K, act):
+    print(f"gemm_f32 {M}x{N}x{K} act {act}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A, W = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    b, r = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    out = mt.op_linear(mt.MT_FP32_CHECK, dev(A), dev(W), dev(b), residual=dev(r), act=act).cpu().numpy()
+    ref = oracle.linear(A, W, b)
+    if act == 1:
+        ref = oracle.gelu(ref)
+    ref = ref + r
+    assert np.abs(out - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("B,S,H,A", [(2, 1, 64, 1), (3, 31, 64, 2), (2, 33, 128, 2), (1, 130, 64, 1), (2, 257, 64, 2)])
+def test_attention_f32_blocks(B, S, H, A):
+    print(f"attention_f32 B={B} S={S} H={H} A={A}", flush=True)
+    rng = np.random.default_rng(S)
+    q, k, v = (rng.standard_normal((B, S, H)).astype(np.float32) for _ in range(3))
+    mask = (np.arange(S)[None, :] < rng.integers(1, S + 1, B)[:, None]).astype(np.int32)
+    mask[0] = 1
+    if S > 8:
+        mask[0, 3:7] = 0
+    qkv = np.concatenate([q, k, v], axis=2).reshape(B * S, 3 * H)
+    ctx = mt.op_attention(mt.MT_FP32_CHECK, dev(qkv), dev(mask), B, S, H, A).cpu().numpy().reshape(B, S, H)
+    assert np.abs(ctx - oracle.attention(q, k, v, mask, A)).max() <= 2e-5
