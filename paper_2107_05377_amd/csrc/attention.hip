@@ -43,6 +43,9 @@ __device__ inline int k_chunk_off(int row, int chunk) { return row * 128 + ((chu
 #define MT_ATTN_CB 2
 #endif
 constexpr int CB = MT_ATTN_CB;        // 32-key blocks per online-softmax chunk
+// TILED: qkv and ctx in the panel layout (tiled_offset): a chunk (8 columns) of consecutive rows is contiguous there, so lanes take
+// consecutive keys of one chunk, which also spreads the transposed writes of the values over the LDS banks.
+template <bool TILED>
 __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnGroup g, const int32_t* __restrict__ mask,
                                                              const int32_t* __restrict__ seq_start,
                                                              const int32_t* __restrict__ seq_len, int B, int S, int H, int Sk_max,
@@ -63,7 +66,9 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const size_t ld = (size_t)3 * H;
-    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (size_t)row0 * ld;
+    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (TILED ? 0 : (size_t)row0 * ld);
+    // element of row `row` of this sequence, column `col`
+    auto at = [&](int row, int col) { return TILED ? tiled_offset(row0 + row, col, ld) : (size_t)row * ld + col; };
     const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * S : nullptr;
     const int nblk = Sk / 32;
 
@@ -74,7 +79,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     bf16x8 qf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-        qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qc * ld + a * 64 + kk * 16 + half * 8);
+        qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + at(qc, a * 64 + kk * 16 + half * 8));
 
     // ---- stage K (rows = keys, 8 chunks of 8 elements) and V transposed (item = a pair of adjacent keys x one
     //      8-wide chunk of d).  All of a thread's global loads of a batch are issued before the first LDS write,
@@ -83,41 +88,39 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     for (int kb = 0; kb < Sk; kb += 128) {
         uint4 kv[KU], v0[VU], v1[VU];
         int m0[VU], m1[VU];
+        auto key_of = [&](int u) { return TILED ? kb + (tid & 127) : kb + ((u * 256 + tid) >> 3); };
+        auto kch_of = [&](int u) { return TILED ? u * 2 + (tid >> 7) : (u * 256 + tid) & 7; };
+        auto pair_of = [&](int u) { return TILED ? kb / 2 + (tid & 63) : kb / 2 + ((u * 256 + tid) >> 3); };
+        auto vch_of = [&](int u) { return TILED ? u * 4 + (tid >> 6) : (u * 256 + tid) & 7; };
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            const int c = kb * 8 + u * 256 + tid;
-            const int key = c >> 3, ch = c & 7;
+            const int key = key_of(u), ch = kch_of(u);
             kv[u] = make_uint4(0, 0, 0, 0);
-            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)key * ld + H + a * 64 + ch * 8);
+            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(qkv + at(key, H + a * 64 + ch * 8));
         }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
-            const int c = kb * 4 + u * 256 + tid;
-            const int pair = c >> 3, ch = c & 7;
-            const int k0 = pair * 2, k1 = k0 + 1;
+            const int ch = vch_of(u), k0 = pair_of(u) * 2, k1 = k0 + 1;
             v0[u] = make_uint4(0, 0, 0, 0);
             v1[u] = make_uint4(0, 0, 0, 0);
             m0[u] = 1;
             m1[u] = 1;
             if (k0 < n_tok) {
-                v0[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k0 * ld + 2 * H + a * 64 + ch * 8);
+                v0[u] = *reinterpret_cast<const uint4*>(qkv + at(k0, 2 * H + a * 64 + ch * 8));
                 if (mrow) m0[u] = mrow[k0];
             }
             if (k1 < n_tok) {
-                v1[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k1 * ld + 2 * H + a * 64 + ch * 8);
+                v1[u] = *reinterpret_cast<const uint4*>(qkv + at(k1, 2 * H + a * 64 + ch * 8));
                 if (mrow) m1[u] = mrow[k1];
             }
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            const int c = kb * 8 + u * 256 + tid;
-            if ((c >> 3) < Sk) *reinterpret_cast<uint4*>(Ks + k_chunk_off(c >> 3, c & 7)) = kv[u];
+            if (key_of(u) < Sk) *reinterpret_cast<uint4*>(Ks + k_chunk_off(key_of(u), kch_of(u))) = kv[u];
         }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
-            const int c = kb * 4 + u * 256 + tid;
-            const int pair = c >> 3, ch = c & 7;
-            const int k0 = pair * 2;
+            const int ch = vch_of(u), k0 = pair_of(u) * 2;
             if (k0 >= Sk) continue;
             if (m0[u] == 0) v0[u] = make_uint4(0, 0, 0, 0);       // a masked key's value row must not leak
             if (m1[u] == 0) v1[u] = make_uint4(0, 0, 0, 0);
@@ -243,14 +246,14 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
                     pack_e4m3(o[dt][qq * 4 + 0] * inv, o[dt][qq * 4 + 1] * inv, o[dt][qq * 4 + 2] * inv, o[dt][qq * 4 + 3] * inv);
     } else if (q < n_tok) {
         const float inv = 1.0f / l_run;
-        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + ((size_t)row0 + q) * H + a * 64;
+        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + (TILED ? tiled_offset(row0 + q, a * 64, H) : ((size_t)row0 + q) * H + a * 64);
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq) {
                 bf16x4 v = {(__bf16)(o[dt][qq * 4 + 0] * inv), (__bf16)(o[dt][qq * 4 + 1] * inv),
                             (__bf16)(o[dt][qq * 4 + 2] * inv), (__bf16)(o[dt][qq * 4 + 3] * inv)};
-                *reinterpret_cast<bf16x4*>(out + dt * 32 + qq * 8 + half * 4) = v;
+                *reinterpret_cast<bf16x4*>(out + (TILED ? (dt * 4 + qq) * 256 : dt * 32 + qq * 8) + half * 4) = v;
             }
     }
 }
@@ -606,11 +609,11 @@ hipError_t launch_attention_cls(const AttnClsGroup& g, int G, int is_bf16, const
 }
 
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt)
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt, int tiled)
 {
     if (!mask && !(seq_start && seq_len)) return hipErrorInvalidValue;
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
-    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1)) return hipErrorInvalidValue;
+    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1) || (tiled && ctx_fmt)) return hipErrorInvalidValue;
     const int Sk = (S + 31) / 32 * 32;
     const size_t lds = (size_t)Sk * 128 + (size_t)64 * (Sk + 4) * 2 + (size_t)Sk * 4 + (size_t)(Sk / 32) * 4;
     static_assert(kAttnBf16MaxSeq % 32 == 0 &&
@@ -619,14 +622,17 @@ hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask,
                       (size_t)(kAttnBf16MaxSeq + 32) * 260 + 512 > 160 * 1024,
                   "kAttnBf16MaxSeq is the largest multiple of 32 whose keys and values fit the LDS");
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static std::atomic<uint64_t> lds_raised{0};
+    static std::atomic<uint64_t> lds_raised[2];
     if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)attention_bf16_kernel, 160 * 1024, lds_raised);
+        hipError_t e = ensure_dynamic_lds(tiled ? (const void*)attention_bf16_kernel<true> : (const void*)attention_bf16_kernel<false>, 160 * 1024, lds_raised[tiled ? 1 : 0]);
         if (e != hipSuccess) return e;
     }
     dim3 grid((S + 127) / 128, A, B * G), block(256);
     const float scale_log2e = (1.0f / sqrtf(64.0f)) * kLog2e;
-    hipLaunchKernelGGL(attention_bf16_kernel, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
+    if (tiled)
+        hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
+    else
+        hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
     return hipGetLastError();
 }
 

@@ -408,8 +408,9 @@ hipError_t p_launch_cfg(const GemmGroup& g, const GemmShape& s, int n_wg, hipStr
     }
 }
 
-// compute units of the current device (cached per device)
-int cu_count()
+}  // namespace
+
+int device_cu_count()
 {
     static std::atomic<int> cached[64] = {};
     int dev = 0;
@@ -421,7 +422,6 @@ int cu_count()
     return v;
 }
 
-}  // namespace
 
 bool gemm_bf16_persist_takes(const GemmShape& s)
 {
@@ -444,14 +444,14 @@ bool gemm_bf16_persist_wants(const GemmShape& s)
     if (!gemm_bf16_persist_takes(s)) return false;
     const long tiles = (long)s.G * ((s.M + 255) / 256) * ((s.N + 255) / 256);
     const bool gelu = s.act == ACT_GELU_ERF || s.act == ACT_GELU_TANH;
-    return tiles >= (long)(gelu ? 4 : 1) * cu_count();
+    return tiles >= (long)(gelu ? 4 : 1) * device_cu_count();
 }
 
 hipError_t launch_gemm_bf16_persist(const GemmGroup& g, const GemmShape& s, hipStream_t stream)
 {
     if (!gemm_bf16_persist_takes(s)) return hipErrorInvalidValue;
     const long tiles = (long)s.G * ((s.M + 255) / 256) * ((s.N + 255) / 256);
-    const int n_wg = (int)std::min<long>(tiles, cu_count());
+    const int n_wg = (int)std::min<long>(tiles, device_cu_count());
     if (n_wg < kPXcds) return hipErrorInvalidValue;          // every XCD's tile range needs a workgroup
     // (rings of two 64-wide and of four 32-wide slices, with a 32 KB park, were measured equal or slower: not instantiated)
     return p_launch_cfg<256, 256, 2, 4, 32, 3, 64>(g, s, n_wg, stream);                       // 96 KB ring, 64 KB park

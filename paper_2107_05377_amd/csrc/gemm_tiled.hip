@@ -1,0 +1,550 @@
+// bfloat16 contraction of the serving path:  C_g[M,N] = epi(A_g[M,K] * W_g[N,K]^T),  g = 0..G-1 in one launch, with both
+// operands and the result in the panel layout of tiled_offset() (kernels.h): 32 rows form a panel, 8 consecutive columns of a
+// panel's 32 rows are stored behind one another.  In that layout
+//   - a 32 x 16 MFMA operand fragment is 1 KB of contiguous memory in lane order, so global -> LDS loads are copies of whole
+//     128-byte lines (64-byte row pieces, as a 32-wide K slice of a row-major matrix has, halve the rate: 28 instead of 50 bytes
+//     per clock and compute unit measured with all of them loading), fragment reads from LDS need no swizzle, and a fragment may as
+//     well go straight from global memory to registers (48 KB by 4 wavefronts: 0.7 us, row-major 1.7 us);
+//   - the accumulator of a 32x32 block (a lane holds 4 consecutive columns of one row) is stored directly in runs of 1 KB: no
+//     trip through LDS in the epilogue.
+//
+// gemm_tiled_kernel.  A workgroup of 4 wavefronts owns TMI panels of rows x 256 columns (KW = 1: each wavefront 64 columns and all
+// rows) or x 128 columns (KW = 2: two wavefronts share 64 columns and take half of K each).  The activation slice (64 of K)
+// goes through a ring of LDS stages, shared by the wavefronts; a weight fragment is used by one wavefront only and is loaded into
+// its registers NB slices ahead.  Per slice and wavefront: 8 TMI matrix instructions, 4 TMI fragment reads, 8 weight and TMI KW
+// activation loads, one barrier.  That leaves LDS (32 KB of reads and 8 KB of writes per 512 matrix clocks at TMI = 8) and the
+// load path (32 bytes per clock at TMI = 8, 48 at TMI = 4) below their limits; with the weights in LDS as well, LDS was the limit.
+// A workgroup walks a list of tiles without draining: the loads of the next tile start during the last slices of a tile.
+//
+// The number of rows is on the device, so the tile height is chosen there (pick_height): the height with the smallest
+// (tiles per compute unit, rounded up) x (height + fixed cost).  18.6 k rows x 2304 columns are 5.1 tiles of 128 rows per compute
+// unit, i.e. 6 rounds, but 6.8 of 96 rows.
+#include "kernels.h"
+#include "device_util.h"
+
+namespace mt {
+
+namespace {
+
+constexpr int kXcds = 8;
+constexpr int kBand = 8;                // row-tiles per raster band
+
+typedef __attribute__((address_space(3))) void* lptr_t;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+template <int ACT>
+__device__ __forceinline__ float t_act(float v)
+{
+    if constexpr (ACT == ACT_GELU_ERF) return gelu_erf_fast(v);
+    else if constexpr (ACT == ACT_GELU_TANH) return gelu_tanh(v);
+    else if constexpr (ACT == ACT_TANH) return tanhf(v);
+    else return v;
+}
+
+// Scheduling of one K step: NM matrix instructions, PER fragment reads behind each of the first ones (the rest of the step covers
+// their latency), the step's two weight loads last.
+template <int NM, int NF, int PER>
+__device__ __forceinline__ void t_interleave()
+{
+    if constexpr (NM > 0) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if constexpr (NF > 0) __builtin_amdgcn_sched_group_barrier(0x100, NF < PER ? NF : PER, 0);
+        t_interleave<NM - 1, (NF > PER ? NF - PER : 0), PER>();
+    } else {
+        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+    }
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t t_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
+// Ring depth and weight prefetch distance by tile height: as deep as two (KW = 1, TMI <= 4: 80 KB of LDS and 256 registers each)
+// or one workgroup per compute unit allow, and within the 63 loads that a wait can count.
+template <int TMI, int KW>
+struct TCfg {
+    static constexpr int WN = 4 / KW;                                   // wavefronts along N
+    static constexpr int AL = KW * TMI;                                 // activation loads per wavefront and slice
+    static constexpr int STAGE = AL * 4096;
+    static constexpr int NB = TMI >= 4 ? 2 : (TMI == 3 ? 3 : 4);        // weight slices in registers
+    static constexpr int S = TMI >= 7 ? 4 : (TMI >= 5 ? 5 : (KW == 2 ? (TMI == 4 ? 3 : (TMI == 3 ? 4 : 5)) : (TMI == 4 ? 5 : 6)));
+    static constexpr int XCHG = KW == 2 ? TMI * 4096 * 4 : 0;           // partial sums of the K halves
+    static constexpr int LDS = S * STAGE + XCHG;
+    // loads younger than the activation slice that must have landed at a slice's barrier, on every path (see below)
+    static constexpr int WAIT = (S - 2) * AL + 8 * (NB < S - 2 ? NB : S - 2) + 6;
+    static_assert(WAIT <= 63 && LDS <= 160 * 1024, "ring");
+};
+
+template <int TMI, int KW, bool OUT_F32, int ACT>
+__device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const TiledShape& s, unsigned char* lds, int panels_m)
+{
+    using Cfg = TCfg<TMI, KW>;
+    constexpr int S = Cfg::S, NB = Cfg::NB, WN = Cfg::WN, AL = Cfg::AL, STAGE = Cfg::STAGE, KK = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = wave % WN, wk = wave / WN;
+    const int panels_n = s.N >> 5;
+    const int tiles_m = (panels_m + TMI - 1) / TMI, tiles_n = (panels_n + 2 * WN - 1) / (2 * WN);
+    const int per_problem = tiles_m * tiles_n, total = s.G * s.splits * per_problem;
+    // this workgroup's tiles: XCD x owns a contiguous range of the tile order, its workgroups stride through it
+    const int xcd = blockIdx.x % kXcds, wi = blockIdx.x / kXcds, wg_x = ((int)gridDim.x - xcd + kXcds - 1) / kXcds;
+    const int q8 = total / kXcds, r8 = total % kXcds, lo = xcd * q8 + min(xcd, r8), cnt = q8 + (xcd < r8 ? 1 : 0);
+    if (wi >= cnt) return;                                                   // uniform over the workgroup
+    const int n_mine = (cnt - wi + wg_x - 1) / wg_x;
+    const int KT = s.K / (64 * KW) / s.splits;                               // slices of a wavefront's K range
+    const uint32_t pa = (uint32_t)s.lda * 64, pw = (uint32_t)s.ldw * 64;     // bytes per panel
+    const int voff = lane * 16;
+
+    struct Ref {
+        __amdgpu_buffer_rsrc_t A, W;      // a panel beyond the last one lies beyond the buffer's end: reads as zero
+        int ao, wo, grp, split, pm0, pn0;
+    };
+    auto locate = [&](int j, Ref& t) {
+        const int tile = lo + wi + j * wg_x;
+        const int gs = tile / per_problem, tt = tile - gs * per_problem;
+        t.grp = gs / s.splits;
+        t.split = gs - t.grp * s.splits;
+        const int band_sz = kBand * tiles_n, band = tt / band_sz, rows_in_band = min(kBand, tiles_m - band * kBand), tb = tt - band * band_sz;
+        const int tn = tb / rows_in_band, tm = band * kBand + tb % rows_in_band;
+        t.pm0 = tm * TMI;
+        t.pn0 = (tn * WN + wn) * 2;
+        const int k0 = t.split * KW * KT * 4096;                             // byte offset of the K range inside a panel
+        t.A = t_rsrc(static_cast<const unsigned char*>(g.A) + (size_t)g.a[t.grp] * 256, panels_m * pa);
+        t.W = t_rsrc(static_cast<const unsigned char*>(g.W) + (size_t)g.w[t.grp] * 256, panels_n * pw);
+        t.ao = t.pm0 * (int)pa + k0 + wave * 1024;
+        t.wo = t.pn0 * (int)pw + k0 + wk * KT * 4096;
+    };
+    Ref cur, nxt;
+    locate(0, cur);
+    if (n_mine > 1) locate(1, nxt);
+    else nxt = cur;                        // no next tile: its loads are repeats of this one, never read
+
+    auto issueA = [&](const Ref& t, int kt, int stage) {
+#pragma unroll
+        for (int i = 0; i < AL; ++i)       // wavefront w fetches K step w of every panel
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(t.A, (lptr_t)(lds + stage * STAGE + (i * 4 + wave) * 1024), 16, voff,
+                                                     t.ao + (i % TMI) * (int)pa + ((i / TMI) * KT + kt) * 4096, 0, 0);
+    };
+    bf16x8 wf[NB][KK][2], af[2][TMI];
+    f32x16 acc[TMI][2];
+    auto loadW = [&](const Ref& t, int kt, int buf, int kk) {
+#pragma unroll
+        for (int jn = 0; jn < 2; ++jn)
+            wf[buf][kk][jn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(t.W, voff + kk * 1024, t.wo + jn * (int)pw + kt * 4096, 0));
+    };
+    auto readA = [&](int buf, int stage, int kk) {
+#pragma unroll
+        for (int i = 0; i < TMI; ++i)
+            af[buf][i] = *reinterpret_cast<const bf16x8*>(lds + stage * STAGE + ((wk * TMI + i) * 4 + kk) * 1024 + voff);
+    };
+    // accumulators start from the bias (of the first K share)
+    auto init_acc = [&](const Ref& t) {
+        const uint32_t bo = OUT_F32 ? kNoBias : g.b[t.grp];
+#pragma unroll
+        for (int jn = 0; jn < 2; ++jn) {
+            f32x16 b0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) b0[e] = 0.f;
+            if (bo != kNoBias && (KW == 1 || wk == 0)) {
+                const float* bp = g.bias + (size_t)bo * 64 + min(t.pn0 + jn, panels_n - 1) * 32 + (lane >> 5) * 4;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 v = *reinterpret_cast<const float4*>(bp + q * 8);
+                    b0[q * 4] = v.x; b0[q * 4 + 1] = v.y; b0[q * 4 + 2] = v.z; b0[q * 4 + 3] = v.w;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TMI; ++i) acc[i][jn] = b0;
+        }
+    };
+    auto store_block = [&](const Ref& t, const f32x16& a, int pm, int pn) {
+        if (pm >= panels_m || pn >= panels_n) return;                        // uniform
+        unsigned char* Cb = static_cast<unsigned char*>(g.C) + (size_t)g.c[t.grp] * 256;
+        if constexpr (OUT_F32) {
+            float* c = reinterpret_cast<float*>(Cb) + (size_t)t.split * s.split_stride + (size_t)pm * 32 * s.ldc + pn * 1024 + (lane & 31) * 8 + (lane >> 5) * 4;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(c + q * 256) = f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]};
+        } else {
+            __bf16* c = reinterpret_cast<__bf16*>(Cb) + (size_t)pm * 32 * s.ldc + pn * 1024 + lane * 8;
+#pragma unroll
+            for (int qp = 0; qp < 2; ++qp) {
+                bf16x4 x, y;                                                 // 4 of the 8 columns of two neighbouring chunks
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] = (__bf16)t_act<ACT>(a[qp * 8 + e]);
+                    y[e] = (__bf16)t_act<ACT>(a[qp * 8 + 4 + e]);
+                }
+                // the half wavefronts exchange so that the lower one holds all of the first chunk, the upper one all of the second
+                const u32x2 xu = __builtin_bit_cast(u32x2, x), yu = __builtin_bit_cast(u32x2, y);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(xu[0], yu[0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(xu[1], yu[1], false, false);
+                *reinterpret_cast<u32x4*>(c + qp * 512) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+            }
+        }
+    };
+
+    // ---- fill, in the order of the steady state (iteration i: activation slice i + S - 1, then weight slice i + NB)
+#pragma unroll
+    for (int i = -(S - 1); i < 0; ++i) {
+        if (i + S - 1 < KT) issueA(cur, i + S - 1, i + S - 1);
+        else issueA(nxt, i + S - 1 - KT, i + S - 1);
+        if (i + NB >= 0) {
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) loadW(i + NB < KT ? cur : nxt, i + NB < KT ? i + NB : i + NB - KT, (i + NB) % NB, kk);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * AL + 8 * (NB < S - 1 ? NB : S - 1) < 63 ? (S - 2) * AL + 8 * (NB < S - 1 ? NB : S - 1) : 63) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    readA(0, 0, 0);
+
+    // ---- slices of all tiles in one sequence; the weight buffer of a slice is its number in the sequence modulo NB
+    int st = 0, kt = 0, j = 0;                 // ring stage, slice of the tile, tile
+    auto slice = [&](auto bufc) {
+        constexpr int buf = decltype(bufc)::value;
+        const int ka = kt + S - 1, kw = kt + NB;
+        const Ref ta = ka < KT ? cur : nxt, tw = kw < KT ? cur : nxt;
+        const int ps = st == 0 ? S - 1 : st - 1, ns = st + 1 == S ? 0 : st + 1;
+        issueA(ta, ka < KT ? ka : ka - KT, ps);            // into the stage of the slice before, which everyone has read
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            if (kk + 1 < KK) {
+                readA((kk + 1) & 1, st, kk + 1);
+            } else {
+                // this slice is in registers and the next one must have landed, for every wavefront.  Loads return in order; those
+                // younger than the next slice's are S - 2 activation slices and at least min(NB, S - 2) weight slices and 3 of 4 steps.
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cfg::WAIT) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                readA(0, ns, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < TMI; ++i)
+#pragma unroll
+                for (int jn = 0; jn < 2; ++jn)
+                    acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][kk][jn], af[kk & 1][i], acc[i][jn], 0, 0, 0);
+            loadW(tw, kw < KT ? kw : kw - KT, buf, kk);
+            t_interleave<TMI * 2, TMI, 2>();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        st = ns;
+        ++kt;
+    };
+    auto epilogue = [&]() {
+        if constexpr (KW == 1) {
+#pragma unroll
+            for (int i = 0; i < TMI; ++i)
+#pragma unroll
+                for (int jn = 0; jn < 2; ++jn) store_block(cur, acc[i][jn], cur.pm0 + i, cur.pn0 + jn);
+        } else {
+            // the wavefronts of a pair exchange a column block: each finishes one
+            float* x = reinterpret_cast<float*>(lds + S * STAGE);
+            float* mine = x + (wk * WN + wn) * TMI * 1024;
+            const float* other = x + ((1 - wk) * WN + wn) * TMI * 1024;
+#pragma unroll
+            for (int i = 0; i < TMI; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mine[(i * 16 + e) * 64 + lane] = wk == 0 ? acc[i][1][e] : acc[i][0][e];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < TMI; ++i) {
+                f32x16 a;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float o = other[(i * 16 + e) * 64 + lane];
+                    a[e] = wk == 0 ? acc[i][0][e] + o : o + acc[i][1][e];
+                }
+                store_block(cur, a, cur.pm0 + i, cur.pn0 + wk);
+            }
+        }
+        cur = nxt;
+        kt = 0;
+        ++j;
+        if (j + 1 < n_mine) locate(j + 1, nxt);
+    };
+    // true when the last tile is done
+    auto finish_tile = [&]() {
+        if (kt < KT) return false;
+        epilogue();
+        if (j == n_mine) return true;
+        init_acc(cur);
+        return false;
+    };
+    if constexpr (NB == 2) {                               // an even number of slices: one copy of the epilogue
+        while (j < n_mine) {
+            init_acc(cur);
+            while (kt < KT) {
+                slice(std::integral_constant<int, 0>{});
+                slice(std::integral_constant<int, 1>{});
+            }
+            epilogue();
+        }
+    } else {
+        init_acc(cur);
+        for (;;) {
+            slice(std::integral_constant<int, 0>{});
+            if (finish_tile()) break;
+            slice(std::integral_constant<int, 1>{});
+            if (finish_tile()) break;
+            slice(std::integral_constant<int, 2>{});
+            if (finish_tile()) break;
+            if constexpr (NB > 3) {
+                slice(std::integral_constant<int, 3>{});
+                if (finish_tile()) break;
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the repeat loads must land before the LDS is released
+}
+
+// Tile height in panels, MINT .. MAXT: fewest rounds x cost of a tile.  Two workgroups on a compute unit share it, so rounds count
+// tiles per compute unit; the fixed cost of a tile (fill, epilogue) is about that of 0.7 panels at K = 768.
+template <int MINT, int MAXT>
+__device__ __forceinline__ int pick_height(int panels_m, int tiles_per_row, int n_cu, int slices)
+{
+    int best = MINT;
+    float best_cost = 3.4e38f;
+#pragma unroll
+    for (int t = MAXT; t >= MINT; --t) {
+        if (t >= 4 && (slices & 1)) continue;              // two weight buffers go with an even number of slices
+        const int tiles = (panels_m + t - 1) / t * tiles_per_row;
+        const float cost = (float)((tiles + n_cu - 1) / n_cu) * ((float)t + 0.7f);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = t;
+        }
+    }
+    return best;
+}
+
+template <int KW, int MAXT, bool OUT_F32, int ACT>
+__global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tiled_kernel(TiledGroup g, TiledShape s, int n_cu, int force)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int M = s.d_M ? min(s.M, *s.d_M) : s.M;
+    const int panels_m = (M + 31) >> 5;
+    const int slices = s.K / (64 * KW) / s.splits;
+    const int per_row = ((s.N >> 5) + 8 / KW - 1) / (8 / KW) * s.G * s.splits;
+    if constexpr (MAXT == 8) {
+        switch (force ? force : pick_height<5, 8>(panels_m, per_row, n_cu, slices)) {
+            case 8: gemm_tiled_body<8, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            case 7: gemm_tiled_body<7, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            case 6: gemm_tiled_body<6, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            default: gemm_tiled_body<5, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+        }
+    } else {
+        switch (force ? force : pick_height<1, MAXT>(panels_m, per_row, n_cu, slices)) {
+            case 4: gemm_tiled_body<4, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            case 3: gemm_tiled_body<3, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            case 2: gemm_tiled_body<2, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+            default: gemm_tiled_body<1, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+        }
+    }
+}
+
+// gemm_tiled_rows_kernel.  Few rows: TM x TN panels of output per workgroup, each of its 4 wavefronts a quarter of K, both operands
+// straight from global memory to registers with all loads of a quarter of K = 768 in flight at once (such a launch is a chain
+// of memory latencies: nothing is staged, there is one barrier), then one exchange of partial sums through LDS.
+template <int TM, int TN, bool OUT_F32, int ACT>
+__global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kernel(TiledGroup g, TiledShape s)
+{
+    constexpr int U = 12, NBLK = TM * TN;
+    __shared__ __attribute__((aligned(16))) float part[4][NBLK][4][64][4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_sub = s.n_sub > 1 ? s.n_sub : 1;
+    const int sub = blockIdx.z % n_sub, gz = blockIdx.z / n_sub;
+    const int grp = gz / s.splits, split = gz - grp * s.splits;
+    const uint32_t off_a = g.a[grp] + sub * s.sub_a, off_w = g.w[grp] + sub * s.sub_w, off_c = g.c[grp] + sub * s.sub_c;
+    const uint32_t off_b = g.b[grp] == kNoBias ? kNoBias : g.b[grp] + sub * s.sub_b;
+    const int panels_n = s.N >> 5;
+    const int pn0 = blockIdx.x * TN, pm0 = blockIdx.y * TM;
+    const int M = s.d_M ? min(s.M, *s.d_M) : s.M;
+    const int panels_m = (M + 31) >> 5;
+    if (pm0 >= panels_m) return;
+    const int steps = s.K / s.splits / 64;                                   // K steps of 16 of a wavefront
+    const size_t k0 = (size_t)(split * 4 + wave) * steps * 1024 + lane * 16;
+    const unsigned char* a[TM];
+    const unsigned char* w[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+        a[i] = static_cast<const unsigned char*>(g.A) + (size_t)off_a * 256 + (size_t)min(pm0 + i, panels_m - 1) * s.lda * 64 + k0;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+        w[j] = static_cast<const unsigned char*>(g.W) + (size_t)off_w * 256 + (size_t)min(pn0 + j, panels_n - 1) * s.ldw * 64 + k0;
+    // this wavefront finishes chunk `wave` of every block
+    float4 bv[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        bv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (off_b != kNoBias)
+            bv[j] = *reinterpret_cast<const float4*>(g.bias + (size_t)off_b * 64 + min(pn0 + j, panels_n - 1) * 32 + wave * 8 + (lane >> 5) * 4);
+    }
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    // one batch of steps: all its loads are issued before its first product (a full batch without conditions: guarded loads are
+    // branches, and the loads then go out one by one)
+    auto batch = [&](int s0, int nb, auto full) {
+        bf16x8 af[U][TM], wf[U][TN];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (full || u < nb) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) wf[u][j] = *reinterpret_cast<const bf16x8*>(w[j] + (size_t)(s0 + u) * 1024);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) af[u][i] = *reinterpret_cast<const bf16x8*>(a[i] + (size_t)(s0 + u) * 1024);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (full || u < nb) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][j], af[u][i], acc[i][j], 0, 0, 0);
+            }
+    };
+    int s0 = 0;
+    for (; s0 + U <= steps; s0 += U) batch(s0, U, std::true_type{});
+    if (s0 < steps) batch(s0, steps - s0, std::false_type{});
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(part[wave][i * TN + j][q][lane]) = f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+    __syncthreads();
+    unsigned char* Cb = static_cast<unsigned char*>(g.C) + (size_t)off_c * 256;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int pm = pm0 + i, pn = pn0 + j;
+            if (pm >= panels_m || pn >= panels_n) continue;
+            f32x4 v = *reinterpret_cast<const f32x4*>(part[0][i * TN + j][wave][lane]);
+#pragma unroll
+            for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(part[p][i * TN + j][wave][lane]);
+            v[0] = t_act<ACT>(v[0] + bv[j].x);
+            v[1] = t_act<ACT>(v[1] + bv[j].y);
+            v[2] = t_act<ACT>(v[2] + bv[j].z);
+            v[3] = t_act<ACT>(v[3] + bv[j].w);
+            const size_t at = (size_t)pm * 32 * s.ldc + pn * 1024 + wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4;
+            if constexpr (OUT_F32) {
+                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(Cb) + (size_t)split * s.split_stride + at) = v;
+            } else {
+                const bf16x4 o = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+                *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(Cb) + at) = o;
+            }
+        }
+}
+
+template <int KW, int MAXT, bool OUT_F32, int ACT>
+hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int force, hipStream_t stream)
+{
+    constexpr int b0 = TCfg<MAXT, KW>::LDS, b1 = TCfg<MAXT - 1, KW>::LDS, b2 = TCfg<MAXT - 2, KW>::LDS, b3 = TCfg<MAXT - 3, KW>::LDS;
+    constexpr int m0 = b0 > b1 ? b0 : b1, m1 = b2 > b3 ? b2 : b3, bytes = m0 > m1 ? m0 : m1;
+    auto kfn = gemm_tiled_kernel<KW, MAXT, OUT_F32, ACT>;
+    static std::atomic<uint64_t> lds_raised{0};
+    if (bytes > 64 * 1024) {
+        hipError_t e = ensure_dynamic_lds((const void*)kfn, bytes, lds_raised);
+        if (e != hipSuccess) return e;
+    }
+    // one (two where two fit) workgroup per compute unit, fewer if the lowest tiles of the row bound are fewer
+    const int low = MAXT == 8 ? 5 : 1;
+    const long tiles = (long)(((s.M + 31) / 32 + low - 1) / low) * ((s.N / 32 + 8 / KW - 1) / (8 / KW)) * s.G * s.splits;
+    const long slots = (long)n_cu * ((MAXT <= 4 && KW == 1) ? 2 : 1);
+    const int n_wg = (int)(tiles < slots ? (tiles < kXcds ? kXcds : tiles) : slots);
+    hipLaunchKernelGGL(kfn, dim3(n_wg), dim3(256), bytes, stream, g, s, n_cu, force);
+    return hipGetLastError();
+}
+
+template <int TM, int TN, bool OUT_F32, int ACT>
+hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t stream)
+{
+    dim3 grid((s.N / 32 + TN - 1) / TN, ((s.M + 31) / 32 + TM - 1) / TM, s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1)), block(256);
+    hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, g, s);
+    return hipGetLastError();
+}
+
+template <bool OUT_F32, int ACT>
+hipError_t launch_form(const TiledGroup& g, const TiledShape& s, int form, int force, hipStream_t stream)
+{
+    const int n_cu = device_cu_count();
+    switch (form) {
+        case TILED_ROWS_1X1: return launch_rows<1, 1, OUT_F32, ACT>(g, s, stream);
+        case TILED_ROWS_2X1: return launch_rows<2, 1, OUT_F32, ACT>(g, s, stream);
+        case TILED_ROWS_2X2: return launch_rows<2, 2, OUT_F32, ACT>(g, s, stream);
+    }
+    if constexpr (ACT != ACT_TANH) {
+        switch (form) {
+            case TILED_K2: return launch_tiles<2, 4, OUT_F32, ACT>(g, s, n_cu, force, stream);
+            case TILED_PAIR: return launch_tiles<1, 4, OUT_F32, ACT>(g, s, n_cu, force, stream);
+            case TILED_TALL:
+                if constexpr (ACT == ACT_NONE) return launch_tiles<1, 8, OUT_F32, ACT>(g, s, n_cu, force, stream);
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+// The kernel form.  `blocks` counts the 32x32 outputs of the launch by its row bound (the rows present, known on the device, are
+// about half of that in a padded batch).  Measured at BERT-base widths, 36 to 18.6 k rows, 1 and 8 problems:
+//   up to 1152 blocks (72 x 2 for 36 rows x 2304 columns): one block per workgroup; a launch is a chain of latencies there and
+//     more, smaller workgroups shorten it (36 rows: QKV 4.3 us, 2x1 4.4, 2x2 5.9, tiles 7.5);
+//   up to 3072: two row panels per workgroup (600 rows x 2304: 8.1 us, 1x1 8.5, K2 9.1), unless there are few column panels and
+//     enough rows for the K2 tiles (2318 rows x 768 x 768: 9.1 us);
+//   beyond: tiles.  Narrow outputs of fewer tiles than fill the chip twice take K2, which halves a workgroup's serial K loop (2318
+//     rows x 768 x 3072: 21.5 us, PAIR 31); long K with many tiles takes TALL (18.6 k rows x 768 x 3072: 75.5 us, PAIR 78), everything
+//     else PAIR, whose two workgroups per compute unit hide each other's epilogues (GELU: 84 us, TALL 100).
+int choose_form(const TiledShape& s)
+{
+    const int pm = (s.M + 31) / 32, pn = s.N / 32;
+    const long blocks = (long)pm * pn * s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1);
+    const int slices = s.K / 64 / s.splits;
+    if (s.n_sub > 1 || s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
+    const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
+    if (blocks <= 1152 || !tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
+    if (blocks <= 3072 && !(k2_ok && pm >= 64 && pn <= 32)) return TILED_ROWS_2X1;
+    const long tiles4 = (long)((pm + 3) / 4) * ((pn + 7) / 8) * s.G * s.splits;     // 128 x 256
+    if (k2_ok && tiles4 <= 256) return TILED_K2;
+    if (s.K >= 2048 && s.act == ACT_NONE && slices % 2 == 0 && tiles4 >= 512) return TILED_TALL;
+    return TILED_PAIR;
+}
+
+}  // namespace
+
+hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream_t stream, int form, int force)
+{
+    if (s.G <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
+    if (s.G > kMaxGroup || s.splits < 1 || s.N % 32 != 0 || s.K % (64 * s.splits) != 0 || s.lda % 16 != 0 || s.ldw % 16 != 0 || s.ldc % 8 != 0 ||
+        s.lda < s.K || s.ldw < s.K || (s.splits > 1 && (!s.out_f32 || s.act != ACT_NONE)))
+        return hipErrorInvalidValue;
+    // byte offsets inside an operand are 31-bit
+    if ((uint64_t)(s.M + 31) / 32 * s.lda * 64 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;
+    if (form == TILED_AUTO) form = choose_form(s);
+    // the tile forms: a tile's loads reach at most into the next tile, so it has at least as many slices as the ring holds ahead
+    const int kw = form == TILED_K2 ? 2 : 1, slices = s.K / (64 * kw) / s.splits;
+    if (form >= TILED_K2 && (s.n_sub > 1 || s.K % (64 * kw * s.splits) != 0 || slices < 5 || (form == TILED_TALL && slices % 2 != 0)))
+        return hipErrorInvalidValue;
+    if (form < TILED_K2 && (long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535) return hipErrorInvalidValue;
+    if (s.out_f32) {
+        if (s.act == ACT_TANH) return launch_form<true, ACT_TANH>(g, s, form, force, stream);
+        if (s.act != ACT_NONE) return hipErrorInvalidValue;
+        return launch_form<true, ACT_NONE>(g, s, form, force, stream);
+    }
+    switch (s.act) {
+        case ACT_NONE: return launch_form<false, ACT_NONE>(g, s, form, force, stream);
+        case ACT_GELU_ERF: return launch_form<false, ACT_GELU_ERF>(g, s, form, force, stream);
+        case ACT_GELU_TANH: return launch_form<false, ACT_GELU_TANH>(g, s, form, force, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace mt

@@ -65,6 +65,83 @@ hipError_t launch_gemm_skinny_bf16(const GemmGroup& g, const GemmShape& s, hipSt
 // mfma_rate_out_floats(n_cu) floats.  Synchronises on the stream.
 hipError_t run_mfma_rate(int iters, int n_cu, float* d_out, hipStream_t stream, float* tflops);
 int mfma_rate_out_floats(int n_cu);
+// ---- panel layout of the bfloat16 path: 32 rows form a panel; inside a panel the columns come in chunks of 8, a chunk holding its
+// 8 columns of row 0, of row 1, ... (512 bytes of bf16, 1 KB of float32).  Weights (rows = output columns), operands and the float32
+// states have it alike.  Element offset of (row, col) in a matrix of `width` columns (a multiple of 8), rows padded to a multiple of 32:
+__host__ __device__ inline size_t tiled_offset(size_t row, size_t col, size_t width)
+{
+    return (row >> 5) * 32 * width + (col >> 3) * 256 + (row & 31) * 8 + (col & 7);
+}
+// Grouped problems as byte offsets from common bases, in units of 256 bytes (all buffers of the arenas are so aligned): a third of the
+// kernel arguments that pointers would be, which the host writes on every launch (4.1 -> 2.9 us of host time a launch).
+constexpr uint32_t kNoBias = 0xFFFFFFFFu;
+struct TiledGroup {
+    const void* A;          // bf16 [M][lda]
+    const void* W;          // bf16 [N][ldw]
+    void* C;                // bf16 or float32 [M][ldc]
+    const float* bias;      // bf16 output and few-row forms only
+    uint32_t a[kMaxGroup], w[kMaxGroup], c[kMaxGroup], b[kMaxGroup];   // b: kNoBias = none
+};
+struct TiledShape {
+    int32_t G, M, N, K;         // M: row bound; N % 32 == 0, K % (64 splits) == 0
+    int32_t lda, ldw, ldc;      // widths of the matrices that the operands' columns are part of
+    int32_t act, out_f32;
+    const int32_t* d_M;         // optional device scalar: rows present
+    int32_t splits;             // K ranges, each with a float32 partial result (no bias), split_stride elements apart
+    int64_t split_stride;
+    // few-row forms only: every problem is n_sub equal ones (heads) whose operands lie so far apart, in units of 256 bytes
+    int32_t n_sub, sub_a, sub_w, sub_c, sub_b;
+};
+// The kernel forms (gemm_tiled.hip); TILED_AUTO chooses by shape.
+enum TiledForm : int { TILED_AUTO = 0, TILED_ROWS_1X1, TILED_ROWS_2X1, TILED_ROWS_2X2, TILED_K2, TILED_PAIR, TILED_TALL };
+hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream_t stream, int form = TILED_AUTO, int force_height = 0);
+// compute units of the current device (cached per device)
+int device_cu_count();
+
+// LayerNorm on the panel layout: out = LN(sum_p x[p] + bias + residual), offsets as above from the workspace and the weights.
+struct TiledLnGroup {
+    const void* ws;
+    const void* wt;
+    uint32_t x[kMaxGroup], res[kMaxGroup], out_f[kMaxGroup], out_b[kMaxGroup];   // outputs: kNoBias = none
+    uint32_t bias[kMaxGroup], gamma[kMaxGroup], beta[kMaxGroup];
+};
+struct TiledLnShape {
+    int32_t G, M, H;
+    const int32_t* d_M;
+    float eps;
+    int32_t n_parts;
+    int64_t part_stride;        // elements
+    const int32_t* res_row;     // optional: residual row of row i is res_row[i] (below res_rows)
+    int32_t res_rows;
+    int32_t split;              // out_b: 0 the row as bf16, 1 as [hi | lo] bf16 halves of a matrix of 2H columns
+};
+hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream);
+// As launch_embed_ln (bf16 tables), states in the panel layout.
+hipError_t launch_embed_ln_tiled(const int32_t* ids, const int32_t* type_ids, int type_vocab, const int32_t* src, const int32_t* d_M, int B, int S,
+                                 int H, int vocab, const void* word, const void* pos, const void* type, const float* gamma, const float* beta,
+                                 float eps, float* out_f32, void* out_bf16, hipStream_t stream);
+struct RowCopyGroup {
+    const float* in_f[kMaxGroup];
+    const void* in_b[kMaxGroup];
+    float* out_f[kMaxGroup];
+    void* out_b[kMaxGroup];
+};
+// out row i = in row index[i] for i < *n (n_max if n is null), float32 and / or bf16 matrices of H columns
+hipError_t launch_copy_rows_tiled(const RowCopyGroup& g, int G, const int32_t* index, const int32_t* n, int n_max, int max_rows, int H, hipStream_t stream);
+
+// First-token attention without projected keys and values (first_token.hip).
+struct FirstTokenGroup {
+    const void* x[kMaxGroup];       // bf16 layer input, all rows
+    const void* Wq[kMaxGroup];      // panels of the query matrix
+    const float* bq[kMaxGroup];
+    const void* WkT[kMaxGroup];     // panels of the transposed key matrix
+    void* qt[kMaxGroup];            // bf16 [B][H / 8][16][8]
+    void* xbar[kMaxGroup];          // per head a bf16 [B][H] panel matrix, xbar_stride elements apart
+};
+hipError_t launch_first_query(const FirstTokenGroup& g, int G, const int32_t* seq_start, int B, int H, int A, int max_rows, hipStream_t stream);
+hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
+                               int64_t xbar_stride, hipStream_t stream);
+
 // float32 operands, products and sums; any shape.
 hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t stream);
 
@@ -87,7 +164,7 @@ struct CastGroup {
 };
 hipError_t launch_cast_bf16_to_e4m3(const CastGroup& g, int G, int M, const int32_t* d_M, int H, hipStream_t stream);
 // out[b*S+s][:] = x[row_of[b*S+s]][:] or 0 (float32, H columns)
-hipError_t launch_unpack_rows(const float* x, const int32_t* row_of, int n_pos, int H, float* out, hipStream_t stream);
+hipError_t launch_unpack_rows(const float* x, const int32_t* row_of, int n_pos, int H, float* out, hipStream_t stream, int tiled = 0);
 
 // Longest sequence the bf16 attention kernel takes: the keys and values of one (sequence, head) are staged in
 // LDS as a whole, 260 bytes per key (rounded up to 32 keys) within the CU's 160 KB.
@@ -98,9 +175,10 @@ struct AttnGroup {
 };
 // Sequence b owns rows seq_start[b] .. +seq_len[b]-1 (all real tokens) when the two arrays are given;
 // otherwise rows b*S .. b*S+S-1 with `mask` ([B][S], 1 = real) marking the keys.  S bounds the length.
+// tiled: qkv and ctx in the panel layout (rows of 3H and H columns).
 // ctx_fmt 0: the context is written as bfloat16; 1: as E4M3 at unit scale (one byte per element, same row order)
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0);
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0, int tiled = 0);
 hipError_t launch_attention_f32(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream);
 
@@ -137,6 +215,8 @@ hipError_t launch_gather_rows(const SplitGroup& g, int G, int B, int H, const in
                               hipStream_t stream);
 hipError_t launch_cls_split(const SplitGroup& g, int G, int B, int H, const int32_t* seq_start, int rows_per_seq, int max_rows,
                             hipStream_t stream);
+// panel layout, x[g] all rows (seq_start given, none compact)
+hipError_t launch_split_first_rows_tiled(const SplitGroup& g, int G, int B, int H, const int32_t* seq_start, int max_rows, hipStream_t stream);
 
 // First-token rows of every sequence, gathered into compact [B][H] arrays: float32 and/or element-type copies.
 struct FirstRowsGroup {
@@ -148,7 +228,7 @@ struct FirstRowsGroup {
 hipError_t launch_gather_first_rows(const FirstRowsGroup& g, int G, int B, int H, int act_bytes, const int32_t* seq_start,
                                     int max_rows, hipStream_t stream);
 // out[b][s][:] = (s == 0) ? x[b][:] : 0 for a [B][S][H] float32 output
-hipError_t launch_place_first_rows(const float* x, int B, int S, int H, float* out, hipStream_t stream);
+hipError_t launch_place_first_rows(const float* x, int B, int S, int H, float* out, hipStream_t stream, int tiled = 0);
 
 // Attention for the first-token query of every sequence only (the last layer of a branch needs nothing else):
 // q[g] is [B][H] (one query row per sequence), keys and values come from kv[g] = [rows][3H] (columns H.. and 2H..),
@@ -185,6 +265,8 @@ struct ClsGroup {
 // out_row: optional device array [B], logits row of compact row b (per-sequence routing); NULL = row b.
 hipError_t launch_classifier(const ClsGroup& g, int G, int B, int H, int maxC, int w_bf16, int64_t ldo, const int32_t* out_row,
                              hipStream_t stream);
+// bf16 Wc, pooled in the panel layout
+hipError_t launch_classifier_tiled(const ClsGroup& g, int G, int B, int H, int maxC, int64_t ldo, const int32_t* out_row, hipStream_t stream);
 
 // Token-level heads: out[g][p*ldo + c] = Wc[g][c] . x[g][row_of[p]] + bc[g][c] for every position p = b*S+s that is a
 // kept row (row_of[p] in [0, *n_rows)), zeros for the positions that are not; positions with row_of[p] == -2 are
@@ -196,8 +278,9 @@ struct TokGroup {
     float* out[kMaxGroup];            // first logit column of the task at position 0, position stride ldo
     int32_t C[kMaxGroup];
 };
+// tiled: x in the panel layout.
 hipError_t launch_token_classifier(const TokGroup& g, int G, int n_pos, int H, int w_bf16, int64_t ldo, const int32_t* row_of,
-                                   const int32_t* n_rows, hipStream_t stream);
+                                   const int32_t* n_rows, hipStream_t stream, int tiled = 0);
 
 // Several request batches served by one forward pass: request r's ids and mask ([batch][seq] each) are copied behind
 // one another into contiguous staging arrays, and afterwards the logits rows of the combined batch go back to each

@@ -84,7 +84,7 @@ struct Scratch {   // byte offsets into the workspace; one set for the trunk and
     int y_parts;   // y holds this many [M][H] float32 partial products (K ranges of a split contraction)
 };
 struct ClsScratch {   // per task with own layers: compact [max_batch] x ... buffers of its last, first-token-only layer
-    size_t in_f, in_a, q, ctx, y, x1f, x1a, u, out_f;
+    size_t in_f = 0, in_a = 0, q = 0, ctx, y, x1f, x1a, u, out_f;      // (panel layout: no in_f, in_a, q)
     size_t qt = 0, scores = 0, xbar = 0;   // bf16 mode: Wk^T q [max_batch][A_pad][H], raw scores [M][A_pad], weighted row sums
 };
 struct RouteMapOff {   // byte offsets of a sub-batch row map (per-sequence routing), one per task
@@ -105,6 +105,7 @@ struct mt_model {
     bool bf16 = true;
     bool fp8 = false;   // MT_FP8_FFN / MT_FP8_LAYER: bf16 everywhere, the two feed-forward contractions of every all-rows layer in E4M3
     bool fp8_attn = false;   // MT_FP8_LAYER: the QKV and attention output projections of such a layer too
+    bool tiled = false;      // MT_BF16 with up to 16 heads: weights, operands and states in the panel layout (kernels.h)
     size_t esz = 2;   // bytes per matrix / activation element
     int C_tot = 0, C_tok = 0;            // widths of the per-sequence and of the per-token logit row
     std::vector<int> logit_off;          // task -> first column inside the row of its kind
@@ -116,7 +117,7 @@ struct mt_model {
     size_t weight_bytes = 0;
 
     // workspace
-    size_t Mmax = 0;
+    size_t Mmax = 0, MBmax = 0;               // rows of a state, and of a one-row-per-sequence matrix
     std::vector<int> tap_of_layer;            // layer index 0..D -> tap slot or -1
     std::vector<size_t> tap_f, tap_b;         // per tap slot
     size_t pp_f[2] = {0, 0}, pp_b[2] = {0, 0};
@@ -217,6 +218,20 @@ Scratch layout_scratch(Bump& b, size_t M, size_t H, size_t F, size_t esz, bool b
     return s;
 }
 
+// Panel layout: the feed-forward buffer lies over the projections and contexts, which are dead when it is written.
+Scratch layout_scratch_tiled(Bump& b, size_t M, size_t H, size_t F, int y_parts)
+{
+    Scratch s;
+    s.y_parts = y_parts;
+    s.qkv = b.take(std::max(align_up(M * 3 * H * 2) + M * H * 2, M * F * 2));
+    s.ctx = s.qkv + align_up(M * 3 * H * 2);
+    s.u = s.qkv;
+    s.y = b.take((size_t)y_parts * M * H * 4);
+    s.x1f = b.take(M * H * 4);
+    s.x1b = b.take(M * H * 2);
+    return s;
+}
+
 inline uint16_t f32_to_bf16_rne(float f)
 {
     uint32_t u;
@@ -289,16 +304,54 @@ void put_matrix(unsigned char* dst, const float* src, size_t n, bool bf16)
     for (auto& t : th) t.join();
 }
 
+// [N][K] float32 -> the panel layout in bf16 (N a multiple of 32, K of 8).
+void put_tiled(unsigned char* dst, const float* src, size_t N, size_t K, size_t width = 0, size_t col0 = 0)
+{
+    uint16_t* d = reinterpret_cast<uint16_t*>(dst);
+    if (!width) width = K;
+    auto panels = [=](size_t lo, size_t hi) {
+        for (size_t p = lo; p < hi; ++p)
+            for (size_t r = 0; r < 32; ++r) {
+                const float* row = src + (p * 32 + r) * K;
+                for (size_t k = 0; k < K; k += 8) {
+                    uint16_t* o = d + tiled_offset(p * 32 + r, col0 + k, width);
+                    for (size_t e = 0; e < 8; ++e) o[e] = f32_to_bf16_rne(row[k + e]);
+                }
+            }
+    };
+    const size_t n_panels = N / 32;
+    const size_t nthreads = N * K > (1u << 19) ? std::min<size_t>({8, n_panels, std::max(1u, std::thread::hardware_concurrency())}) : 1;
+    if (nthreads <= 1) {
+        panels(0, n_panels);
+        return;
+    }
+    std::vector<std::thread> th;
+    const size_t per = (n_panels + nthreads - 1) / nthreads;
+    for (size_t t = 0; t < nthreads && t * per < n_panels; ++t) th.emplace_back(panels, t * per, std::min(n_panels, (t + 1) * per));
+    for (auto& t : th) t.join();
+}
+
 // Convert one encoder layer from the blob order into the arena image; returns floats consumed.
 size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* img, size_t img_base)
 {
     const size_t H = m->cfg.hidden, F = m->cfg.ffn;
     const float* p0 = p;
     auto at = [&](size_t off) { return img + (off - img_base); };
+    auto put_linear = [&](unsigned char* dst, const float* src, size_t N, size_t K) {
+        if (m->tiled) put_tiled(dst, src, N, K);
+        else put_matrix(dst, src, N * K, m->bf16);
+    };
     if (L.WkT) {                    // Wk^T for the first-token attention of a task's last layer (bf16 mode)
         const float* wk = p + (H * H + H);
-        std::vector<float> col(H);
-        for (size_t n = 0; n < H; ++n) {
+        if (m->tiled) {
+            std::vector<float> t(H * H);
+            for (size_t r0 = 0; r0 < H; r0 += 32)
+                for (size_t n = 0; n < H; ++n)
+                    for (size_t r = r0; r < r0 + 32; ++r) t[n * H + r] = wk[r * H + n];
+            put_tiled(at(L.WkT), t.data(), H, H);
+        }
+        std::vector<float> col(m->tiled ? 0 : H);
+        for (size_t n = 0; n < H && !m->tiled; ++n) {
             for (size_t r = 0; r < H; ++r) col[r] = wk[r * H + n];
             put_matrix(at(L.WkT) + n * H * 2, col.data(), H, true);
         }
@@ -315,12 +368,12 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
         L.inv_sqkv = 1.0f / sc;
     }
     for (int i = 0; i < 3; ++i) {   // Wq bq Wk bk Wv bv -> one [3H,H] matrix and one [3H] bias
-        put_matrix(at(L.Wqkv) + (size_t)i * H * H * m->esz, p, H * H, m->bf16);
+        put_linear(at(L.Wqkv) + (size_t)i * H * H * m->esz, p, H, H);
         p += H * H;
         memcpy(at(L.bqkv) + (size_t)i * H * 4, p, H * 4);
         p += H;
     }
-    put_matrix(at(L.Wo), p, H * H, m->bf16);
+    put_linear(at(L.Wo), p, H, H);
     if (L.Woq) {
         const float sc = e4m3_scale_for(p, H * H);
         uint8_t* q = at(L.Woq);
@@ -337,11 +390,11 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
         for (size_t i = 0; i < n; ++i) q[i] = f32_to_e4m3_rne(w[i] * sc);
         return 1.0f / sc;
     };
-    put_matrix(at(L.W1), p, F * H, m->bf16);
+    put_linear(at(L.W1), p, F, H);
     if (L.W1q) L.inv_s1 = put_e4m3(L.W1q, p, F * H);
     p += F * H;
     memcpy(at(L.b1), p, F * 4); p += F;
-    put_matrix(at(L.W2), p, H * F, m->bf16);
+    put_linear(at(L.W2), p, H, F);
     if (L.W2q) L.inv_s2 = put_e4m3(L.W2q, p, H * F);
     p += H * F;
     memcpy(at(L.b2), p, H * 4); p += H;
@@ -402,6 +455,12 @@ struct Launcher {
         begin(klass);
         if (m->bf16) check(launch_gemm_bf16(g, s, st));
         else check(launch_gemm_f32(g, s, st));
+        end();
+    }
+    void tiled(int klass, const TiledGroup& g, const TiledShape& s)
+    {
+        begin(klass);
+        check(launch_gemm_tiled(g, s, st));
         end();
     }
 };
@@ -604,6 +663,7 @@ struct LastIO {
     const LayerW* w;
     const Scratch* scr;    // qkv buffer receives K | V of all rows
     const ClsScratch* cls;
+    size_t split;          // panel layout: workspace offset of the pooler's [hi | lo] operand
 };
 
 void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowMap& rm, int B, int S)
@@ -805,6 +865,216 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
     L.end();
 }
 
+// ---- the bfloat16 path on the panel layout (MT_BF16, up to 16 heads)
+
+uint32_t units(size_t byte_offset) { return (uint32_t)(byte_offset / 256); }      // arena offsets are multiples of 256 bytes
+
+TiledGroup tiled_group(const mt_model* m)
+{
+    TiledGroup g;
+    g.A = m->ws_act;
+    g.W = m->d_w;
+    g.C = m->ws_act;
+    g.bias = reinterpret_cast<const float*>(m->d_w);
+    for (int i = 0; i < kMaxGroup; ++i) g.b[i] = kNoBias;
+    return g;
+}
+
+// K ranges of a contraction with a float32 result: a long K over few output blocks (a row bound of up to 128 at 768 columns) leaves
+// most of the chip idle otherwise; 36 rows x 768 x 3072: 10 us whole, 4.4 us in 4 ranges that the LayerNorm adds up.  The number of
+// problems does not enter: a task's result does not depend on which others are enabled.
+int tiled_splits(int M, int N, int K, int most)
+{
+    if (K < 2048) return 1;
+    const long blocks = (long)((M + 31) / 32) * (N / 32);
+    int sp = 1;
+    while (sp < most && blocks * sp < 192 && K % (128 * sp) == 0) sp *= 2;
+    return sp;
+}
+
+void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const RowMap& rm, int B, int S)
+{
+    mt_model* m = L.m;
+    const int H = m->cfg.hidden, F = m->cfg.ffn, A = m->cfg.heads, M = B * S, n = (int)io.size();
+    unsigned char* ws = m->ws_act;
+    const int gelu_act = m->cfg.gelu == MT_GELU_TANH ? ACT_GELU_TANH : ACT_GELU_ERF;
+    auto off = [&](const void* p) { return units(static_cast<const unsigned char*>(p) - ws); };
+    const int64_t part = (int64_t)m->Mmax * H;
+
+    TiledGroup g = tiled_group(m);
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = off(io[i].in_b);
+        g.w[i] = units(io[i].w->Wqkv);
+        g.b[i] = units(io[i].w->bqkv);
+        g.c[i] = units(io[i].scr->qkv);
+    }
+    L.tiled(MT_K_GEMM_QKV, g, TiledShape{n, M, 3 * H, H, H, H, 3 * H, ACT_NONE, 0, rm.n_rows, 1, 0});
+
+    AttnGroup ag;
+    for (int i = 0; i < n; ++i) {
+        ag.qkv[i] = ws + io[i].scr->qkv;
+        ag.ctx[i] = ws + io[i].scr->ctx;
+    }
+    L.begin(MT_K_ATTN);
+    L.check(launch_attention_bf16(ag, n, nullptr, rm.seq_start, rm.seq_len, B, S, H, A, L.st, 0, 1));
+    L.end();
+
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].scr->ctx);
+        g.w[i] = units(io[i].w->Wo);
+        g.b[i] = kNoBias;
+        g.c[i] = units(io[i].scr->y);
+    }
+    L.tiled(MT_K_GEMM_OUT, g, TiledShape{n, M, H, H, H, H, H, ACT_NONE, 1, rm.n_rows, 1, 0});
+
+    TiledLnGroup lg;
+    lg.ws = ws;
+    lg.wt = m->d_w;
+    for (int i = 0; i < n; ++i) {
+        lg.x[i] = units(io[i].scr->y);
+        lg.res[i] = off(io[i].in_f);
+        lg.out_f[i] = units(io[i].scr->x1f);
+        lg.out_b[i] = units(io[i].scr->x1b);
+        lg.bias[i] = units(io[i].w->bo);
+        lg.gamma[i] = units(io[i].w->ln1g);
+        lg.beta[i] = units(io[i].w->ln1b);
+    }
+    TiledLnShape ls{n, M, H, rm.n_rows, m->cfg.ln_eps, 1, part, nullptr, 0, 0};
+    L.begin(MT_K_LN);
+    L.check(launch_layernorm_tiled(lg, ls, L.st));
+    L.end();
+
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].scr->x1b);
+        g.w[i] = units(io[i].w->W1);
+        g.b[i] = units(io[i].w->b1);
+        g.c[i] = units(io[i].scr->u);
+    }
+    L.tiled(MT_K_GEMM_FFN1, g, TiledShape{n, M, F, H, H, H, F, gelu_act, 0, rm.n_rows, 1, 0});
+
+    const int sp = n == 1 && io[0].scr->y_parts >= 4 ? tiled_splits(M, H, F, 4) : 1;      // (only the trunk has room for partial results)
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].scr->u);
+        g.w[i] = units(io[i].w->W2);
+        g.b[i] = kNoBias;
+        g.c[i] = units(io[i].scr->y);
+    }
+    L.tiled(MT_K_GEMM_FFN2, g, TiledShape{n, M, H, F, F, F, H, ACT_NONE, 1, rm.n_rows, sp, part});
+
+    for (int i = 0; i < n; ++i) {
+        lg.res[i] = units(io[i].scr->x1f);
+        lg.out_f[i] = off(io[i].out_f);
+        lg.out_b[i] = off(io[i].out_b);
+        lg.bias[i] = units(io[i].w->b2);
+        lg.gamma[i] = units(io[i].w->ln2g);
+        lg.beta[i] = units(io[i].w->ln2b);
+    }
+    ls.n_parts = sp;
+    L.begin(MT_K_LN);
+    L.check(launch_layernorm_tiled(lg, ls, L.st));
+    L.end();
+}
+
+// The last own layer of n tasks for the first token of every sequence; writes the pooler's operand as well.
+void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, const RowMap& rm, int B, int S)
+{
+    mt_model* m = L.m;
+    const int H = m->cfg.hidden, F = m->cfg.ffn, A = m->cfg.heads, M = B * S, n = (int)io.size();
+    unsigned char* ws = m->ws_act;
+    const int gelu_act = m->cfg.gelu == MT_GELU_TANH ? ACT_GELU_TANH : ACT_GELU_ERF;
+    auto off = [&](const void* p) { return units(static_cast<const unsigned char*>(p) - ws); };
+    const size_t MB = m->MBmax;
+    const int64_t part = (int64_t)MB * H, xbar_stride = (int64_t)MB * H;
+
+    FirstTokenGroup fg;
+    for (int i = 0; i < n; ++i) {
+        fg.x[i] = io[i].in_a;
+        fg.Wq[i] = m->d_w + io[i].w->Wqkv;
+        fg.bq[i] = (const float*)(m->d_w + io[i].w->bqkv);
+        fg.WkT[i] = m->d_w + io[i].w->WkT;
+        fg.qt[i] = ws + io[i].cls->qt;
+        fg.xbar[i] = ws + io[i].cls->xbar;
+    }
+    L.begin(MT_K_GEMM_FIRST);
+    L.check(launch_first_query(fg, n, rm.seq_start, B, H, A, M, L.st));
+    L.end();
+    L.begin(MT_K_ATTN);
+    L.check(launch_first_attend(fg, n, rm.seq_start, rm.seq_len, B, S, H, A, xbar_stride, L.st));
+    L.end();
+
+    // contexts: per head, [B x H] row sums against the head's 64 rows of Wv
+    TiledGroup g = tiled_group(m);
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].cls->xbar);
+        g.w[i] = units(io[i].w->Wqkv + (size_t)2 * H * H * 2);
+        g.b[i] = units(io[i].w->bqkv + (size_t)2 * H * 4);
+        g.c[i] = units(io[i].cls->ctx);
+    }
+    TiledShape s{n, B, 64, H, H, H, H, ACT_NONE, 0, nullptr, 1, 0};
+    s.n_sub = A;
+    s.sub_a = (int32_t)units((size_t)xbar_stride * 2);
+    s.sub_w = (int32_t)units((size_t)64 * H * 2);
+    s.sub_c = (int32_t)units(8 * 512);
+    s.sub_b = 1;
+    L.tiled(MT_K_GEMM_FIRST, g, s);
+
+    const int sp_o = tiled_splits(B, H, H, 2);
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].cls->ctx);
+        g.w[i] = units(io[i].w->Wo);
+        g.b[i] = kNoBias;
+        g.c[i] = units(io[i].cls->y);
+    }
+    L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, H, H, H, H, ACT_NONE, 1, nullptr, sp_o, part});
+
+    TiledLnGroup lg;
+    lg.ws = ws;
+    lg.wt = m->d_w;
+    for (int i = 0; i < n; ++i) {
+        lg.x[i] = units(io[i].cls->y);
+        lg.res[i] = off(io[i].in_f);
+        lg.out_f[i] = units(io[i].cls->x1f);
+        lg.out_b[i] = units(io[i].cls->x1a);
+        lg.bias[i] = units(io[i].w->bo);
+        lg.gamma[i] = units(io[i].w->ln1g);
+        lg.beta[i] = units(io[i].w->ln1b);
+    }
+    TiledLnShape ls{n, B, H, nullptr, m->cfg.ln_eps, sp_o, part, rm.seq_start, M, 0};
+    L.begin(MT_K_LN);
+    L.check(launch_layernorm_tiled(lg, ls, L.st));
+    L.end();
+
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].cls->x1a);
+        g.w[i] = units(io[i].w->W1);
+        g.b[i] = units(io[i].w->b1);
+        g.c[i] = units(io[i].cls->u);
+    }
+    L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, F, H, H, H, F, gelu_act, 0, nullptr, 1, 0});
+
+    const int sp_f = tiled_splits(B, H, F, 2);
+    for (int i = 0; i < n; ++i) {
+        g.a[i] = units(io[i].cls->u);
+        g.w[i] = units(io[i].w->W2);
+        g.b[i] = kNoBias;
+        g.c[i] = units(io[i].cls->y);
+    }
+    L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, F, F, F, H, ACT_NONE, 1, nullptr, sp_f, part});
+
+    for (int i = 0; i < n; ++i) {
+        lg.res[i] = units(io[i].cls->x1f);
+        lg.out_f[i] = units(io[i].cls->out_f);
+        lg.out_b[i] = units(io[i].split);
+        lg.bias[i] = units(io[i].w->b2);
+        lg.gamma[i] = units(io[i].w->ln2g);
+        lg.beta[i] = units(io[i].w->ln2b);
+    }
+    ls = TiledLnShape{n, B, H, nullptr, m->cfg.ln_eps, sp_f, part, nullptr, 0, 1};
+    L.begin(MT_K_LN);
+    L.check(launch_layernorm_tiled(lg, ls, L.st));
+    L.end();
+}
+
 }  // namespace
 
 extern "C" {
@@ -860,6 +1130,7 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->bf16 = cfg->precision != MT_FP32_CHECK;
     m->fp8 = cfg->precision == MT_FP8_FFN || cfg->precision == MT_FP8_LAYER;
     m->fp8_attn = cfg->precision == MT_FP8_LAYER;
+    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16;
     m->esz = m->bf16 ? 2 : 4;
     const size_t H = cfg->hidden, F = cfg->ffn, T = cfg->n_tasks, D = cfg->n_trunk_layers;
     for (const auto& d : m->tasks) {
@@ -893,7 +1164,10 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->weight_bytes = wb.off;
 
     // ---- workspace
-    m->Mmax = (size_t)cfg->max_batch * cfg->max_seq;
+    // (panel layout: row counts are whole panels)
+    auto rows = [&](size_t n) { return m->tiled ? (n + 31) / 32 * 32 : n; };
+    m->Mmax = rows((size_t)cfg->max_batch * cfg->max_seq);
+    m->MBmax = rows((size_t)cfg->max_batch);
     const size_t M = m->Mmax;
     Bump sb;
     m->tap_of_layer.assign(D + 1, -1);
@@ -908,18 +1182,35 @@ int mt_create(const mt_config* cfg, mt_model** out)
         m->pp_f[i] = sb.take(M * H * 4);
         m->pp_b[i] = m->bf16 ? sb.take(M * H * 2) : 0;
     }
-    m->trunk_scr = layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
-    const size_t MB = (size_t)cfg->max_batch;
+    m->trunk_scr = m->tiled ? layout_scratch_tiled(sb, M, H, F, 4) : layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
+    const size_t MB = m->MBmax;
     for (size_t t = 0; t < T; ++t) {
         if (m->tasks[t].n_layers > 0 && m->tasks[t].head == MT_HEAD_TOKEN) {   // every layer runs on all rows
-            m->task_scr.push_back(layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
+            m->task_scr.push_back(m->tiled ? layout_scratch_tiled(sb, M, H, F, 1) : layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
             m->task_xf.push_back(sb.take(M * H * 4));
             m->task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
             m->task_cls.push_back(ClsScratch{});
         } else if (m->tasks[t].n_layers > 0) {
-            m->task_scr.push_back(layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
+            const size_t scr_begin = sb.off;
+            m->task_scr.push_back(m->tiled ? layout_scratch_tiled(sb, M, H, F, 1) : layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
+            const size_t scr_end = sb.off;
+            if (m->tiled) {        // the first-token layer's buffers lie over those of the full layers before it
+                sb.off = scr_begin;
+                ClsScratch c;
+                c.qt = sb.take(MB * 16 * H * 2);
+                c.xbar = sb.take((size_t)cfg->heads * MB * H * 2);
+                c.ctx = sb.take(MB * H * 2);
+                c.y = sb.take(4 * MB * H * 4);
+                c.x1f = sb.take(MB * H * 4);
+                c.x1a = sb.take(MB * H * 2);
+                c.u = sb.take(MB * F * 2);
+                c.out_f = sb.take(MB * H * 4);
+                sb.off = std::max(sb.off, scr_end);
+                m->task_cls.push_back(c);
+            }
             m->task_xf.push_back(sb.take(M * H * 4));
             m->task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
+            if (m->tiled) continue;
             ClsScratch c;
             c.in_f = sb.take(MB * H * 4);
             c.in_a = m->bf16 ? sb.take(MB * H * 2) : c.in_f;
@@ -959,8 +1250,8 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->rm_rowof = sb.take(M * 4);
     m->rm_start = sb.take((size_t)cfg->max_batch * 4);
     m->rm_len = sb.take((size_t)cfg->max_batch * 4);
-    m->pooled = sb.take(T * (size_t)cfg->max_batch * H * 4);
-    m->cls_split = sb.take(T * (size_t)cfg->max_batch * H * 4);   // [hi | lo] bf16 halves, or float32 rows in the validation mode
+    m->pooled = sb.take(T * MB * H * 4);
+    m->cls_split = sb.take(T * MB * H * 4);   // [hi | lo] bf16 halves, or float32 rows in the validation mode
     m->chk_count = sb.take(4);
     m->mr_ids = sb.take(M * 4);
     m->mr_mask = sb.take(M * 4);
@@ -1137,6 +1428,9 @@ int mt_load_weights(mt_model* m, int32_t scope, const void* h_blob, size_t nbyte
         const bool seq_head = m->tasks[scope].head == MT_HEAD_SEQUENCE;
         if (!seq_head) {
             // a token-level scope carries no pooler
+        } else if (m->tiled) {  // [W | W]
+            put_tiled(at(tw.Wp), p, H, H, 2 * H, 0);
+            put_tiled(at(tw.Wp), p, H, H, 2 * H, H);
         } else if (m->bf16) {   // rows of [W | W]
             std::vector<uint16_t> row(H);
             for (size_t r = 0; r < H; ++r) {
@@ -1255,6 +1549,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             ob = bf ? (void*)(ws + m->pp_b[pp]) : nullptr;
         }
     };
+    auto split_of = [&](int t) { return m->cls_split + (size_t)t * m->MBmax * H * 4; };
     RowMap rm{(int32_t*)(ws + m->rm_n), (int32_t*)(ws + m->rm_src), (int32_t*)(ws + m->rm_rowof), (int32_t*)(ws + m->rm_start),
               (int32_t*)(ws + m->rm_len)};
     float* cur_f;
@@ -1262,6 +1557,11 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     trunk_out(0, 0, cur_f, cur_b);
     L.begin(MT_K_EMBED);
     L.check(launch_build_row_map(d_attn_mask, B, S, rm, L.st));
+    if (m->tiled)
+        L.check(launch_embed_ln_tiled(d_input_ids, d_token_type_ids, m->cfg.type_vocab, rm.src, rm.n_rows, B, S, H, m->cfg.vocab, W + m->w_word,
+                                      W + m->w_pos, W + m->w_type, (const float*)(W + m->w_embg), (const float*)(W + m->w_embb), m->cfg.ln_eps,
+                                      cur_f, cur_b, L.st));
+    else
     L.check(launch_embed_ln(d_input_ids, d_token_type_ids, m->cfg.type_vocab, rm.src, rm.n_rows, B, S, H, m->cfg.vocab, W + m->w_word, W + m->w_pos, W + m->w_type, bf ? 1 : 0,
                             (const float*)(W + m->w_embg), (const float*)(W + m->w_embb), m->cfg.ln_eps, cur_f,
                             (bf16_t*)cur_b, L.st));
@@ -1300,7 +1600,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                 in_b = bf ? (const void*)(ws + m->task_xb[t]) : nullptr;
             }
             if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE) {
-                last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t]});
+                last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t], split_of(t)});
             } else {
                 full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &m->task_scr[t], (float*)(ws + m->task_xf[t]),
                                        bf ? (void*)(ws + m->task_xb[t]) : nullptr});
@@ -1308,11 +1608,11 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         }
         for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
             std::vector<LayerIO> part(full.begin() + lo, full.begin() + std::min(full.size(), lo + (size_t)kMaxGroup));
-            run_layer_group(L, part, rm, B, S);
+            (m->tiled ? run_layer_group_tiled : run_layer_group)(L, part, rm, B, S);
         }
         for (size_t lo = 0; lo < last.size(); lo += kMaxGroup) {
             std::vector<LastIO> part(last.begin() + lo, last.begin() + std::min(last.size(), lo + (size_t)kMaxGroup));
-            run_last_layer_group(L, part, rm, B, S);
+            (m->tiled ? run_last_layer_group_tiled : run_last_layer_group)(L, part, rm, B, S);
         }
         if (step < depth) {
             cur_f = nf;
@@ -1334,31 +1634,50 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         memset(&sg, 0, sizeof sg);
         ClsGroup cg;
         memset(&cg, 0, sizeof cg);
-        int maxC = 0;
+        TiledGroup tg = tiled_group(m);
+        int maxC = 0, n_split = 0;
         for (int i = 0; i < n; ++i) {
             const int t = list[lo + i];
             const mt_task_desc& d = m->tasks[t];
             const float* z = d.n_layers > 0 ? (const float*)(ws + m->task_cls[t].out_f)     // one row per sequence already
                              : gathered     ? (const float*)(ws + m->task_xf[t])          // the sub-batch's copy of the tap
                                             : (const float*)(ws + m->tap_f[m->tap_of_layer[d.fork_layer]]);
-            float* pooled = (float*)(ws + m->pooled + (size_t)t * m->cfg.max_batch * H * 4);
-            sg.x[i] = z;
-            sg.compact[i] = d.n_layers > 0 ? 1 : 0;
-            sg.out[i] = bf ? (bf16_t*)(ws + m->cls_split + (size_t)t * m->cfg.max_batch * 2 * H * 2)
-                           : (bf16_t*)(ws + m->cls_split + (size_t)t * m->cfg.max_batch * H * 4);   // fp32 mode: float32 rows
-            g.A[i] = bf ? (const void*)sg.out[i] : (const void*)(ws + m->cls_split + (size_t)t * m->cfg.max_batch * H * 4);
-            g.W[i] = W + m->taskw[t].Wp;
-            g.bias[i] = (const float*)(W + m->taskw[t].bp);
-            g.C[i] = pooled;
-            g.N[i] = H;
+            float* pooled = (float*)(ws + m->pooled + (size_t)t * m->MBmax * H * 4);
             cg.pooled[i] = pooled;
             cg.Wc[i] = W + m->taskw[t].Wc;
             cg.bc[i] = (const float*)(W + m->taskw[t].bc);
             cg.out[i] = d_out_logits + m->logit_off[t];
             cg.C[i] = d.n_classes;
             maxC = std::max(maxC, d.n_classes);
+            if (m->tiled) {
+                if (d.n_layers == 0) {             // the others' operands were written with their last LayerNorm
+                    sg.x[n_split] = z;
+                    sg.out[n_split++] = (bf16_t*)(ws + split_of(t));
+                }
+                tg.a[i] = units(split_of(t));
+                tg.w[i] = units(m->taskw[t].Wp);
+                tg.b[i] = units(m->taskw[t].bp);
+                tg.c[i] = units((const unsigned char*)pooled - ws);
+                continue;
+            }
+            sg.x[i] = z;
+            sg.compact[i] = d.n_layers > 0 ? 1 : 0;
+            sg.out[i] = bf ? (bf16_t*)(ws + m->cls_split + (size_t)t * m->MBmax * 2 * H * 2)
+                           : (bf16_t*)(ws + m->cls_split + (size_t)t * m->MBmax * H * 4);   // fp32 mode: float32 rows
+            g.A[i] = bf ? (const void*)sg.out[i] : (const void*)(ws + m->cls_split + (size_t)t * m->MBmax * H * 4);
+            g.W[i] = W + m->taskw[t].Wp;
+            g.bias[i] = (const float*)(W + m->taskw[t].bp);
+            g.C[i] = pooled;
+            g.N[i] = H;
         }
         L.begin(MT_K_POOL);
+        if (m->tiled) {
+            L.check(launch_split_first_rows_tiled(sg, n_split, HB, H, hrm.seq_start, HB * S, L.st));
+            L.check(launch_gemm_tiled(tg, TiledShape{n, HB, H, 2 * H, 2 * H, 2 * H, H, ACT_TANH, 1, nullptr, 1, 0}, L.st));
+            L.check(launch_classifier_tiled(cg, n, HB, H, maxC, m->C_tot, out_row, L.st));
+            L.end();
+            continue;
+        }
         if (bf) {
             L.check(launch_cls_split(sg, n, HB, H, hrm.seq_start, S, HB * S, L.st));
             GemmShape s{n, HB, H, 2 * H, 2 * H, H, 0, ACT_TANH, 1, nullptr, 1, 0};
@@ -1393,7 +1712,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                 tg.C[i] = d.n_classes;
             }
             L.begin(MT_K_POOL);
-            L.check(launch_token_classifier(tg, n, B * S, H, bf ? 1 : 0, m->C_tok, pos_row, n_rows, L.st));
+            L.check(launch_token_classifier(tg, n, B * S, H, bf ? 1 : 0, m->C_tok, pos_row, n_rows, L.st, m->tiled ? 1 : 0));
             L.end();
         }
     };
@@ -1450,12 +1769,27 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             int32_t* c_seq = (int32_t*)(ws + ro.seq);
             GL.begin(MT_K_EMBED);
             GL.check(launch_route_map(idx, nb, rm.seq_start, rm.seq_len, crm.seq_start, crm.seq_len, crm.src, c_seq, crm.n_rows, GL.st));
+            RowCopyGroup rc;
+            int n_copy = 0;
+            auto flush_copies = [&] {
+                GL.check(launch_copy_rows_tiled(rc, n_copy, crm.src, crm.n_rows, nb * S, B * S, H, GL.st));
+                n_copy = 0;
+            };
             for (int t : grp_tasks) {
                 const int tap = m->tap_of_layer[m->tasks[t].fork_layer];
+                if (m->tiled) {
+                    rc.in_f[n_copy] = (const float*)(ws + m->tap_f[tap]);
+                    rc.in_b[n_copy] = ws + m->tap_b[tap];
+                    rc.out_f[n_copy] = (float*)(ws + m->task_xf[t]);
+                    rc.out_b[n_copy++] = ws + m->task_xb[t];
+                    if (n_copy == kMaxGroup) flush_copies();
+                    continue;
+                }
                 GL.check(launch_route_gather((const float*)(ws + m->tap_f[tap]), bf ? (const void*)(ws + m->tap_b[tap]) : nullptr,
                                              (float*)(ws + m->task_xf[t]), bf ? (void*)(ws + m->task_xb[t]) : nullptr, crm.src, crm.n_rows,
                                              nb * S, H, 2, GL.st));
             }
+            flush_copies();
             GL.end();
             int gy = 0;
             for (int t : grp_tasks) gy = std::max(gy, m->tasks[t].n_layers);
@@ -1468,18 +1802,18 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                     const float* in_f = (const float*)(ws + m->task_xf[t]);
                     const void* in_b = bf ? (const void*)(ws + m->task_xb[t]) : nullptr;
                     if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE)
-                        last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t]});
+                        last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t], split_of(t)});
                     else
                         full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &m->task_scr[t], (float*)(ws + m->task_xf[t]),
                                                bf ? (void*)(ws + m->task_xb[t]) : nullptr});
                 }
                 for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
                     std::vector<LayerIO> part(full.begin() + lo, full.begin() + std::min(full.size(), lo + (size_t)kMaxGroup));
-                    run_layer_group(GL, part, crm, nb, S);
+                    (m->tiled ? run_layer_group_tiled : run_layer_group)(GL, part, crm, nb, S);
                 }
                 for (size_t lo = 0; lo < last.size(); lo += kMaxGroup) {
                     std::vector<LastIO> part(last.begin() + lo, last.begin() + std::min(last.size(), lo + (size_t)kMaxGroup));
-                    run_last_layer_group(GL, part, crm, nb, S);
+                    (m->tiled ? run_last_layer_group_tiled : run_last_layer_group)(GL, part, crm, nb, S);
                 }
             }
             run_heads(GL, grp_tasks, crm, nb, true, c_seq);
@@ -1700,7 +2034,7 @@ int mt_read_hidden(mt_model* m, int32_t task, int32_t layer, float* d_out, size_
             src = m->ws_act + m->task_xf[task];
         } else if (d.n_layers > 0) {   // only the first-token rows of a branch's final state exist
             hipError_t e = launch_place_first_rows((const float*)(m->ws_act + m->task_cls[task].out_f), m->last_B, m->last_S,
-                                                   m->cfg.hidden, d_out, static_cast<hipStream_t>(hip_stream));
+                                                   m->cfg.hidden, d_out, static_cast<hipStream_t>(hip_stream), m->tiled ? 1 : 0);
             if (e != hipSuccess) return fail(m, MT_ERR_HIP, "mt_read_hidden: %s", hipGetErrorString(e));
             return MT_OK;
         } else {
@@ -1708,7 +2042,7 @@ int mt_read_hidden(mt_model* m, int32_t task, int32_t layer, float* d_out, size_
         }
     }
     hipError_t e = launch_unpack_rows((const float*)src, (const int32_t*)(m->ws_act + m->rm_rowof), m->last_B * m->last_S, m->cfg.hidden,
-                                      d_out, static_cast<hipStream_t>(hip_stream));
+                                      d_out, static_cast<hipStream_t>(hip_stream), m->tiled ? 1 : 0);
     if (e != hipSuccess) return fail(m, MT_ERR_HIP, "mt_read_hidden: %s", hipGetErrorString(e));
     return MT_OK;
 }

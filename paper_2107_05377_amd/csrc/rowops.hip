@@ -309,13 +309,13 @@ __global__ __launch_bounds__(256) void row_place_kernel(int B, int S, int32_t* _
 }
 
 __global__ __launch_bounds__(256) void unpack_rows_kernel(const float* __restrict__ x, const int32_t* __restrict__ row_of, int n_pos,
-                                                          int H, float* __restrict__ out)
+                                                          int H, float* __restrict__ out, int tiled)
 {
     const int p = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (p >= n_pos) return;
     const int r = row_of[p];
-    for (int i = lane; i < H; i += 64) out[(size_t)p * H + i] = r >= 0 ? x[(size_t)r * H + i] : 0.f;
+    for (int i = lane; i < H; i += 64) out[(size_t)p * H + i] = r >= 0 ? x[tiled ? tiled_offset(r, i, H) : (size_t)r * H + i] : 0.f;
 }
 
 __global__ __launch_bounds__(256) void cls_split_kernel(SplitGroup g, int H, const int32_t* __restrict__ seq_start,
@@ -362,14 +362,14 @@ __global__ __launch_bounds__(256) void gather_first_rows_kernel(FirstRowsGroup g
 }
 
 __global__ __launch_bounds__(256) void place_first_rows_kernel(const float* __restrict__ x, int n_pos, int S, int H,
-                                                               float* __restrict__ out)
+                                                               float* __restrict__ out, int tiled)
 {
     const int p = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (p >= n_pos) return;
     const bool first = (p % S) == 0;
-    const float* src = x + (size_t)(p / S) * H;
-    for (int i = lane; i < H; i += 64) out[(size_t)p * H + i] = first ? src[i] : 0.f;
+    const size_t b = p / S;
+    for (int i = lane; i < H; i += 64) out[(size_t)p * H + i] = first ? x[tiled ? tiled_offset(b, i, H) : b * H + i] : 0.f;
 }
 
 template <typename TW>
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(256) void classifier_kernel(ClsGroup g, int B, int 
 // of Wc is fetched once per 4 positions; lanes stride over the hidden dimension, float32 accumulation.
 constexpr int kTokPosPerWave = 4;
 constexpr int kRowSkip = -2;          // row_of value: the position belongs to no sequence of this launch (see launch_route_rowof)
-template <typename TW>
+template <typename TW, bool TILED>
 __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n_pos, int H, int64_t ldo,
                                                                const int32_t* __restrict__ row_of,
                                                                const int32_t* __restrict__ n_rows)
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n
     if (p0 >= n_pos) return;
     const int kept = *n_rows;
     const int C = g.C[grp];
-    const float* xr[kTokPosPerWave];
+    size_t xr[kTokPosPerWave];
     bool live[kTokPosPerWave], skip[kTokPosPerWave];
 #pragma unroll
     for (int j = 0; j < kTokPosPerWave; ++j) {
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n
         const int r = p < n_pos ? row_of[p] : kRowSkip;
         live[j] = r >= 0 && r < kept;
         skip[j] = r == kRowSkip;
-        xr[j] = g.x[grp] + (size_t)(live[j] ? r : 0) * H;
+        xr[j] = live[j] ? r : 0;
     }
     const bool any = live[0] || live[1] || live[2] || live[3];
     for (int c = 0; c < C; ++c) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n
             for (int i = lane; i < H; i += 64) {
                 const float wv = (float)w[i];
 #pragma unroll
-                for (int j = 0; j < kTokPosPerWave; ++j) acc[j] = fmaf(live[j] ? xr[j][i] : 0.f, wv, acc[j]);
+                for (int j = 0; j < kTokPosPerWave; ++j) acc[j] = fmaf(live[j] ? g.x[grp][TILED ? tiled_offset(xr[j], i, H) : xr[j] * H + i] : 0.f, wv, acc[j]);
             }
         }
         const float bias = g.bc[grp][c];
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n
 
 // The same for H = NV * 256: one wavefront per position keeps its row in registers (NV float4 per lane) and takes
 // the classes four at a time, so the loads of four weight rows are in flight together.
-template <typename TW, int NV>
+template <typename TW, int NV, bool TILED>
 __global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, int n_pos, int64_t ldo,
                                                                     const int32_t* __restrict__ row_of,
                                                                     const int32_t* __restrict__ n_rows)
@@ -453,10 +453,13 @@ __global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, 
         for (int c = lane; c < C; c += 64) out[c] = 0.f;
         return;
     }
-    const float* x = g.x[grp] + (size_t)r * H;
+    const float* x = g.x[grp] + (TILED ? tiled_offset(r, 0, H) : (size_t)r * H);
     float4 xv[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) xv[v] = load4<float>(x + (v * 64 + lane) * 4);
+    for (int v = 0; v < NV; ++v) {
+        const int col = (v * 64 + lane) * 4;
+        xv[v] = load4<float>(x + (TILED ? (col >> 3) * 256 + (col & 7) : col));
+    }
     const TW* W = static_cast<const TW*>(g.Wc[grp]);
     for (int c0 = 0; c0 < C; c0 += 4) {
         float acc[4];
@@ -606,26 +609,27 @@ hipError_t launch_gather_first_rows(const FirstRowsGroup& g, int G, int B, int H
     return hipGetLastError();
 }
 
-hipError_t launch_place_first_rows(const float* x, int B, int S, int H, float* out, hipStream_t stream)
+hipError_t launch_place_first_rows(const float* x, int B, int S, int H, float* out, hipStream_t stream, int tiled)
 {
     if (B <= 0 || S <= 0) return hipSuccess;
     const int n_pos = B * S;
     hipLaunchKernelGGL(place_first_rows_kernel, dim3((n_pos + kRowsPerBlock - 1) / kRowsPerBlock), dim3(256), 0, stream, x, n_pos, S, H,
-                       out);
+                       out, tiled);
     return hipGetLastError();
 }
 
 hipError_t launch_token_classifier(const TokGroup& g, int G, int n_pos, int H, int w_bf16, int64_t ldo, const int32_t* row_of,
-                                   const int32_t* n_rows, hipStream_t stream)
+                                   const int32_t* n_rows, hipStream_t stream, int tiled)
 {
     if (G <= 0 || n_pos <= 0) return hipSuccess;
-    if (G > kMaxGroup || !row_of || !n_rows || H < 1) return hipErrorInvalidValue;
+    if (G > kMaxGroup || !row_of || !n_rows || H < 1 || (tiled && !w_bf16)) return hipErrorInvalidValue;
     if (H % 256 == 0 && H <= 1280) {          // classifier rows are then 16-byte aligned for either element type
         const dim3 rgrid((n_pos + 3) / 4, G);
 #define MT_TOK_ROWS(NV)                                                                                                            \
     case NV:                                                                                                                       \
-        if (w_bf16) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows); \
-        else hipLaunchKernelGGL((token_classifier_rows_kernel<float, NV>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows);         \
+        if (tiled) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, true>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows); \
+        else if (w_bf16) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows); \
+        else hipLaunchKernelGGL((token_classifier_rows_kernel<float, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows);       \
         break;
         switch (H / 256) {
             MT_TOK_ROWS(1) MT_TOK_ROWS(2) MT_TOK_ROWS(3) MT_TOK_ROWS(4) MT_TOK_ROWS(5)
@@ -634,8 +638,9 @@ hipError_t launch_token_classifier(const TokGroup& g, int G, int n_pos, int H, i
         return hipGetLastError();
     }
     const dim3 grid((n_pos + 4 * kTokPosPerWave - 1) / (4 * kTokPosPerWave), G);
-    if (w_bf16) hipLaunchKernelGGL((token_classifier_kernel<__bf16>), grid, dim3(256), 0, stream, g, n_pos, H, ldo, row_of, n_rows);
-    else hipLaunchKernelGGL((token_classifier_kernel<float>), grid, dim3(256), 0, stream, g, n_pos, H, ldo, row_of, n_rows);
+    if (tiled) hipLaunchKernelGGL((token_classifier_kernel<__bf16, true>), grid, dim3(256), 0, stream, g, n_pos, H, ldo, row_of, n_rows);
+    else if (w_bf16) hipLaunchKernelGGL((token_classifier_kernel<__bf16, false>), grid, dim3(256), 0, stream, g, n_pos, H, ldo, row_of, n_rows);
+    else hipLaunchKernelGGL((token_classifier_kernel<float, false>), grid, dim3(256), 0, stream, g, n_pos, H, ldo, row_of, n_rows);
     return hipGetLastError();
 }
 
@@ -741,11 +746,11 @@ hipError_t launch_build_row_map(const int32_t* mask, int B, int S, const RowMap&
     return hipGetLastError();
 }
 
-hipError_t launch_unpack_rows(const float* x, const int32_t* row_of, int n_pos, int H, float* out, hipStream_t stream)
+hipError_t launch_unpack_rows(const float* x, const int32_t* row_of, int n_pos, int H, float* out, hipStream_t stream, int tiled)
 {
     if (n_pos <= 0) return hipSuccess;
     hipLaunchKernelGGL(unpack_rows_kernel, dim3((n_pos + kRowsPerBlock - 1) / kRowsPerBlock), dim3(256), 0, stream, x, row_of,
-                       n_pos, H, out);
+                       n_pos, H, out, tiled);
     return hipGetLastError();
 }
 
