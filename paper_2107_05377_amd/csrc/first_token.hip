@@ -1,8 +1,8 @@
 // First-token attention of a branch's last layer on the panel layout, keys and values not projected (bfloat16 path): with
 // q~[b][a] = Wk_a^T (Wq_a x_b + bq_a) the score of key j is q~ . x_j up to a constant that the softmax drops, and the head's context
 // is Wv_a (sum_j p_j x_j) + bv_a.  Two launches per group of tasks (the contexts are one more, gemm_tiled_rows_kernel):
-//   first_query_kernel   one workgroup per (task, 32 sequences, head): query of the sequences' first rows, which are read in place, then
-//                        q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
+//   first_query_kernel   one workgroup per (task, 32 sequences, head): query of the sequences' first rows (gathered before: in place, 16
+//                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences), then q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
 //                        fragments are in flight at once.
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, 32
 //                        keys at a time with a running maximum; a key block is loaded while the one before is worked on.  The sums are
@@ -16,8 +16,9 @@ namespace mt {
 namespace {
 
 constexpr int kHeadsPad = 16;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, const int32_t* __restrict__ seq_start, int B, int H, int max_rows)
+__global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, int B, int H)
 {
     constexpr int U = 12, MAXP = 8;
     __shared__ __attribute__((aligned(16))) float part[4][2][4][64][4];
@@ -38,9 +39,7 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, 
     float4 bv[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const float4*>(g.bq[grp] + a * 64 + j * 32 + wave * 8 + half * 4);
-    const int row = min(seq_start[min(b0 + l32, B - 1)], max_rows - 1);
-    const unsigned char* x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)(row >> 5) * pw + (row & 31) * 16 +
-                             ((size_t)wave * steps * 2 + half) * 512;
+    const unsigned char* x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)blockIdx.y * pw + (size_t)wave * steps * 1024 + lane * 16;
     f32x16 acc[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -136,12 +135,12 @@ __global__ __launch_bounds__(512) void first_attend_kernel(FirstTokenGroup g, co
     bf16x8 qf[SU];
 #pragma unroll
     for (int u = 0; u < SU; ++u) qf[u] = *reinterpret_cast<const bf16x8*>(qt + (size_t)(min(st0 + u, H / 16 - 1) * 2 + half) * 128);
-    uint4 xv[XU];
+    u32x4 xv[XU];
     auto fetch = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < XU; ++u) {
             const int i = tid + u * nt, key = i & 31, chunk = min(i >> 5, n_chunks - 1);
-            xv[u] = *reinterpret_cast<const uint4*>(x + tiled_offset(row0 + min(kb + key, n - 1), chunk * 8, H));
+            xv[u] = *reinterpret_cast<const u32x4*>(x + tiled_offset(row0 + min(kb + key, n - 1), chunk * 8, H));
         }
     };
     float acc[NH][2];
@@ -153,10 +152,10 @@ __global__ __launch_bounds__(512) void first_attend_kernel(FirstTokenGroup g, co
 #pragma unroll
         for (int u = 0; u < XU; ++u) {
             const int i = tid + u * nt;
-            if ((i >> 5) < n_chunks) *reinterpret_cast<uint4*>(xs + (i >> 5) * kChunkStride + (i & 31) * 16) = xv[u];
+            if ((i >> 5) < n_chunks) *reinterpret_cast<u32x4*>(xs + (i >> 5) * kChunkStride + (i & 31) * 16) = xv[u];
         }
         __syncthreads();
-        if (kb + 32 < n) fetch(kb + 32);
+        fetch(kb + 32);                                                      // (beyond the last block: its last key again)
         f32x16 sc;
 #pragma unroll
         for (int e = 0; e < 16; ++e) sc[e] = 0.f;
@@ -240,11 +239,11 @@ __global__ __launch_bounds__(512) void first_attend_kernel(FirstTokenGroup g, co
 
 }  // namespace
 
-hipError_t launch_first_query(const FirstTokenGroup& g, int G, const int32_t* seq_start, int B, int H, int A, int max_rows, hipStream_t stream)
+hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream)
 {
     if (G <= 0 || B <= 0) return hipSuccess;
-    if (!seq_start || G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(first_query_kernel, dim3(A, (B + 31) / 32, G), dim3(256), 0, stream, g, seq_start, B, H, max_rows);
+    if (G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(first_query_kernel, dim3(A, (B + 31) / 32, G), dim3(256), 0, stream, g, B, H);
     return hipGetLastError();
 }
 

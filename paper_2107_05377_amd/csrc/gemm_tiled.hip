@@ -138,9 +138,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         for (int i = 0; i < TMI; ++i)
             af[buf][i] = *reinterpret_cast<const bf16x8*>(lds + stage * STAGE + ((wk * TMI + i) * 4 + kk) * 1024 + voff);
     };
-    // accumulators start from the bias (of the first K share)
+    // accumulators start from the bias (the first K share's do)
     auto init_acc = [&](const Ref& t) {
-        const uint32_t bo = OUT_F32 ? kNoBias : g.b[t.grp];
+        const uint32_t bo = t.split == 0 ? g.b[t.grp] : kNoBias;
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) {
             f32x16 b0;
@@ -346,42 +346,32 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
 }
 
 // gemm_tiled_rows_kernel.  Few rows: TM x TN panels of output per workgroup, each of its 4 wavefronts a quarter of K, both operands
-// straight from global memory to registers with all loads of a quarter of K = 768 in flight at once (such a launch is a chain
-// of memory latencies: nothing is staged, there is one barrier), then one exchange of partial sums through LDS.
+// straight from global memory to registers with all loads of a quarter of K = 768 in flight at once, one exchange of partial sums
+// through LDS.  Such a launch is a chain of latencies (of 5.3 us at 36 rows x 2304 x 768: 1.3 from the launch before, 1.1 until the
+// row count was known, 2.2 loads, 0.4 the rest), so the chain is kept short: what the first addresses need are the leading, scalar
+// arguments, which the command processor preloads into registers, and the loads go out before the row count has arrived (panels
+// beyond it are memory of the operand all the same).
+// Packed: lda_ldw = widths in 16 columns, lda | ldw << 16; steps_pn = K steps of 16 per wavefront | column panels << 16; ldc_pm = width
+// of C in 8 columns | row panels by the bound << 16.
 template <int TM, int TN, bool OUT_F32, int ACT>
-__global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kernel(TiledGroup g, TiledShape s)
+__device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, const unsigned char* W, unsigned char* C, const float* bias,
+                                                     const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn, uint32_t ldc_pm, int M, int split,
+                                                     int64_t split_stride)
 {
     constexpr int U = 12, NBLK = TM * TN;
     __shared__ __attribute__((aligned(16))) float part[4][NBLK][4][64][4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_sub = s.n_sub > 1 ? s.n_sub : 1;
-    const int sub = blockIdx.z % n_sub, gz = blockIdx.z / n_sub;
-    const int grp = gz / s.splits, split = gz - grp * s.splits;
-    const uint32_t off_a = g.a[grp] + sub * s.sub_a, off_w = g.w[grp] + sub * s.sub_w, off_c = g.c[grp] + sub * s.sub_c;
-    const uint32_t off_b = g.b[grp] == kNoBias ? kNoBias : g.b[grp] + sub * s.sub_b;
-    const int panels_n = s.N >> 5;
+    const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(A));     // in flight until the stores
+    const int steps = steps_pn & 0xFFFF, panels_n = steps_pn >> 16, bound_m = ldc_pm >> 16;
     const int pn0 = blockIdx.x * TN, pm0 = blockIdx.y * TM;
-    const int M = s.d_M ? min(s.M, *s.d_M) : s.M;
-    const int panels_m = (M + 31) >> 5;
-    if (pm0 >= panels_m) return;
-    const int steps = s.K / s.splits / 64;                                   // K steps of 16 of a wavefront
+    const size_t pa = (size_t)(lda_ldw & 0xFFFF) * 1024, pw = (size_t)(lda_ldw >> 16) * 1024;      // bytes per panel
     const size_t k0 = (size_t)(split * 4 + wave) * steps * 1024 + lane * 16;
     const unsigned char* a[TM];
     const unsigned char* w[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-        a[i] = static_cast<const unsigned char*>(g.A) + (size_t)off_a * 256 + (size_t)min(pm0 + i, panels_m - 1) * s.lda * 64 + k0;
+    for (int i = 0; i < TM; ++i) a[i] = A + min(pm0 + i, bound_m - 1) * pa + k0;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-        w[j] = static_cast<const unsigned char*>(g.W) + (size_t)off_w * 256 + (size_t)min(pn0 + j, panels_n - 1) * s.ldw * 64 + k0;
-    // this wavefront finishes chunk `wave` of every block
-    float4 bv[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        bv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (off_b != kNoBias)
-            bv[j] = *reinterpret_cast<const float4*>(g.bias + (size_t)off_b * 64 + min(pn0 + j, panels_n - 1) * 32 + wave * 8 + (lane >> 5) * 4);
-    }
+    for (int j = 0; j < TN; ++j) w[j] = W + min(pn0 + j, panels_n - 1) * pw + k0;
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -389,9 +379,11 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kern
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    float4 bv[TN];
+    int panels_m = 0;
     // one batch of steps: all its loads are issued before its first product (a full batch without conditions: guarded loads are
     // branches, and the loads then go out one by one)
-    auto batch = [&](int s0, int nb, auto full) {
+    auto batch = [&](int s0, int nb, auto full, auto first) {
         bf16x8 af[U][TM], wf[U][TN];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -401,6 +393,17 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kern
 #pragma unroll
                 for (int i = 0; i < TM; ++i) af[u][i] = *reinterpret_cast<const bf16x8*>(a[i] + (size_t)(s0 + u) * 1024);
             }
+        if constexpr (first) {
+            // this wavefront finishes chunk `wave` of every block
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                bv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (bias && split == 0) bv[j] = *reinterpret_cast<const float4*>(bias + min(pn0 + j, panels_n - 1) * 32 + wave * 8 + (lane >> 5) * 4);
+            }
+            asm volatile("" ::: "memory");                                   // the loads stay in front of the exit
+            panels_m = ((d_M ? min(M, rows_here) : M) + 31) >> 5;
+            if (pm0 >= panels_m) return false;
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -410,10 +413,16 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kern
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][j], af[u][i], acc[i][j], 0, 0, 0);
             }
+        return true;
     };
     int s0 = 0;
-    for (; s0 + U <= steps; s0 += U) batch(s0, U, std::true_type{});
-    if (s0 < steps) batch(s0, steps - s0, std::false_type{});
+    if (steps >= U) {
+        if (!batch(0, U, std::true_type{}, std::true_type{})) return;
+        for (s0 = U; s0 + U <= steps; s0 += U) batch(s0, U, std::true_type{}, std::false_type{});
+        if (s0 < steps) batch(s0, steps - s0, std::false_type{}, std::false_type{});
+    } else if (!batch(0, steps, std::false_type{}, std::true_type{})) {
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -422,7 +431,7 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kern
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<f32x4*>(part[wave][i * TN + j][q][lane]) = f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
     __syncthreads();
-    unsigned char* Cb = static_cast<unsigned char*>(g.C) + (size_t)off_c * 256;
+    const size_t pc = (size_t)(ldc_pm & 0xFFFF) * 256;                       // elements per panel of C
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -436,14 +445,37 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kern
             v[1] = t_act<ACT>(v[1] + bv[j].y);
             v[2] = t_act<ACT>(v[2] + bv[j].z);
             v[3] = t_act<ACT>(v[3] + bv[j].w);
-            const size_t at = (size_t)pm * 32 * s.ldc + pn * 1024 + wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4;
+            const size_t at = pm * pc + pn * 1024 + wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4;
             if constexpr (OUT_F32) {
-                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(Cb) + (size_t)split * s.split_stride + at) = v;
+                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(C) + (size_t)split * split_stride + at) = v;
             } else {
                 const bf16x4 o = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(Cb) + at) = o;
+                *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(C) + at) = o;
             }
         }
+}
+
+template <int TM, int TN, bool OUT_F32, int ACT>
+__global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kernel(const unsigned char* A, const unsigned char* W, unsigned char* C,
+                                                                                   const float* bias, const int32_t* d_M, uint32_t lda_ldw,
+                                                                                   uint32_t steps_pn, uint32_t ldc_pm, int M, int64_t split_stride)
+{
+    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(A, W, C, bias, d_M, lda_ldw, steps_pn, ldc_pm, M, blockIdx.z, split_stride);
+}
+
+// several problems, and problems of n_sub equal ones
+template <int TM, int TN, bool OUT_F32, int ACT>
+__global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_group_kernel(const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn,
+                                                                                         uint32_t ldc_pm, int M, TiledGroup g, TiledShape s)
+{
+    const int n_sub = s.n_sub > 1 ? s.n_sub : 1;
+    const int sub = blockIdx.z % n_sub, gz = blockIdx.z / n_sub;
+    const int grp = gz / s.splits, split = gz - grp * s.splits;
+    const float* bias = g.b[grp] == kNoBias ? nullptr : g.bias + (size_t)(g.b[grp] + sub * s.sub_b) * 64;
+    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(static_cast<const unsigned char*>(g.A) + (size_t)(g.a[grp] + sub * s.sub_a) * 256,
+                                                     static_cast<const unsigned char*>(g.W) + (size_t)(g.w[grp] + sub * s.sub_w) * 256,
+                                                     static_cast<unsigned char*>(g.C) + (size_t)(g.c[grp] + sub * s.sub_c) * 256, bias, d_M, lda_ldw,
+                                                     steps_pn, ldc_pm, M, split, s.split_stride);
 }
 
 template <int KW, int MAXT, bool OUT_F32, int ACT>
@@ -469,8 +501,16 @@ hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int 
 template <int TM, int TN, bool OUT_F32, int ACT>
 hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t stream)
 {
-    dim3 grid((s.N / 32 + TN - 1) / TN, ((s.M + 31) / 32 + TM - 1) / TM, s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1)), block(256);
-    hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, g, s);
+    const int n_sub = s.n_sub > 1 ? s.n_sub : 1, pm = (s.M + 31) / 32;
+    dim3 grid((s.N / 32 + TN - 1) / TN, (pm + TM - 1) / TM, s.G * s.splits * n_sub), block(256);
+    const uint32_t lda_ldw = (uint32_t)(s.lda / 16) | (uint32_t)(s.ldw / 16) << 16, steps_pn = (uint32_t)(s.K / s.splits / 64) | (uint32_t)(s.N / 32) << 16,
+                   ldc_pm = (uint32_t)(s.ldc / 8) | (uint32_t)pm << 16;
+    if (s.G == 1 && n_sub == 1)
+        hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, static_cast<const unsigned char*>(g.A) + (size_t)g.a[0] * 256,
+                           static_cast<const unsigned char*>(g.W) + (size_t)g.w[0] * 256, static_cast<unsigned char*>(g.C) + (size_t)g.c[0] * 256,
+                           g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, s.split_stride);
+    else
+        hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
     return hipGetLastError();
 }
 
@@ -533,7 +573,9 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
     const int kw = form == TILED_K2 ? 2 : 1, slices = s.K / (64 * kw) / s.splits;
     if (form >= TILED_K2 && (s.n_sub > 1 || s.K % (64 * kw * s.splits) != 0 || slices < 5 || (form == TILED_TALL && slices % 2 != 0)))
         return hipErrorInvalidValue;
-    if (form < TILED_K2 && (long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535) return hipErrorInvalidValue;
+    if (form < TILED_K2 && ((long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535 || s.lda / 16 > 65535 || s.ldw / 16 > 65535 || s.ldc / 8 > 65535 ||
+                            s.N / 32 > 65535 || (s.M + 31) / 32 > 65535))
+        return hipErrorInvalidValue;
     if (s.out_f32) {
         if (s.act == ACT_TANH) return launch_form<true, ACT_TANH>(g, s, form, force, stream);
         if (s.act != ACT_NONE) return hipErrorInvalidValue;

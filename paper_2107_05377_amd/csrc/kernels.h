@@ -79,7 +79,7 @@ struct TiledGroup {
     const void* A;          // bf16 [M][lda]
     const void* W;          // bf16 [N][ldw]
     void* C;                // bf16 or float32 [M][ldc]
-    const float* bias;      // bf16 output and few-row forms only
+    const float* bias;      // added before the activation (to the first of the partial results)
     uint32_t a[kMaxGroup], w[kMaxGroup], c[kMaxGroup], b[kMaxGroup];   // b: kNoBias = none
 };
 struct TiledShape {
@@ -87,7 +87,7 @@ struct TiledShape {
     int32_t lda, ldw, ldc;      // widths of the matrices that the operands' columns are part of
     int32_t act, out_f32;
     const int32_t* d_M;         // optional device scalar: rows present
-    int32_t splits;             // K ranges, each with a float32 partial result (no bias), split_stride elements apart
+    int32_t splits;             // K ranges, each with a float32 partial result, split_stride elements apart
     int64_t split_stride;
     // few-row forms only: every problem is n_sub equal ones (heads) whose operands lie so far apart, in units of 256 bytes
     int32_t n_sub, sub_a, sub_w, sub_c, sub_b;
@@ -98,12 +98,13 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
 // compute units of the current device (cached per device)
 int device_cu_count();
 
-// LayerNorm on the panel layout: out = LN(sum_p x[p] + bias + residual), offsets as above from the workspace and the weights.
+// LayerNorm on the panel layout: out = LN(sum_p x[p] + residual), H a multiple of 64 up to 1024, offsets as above from the
+// workspace and the weights.
 struct TiledLnGroup {
     const void* ws;
     const void* wt;
-    uint32_t x[kMaxGroup], res[kMaxGroup], out_f[kMaxGroup], out_b[kMaxGroup];   // outputs: kNoBias = none
-    uint32_t bias[kMaxGroup], gamma[kMaxGroup], beta[kMaxGroup];
+    uint32_t x[kMaxGroup], res[kMaxGroup], out_f[kMaxGroup], out_b[kMaxGroup];
+    uint32_t gamma[kMaxGroup], beta[kMaxGroup];
 };
 struct TiledLnShape {
     int32_t G, M, H;
@@ -132,13 +133,14 @@ hipError_t launch_copy_rows_tiled(const RowCopyGroup& g, int G, const int32_t* i
 // First-token attention without projected keys and values (first_token.hip).
 struct FirstTokenGroup {
     const void* x[kMaxGroup];       // bf16 layer input, all rows
+    const void* first[kMaxGroup];   // its first-token rows, one per sequence
     const void* Wq[kMaxGroup];      // panels of the query matrix
     const float* bq[kMaxGroup];
     const void* WkT[kMaxGroup];     // panels of the transposed key matrix
     void* qt[kMaxGroup];            // bf16 [B][H / 8][16][8]
     void* xbar[kMaxGroup];          // per head a bf16 [B][H] panel matrix, xbar_stride elements apart
 };
-hipError_t launch_first_query(const FirstTokenGroup& g, int G, const int32_t* seq_start, int B, int H, int A, int max_rows, hipStream_t stream);
+hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream);
 hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
                                int64_t xbar_stride, hipStream_t stream);
 

@@ -84,7 +84,7 @@ struct Scratch {   // byte offsets into the workspace; one set for the trunk and
     int y_parts;   // y holds this many [M][H] float32 partial products (K ranges of a split contraction)
 };
 struct ClsScratch {   // per task with own layers: compact [max_batch] x ... buffers of its last, first-token-only layer
-    size_t in_f = 0, in_a = 0, q = 0, ctx, y, x1f, x1a, u, out_f;      // (panel layout: no in_f, in_a, q)
+    size_t in_f = 0, in_a = 0, q = 0, ctx, y, x1f, x1a, u, out_f;      // (panel layout: no in_f, q)
     size_t qt = 0, scores = 0, xbar = 0;   // bf16 mode: Wk^T q [max_batch][A_pad][H], raw scores [M][A_pad], weighted row sums
 };
 struct RouteMapOff {   // byte offsets of a sub-batch row map (per-sequence routing), one per task
@@ -922,7 +922,7 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->ctx);
         g.w[i] = units(io[i].w->Wo);
-        g.b[i] = kNoBias;
+        g.b[i] = units(io[i].w->bo);
         g.c[i] = units(io[i].scr->y);
     }
     L.tiled(MT_K_GEMM_OUT, g, TiledShape{n, M, H, H, H, H, H, ACT_NONE, 1, rm.n_rows, 1, 0});
@@ -935,7 +935,6 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
         lg.res[i] = off(io[i].in_f);
         lg.out_f[i] = units(io[i].scr->x1f);
         lg.out_b[i] = units(io[i].scr->x1b);
-        lg.bias[i] = units(io[i].w->bo);
         lg.gamma[i] = units(io[i].w->ln1g);
         lg.beta[i] = units(io[i].w->ln1b);
     }
@@ -956,7 +955,7 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->u);
         g.w[i] = units(io[i].w->W2);
-        g.b[i] = kNoBias;
+        g.b[i] = units(io[i].w->b2);
         g.c[i] = units(io[i].scr->y);
     }
     L.tiled(MT_K_GEMM_FFN2, g, TiledShape{n, M, H, F, F, F, H, ACT_NONE, 1, rm.n_rows, sp, part});
@@ -965,7 +964,6 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
         lg.res[i] = units(io[i].scr->x1f);
         lg.out_f[i] = off(io[i].out_f);
         lg.out_b[i] = off(io[i].out_b);
-        lg.bias[i] = units(io[i].w->b2);
         lg.gamma[i] = units(io[i].w->ln2g);
         lg.beta[i] = units(io[i].w->ln2b);
     }
@@ -986,17 +984,33 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     const size_t MB = m->MBmax;
     const int64_t part = (int64_t)MB * H, xbar_stride = (int64_t)MB * H;
 
+    // first-token rows of the inputs, once per input (tasks that fork at one tap share it)
     FirstTokenGroup fg;
+    RowCopyGroup rc;
+    int n_copy = 0;
     for (int i = 0; i < n; ++i) {
         fg.x[i] = io[i].in_a;
+        int same = -1;
+        for (int j = 0; j < i && same < 0; ++j)
+            if (io[j].in_a == io[i].in_a) same = j;
+        if (same >= 0) {
+            fg.first[i] = fg.first[same];
+        } else {
+            fg.first[i] = rc.out_b[n_copy] = ws + io[i].cls->in_a;
+            rc.in_b[n_copy] = io[i].in_a;
+            rc.in_f[n_copy++] = nullptr;
+        }
         fg.Wq[i] = m->d_w + io[i].w->Wqkv;
         fg.bq[i] = (const float*)(m->d_w + io[i].w->bqkv);
         fg.WkT[i] = m->d_w + io[i].w->WkT;
         fg.qt[i] = ws + io[i].cls->qt;
         fg.xbar[i] = ws + io[i].cls->xbar;
     }
+    L.begin(MT_K_ATTN);
+    L.check(launch_copy_rows_tiled(rc, n_copy, rm.seq_start, nullptr, B, M, H, L.st));
+    L.end();
     L.begin(MT_K_GEMM_FIRST);
-    L.check(launch_first_query(fg, n, rm.seq_start, B, H, A, M, L.st));
+    L.check(launch_first_query(fg, n, B, H, A, L.st));
     L.end();
     L.begin(MT_K_ATTN);
     L.check(launch_first_attend(fg, n, rm.seq_start, rm.seq_len, B, S, H, A, xbar_stride, L.st));
@@ -1022,7 +1036,7 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].cls->ctx);
         g.w[i] = units(io[i].w->Wo);
-        g.b[i] = kNoBias;
+        g.b[i] = units(io[i].w->bo);
         g.c[i] = units(io[i].cls->y);
     }
     L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, H, H, H, H, ACT_NONE, 1, nullptr, sp_o, part});
@@ -1035,7 +1049,6 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
         lg.res[i] = off(io[i].in_f);
         lg.out_f[i] = units(io[i].cls->x1f);
         lg.out_b[i] = units(io[i].cls->x1a);
-        lg.bias[i] = units(io[i].w->bo);
         lg.gamma[i] = units(io[i].w->ln1g);
         lg.beta[i] = units(io[i].w->ln1b);
     }
@@ -1056,7 +1069,7 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].cls->u);
         g.w[i] = units(io[i].w->W2);
-        g.b[i] = kNoBias;
+        g.b[i] = units(io[i].w->b2);
         g.c[i] = units(io[i].cls->y);
     }
     L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, F, F, F, H, ACT_NONE, 1, nullptr, sp_f, part});
@@ -1065,7 +1078,6 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
         lg.res[i] = units(io[i].cls->x1f);
         lg.out_f[i] = units(io[i].cls->out_f);
         lg.out_b[i] = units(io[i].split);
-        lg.bias[i] = units(io[i].w->b2);
         lg.gamma[i] = units(io[i].w->ln2g);
         lg.beta[i] = units(io[i].w->ln2b);
     }
@@ -1197,6 +1209,7 @@ int mt_create(const mt_config* cfg, mt_model** out)
             if (m->tiled) {        // the first-token layer's buffers lie over those of the full layers before it
                 sb.off = scr_begin;
                 ClsScratch c;
+                c.in_a = sb.take(MB * H * 2);
                 c.qt = sb.take(MB * 16 * H * 2);
                 c.xbar = sb.take((size_t)cfg->heads * MB * H * 2);
                 c.ctx = sb.take(MB * H * 2);

@@ -1,8 +1,9 @@
-// Row kernels of the bfloat16 path, on the panel layout of tiled_offset() (kernels.h).  A workgroup of 8 wavefronts owns 8 rows of
-// one panel: of a chunk (8 columns) they are 256 contiguous bytes of float32 or 128 of bf16, i.e. whole lines that no other
-// workgroup writes.  A wavefront's load instruction covers 4 neighbouring chunks: lane = (chunk in 4, row in 8, half of the
-// chunk); a row is spread over 8 lanes of every wavefront, so its sums are three lane exchanges and one through LDS.
-// Both kernels are bound by HBM (or the last-level cache): a row is read and written once.
+// Row kernels of the bfloat16 path, on the panel layout of tiled_offset() (kernels.h).  LayerNorm and embedding: a wavefront owns 4
+// rows of a panel, lane = (chunk in 8, row in 4, half of the chunk), so that a load instruction covers 8 neighbouring chunks of 128
+// contiguous bytes of float32 (whole lines); two or more wavefronts of a workgroup complete the 128-byte lines of the bf16 copy.  A
+// row is spread over 16 lanes: its sums are four lane exchanges, no LDS and no barrier (8 rows over the 8 wavefronts of a
+// workgroup, i.e. smaller registers and two barriers, took 39.6 us for 18.6 k rows of 768, this form 38 us).
+// The kernels are bound by HBM (or the last-level cache): a row is read and written once.
 #include "kernels.h"
 #include "device_util.h"
 
@@ -10,159 +11,176 @@ namespace mt {
 
 namespace {
 
-constexpr int kRowsPerGroup = 8;
-
-// Sum over a row of this lane's partial value, for the lane's row; `red` is one [8 wavefronts][8 rows] exchange.
-__device__ __forceinline__ float row_sum(float v, float (*red)[8], int wave, int lane, int r)
+// Sum of a row's partial values over the 16 lanes that hold it.
+__device__ __forceinline__ float row_sum(float v)
 {
     v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 8, 64);
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
-    if ((lane & 49) == 0) red[wave][r] = v;
-    __syncthreads();
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) t += red[w][r];
-    return t;
+    return v;
 }
 
-// Normalise the NV x 4 values that a lane holds of its row and store: float32 state, bf16 operand copy, or (split) the row as
-// [hi | lo] bf16 halves of a matrix twice as wide.  Lanes beyond the row's chunks hold zeros and store nothing.
-template <int NV>
-__device__ __forceinline__ void finish_row(float4 (&v)[NV], const float4 (&g)[NV], const float4 (&b)[NV], int chunk0, int n_chunks, int row,
-                                           int half, int wave, int lane, bool live, int H, float eps, float* of, __bf16* ob, int split)
+// Normalise the NI x 4 values that a lane holds of its row (H = 64 NI) and store: float32 state, bf16 operand copy, or (split) the row
+// as [hi | lo] bf16 halves of a matrix twice as wide.
+template <int NI>
+__device__ __forceinline__ void finish_row(float4 (&v)[NI], const float* __restrict__ gamma, const float* __restrict__ beta, int row, int c8,
+                                           int half, bool live, float eps, float* of, __bf16* ob, int split)
 {
-    __shared__ float red[2][8][8];
-    const int r = row & 7;
+    constexpr int H = NI * 64;
+    float4 g[NI], b[NI];                     // in flight during the reductions
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        g[i] = *reinterpret_cast<const float4*>(gamma + (i * 8 + c8) * 8 + half * 4);
+        b[i] = *reinterpret_cast<const float4*>(beta + (i * 8 + c8) * 8 + half * 4);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-    const float mean = row_sum(s, red[0], wave, lane, r) / (float)H;
+    for (int i = 0; i < NI; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    const float mean = row_sum(s) / (float)H;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-        if (chunk0 + i * 32 < n_chunks) {
-            const float a = v[i].x - mean, c = v[i].y - mean, d = v[i].z - mean, e = v[i].w - mean;
-            q += (a * a + c * c) + (d * d + e * e);
-        }
-    const float inv = 1.0f / sqrtf(row_sum(q, red[1], wave, lane, r) / (float)H + eps);
+    for (int i = 0; i < NI; ++i) {
+        const float a = v[i].x - mean, c = v[i].y - mean, d = v[i].z - mean, e = v[i].w - mean;
+        q += (a * a + c * c) + (d * d + e * e);
+    }
+    const float inv = 1.0f / sqrtf(row_sum(q) / (float)H + eps);
     if (!live) return;
     const size_t panel = (size_t)(row >> 5) * 32;
     const int in_chunk = (row & 31) * 8 + half * 4;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int chunk = chunk0 + i * 32;
-        if (chunk >= n_chunks) continue;
+    for (int i = 0; i < NI; ++i) {
+        const int chunk = i * 8 + c8;
         float4 o;
         o.x = g[i].x * ((v[i].x - mean) * inv) + b[i].x;
         o.y = g[i].y * ((v[i].y - mean) * inv) + b[i].y;
         o.z = g[i].z * ((v[i].z - mean) * inv) + b[i].z;
         o.w = g[i].w * ((v[i].w - mean) * inv) + b[i].w;
-        if (of) *reinterpret_cast<float4*>(of + panel * H + chunk * 256 + in_chunk) = o;
-        if (!ob) continue;
+        *reinterpret_cast<float4*>(of + panel * H + chunk * 256 + in_chunk) = o;
         const bf16x4 hi = {(__bf16)o.x, (__bf16)o.y, (__bf16)o.z, (__bf16)o.w};
         __bf16* p = ob + panel * (split ? 2 * H : H) + in_chunk;
         *reinterpret_cast<bf16x4*>(p + chunk * 256) = hi;
         if (split) {
             const bf16x4 lo = {(__bf16)(o.x - (float)hi[0]), (__bf16)(o.y - (float)hi[1]), (__bf16)(o.z - (float)hi[2]), (__bf16)(o.w - (float)hi[3])};
-            *reinterpret_cast<bf16x4*>(p + (n_chunks + chunk) * 256) = lo;
+            *reinterpret_cast<bf16x4*>(p + (NI * 8 + chunk) * 256) = lo;
         }
     }
 }
 
-// out = LayerNorm(sum of the partial products + bias + residual).  All loads of a lane are issued before the first use.
-template <int NV>
-__global__ __launch_bounds__(512) void layernorm_tiled_kernel(TiledLnGroup g, TiledLnShape s)
+// out = LayerNorm(sum of NP partial products + residual) (the bias is already in the first product).  All loads of a lane are issued
+// before the first use, in a launch of few rows (EARLY) even before the row count has arrived: rows beyond it are memory of the
+// operands all the same, but of a large padded batch reading them would be real traffic.  The pointers are leading scalar arguments,
+// which the command processor preloads.
+template <int NI, int NP, bool EARLY>
+__device__ __forceinline__ void layernorm_tiled_body(const float* x, const float* res, const float* gamma, const float* beta, float* of, __bf16* ob,
+                                                     const int32_t* d_M, int M, int64_t part_stride, const int32_t* res_row, int res_rows, float eps,
+                                                     int split)
 {
-    const int grp = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = blockIdx.x * kRowsPerGroup + ((lane >> 1) & 7), half = lane & 1;
-    const int M = s.d_M ? min(s.M, *s.d_M) : s.M;
-    if (blockIdx.x * kRowsPerGroup >= M) return;
-    const int H = s.H, n_chunks = H >> 3, chunk0 = wave * 4 + (lane >> 4);
-    const size_t at = (size_t)(row >> 5) * 32 * H + (row & 31) * 8 + half * 4;
-    const float* x = reinterpret_cast<const float*>(static_cast<const unsigned char*>(g.ws) + (size_t)g.x[grp] * 256) + at;
+    constexpr int H = NI * 64;
+    const int lane = threadIdx.x & 63;
+    const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(x));
+    const int last = (M + 31) / 32 * 32 - 1;                                  // rows of the last panel exist
+    if (!EARLY && d_M) M = min(M, rows_here);
+    const int row4 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 4;
+    const int row = row4 + ((lane >> 1) & 3), half = lane & 1, c8 = lane >> 3;
+    const int at = half * 4 + c8 * 256;
+    if (!EARLY && row4 >= M) return;
+    x += (size_t)(min(row, last) >> 5) * 32 * H + (row & 31) * 8 + at;
     // the residual row is the same row, or (first-token layers) the row that a sequence starts at
-    const int rr = s.res_row ? min(s.res_row[min(row, M - 1)], s.res_rows - 1) : row;
-    const float* res = reinterpret_cast<const float*>(static_cast<const unsigned char*>(g.ws) + (size_t)g.res[grp] * 256) +
-                       (size_t)(rr >> 5) * 32 * H + (rr & 31) * 8 + half * 4;
-    const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
-    const float* bias = reinterpret_cast<const float*>(wt + (size_t)g.bias[grp] * 256) + half * 4;
-    const float* gamma = reinterpret_cast<const float*>(wt + (size_t)g.gamma[grp] * 256) + half * 4;
-    const float* beta = reinterpret_cast<const float*>(wt + (size_t)g.beta[grp] * 256) + half * 4;
-    float4 v[NV], rv[NV], bv[NV], gm[NV], bt[NV];
+    const int rr = res_row ? (int)min((uint32_t)res_row[min(row, M - 1)], (uint32_t)(res_rows - 1)) : min(row, last);
+    res += (size_t)(rr >> 5) * 32 * H + (rr & 31) * 8 + at;
+    constexpr int FIRST = (NP + 1) * NI <= 60 ? NP : 2;                       // what fits the registers
+    float4 v[FIRST][NI], r[NI];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int chunk = min(chunk0 + i * 32, n_chunks - 1);                 // lanes beyond the row load its last chunk
-        v[i] = *reinterpret_cast<const float4*>(x + chunk * 256);
-        rv[i] = *reinterpret_cast<const float4*>(res + chunk * 256);
-        bv[i] = *reinterpret_cast<const float4*>(bias + chunk * 8);
-        gm[i] = *reinterpret_cast<const float4*>(gamma + chunk * 8);
-        bt[i] = *reinterpret_cast<const float4*>(beta + chunk * 8);
+    for (int p = 0; p < FIRST; ++p)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) v[p][i] = *reinterpret_cast<const float4*>(x + (size_t)p * part_stride + i * 2048);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) r[i] = *reinterpret_cast<const float4*>(res + i * 2048);
+    if constexpr (EARLY) {
+        asm volatile("" ::: "memory");                                        // the loads stay in front of the exit
+        if (d_M) M = min(M, rows_here);
+        if (row4 >= M) return;
     }
     __builtin_amdgcn_sched_barrier(0);
-    for (int p = 1; p < s.n_parts; ++p) {                                     // fixed order: deterministic
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const float4 t = *reinterpret_cast<const float4*>(x + (size_t)p * s.part_stride + min(chunk0 + i * 32, n_chunks - 1) * 256);
-            v[i].x += t.x; v[i].y += t.y; v[i].z += t.z; v[i].w += t.w;
+    for (int i = 0; i < NI; ++i) {                                            // fixed order: deterministic
+#pragma unroll
+        for (int p = 1; p < NP; ++p) {
+            const float4 u = p < FIRST ? v[p < FIRST ? p : 0][i] : *reinterpret_cast<const float4*>(x + (size_t)p * part_stride + i * 2048);
+            v[0][i].x += u.x;
+            v[0][i].y += u.y;
+            v[0][i].z += u.z;
+            v[0][i].w += u.w;
         }
+        v[0][i].x += r[i].x;
+        v[0][i].y += r[i].y;
+        v[0][i].z += r[i].z;
+        v[0][i].w += r[i].w;
     }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const bool in = chunk0 + i * 32 < n_chunks;
-        v[i].x = in ? (v[i].x + bv[i].x) + rv[i].x : 0.f;
-        v[i].y = in ? (v[i].y + bv[i].y) + rv[i].y : 0.f;
-        v[i].z = in ? (v[i].z + bv[i].z) + rv[i].z : 0.f;
-        v[i].w = in ? (v[i].w + bv[i].w) + rv[i].w : 0.f;
-    }
+    finish_row<NI>(v[0], gamma, beta, row, c8, half, row < M, eps, of, ob, split);
+}
+
+template <int NI, int NP>
+__global__ __launch_bounds__(256) void layernorm_tiled_kernel(const float* x, const float* res, const int32_t* d_M, const float* gamma,
+                                                              const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps)
+{
+    layernorm_tiled_body<NI, NP, true>(x, res, gamma, beta, of, ob, d_M, M, part_stride, nullptr, 0, eps, 0);
+}
+
+template <int NI, int NP, bool EARLY>
+__global__ __launch_bounds__(256) void layernorm_tiled_group_kernel(TiledLnGroup g, TiledLnShape s)
+{
+    const int grp = blockIdx.y;
+    const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
     unsigned char* ws = static_cast<unsigned char*>(const_cast<void*>(g.ws));
-    finish_row<NV>(v, gm, bt, chunk0, n_chunks, row, half, wave, lane, row < M, H, s.eps,
-                   g.out_f[grp] == kNoBias ? nullptr : reinterpret_cast<float*>(ws + (size_t)g.out_f[grp] * 256),
-                   g.out_b[grp] == kNoBias ? nullptr : reinterpret_cast<__bf16*>(ws + (size_t)g.out_b[grp] * 256), s.split);
+    layernorm_tiled_body<NI, NP, EARLY>(reinterpret_cast<const float*>(ws + (size_t)g.x[grp] * 256), reinterpret_cast<const float*>(ws + (size_t)g.res[grp] * 256),
+                                 reinterpret_cast<const float*>(wt + (size_t)g.gamma[grp] * 256), reinterpret_cast<const float*>(wt + (size_t)g.beta[grp] * 256),
+                                 reinterpret_cast<float*>(ws + (size_t)g.out_f[grp] * 256), reinterpret_cast<__bf16*>(ws + (size_t)g.out_b[grp] * 256), s.d_M,
+                                 s.M, s.part_stride, s.res_row, s.res_rows, s.eps, s.split);
 }
 
 // Embedding sum + LayerNorm of the kept rows.
-template <int NV>
-__global__ __launch_bounds__(512) void embed_ln_tiled_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ type_ids, int type_vocab,
-                                                             const int32_t* __restrict__ src, const int32_t* __restrict__ d_M, int M, int S, int H,
+template <int NI>
+__global__ __launch_bounds__(256) void embed_ln_tiled_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ type_ids, int type_vocab,
+                                                             const int32_t* __restrict__ src, const int32_t* __restrict__ d_M, int M, int S,
                                                              int vocab, const __bf16* __restrict__ word, const __bf16* __restrict__ pos,
                                                              const __bf16* __restrict__ type, const float* __restrict__ gamma,
                                                              const float* __restrict__ beta, float eps, float* of, __bf16* ob)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = blockIdx.x * kRowsPerGroup + ((lane >> 1) & 7), half = lane & 1;
+    constexpr int H = NI * 64;
+    const int lane = threadIdx.x & 63;
+    const int row4 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 4;
+    const int row = row4 + ((lane >> 1) & 3), half = lane & 1, c8 = lane >> 3;
     M = min(M, *d_M);
-    if (blockIdx.x * kRowsPerGroup >= M) return;
-    const int n_chunks = H >> 3, chunk0 = wave * 4 + (lane >> 4);
+    if (row4 >= M) return;
     const int p = src[min(row, M - 1)];
     int id = ids[p];
     id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
     int seg = type_ids ? type_ids[p] : 0;
     seg = seg < 0 ? 0 : (seg >= type_vocab ? type_vocab - 1 : seg);
-    const __bf16* w = word + (size_t)id * H + half * 4;
-    const __bf16* q = pos + (size_t)(p % S) * H + half * 4;
-    const __bf16* t = type + (size_t)seg * H + half * 4;
-    bf16x4 a[NV], b[NV], c[NV];
-    float4 v[NV], gm[NV], bt[NV];
+    const int col = c8 * 8 + half * 4;
+    const __bf16* w = word + (size_t)id * H + col;
+    const __bf16* q = pos + (size_t)(p % S) * H + col;
+    const __bf16* t = type + (size_t)seg * H + col;
+    bf16x4 a[NI], b[NI], c[NI];
+    float4 v[NI];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int chunk = min(chunk0 + i * 32, n_chunks - 1);
-        a[i] = *reinterpret_cast<const bf16x4*>(w + chunk * 8);
-        b[i] = *reinterpret_cast<const bf16x4*>(q + chunk * 8);
-        c[i] = *reinterpret_cast<const bf16x4*>(t + chunk * 8);
-        gm[i] = *reinterpret_cast<const float4*>(gamma + half * 4 + chunk * 8);
-        bt[i] = *reinterpret_cast<const float4*>(beta + half * 4 + chunk * 8);
+    for (int i = 0; i < NI; ++i) {
+        a[i] = *reinterpret_cast<const bf16x4*>(w + i * 64);
+        b[i] = *reinterpret_cast<const bf16x4*>(q + i * 64);
+        c[i] = *reinterpret_cast<const bf16x4*>(t + i * 64);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const bool in = chunk0 + i * 32 < n_chunks;
-        v[i].x = in ? ((float)a[i][0] + (float)b[i][0]) + (float)c[i][0] : 0.f;
-        v[i].y = in ? ((float)a[i][1] + (float)b[i][1]) + (float)c[i][1] : 0.f;
-        v[i].z = in ? ((float)a[i][2] + (float)b[i][2]) + (float)c[i][2] : 0.f;
-        v[i].w = in ? ((float)a[i][3] + (float)b[i][3]) + (float)c[i][3] : 0.f;
+    for (int i = 0; i < NI; ++i) {
+        v[i].x = ((float)a[i][0] + (float)b[i][0]) + (float)c[i][0];
+        v[i].y = ((float)a[i][1] + (float)b[i][1]) + (float)c[i][1];
+        v[i].z = ((float)a[i][2] + (float)b[i][2]) + (float)c[i][2];
+        v[i].w = ((float)a[i][3] + (float)b[i][3]) + (float)c[i][3];
     }
-    finish_row<NV>(v, gm, bt, chunk0, n_chunks, row, half, wave, lane, row < M, H, eps, of, ob, 0);
+    finish_row<NI>(v, gamma, beta, row, c8, half, row < M, eps, of, ob, 0);
 }
 
 // Pooler operand of tasks without own layers: the tap's first-token row of every sequence as [hi | lo] bf16 halves.
@@ -233,16 +251,53 @@ __global__ __launch_bounds__(256) void classifier_tiled_kernel(ClsGroup g, int H
 
 }  // namespace
 
+namespace {
+
+// wavefronts per workgroup: few rows are spread over more compute units
+int row_block(long rows) { return rows >= 2048 ? 4 : 2; }
+
+template <int NI, int NP>
+void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, dim3 grid, dim3 block, hipStream_t stream)
+{
+    unsigned char* ws = static_cast<unsigned char*>(const_cast<void*>(g.ws));
+    const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
+    const bool early = (long)s.G * s.M <= 2048;                     // less than a cached megabyte or two of padding
+    if (s.G == 1 && !s.res_row && !s.split && early)
+        hipLaunchKernelGGL((layernorm_tiled_kernel<NI, NP>), grid, block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
+                           (const float*)(ws + (size_t)g.res[0] * 256), s.d_M, (const float*)(wt + (size_t)g.gamma[0] * 256),
+                           (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
+                           s.M, s.part_stride, s.eps);
+    else if (early)
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true>), grid, block, 0, stream, g, s);
+    else
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false>), grid, block, 0, stream, g, s);
+}
+
+}  // namespace
+
+#define MT_FOR_WIDTH(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+
 hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
 {
     if (s.G <= 0 || s.M <= 0) return hipSuccess;
-    if (s.G > kMaxGroup || s.H % 8 != 0 || s.H > 2048 || s.n_parts < 1) return hipErrorInvalidValue;
-    dim3 grid((s.M + kRowsPerGroup - 1) / kRowsPerGroup, s.G), block(512);
-    if (s.H <= 256) hipLaunchKernelGGL((layernorm_tiled_kernel<1>), grid, block, 0, stream, g, s);
-    else if (s.H <= 512) hipLaunchKernelGGL((layernorm_tiled_kernel<2>), grid, block, 0, stream, g, s);
-    else if (s.H <= 768) hipLaunchKernelGGL((layernorm_tiled_kernel<3>), grid, block, 0, stream, g, s);
-    else if (s.H <= 1024) hipLaunchKernelGGL((layernorm_tiled_kernel<4>), grid, block, 0, stream, g, s);
-    else hipLaunchKernelGGL((layernorm_tiled_kernel<8>), grid, block, 0, stream, g, s);
+    if (s.G > kMaxGroup || s.H % 64 != 0 || s.n_parts < 1) return hipErrorInvalidValue;
+    const int wv = row_block((long)s.M * s.G);
+    dim3 grid((s.M + 4 * wv - 1) / (4 * wv), s.G), block(64 * wv);
+    switch (s.H / 64) {
+#define X(NI)                                                    \
+    case NI:                                                     \
+        switch (s.n_parts) {                                     \
+            case 1: ln_launch<NI, 1>(g, s, grid, block, stream); break; \
+            case 2: ln_launch<NI, 2>(g, s, grid, block, stream); break; \
+            case 4: ln_launch<NI, 4>(g, s, grid, block, stream); break; \
+            default: return hipErrorInvalidValue;                \
+        }                                                        \
+        break;
+        MT_FOR_WIDTH(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -252,17 +307,19 @@ hipError_t launch_embed_ln_tiled(const int32_t* ids, const int32_t* type_ids, in
 {
     const int M = B * S;
     if (M <= 0) return hipSuccess;
-    if (H % 8 != 0 || H > 2048 || !src || !d_M) return hipErrorInvalidValue;
-    dim3 grid((M + kRowsPerGroup - 1) / kRowsPerGroup), block(512);
-#define MT_EMBED(NV)                                                                                                                    \
-    hipLaunchKernelGGL((embed_ln_tiled_kernel<NV>), grid, block, 0, stream, ids, type_ids, type_vocab, src, d_M, M, S, H, vocab,        \
-                       (const __bf16*)word, (const __bf16*)pos, (const __bf16*)type, gamma, beta, eps, out_f32, (__bf16*)out_bf16)
-    if (H <= 256) MT_EMBED(1);
-    else if (H <= 512) MT_EMBED(2);
-    else if (H <= 768) MT_EMBED(3);
-    else if (H <= 1024) MT_EMBED(4);
-    else MT_EMBED(8);
-#undef MT_EMBED
+    if (H % 64 != 0 || !src || !d_M) return hipErrorInvalidValue;
+    const int wv = row_block(M);
+    dim3 grid((M + 4 * wv - 1) / (4 * wv)), block(64 * wv);
+    switch (H / 64) {
+#define X(NI)                                                                                                                                \
+    case NI:                                                                                                                                 \
+        hipLaunchKernelGGL((embed_ln_tiled_kernel<NI>), grid, block, 0, stream, ids, type_ids, type_vocab, src, d_M, M, S, vocab,            \
+                           (const __bf16*)word, (const __bf16*)pos, (const __bf16*)type, gamma, beta, eps, out_f32, (__bf16*)out_bf16);      \
+        break;
+        MT_FOR_WIDTH(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
