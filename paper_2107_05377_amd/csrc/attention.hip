@@ -43,9 +43,6 @@ __device__ inline int k_chunk_off(int row, int chunk) { return row * 128 + ((chu
 #define MT_ATTN_CB 2
 #endif
 constexpr int CB = MT_ATTN_CB;        // 32-key blocks per online-softmax chunk
-// TILED: qkv and ctx in the panel layout (tiled_offset): a chunk (8 columns) of consecutive rows is contiguous there, so lanes take
-// consecutive keys of one chunk, which also spreads the transposed writes of the values over the LDS banks.
-template <bool TILED>
 __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnGroup g, const int32_t* __restrict__ mask,
                                                              const int32_t* __restrict__ seq_start,
                                                              const int32_t* __restrict__ seq_len, int B, int S, int H, int Sk_max,
@@ -66,9 +63,9 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const size_t ld = (size_t)3 * H;
-    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (TILED ? 0 : (size_t)row0 * ld);
+    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (size_t)row0 * ld;
     // element of row `row` of this sequence, column `col`
-    auto at = [&](int row, int col) { return TILED ? tiled_offset(row0 + row, col, ld) : (size_t)row * ld + col; };
+    auto at = [&](int row, int col) { return (size_t)row * ld + col; };
     const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * S : nullptr;
     const int nblk = Sk / 32;
 
@@ -88,10 +85,10 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     for (int kb = 0; kb < Sk; kb += 128) {
         uint4 kv[KU], v0[VU], v1[VU];
         int m0[VU], m1[VU];
-        auto key_of = [&](int u) { return TILED ? kb + (tid & 127) : kb + ((u * 256 + tid) >> 3); };
-        auto kch_of = [&](int u) { return TILED ? u * 2 + (tid >> 7) : (u * 256 + tid) & 7; };
-        auto pair_of = [&](int u) { return TILED ? kb / 2 + (tid & 63) : kb / 2 + ((u * 256 + tid) >> 3); };
-        auto vch_of = [&](int u) { return TILED ? u * 4 + (tid >> 6) : (u * 256 + tid) & 7; };
+        auto key_of = [&](int u) { return kb + ((u * 256 + tid) >> 3); };
+        auto kch_of = [&](int u) { return (u * 256 + tid) & 7; };
+        auto pair_of = [&](int u) { return kb / 2 + ((u * 256 + tid) >> 3); };
+        auto vch_of = [&](int u) { return (u * 256 + tid) & 7; };
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
             const int key = key_of(u), ch = kch_of(u);
@@ -246,14 +243,14 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
                     pack_e4m3(o[dt][qq * 4 + 0] * inv, o[dt][qq * 4 + 1] * inv, o[dt][qq * 4 + 2] * inv, o[dt][qq * 4 + 3] * inv);
     } else if (q < n_tok) {
         const float inv = 1.0f / l_run;
-        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + (TILED ? tiled_offset(row0 + q, a * 64, H) : ((size_t)row0 + q) * H + a * 64);
+        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + ((size_t)row0 + q) * H + a * 64;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq) {
                 bf16x4 v = {(__bf16)(o[dt][qq * 4 + 0] * inv), (__bf16)(o[dt][qq * 4 + 1] * inv),
                             (__bf16)(o[dt][qq * 4 + 2] * inv), (__bf16)(o[dt][qq * 4 + 3] * inv)};
-                *reinterpret_cast<bf16x4*>(out + (TILED ? (dt * 4 + qq) * 256 : dt * 32 + qq * 8) + half * 4) = v;
+                *reinterpret_cast<bf16x4*>(out + dt * 32 + qq * 8 + half * 4) = v;
             }
     }
 }
@@ -609,11 +606,11 @@ hipError_t launch_attention_cls(const AttnClsGroup& g, int G, int is_bf16, const
 }
 
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt, int tiled)
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt)
 {
     if (!mask && !(seq_start && seq_len)) return hipErrorInvalidValue;
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
-    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1) || (tiled && ctx_fmt)) return hipErrorInvalidValue;
+    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1)) return hipErrorInvalidValue;
     const int Sk = (S + 31) / 32 * 32;
     const size_t lds = (size_t)Sk * 128 + (size_t)64 * (Sk + 4) * 2 + (size_t)Sk * 4 + (size_t)(Sk / 32) * 4;
     static_assert(kAttnBf16MaxSeq % 32 == 0 &&
@@ -622,17 +619,14 @@ hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask,
                       (size_t)(kAttnBf16MaxSeq + 32) * 260 + 512 > 160 * 1024,
                   "kAttnBf16MaxSeq is the largest multiple of 32 whose keys and values fit the LDS");
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static std::atomic<uint64_t> lds_raised[2];
+    static std::atomic<uint64_t> lds_raised;
     if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds(tiled ? (const void*)attention_bf16_kernel<true> : (const void*)attention_bf16_kernel<false>, 160 * 1024, lds_raised[tiled ? 1 : 0]);
+        hipError_t e = ensure_dynamic_lds((const void*)attention_bf16_kernel, 160 * 1024, lds_raised);
         if (e != hipSuccess) return e;
     }
     dim3 grid((S + 127) / 128, A, B * G), block(256);
     const float scale_log2e = (1.0f / sqrtf(64.0f)) * kLog2e;
-    if (tiled)
-        hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
-    else
-        hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
+    hipLaunchKernelGGL(attention_bf16_kernel, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
     return hipGetLastError();
 }
 

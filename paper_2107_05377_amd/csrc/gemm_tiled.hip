@@ -167,6 +167,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
             for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(c + q * 256) = f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]};
         } else {
             __bf16* c = reinterpret_cast<__bf16*>(Cb) + (size_t)pm * 32 * s.ldc + pn * 1024 + lane * 8;
+            [[maybe_unused]] f32x16 tr;
 #pragma unroll
             for (int qp = 0; qp < 2; ++qp) {
                 bf16x4 x, y;                                                 // 4 of the 8 columns of two neighbouring chunks
@@ -179,7 +180,34 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
                 const u32x2 xu = __builtin_bit_cast(u32x2, x), yu = __builtin_bit_cast(u32x2, y);
                 const auto s0 = __builtin_amdgcn_permlane32_swap(xu[0], yu[0], false, false);
                 const auto s1 = __builtin_amdgcn_permlane32_swap(xu[1], yu[1], false, false);
-                *reinterpret_cast<u32x4*>(c + qp * 512) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+                const u32x4 r = u32x4{s0[0], s1[0], s0[1], s1[1]};
+                if constexpr (ACT == ACT_NONE) {
+                    if (s.vt_panel && pn >= s.vt_panel) {
+                        // transposed: the half block just formed is a matrix operand (32 rows x 16 columns); its product with the
+                        // unit matrix moves the columns to the lanes, exactly (exchanging the operands of the whole tile instead
+                        // needs a second copy of the main loop, which did not fit the registers)
+                        const int d = (lane & 31) - qp * 16 - (lane >> 5) * 8;
+                        u32x4 unit;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) unit[e] = d == 2 * e ? 0x3F80u : (d == 2 * e + 1 ? 0x3F800000u : 0u);
+                        if (qp == 0) {
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) tr[e] = 0.f;
+                        }
+                        tr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r), __builtin_bit_cast(bf16x8, unit), tr, 0, 0, 0);
+                        if (qp == 1) {
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                bf16x8 v;
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) v[e] = (__bf16)tr[h * 8 + e];
+                                *reinterpret_cast<bf16x8*>(c + h * 512) = v;
+                            }
+                        }
+                        continue;
+                    }
+                }
+                *reinterpret_cast<u32x4*>(c + qp * 512) = r;
             }
         }
     };
@@ -356,7 +384,7 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
 template <int TM, int TN, bool OUT_F32, int ACT>
 __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, const unsigned char* W, unsigned char* C, const float* bias,
                                                      const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn, uint32_t ldc_pm, int M, int split,
-                                                     int64_t split_stride)
+                                                     int64_t split_stride, int vt_panel)
 {
     constexpr int U = 12, NBLK = TM * TN;
     __shared__ __attribute__((aligned(16))) float part[4][NBLK][4][64][4];
@@ -379,6 +407,8 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    // blocks to store transposed are computed transposed (vt_panel is even: both column panels of a workgroup are, or none)
+    const bool vt = !OUT_F32 && ACT == ACT_NONE && vt_panel && pn0 >= vt_panel;
     float4 bv[TN];
     int panels_m = 0;
     // one batch of steps: all its loads are issued before its first product (a full batch without conditions: guarded loads are
@@ -398,21 +428,37 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 bv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (bias && split == 0) bv[j] = *reinterpret_cast<const float4*>(bias + min(pn0 + j, panels_n - 1) * 32 + wave * 8 + (lane >> 5) * 4);
+                if (bias && split == 0) {
+                    const float* bp = bias + min(pn0 + j, panels_n - 1) * 32;
+                    if (vt) bv[j].x = bv[j].y = bv[j].z = bv[j].w = bp[lane & 31];
+                    else bv[j] = *reinterpret_cast<const float4*>(bp + wave * 8 + (lane >> 5) * 4);
+                }
             }
             asm volatile("" ::: "memory");                                   // the loads stay in front of the exit
             panels_m = ((d_M ? min(M, rows_here) : M) + 31) >> 5;
             if (pm0 >= panels_m) return false;
         }
         __builtin_amdgcn_sched_barrier(0);
+        auto products = [&](auto swap) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (full || u < nb) {
+            for (int u = 0; u < U; ++u)
+                if (full || u < nb) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][j], af[u][i], acc[i][j], 0, 0, 0);
+                        for (int j = 0; j < TN; ++j) {
+                            if constexpr (swap) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u][i], wf[u][j], acc[i][j], 0, 0, 0);
+                            else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][j], af[u][i], acc[i][j], 0, 0, 0);
+                        }
+                }
+        };
+        if constexpr (!OUT_F32 && ACT == ACT_NONE) {
+            if (vt) {
+                products(std::true_type{});
+                return true;
             }
+        }
+        products(std::false_type{});
         return true;
     };
     int s0 = 0;
@@ -445,7 +491,7 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
             v[1] = t_act<ACT>(v[1] + bv[j].y);
             v[2] = t_act<ACT>(v[2] + bv[j].z);
             v[3] = t_act<ACT>(v[3] + bv[j].w);
-            const size_t at = pm * pc + pn * 1024 + wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4;
+            const size_t at = pm * pc + pn * 1024 + (vt ? (wave >> 1) * 512 + lane * 8 + (wave & 1) * 4 : wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4);
             if constexpr (OUT_F32) {
                 *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(C) + (size_t)split * split_stride + at) = v;
             } else {
@@ -458,9 +504,9 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
 template <int TM, int TN, bool OUT_F32, int ACT>
 __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kernel(const unsigned char* A, const unsigned char* W, unsigned char* C,
                                                                                    const float* bias, const int32_t* d_M, uint32_t lda_ldw,
-                                                                                   uint32_t steps_pn, uint32_t ldc_pm, int M, int64_t split_stride)
+                                                                                   uint32_t steps_pn, uint32_t ldc_pm, int M, int vt_panel, int64_t split_stride)
 {
-    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(A, W, C, bias, d_M, lda_ldw, steps_pn, ldc_pm, M, blockIdx.z, split_stride);
+    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(A, W, C, bias, d_M, lda_ldw, steps_pn, ldc_pm, M, blockIdx.z, split_stride, vt_panel);
 }
 
 // several problems, and problems of n_sub equal ones
@@ -475,7 +521,7 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_grou
     gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(static_cast<const unsigned char*>(g.A) + (size_t)(g.a[grp] + sub * s.sub_a) * 256,
                                                      static_cast<const unsigned char*>(g.W) + (size_t)(g.w[grp] + sub * s.sub_w) * 256,
                                                      static_cast<unsigned char*>(g.C) + (size_t)(g.c[grp] + sub * s.sub_c) * 256, bias, d_M, lda_ldw,
-                                                     steps_pn, ldc_pm, M, split, s.split_stride);
+                                                     steps_pn, ldc_pm, M, split, s.split_stride, s.vt_panel);
 }
 
 template <int KW, int MAXT, bool OUT_F32, int ACT>
@@ -508,7 +554,7 @@ hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t str
     if (s.G == 1 && n_sub == 1)
         hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, static_cast<const unsigned char*>(g.A) + (size_t)g.a[0] * 256,
                            static_cast<const unsigned char*>(g.W) + (size_t)g.w[0] * 256, static_cast<unsigned char*>(g.C) + (size_t)g.c[0] * 256,
-                           g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, s.split_stride);
+                           g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, s.vt_panel, s.split_stride);
     else
         hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
     return hipGetLastError();
@@ -564,7 +610,7 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
 {
     if (s.G <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
     if (s.G > kMaxGroup || s.splits < 1 || s.N % 32 != 0 || s.K % (64 * s.splits) != 0 || s.lda % 16 != 0 || s.ldw % 16 != 0 || s.ldc % 8 != 0 ||
-        s.lda < s.K || s.ldw < s.K || (s.splits > 1 && (!s.out_f32 || s.act != ACT_NONE)))
+        s.lda < s.K || s.ldw < s.K || (s.vt_panel && (s.out_f32 || s.act != ACT_NONE || s.vt_panel % 2 != 0)) || (s.splits > 1 && (!s.out_f32 || s.act != ACT_NONE)))
         return hipErrorInvalidValue;
     // byte offsets inside an operand are 31-bit
     if ((uint64_t)(s.M + 31) / 32 * s.lda * 64 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;

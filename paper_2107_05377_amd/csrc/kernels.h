@@ -91,6 +91,9 @@ struct TiledShape {
     int64_t split_stride;
     // few-row forms only: every problem is n_sub equal ones (heads) whose operands lie so far apart, in units of 256 bytes
     int32_t n_sub, sub_a, sub_w, sub_c, sub_b;
+    // bf16 results without activation: from this column panel on (0 = none) a 32x32 block is stored transposed, as the operand of a
+    // product over its rows: [16 rows][half][32 columns][8 rows], rows of a (16, half) run: 4 half + 0..3, 8 + 4 half + 0..3
+    int32_t vt_panel;
 };
 // The kernel forms (gemm_tiled.hip); TILED_AUTO chooses by shape.
 enum TiledForm : int { TILED_AUTO = 0, TILED_ROWS_1X1, TILED_ROWS_2X1, TILED_ROWS_2X2, TILED_K2, TILED_PAIR, TILED_TALL };
@@ -177,10 +180,17 @@ struct AttnGroup {
 };
 // Sequence b owns rows seq_start[b] .. +seq_len[b]-1 (all real tokens) when the two arrays are given;
 // otherwise rows b*S .. b*S+S-1 with `mask` ([B][S], 1 = real) marking the keys.  S bounds the length.
-// tiled: qkv and ctx in the panel layout (rows of 3H and H columns).
 // ctx_fmt 0: the context is written as bfloat16; 1: as E4M3 at unit scale (one byte per element, same row order)
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0, int tiled = 0);
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0);
+// Panel layout, packed sequences: projections with the values transposed (TiledShape::vt_panel), context as an operand; offsets in 256 bytes.
+struct AttnTiledGroup {
+    const void* base_qkv;
+    void* base_ctx;
+    uint32_t qkv[kMaxGroup], ctx[kMaxGroup];
+};
+hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
+                                  hipStream_t stream);
 hipError_t launch_attention_f32(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream);
 

@@ -908,15 +908,17 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
         g.b[i] = units(io[i].w->bqkv);
         g.c[i] = units(io[i].scr->qkv);
     }
-    L.tiled(MT_K_GEMM_QKV, g, TiledShape{n, M, 3 * H, H, H, H, 3 * H, ACT_NONE, 0, rm.n_rows, 1, 0});
+    L.tiled(MT_K_GEMM_QKV, g, TiledShape{n, M, 3 * H, H, H, H, 3 * H, ACT_NONE, 0, rm.n_rows, 1, 0, 0, 0, 0, 0, 0, 2 * H / 32});
 
-    AttnGroup ag;
+    AttnTiledGroup ag;
+    ag.base_qkv = ws;
+    ag.base_ctx = ws;
     for (int i = 0; i < n; ++i) {
-        ag.qkv[i] = ws + io[i].scr->qkv;
-        ag.ctx[i] = ws + io[i].scr->ctx;
+        ag.qkv[i] = units(io[i].scr->qkv);
+        ag.ctx[i] = units(io[i].scr->ctx);
     }
     L.begin(MT_K_ATTN);
-    L.check(launch_attention_bf16(ag, n, nullptr, rm.seq_start, rm.seq_len, B, S, H, A, L.st, 0, 1));
+    L.check(launch_attention_tiled(ag, n, rm.seq_start, rm.seq_len, B, S, H, A, L.st));
     L.end();
 
     for (int i = 0; i < n; ++i) {
