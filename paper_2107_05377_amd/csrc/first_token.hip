@@ -4,9 +4,9 @@
 //   first_query_kernel   one workgroup per (task, 32 sequences, head): query of the sequences' first rows (gathered before: in place, 16
 //                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences), then q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
 //                        fragments are in flight at once.
-//   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, 32
-//                        keys at a time with a running maximum; a key block is loaded while the one before is worked on.  The sums are
-//                        float32 on the vector units: 2 H FMAs per key and head are what bounds it.
+//   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
+//                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
+//                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509, now 117 and 34); bound by reading the rows.
 // Scores and sums were two kernels that read the rows once each (85 + 107 us for 8 tasks x 256 sequences).
 #include "kernels.h"
 #include "device_util.h"
@@ -18,14 +18,17 @@ namespace {
 constexpr int kHeadsPad = 16;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, int B, int H)
+__global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, FirstTokenGroup g)
 {
     constexpr int U = 12, MAXP = 8;
     __shared__ __attribute__((aligned(16))) float part[4][2][4][64][4];
     __shared__ __attribute__((aligned(16))) __bf16 qs[8 * 256];              // 64 columns of 32 rows, panel layout
-    const int a = blockIdx.x, grp = blockIdx.z, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the nb workgroups of a (task, head), which share its weight slices, follow one another on one XCD
+    const int i8 = blockIdx.x >> 3, pi = nb == 1 ? i8 : i8 / nb, pair = pi * 8 + (blockIdx.x & 7), yb = i8 - pi * nb;
+    if (pair >= pairs) return;
+    const int grp = pair / A, a = pair - grp * A, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int b0 = blockIdx.y * 32, panels = H >> 5;
+    const int b0 = yb * 32, panels = H >> 5;
     const size_t pw = (size_t)H * 64;                                        // bytes per panel
     const int steps = H / 64;                                                // K steps of 16 of a wavefront
     const unsigned char* wq = static_cast<const unsigned char*>(g.Wq[grp]) + (size_t)a * 2 * pw + (size_t)wave * steps * 1024 + lane * 16;
@@ -39,7 +42,7 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, 
     float4 bv[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const float4*>(g.bq[grp] + a * 64 + j * 32 + wave * 8 + half * 4);
-    const unsigned char* x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)blockIdx.y * pw + (size_t)wave * steps * 1024 + lane * 16;
+    const unsigned char* x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)yb * pw + (size_t)wave * steps * 1024 + lane * 16;
     f32x16 acc[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -83,8 +86,8 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, 
     bf16x8 qf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qs + kk * 512 + lane * 8);
-    // q~ of a sequence: [H / 8 chunks][16 heads][8], the operand order of the scores
-    __bf16* qt = static_cast<__bf16*>(g.qt[grp]) + (size_t)(b0 + l32) * H * kHeadsPad + a * 8 + half * 4;
+    // q~: [sequence][16 heads][H], so that a workgroup writes whole lines
+    __bf16* qt = static_cast<__bf16*>(g.qt[grp]) + ((size_t)(b0 + l32) * kHeadsPad + a) * H + half * 4;
 #pragma unroll
     for (int i = 0; i < MAXP; ++i) {
         const int p = wave + 4 * i;
@@ -98,142 +101,148 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(FirstTokenGroup g, 
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const bf16x4 o = {(__bf16)c[q * 4], (__bf16)c[q * 4 + 1], (__bf16)c[q * 4 + 2], (__bf16)c[q * 4 + 3]};
-                *reinterpret_cast<bf16x4*>(qt + (size_t)(p * 4 + q) * 128) = o;
+                *reinterpret_cast<bf16x4*>(qt + (p * 4 + q) * 8) = o;
             }
         }
     }
 }
 
-constexpr int kChunkStride = 528;       // bytes of a chunk of 32 keys in LDS: 16 more, so that the columns of a key spread over the banks
-
-template <int NA4>                      // heads / 4, rounded up
-__global__ __launch_bounds__(512) void first_attend_kernel(FirstTokenGroup g, const int32_t* __restrict__ seq_start,
-                                                           const int32_t* __restrict__ seq_len, int Smax, int H, int A, int64_t xbar_stride,
-                                                           float scale_log2e)
+// NW wavefronts, each 128 of the H columns (the last one perhaps 64).  Per key panel: a wavefront loads its columns of the 32 rows as matrix
+// operands (16 x 32, straight from global memory), forms its share of the scores with q~ and leaves it in LDS; after the only barrier all
+// wavefronts add the shares, each for itself, and have the weights of all heads in the operand order of the next product.  For that the
+// rows are needed transposed: a product with the unit matrix, exact, moves the columns to the lanes.
+template <int NW>
+__global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(const int32_t* __restrict__ seq_start,
+                                                                                    const int32_t* __restrict__ seq_len, int B, int Smax, int H,
+                                                                                    int A, int64_t xbar_stride, FirstTokenGroup g)
 {
-    constexpr int NH = NA4 * 4, XU = 8, SU = 8;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int grp = blockIdx.y, b = blockIdx.x;
-    const int row0 = seq_start[b], n = min(seq_len[b], Smax);
+    constexpr float kScale = 0.125f * 1.4426950408889634f;
+    __shared__ __attribute__((aligned(16))) float part[2][NW][2][64][4];
+    // an XCD takes neighbouring sequences: 16 bytes of each make up the lines of the result, which its second-level cache completes
+    const int per = (B + 7) >> 3, b = (blockIdx.x & 7) * per + (blockIdx.x >> 3), grp = blockIdx.y;
+    if (b >= B) return;
+    const int row0 = seq_start[b], n = min(seq_len[b], Smax), end = row0 + n;
     if (n <= 0) return;
-    const int nt = blockDim.x, nw = nt >> 6, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, half = lane >> 5, n_chunks = H >> 3;
-    unsigned char* xs = lds;                                                 // [chunk][32 keys][16 B]
-    float* part = reinterpret_cast<float*>(lds + n_chunks * kChunkStride);   // [wavefront][32 keys][16 heads]
-    float* ps = part + nw * 512;                                             // [32 keys][16 heads]
-    float* ms = ps + 512;                                                    // running maximum, sum and the block's rescale per head
-    float* ls = ms + 16;
-    float* al = ls + 16;
-    if (tid < 16) {
-        ms[tid] = -INFINITY;
-        ls[tid] = 0.f;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, l4 = lane >> 4;
+    const int p0 = row0 >> 5, p1 = (end + 31) >> 5;                          // panels of the sequence
+    const int steps = min(4, (H - wave * 128) / 32);                         // of 32 columns: 4 or 2
+    const size_t pitch = (size_t)H * 64;                                     // bytes of a panel
+    const unsigned char* x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)wave * 16 * 512 + l4 * 512 + l16 * 16;
+    const __bf16* qt = static_cast<const __bf16*>(g.qt[grp]) + ((size_t)b * kHeadsPad + min(l16, A - 1)) * H + wave * 128 + l4 * 8;
+    bf16x8 qf[4];
+    f32x4 acc[8];                                                            // 16 columns x 16 heads each; lane: head l16, columns 4 l4 + 0..3
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        qf[k] = *reinterpret_cast<const bf16x8*>(qt + min(k, steps - 1) * 32);
+        if (k >= steps) qf[k] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});          // columns beyond H repeat others, to no effect
     }
-    const __bf16* __restrict__ x = static_cast<const __bf16*>(g.x[grp]);
-    // this wavefront's share of the K steps and its q~ fragments (columns beyond the heads repeat others and are not used)
-    const int per = (H / 16 + nw - 1) / nw, st0 = wave * per, st1 = min(st0 + per, H / 16);
-    const __bf16* qt = static_cast<const __bf16*>(g.qt[grp]) + (size_t)b * H * kHeadsPad + (l32 & 15) * 8;
-    bf16x8 qf[SU];
 #pragma unroll
-    for (int u = 0; u < SU; ++u) qf[u] = *reinterpret_cast<const bf16x8*>(qt + (size_t)(min(st0 + u, H / 16 - 1) * 2 + half) * 128);
-    u32x4 xv[XU];
-    auto fetch = [&](int kb) {
+    for (int c = 0; c < 8; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 unit[2];                                                          // [16 columns][32]: the first and the second 16 of a step
 #pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int i = tid + u * nt, key = i & 31, chunk = min(i >> 5, n_chunks - 1);
-            xv[u] = *reinterpret_cast<const u32x4*>(x + tiled_offset(row0 + min(kb + key, n - 1), chunk * 8, H));
+    for (int c = 0; c < 2; ++c) {
+        const int d = l16 + c * 16 - l4 * 8;
+        u32x4 u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = d == 2 * e ? 0x3F80u : (d == 2 * e + 1 ? 0x3F800000u : 0u);
+        unit[c] = __builtin_bit_cast(bf16x8, u);
+    }
+    float m_run = -INFINITY, l_run = 0.f;
+    bf16x8 xa[2][4], xb[2][4];                                               // [upper or lower 16 keys][step]
+    auto fetch = [&](bf16x8 (&v)[2][4], int kb) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) v[h][k] = *reinterpret_cast<const bf16x8*>(x + (size_t)kb * pitch + min(k, steps - 1) * 2048 + h * 256);
+    };
+    auto block = [&](const bf16x8 (&v)[2][4], int kb, int buf) {
+        f32x4 sc[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            sc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], sc[h], 0, 0, 0);    // row: key, column: head
+            if constexpr (NW > 1) *reinterpret_cast<f32x4*>(part[buf][wave][h][lane]) = sc[h];
+        }
+        if constexpr (NW > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                sc[h] = *reinterpret_cast<const f32x4*>(part[buf][0][h][lane]);
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sc[h] += *reinterpret_cast<const f32x4*>(part[buf][w][h][lane]);
+                __builtin_amdgcn_sched_barrier(0);                           // (fewer of the shares in registers at a time)
+            }
+        }
+        // keys 16 h + 4 l4 + e of this panel; what belongs to a neighbouring sequence counts as nothing, whatever it is
+        const bool edge = kb * 32 < row0 || kb * 32 + 32 > end;
+        u32x4 keep = {~0u, ~0u, ~0u, ~0u};
+        if (edge) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((unsigned)(kb * 32 + h * 16 + l4 * 4 + e - row0) >= (unsigned)n) {
+                        sc[h][e] = -INFINITY;
+                        keep[h * 2 + (e >> 1)] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+                    }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[h][e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * kScale;
+        if (__any(l16 < A && mx > m_run + 8.f)) {                            // the maximum follows only when a score exceeds it by 2^8
+            const float m_new = fmaxf(m_run, mx), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+        }
+        bf16x8 pf;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(sc[h][e], kScale, -m_run));
+                l_run += p;
+                pf[h * 4 + e] = (__bf16)p;
+            }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            bf16x8 xt;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][c >> 1], unit[c & 1], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xt[h * 4 + e] = (__bf16)t[e];
+            }
+            xt = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, xt) & keep);
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt, pf, acc[c], 0, 0, 0);                                    // row: column, column: head
+            if (c & 1) __builtin_amdgcn_sched_barrier(0);                    // (two at a time, for the registers)
         }
     };
-    float acc[NH][2];
-#pragma unroll
-    for (int h = 0; h < NH; ++h) acc[h][0] = acc[h][1] = 0.f;
-    fetch(0);
-    for (int kb = 0; kb < n; kb += 32) {
-        __syncthreads();                                                     // the block before has been summed
-#pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int i = tid + u * nt;
-            if ((i >> 5) < n_chunks) *reinterpret_cast<u32x4*>(xs + (i >> 5) * kChunkStride + (i & 31) * 16) = xv[u];
-        }
-        __syncthreads();
-        fetch(kb + 32);                                                      // (beyond the last block: its last key again)
-        f32x16 sc;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
-#pragma unroll
-        for (int u = 0; u < SU; ++u)
-            if (st0 + u < st1) {
-                const bf16x8 kf = *reinterpret_cast<const bf16x8*>(xs + ((st0 + u) * 2 + half) * kChunkStride + l32 * 16);
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[u], sc, 0, 0, 0);     // row: key, column: head
-            }
-        if (l32 < 16) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) part[wave * 512 + ((e >> 2) * 8 + half * 4 + (e & 3)) * 16 + l32] = sc[e];
-        }
-        __syncthreads();
-        // softmax step: 16 lanes per head, two keys each
-        for (int h = tid >> 4; h < A; h += nt >> 4) {
-            const int k = tid & 15;
-            float s0 = 0.f, s1 = 0.f;
-            for (int w = 0; w < nw; ++w) {
-                s0 += part[w * 512 + k * 16 + h];
-                s1 += part[w * 512 + (k + 16) * 16 + h];
-            }
-            s0 = kb + k < n ? s0 * scale_log2e : -INFINITY;
-            s1 = kb + k + 16 < n ? s1 * scale_log2e : -INFINITY;
-            float mx = fmaxf(s0, s1);
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-            const float m_old = ms[h], m_new = fmaxf(m_old, mx), alpha = __builtin_amdgcn_exp2f(m_old - m_new);
-            const float p0 = __builtin_amdgcn_exp2f(s0 - m_new), p1 = __builtin_amdgcn_exp2f(s1 - m_new);
-            float sum = p0 + p1;
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) sum += __shfl_xor(sum, o, 64);
-            ps[k * 16 + h] = p0;
-            ps[(k + 16) * 16 + h] = p1;
-            if (k == 0) {
-                const float l_old = ls[h];
-                ms[h] = m_new;
-                ls[h] = l_old * alpha + sum;
-                al[h] = alpha;
-            }
-        }
-        __syncthreads();
-        if (tid * 2 < H) {                                                   // two columns per thread
-#pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const float r = al[h];
-                acc[h][0] *= r;
-                acc[h][1] *= r;
-            }
-            const unsigned char* xc = xs + (tid >> 2) * kChunkStride + (tid & 3) * 4;
-            const int kn = min(32, n - kb);
-#pragma unroll 4
-            for (int key = 0; key < kn; ++key) {
-                const uint32_t w = *reinterpret_cast<const uint32_t*>(xc + key * 16);
-                const float x0 = __uint_as_float(w << 16), x1 = __uint_as_float(w & 0xFFFF0000u);
-#pragma unroll
-                for (int h4 = 0; h4 < NA4; ++h4) {
-                    const float4 p = *reinterpret_cast<const float4*>(ps + key * 16 + h4 * 4);
-                    acc[h4 * 4 + 0][0] = fmaf(p.x, x0, acc[h4 * 4 + 0][0]);
-                    acc[h4 * 4 + 0][1] = fmaf(p.x, x1, acc[h4 * 4 + 0][1]);
-                    acc[h4 * 4 + 1][0] = fmaf(p.y, x0, acc[h4 * 4 + 1][0]);
-                    acc[h4 * 4 + 1][1] = fmaf(p.y, x1, acc[h4 * 4 + 1][1]);
-                    acc[h4 * 4 + 2][0] = fmaf(p.z, x0, acc[h4 * 4 + 2][0]);
-                    acc[h4 * 4 + 2][1] = fmaf(p.z, x1, acc[h4 * 4 + 2][1]);
-                    acc[h4 * 4 + 3][0] = fmaf(p.w, x0, acc[h4 * 4 + 3][0]);
-                    acc[h4 * 4 + 3][1] = fmaf(p.w, x1, acc[h4 * 4 + 3][1]);
-                }
-            }
-        }
+    fetch(xa, p0);
+    for (int kb = p0; kb < p1; kb += 2) {
+        if (kb + 1 < p1) fetch(xb, kb + 1);
+        block(xa, kb, 0);
+        if (kb + 1 >= p1) break;
+        if (kb + 2 < p1) fetch(xa, kb + 2);
+        block(xb, kb + 1, 1);
     }
-    if (tid * 2 >= H) return;
-    __bf16* out = static_cast<__bf16*>(g.xbar[grp]) + tiled_offset(b, tid * 2, H);
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (l16 >= A) return;
+    const float inv = 1.0f / l_run;
+    __bf16* out = static_cast<__bf16*>(g.xbar[grp]) + l16 * xbar_stride + tiled_offset(b, wave * 128 + l4 * 4, H);
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
-        if (h < A) {
-            const float inv = 1.0f / ls[h];
-            const bf16x2 o = {(__bf16)(acc[h][0] * inv), (__bf16)(acc[h][1] * inv)};
-            *reinterpret_cast<bf16x2*>(out + h * xbar_stride) = o;
+    for (int c = 0; c < 8; ++c)
+        if (c < 4 || steps == 4) {
+            const bf16x4 o = {(__bf16)(acc[c][0] * inv), (__bf16)(acc[c][1] * inv), (__bf16)(acc[c][2] * inv), (__bf16)(acc[c][3] * inv)};
+            *reinterpret_cast<bf16x4*>(out + c * 512) = o;
         }
 }
 
@@ -243,7 +252,8 @@ hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int
 {
     if (G <= 0 || B <= 0) return hipSuccess;
     if (G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(first_query_kernel, dim3(A, (B + 31) / 32, G), dim3(256), 0, stream, g, B, H);
+    const int nb = (B + 31) / 32, pairs = A * G;
+    hipLaunchKernelGGL(first_query_kernel, dim3((pairs + 7) / 8 * 8 * nb), dim3(256), 0, stream, B, H, A, nb, pairs, g);
     return hipGetLastError();
 }
 
@@ -252,23 +262,16 @@ hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* s
 {
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
     if (!seq_start || !seq_len || G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-    const int nt = (H / 2 + 63) / 64 * 64;                                  // <= 512
-    const size_t bytes = (size_t)(H / 8) * kChunkStride + (size_t)(nt / 64) * 2048 + 2048 + 3 * 64;
-    const float scale = 0.125f * 1.4426950408889634f;
-#define MT_ATTEND(N)                                                                                                                      \
-    do {                                                                                                                                  \
-        static std::atomic<uint64_t> raised{0};                                                                                           \
-        if (bytes > 64 * 1024) {                                                                                                          \
-            hipError_t e = ensure_dynamic_lds((const void*)first_attend_kernel<N>, 96 * 1024, raised);                                    \
-            if (e != hipSuccess) return e;                                                                                                \
-        }                                                                                                                                 \
-        hipLaunchKernelGGL(first_attend_kernel<N>, dim3(B, G), dim3(nt), bytes, stream, g, seq_start, seq_len, S, H, A, xbar_stride, scale); \
-    } while (0)
-    switch ((A + 3) / 4) {
-        case 1: MT_ATTEND(1); break;
-        case 2: MT_ATTEND(2); break;
-        case 3: MT_ATTEND(3); break;
-        default: MT_ATTEND(4); break;
+#define MT_ATTEND(N) case N: hipLaunchKernelGGL(first_attend_kernel<N>, dim3((B + 7) / 8 * 8, G), dim3(N * 64), 0, stream, seq_start, seq_len, B, S, H, A, xbar_stride, g); break
+    switch ((H + 127) / 128) {
+        MT_ATTEND(1);
+        MT_ATTEND(2);
+        MT_ATTEND(3);
+        MT_ATTEND(4);
+        MT_ATTEND(5);
+        MT_ATTEND(6);
+        MT_ATTEND(7);
+        MT_ATTEND(8);
     }
 #undef MT_ATTEND
     return hipGetLastError();
