@@ -84,11 +84,11 @@ def host_description():
     return {"logical_cpus": os.cpu_count(), "usable_cpus": usable, "model": model}
 
 
-TRAFFIC_SOURCES = ("gemm_bf16.hip", "gemm_bf16_persist.hip", "mt_model.cpp")     # kernels and the host code that picks launch shapes
+TRAFFIC_SOURCES = ("gemm_tiled.hip", "mt_model.cpp")     # kernels and the host code that picks launch shapes
 
 
 def traffic_source_hash():
-    """One hash over the sources that decide the tiled contractions' HBM traffic: both kernels and the scheduler."""
+    """One hash over the sources that decide the tiled contractions' HBM traffic: the kernels and the scheduler."""
     import hashlib
     h = hashlib.sha256()
     for f in TRAFFIC_SOURCES:
@@ -489,7 +489,7 @@ def main():
     peak = PEAK_BF16_MFMA_TFLOPS if bf16 else PEAK_FP32_VALU_TFLOPS
     flops, main_flops, gemm_ms, gemm_ms_raw, gemm_launches = gemm_summary(spec, B, rows, prof, dur, kernels, args.steps, peak)
     gemm_tflops = main_flops / (gemm_ms * 1e-3) / 1e12
-    kname = ("gemm_bf16_kernel + gemm_bf16_persist_kernel" if rows * sv.R > 256 else "gemm_skinny_bf16_kernel") if bf16 else "gemm_f32_kernel"
+    kname = ("gemm_tiled_kernel" if rows * sv.R > 256 else "gemm_tiled_rows_kernel") if bf16 else "gemm_f32_kernel"
     traffic = stored_traffic(spec.name, sv.R) if (bf16 and B == spec.batch and rows * sv.R > 256) else None
     measured_peak = mt.mfma_peak() if bf16 else None
     # per LAUNCH: a launch serves the rows of all request batches of its call

@@ -97,7 +97,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
     const int voff = lane * 16;
 
     struct Ref {
-        __amdgpu_buffer_rsrc_t A, W;      // a panel beyond the last one lies beyond the buffer's end: reads as zero
+        // A starts at the tile's first panel (the whole operand may exceed the 31 bits of an offset); a panel beyond the last one lies
+        // beyond the buffer's end: reads as zero
+        __amdgpu_buffer_rsrc_t A, W;
         int ao, wo, grp, split, pm0, pn0;
     };
     auto locate = [&](int j, Ref& t) {
@@ -110,9 +112,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         t.pm0 = tm * TMI;
         t.pn0 = (tn * WN + wn) * 2;
         const int k0 = t.split * KW * KT * 4096;                             // byte offset of the K range inside a panel
-        t.A = t_rsrc(static_cast<const unsigned char*>(g.A) + (size_t)g.a[t.grp] * 256, panels_m * pa);
+        t.A = t_rsrc(static_cast<const unsigned char*>(g.A) + (size_t)g.a[t.grp] * 256 + (size_t)t.pm0 * pa, min(panels_m - t.pm0, TMI) * pa);
         t.W = t_rsrc(static_cast<const unsigned char*>(g.W) + (size_t)g.w[t.grp] * 256, panels_n * pw);
-        t.ao = t.pm0 * (int)pa + k0 + wave * 1024;
+        t.ao = k0 + wave * 1024;
         t.wo = t.pn0 * (int)pw + k0 + wk * KT * 4096;
     };
     Ref cur, nxt;
@@ -612,8 +614,8 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
     if (s.G > kMaxGroup || s.splits < 1 || s.N % 32 != 0 || s.K % (64 * s.splits) != 0 || s.lda % 16 != 0 || s.ldw % 16 != 0 || s.ldc % 8 != 0 ||
         s.lda < s.K || s.ldw < s.K || (s.vt_panel && (s.out_f32 || s.act != ACT_NONE || s.vt_panel % 2 != 0)) || (s.splits > 1 && (!s.out_f32 || s.act != ACT_NONE)))
         return hipErrorInvalidValue;
-    // byte offsets inside an operand are 31-bit
-    if ((uint64_t)(s.M + 31) / 32 * s.lda * 64 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;
+    // byte offsets inside the weights, and inside the 8 row panels of a tile, are 31-bit
+    if ((uint64_t)s.lda * 64 * 8 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;
     if (form == TILED_AUTO) form = choose_form(s);
     // the tile forms: a tile's loads reach at most into the next tile, so it has at least as many slices as the ring holds ahead
     const int kw = form == TILED_K2 ? 2 : 1, slices = s.K / (64 * kw) / s.splits;

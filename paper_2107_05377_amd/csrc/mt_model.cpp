@@ -105,7 +105,7 @@ struct mt_model {
     bool bf16 = true;
     bool fp8 = false;   // MT_FP8_FFN / MT_FP8_LAYER: bf16 everywhere, the two feed-forward contractions of every all-rows layer in E4M3
     bool fp8_attn = false;   // MT_FP8_LAYER: the QKV and attention output projections of such a layer too
-    bool tiled = false;      // MT_BF16 with up to 16 heads: weights, operands and states in the panel layout (kernels.h)
+    bool tiled = false;      // MT_BF16 with up to 16 heads (mt_create has the rule): weights, operands and states in the panel layout (kernels.h)
     size_t esz = 2;   // bytes per matrix / activation element
     int C_tot = 0, C_tok = 0;            // widths of the per-sequence and of the per-token logit row
     std::vector<int> logit_off;          // task -> first column inside the row of its kind
@@ -1144,7 +1144,9 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->bf16 = cfg->precision != MT_FP32_CHECK;
     m->fp8 = cfg->precision == MT_FP8_FFN || cfg->precision == MT_FP8_LAYER;
     m->fp8_attn = cfg->precision == MT_FP8_LAYER;
-    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16;
+    // (the few-row contraction, the only form for K < 320, packs its row panels into 16 bits)
+    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16 &&
+               ((int64_t)cfg->max_batch * cfg->max_seq <= 65535 * 32 || std::min(cfg->hidden, cfg->ffn) >= 320);
     m->esz = m->bf16 ? 2 : 4;
     const size_t H = cfg->hidden, F = cfg->ffn, T = cfg->n_tasks, D = cfg->n_trunk_layers;
     for (const auto& d : m->tasks) {

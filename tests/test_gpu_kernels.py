@@ -50,3 +50,29 @@ def test_attention_f32_blocks(B, S, H, A):
     qkv = np.concatenate([q, k, v], axis=2).reshape(B * S, 3 * H)
     ctx = mt.op_attention(mt.MT_FP32_CHECK, dev(qkv), dev(mask), B, S, H, A).cpu().numpy().reshape(B, S, H)
     assert np.abs(ctx - oracle.attention(q, k, v, mask, A)).max() <= 2e-5
+
+
+# bfloat16 kernels of the panel layout through a whole model: ragged rows, both contractions' halves that a launch rule can choose.
+# Bound on the logits: bfloat16 operands (2^-9 each) through three layers give at most 2e-2 at logits of order 1.
+@pytest.mark.parametrize("heads,ffn,batch,seq,lo", [
+    (1, 64, 1, 1, 1),            # one row; K below one tile's ring
+    (16, 192, 33, 65, 1),        # 16 heads; one sequence over a panel of first tokens; sequences that end one row into a key panel
+    (2, 320, 2, 289, 280),       # key panels shared by two wavefronts, an odd number of them
+    (10, 2112, 300, 9, 1),       # K split between wavefronts; a long K that no tile's slices divide
+    (10, 2048, 720, 31, 17),     # pairs of workgroups per compute unit; tall tiles for the long K
+    (1, 16384, 2048, 33, 2),     # an operand of more than 2 GiB
+])
+def test_panel_layout_forms(heads, ffn, batch, seq, lo):
+    print(f"panel layout: {heads} heads, ffn {ffn}, {batch} x {seq}", flush=True)
+    spec = ms.MTSpec("panels", vocab=300, hidden=64 * heads, heads=heads, ffn=ffn, max_pos=seq + 1, n_trunk_layers=1,
+                     tasks=(ms.TaskSpec(1, 2, 3), ms.TaskSpec(0, 1, 2), ms.TaskSpec(1, 0, 2)), precision="bf16", batch=batch, seq=seq,
+                     len_lo=lo, len_hi=seq, input_seed=heads + seq)
+    model, (trunk, tasks) = mt.load_synthetic(spec, keep_params=True, std=0.03)
+    ids, mask, _ = ms.make_inputs(spec)
+    got = model.forward(dev(ids), dev(mask)).cpu().numpy()
+    pick = np.unique(np.linspace(0, batch - 1, 7).astype(int))
+    ref = oracle.Oracle(spec, trunk, tasks).mt_forward(ids[pick], mask[pick])
+    err = np.abs(got[pick] - ref).max()
+    print(f"  max |dlogit| {err:.3g}, logits up to {np.abs(ref).max():.3g}", flush=True)
+    assert np.isfinite(got).all() and err <= 2e-2
+    model.close()
