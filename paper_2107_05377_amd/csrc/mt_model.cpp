@@ -889,6 +889,12 @@ int tiled_splits(int M, int N, int K, int most)
     const long blocks = (long)((M + 31) / 32) * (N / 32);
     int sp = 1;
     while (sp < most && blocks * sp < 192 && K % (128 * sp) == 0) sp *= 2;
+    // One round of K2 tiles (gemm_tiled.hip) leaves a serial K loop on compute units that are not all busy: two ranges of K, where the
+    // launch then takes that form (choose_form: more than 3072 blocks, or 64 row panels) and fewer than 7/8 of 256 compute units had a
+    // tile.  A pass over 32 x 128 tokens at BERT-base widths 1265 -> 1248 us, 7 x 509 1312 -> 1293, 16 x 200 at BERT-large's 2680 -> 2617;
+    // 64 x 128, beyond the line, is the same either way, and the few-row form, below it, loses (15 x 128: 905 -> 923).
+    const long panels = (M + 31) / 32, tiles = (panels + 3) / 4 * ((N + 127) / 128);
+    if (sp == 1 && most >= 4 && K % 256 == 0 && tiles < 224 && 2 * blocks > 1152 && (panels >= 64 || 2 * blocks > 3072)) sp = 2;
     return sp;
 }
 

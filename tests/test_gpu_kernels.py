@@ -60,6 +60,7 @@ def test_attention_f32_blocks(B, S, H, A):
     (2, 320, 2, 289, 280),       # key panels shared by two wavefronts, an odd number of them
     (10, 2112, 300, 9, 1),       # K split between wavefronts; a long K that no tile's slices divide
     (10, 2048, 720, 31, 17),     # pairs of workgroups per compute unit; tall tiles for the long K
+    (12, 2048, 29, 70, 30),      # the trunk's long K in two ranges of tiles, 64 row panels by the bound
     (1, 16384, 2048, 33, 2),     # an operand of more than 2 GiB
 ])
 def test_panel_layout_forms(heads, ffn, batch, seq, lo):
