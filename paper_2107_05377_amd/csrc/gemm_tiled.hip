@@ -382,7 +382,8 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
 // arguments, which the command processor preloads into registers, and the loads go out before the row count has arrived (panels
 // beyond it are memory of the operand all the same).
 // Packed: lda_ldw = widths in 16 columns, lda | ldw << 16; steps_pn = K steps of 16 per wavefront | column panels << 16; ldc_pm = width
-// of C in 8 columns | row panels by the bound << 16.
+// of C in 8 columns | first row panel / 65536 << 16 (more row panels than a grid can have take several launches, see launch_rows).
+constexpr int kLaunchPanels = 65536;
 template <int TM, int TN, bool OUT_F32, int ACT>
 __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, const unsigned char* W, unsigned char* C, const float* bias,
                                                      const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn, uint32_t ldc_pm, int M, int split,
@@ -392,8 +393,8 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
     __shared__ __attribute__((aligned(16))) float part[4][NBLK][4][64][4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(A));     // in flight until the stores
-    const int steps = steps_pn & 0xFFFF, panels_n = steps_pn >> 16, bound_m = ldc_pm >> 16;
-    const int pn0 = blockIdx.x * TN, pm0 = blockIdx.y * TM;
+    const int steps = steps_pn & 0xFFFF, panels_n = steps_pn >> 16, bound_m = (M + 31) >> 5;
+    const int pn0 = blockIdx.x * TN, pm0 = (int)blockIdx.y * TM + (int)(ldc_pm & ~0xFFFFu);
     const size_t pa = (size_t)(lda_ldw & 0xFFFF) * 1024, pw = (size_t)(lda_ldw >> 16) * 1024;      // bytes per panel
     const size_t k0 = (size_t)(split * 4 + wave) * steps * 1024 + lane * 16;
     const unsigned char* a[TM];
@@ -549,16 +550,20 @@ hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int 
 template <int TM, int TN, bool OUT_F32, int ACT>
 hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t stream)
 {
-    const int n_sub = s.n_sub > 1 ? s.n_sub : 1, pm = (s.M + 31) / 32;
-    dim3 grid((s.N / 32 + TN - 1) / TN, (pm + TM - 1) / TM, s.G * s.splits * n_sub), block(256);
-    const uint32_t lda_ldw = (uint32_t)(s.lda / 16) | (uint32_t)(s.ldw / 16) << 16, steps_pn = (uint32_t)(s.K / s.splits / 64) | (uint32_t)(s.N / 32) << 16,
-                   ldc_pm = (uint32_t)(s.ldc / 8) | (uint32_t)pm << 16;
-    if (s.G == 1 && n_sub == 1)
-        hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, static_cast<const unsigned char*>(g.A) + (size_t)g.a[0] * 256,
-                           static_cast<const unsigned char*>(g.W) + (size_t)g.w[0] * 256, static_cast<unsigned char*>(g.C) + (size_t)g.c[0] * 256,
-                           g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, s.vt_panel, s.split_stride);
-    else
-        hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
+    const int n_sub = s.n_sub > 1 ? s.n_sub : 1, panels = (s.M + 31) / 32;
+    if (TM == 1 && panels > 65535) return hipErrorInvalidValue;      // (choose_form takes it for up to 1152 blocks)
+    const uint32_t lda_ldw = (uint32_t)(s.lda / 16) | (uint32_t)(s.ldw / 16) << 16, steps_pn = (uint32_t)(s.K / s.splits / 64) | (uint32_t)(s.N / 32) << 16;
+    for (int pm0 = 0; pm0 < panels; pm0 += kLaunchPanels) {
+        dim3 grid((s.N / 32 + TN - 1) / TN, (std::min(panels - pm0, kLaunchPanels) + TM - 1) / TM, s.G * s.splits * n_sub), block(256);
+        const uint32_t ldc_pm = (uint32_t)(s.ldc / 8) | (uint32_t)pm0;
+        if (s.G == 1 && n_sub == 1)
+            hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream,
+                               static_cast<const unsigned char*>(g.A) + (size_t)g.a[0] * 256, static_cast<const unsigned char*>(g.W) + (size_t)g.w[0] * 256,
+                               static_cast<unsigned char*>(g.C) + (size_t)g.c[0] * 256, g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M,
+                               lda_ldw, steps_pn, ldc_pm, s.M, s.vt_panel, s.split_stride);
+        else
+            hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
+    }
     return hipGetLastError();
 }
 
@@ -622,7 +627,7 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
     if (form >= TILED_K2 && (s.n_sub > 1 || s.K % (64 * kw * s.splits) != 0 || slices < 5 || (form == TILED_TALL && slices % 2 != 0)))
         return hipErrorInvalidValue;
     if (form < TILED_K2 && ((long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535 || s.lda / 16 > 65535 || s.ldw / 16 > 65535 || s.ldc / 8 > 65535 ||
-                            s.N / 32 > 65535 || (s.M + 31) / 32 > 65535))
+                            s.N / 32 > 65535))
         return hipErrorInvalidValue;
     if (s.out_f32) {
         if (s.act == ACT_TANH) return launch_form<true, ACT_TANH>(g, s, form, force, stream);

@@ -1150,9 +1150,8 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->bf16 = cfg->precision != MT_FP32_CHECK;
     m->fp8 = cfg->precision == MT_FP8_FFN || cfg->precision == MT_FP8_LAYER;
     m->fp8_attn = cfg->precision == MT_FP8_LAYER;
-    // (the few-row contraction, the only form for K < 320, packs its row panels into 16 bits)
-    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16 &&
-               ((int64_t)cfg->max_batch * cfg->max_seq <= 65535 * 32 || std::min(cfg->hidden, cfg->ffn) >= 320);
+    // (nothing that handles on one weight arena may differ in decides its layout: neither max_batch nor max_seq, see mt_share_weights)
+    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16;
     m->esz = m->bf16 ? 2 : 4;
     const size_t H = cfg->hidden, F = cfg->ffn, T = cfg->n_tasks, D = cfg->n_trunk_layers;
     for (const auto& d : m->tasks) {

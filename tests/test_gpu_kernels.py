@@ -77,3 +77,32 @@ def test_panel_layout_forms(heads, ffn, batch, seq, lo):
     print(f"  max |dlogit| {err:.3g}, logits up to {np.abs(ref).max():.3g}", flush=True)
     assert np.isfinite(got).all() and err <= 2e-2
     model.close()
+
+
+def test_weight_layout_does_not_depend_on_a_handles_bounds():
+    """Handles of different max_batch x max_seq share one weight arena (mt_share_weights), so its layout must be the same for all of them.  The
+    owner's bound is beyond 65535 x 32 rows and takes more few-row workgroups along the rows than a grid has (65535 of 64 rows)."""
+    batch, seq = 65535, 65
+    spec = ms.MTSpec("bounds", vocab=300, hidden=64, heads=1, ffn=64, max_pos=seq, n_trunk_layers=1, tasks=(ms.TaskSpec(1, 2, 3), ms.TaskSpec(0, 1, 2)),
+                     precision="bf16", batch=batch, seq=seq, len_lo=1, len_hi=seq, input_seed=5)
+    owner, (trunk, tasks) = mt.load_synthetic(spec, keep_params=True, std=0.1)
+    small = mt.Model(mt.make_config(spec, max_batch=5, max_seq=seq), bind=False)
+    small.weights = owner.weights
+    small.workspace = torch.empty(small.workspace_bytes(), dtype=torch.uint8, device="cuda")
+    small._check(mt.lib().mt_bind(small.h, owner.weights.data_ptr(), owner.weights.numel(), small.workspace.data_ptr(), small.workspace.numel()))
+    small._check(mt.lib().mt_share_weights(small.h, owner.h))
+    ids, mask, _ = ms.make_inputs(spec)
+    mask[-1] = 1                                   # the last panel of the bound is reached if every position before it is kept
+    pick = np.array([0, 1, 31000, 65533, 65534])
+    ref = oracle.Oracle(spec, trunk, tasks).mt_forward(ids[pick], mask[pick])
+    bound = 2e-2 * max(1.0, np.abs(ref).max())     # bfloat16 operands through three layers, relative to the logits
+    few = small.forward(dev(ids[pick]), dev(mask[pick])).cpu().numpy()
+    print(f"replica: max |dlogit| {np.abs(few - ref).max():.3g}, logits up to {np.abs(ref).max():.3g}", flush=True)
+    assert np.abs(few - ref).max() <= bound
+    for m in (mask, np.ones_like(mask)):           # 2.1 and 4.3 million rows
+        ref = oracle.Oracle(spec, trunk, tasks).mt_forward(ids[pick], m[pick])
+        got = owner.forward(dev(ids), dev(m)).cpu().numpy()[pick]
+        print(f"owner: max |dlogit| {np.abs(got - ref).max():.3g}", flush=True)
+        assert np.abs(got - ref).max() <= bound
+    small.close()
+    owner.close()
