@@ -203,7 +203,9 @@ int mt_forward_requests(mt_model* m, int32_t n_requests, const int32_t* const* h
  * argument is not touched by this call).
  *   - Limit: mt_workspace_bytes(m) <= MT_STATIC_SCRATCH_BYTES, i.e. create the model with max_batch x max_seq
  *     small enough (at BERT-base width with 8 two-layer tasks on 6 shared layers: 2 x 64 tokens); larger models get
- *     MT_ERR_SHAPE with a message that names both sizes, and nothing is enqueued.
+ *     MT_ERR_SHAPE with a message that names both sizes, and nothing is enqueued.  A model that is over the limit only
+ *     because MT_BF16 pads every matrix to 32 rows (few sequences and many tasks: 60 tasks, one sequence) is served
+ *     all the same: its tasks then take turns at fewer sets of buffers.
  *   - All calls on one GPU, from every model and every stream, share that GPU's array: calls that overlap on one
  *     GPU race.  Issue them on one stream, or order them yourself.  Nothing in the array needs to start at
  *     zero: each call rewrites what it reads, so contents left by an earlier (larger or smaller) call are harmless.

@@ -91,6 +91,21 @@ struct RouteMapOff {   // byte offsets of a sub-batch row map (per-sequence rout
     size_t n, src, start, len, seq;
     size_t rowof;      // position -> compact row, for token-level heads
 };
+struct WsLayout {   // byte offsets into a workspace
+    std::vector<size_t> tap_f, tap_b;         // per tap slot
+    size_t pp_f[2] = {0, 0}, pp_b[2] = {0, 0};
+    Scratch trunk_scr{};
+    size_t slots = 0;                         // task t's buffers (but its final state) are also those of t + slots, t + 2 slots, ..
+    std::vector<Scratch> task_scr;
+    std::vector<size_t> task_xf, task_xb;
+    std::vector<ClsScratch> task_cls;
+    std::vector<size_t> pooled, split;        // pooler output, and its operand: [hi | lo] bf16 halves, or float32 rows in the validation mode
+    size_t rm_n = 0, rm_src = 0, rm_rowof = 0, rm_start = 0, rm_len = 0;   // padding-free row map of the current batch
+    size_t chk_count = 0;                                                   // mt_check_mask: one int32
+    size_t mr_ids = 0, mr_mask = 0, mr_logits = 0;                          // mt_forward_multi: the combined batch's ids, mask, logits
+    std::vector<RouteMapOff> route;
+    size_t bytes = 0;
+};
 struct ProfRec {
     int klass;
     hipEvent_t t0, t1;
@@ -119,17 +134,9 @@ struct mt_model {
     // workspace
     size_t Mmax = 0, MBmax = 0;               // rows of a state, and of a one-row-per-sequence matrix
     std::vector<int> tap_of_layer;            // layer index 0..D -> tap slot or -1
-    std::vector<size_t> tap_f, tap_b;         // per tap slot
-    size_t pp_f[2] = {0, 0}, pp_b[2] = {0, 0};
-    Scratch trunk_scr{};
-    std::vector<Scratch> task_scr;
-    std::vector<size_t> task_xf, task_xb;
-    std::vector<ClsScratch> task_cls;
-    size_t pooled = 0, cls_split = 0;
-    size_t rm_n = 0, rm_src = 0, rm_rowof = 0, rm_start = 0, rm_len = 0;   // padding-free row map of the current batch
-    size_t chk_count = 0;                                                   // mt_check_mask: one int32
-    size_t mr_ids = 0, mr_mask = 0, mr_logits = 0;                          // mt_forward_multi: the combined batch's ids, mask, logits
-    size_t workspace_bytes = 0;
+    WsLayout bound;                           // of the arena given to mt_bind
+    WsLayout fixed;                           // of mt_forward_static's array: `bound`, or one with fewer slots
+    const WsLayout* lay = &bound;             // of the forward pass being enqueued / enqueued last
 
     unsigned char* d_w = nullptr;
     unsigned char* d_ws = nullptr;
@@ -144,7 +151,6 @@ struct mt_model {
     bool profiling = false;
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> event_pool;
-    std::vector<RouteMapOff> route;
     // per-sequence routing: groups of tasks run side by side on streams of the model's own (default priority),
     // forked from and joined back into the caller's stream with events; created by the first routed forward
     std::vector<hipStream_t> aux_streams;
@@ -230,6 +236,33 @@ Scratch layout_scratch_tiled(Bump& b, size_t M, size_t H, size_t F, int y_parts)
     s.x1f = b.take(M * H * 4);
     s.x1b = b.take(M * H * 2);
     return s;
+}
+
+// Panel layout, first-token layer of a task.  A matrix of one row per sequence is at least one panel of 32 rows, 32 times what a single
+// sequence needs, so buffers that are never live together lie over one another: the contexts, then the result, over the gathered rows
+// and q~ (dead after first_attend); the row layers' buffers over the weighted row sums (dead after the contexts).  21 tasks at BERT-base
+// width and one sequence: 22 MiB of workspace instead of 54.  q~ is no panel matrix: its rows are the sequences.
+ClsScratch layout_cls_tiled(Bump& b, size_t B, size_t MB, size_t H, size_t F, size_t heads)
+{
+    ClsScratch c;
+    const size_t begin = b.off;
+    c.in_a = b.take(MB * H * 2);
+    c.qt = b.take(B * 16 * H * 2);
+    const size_t end_query = b.off;
+    b.off = begin;
+    c.ctx = b.take(MB * H * 2);
+    b.off = begin;
+    c.out_f = b.take(MB * H * 4);
+    b.off = std::max(b.off, end_query);
+    c.xbar = b.take(heads * MB * H * 2);
+    const size_t end_sums = b.off;
+    b.off = c.xbar;
+    c.y = b.take(2 * MB * H * 4);          // (tiled_splits: at most two K ranges)
+    c.x1f = b.take(MB * H * 4);
+    c.x1a = b.take(MB * H * 2);
+    c.u = b.take(MB * F * 2);
+    b.off = std::max(b.off, end_sums);
+    return c;
 }
 
 inline uint16_t f32_to_bf16_rne(float f)
@@ -1095,6 +1128,102 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     L.end();
 }
 
+// rows of a state or of a one-row-per-sequence matrix: whole panels in the panel layout
+size_t state_rows(bool tiled, size_t n) { return tiled ? (n + 31) / 32 * 32 : n; }
+
+// The workspace for a model's bounds, in the panel or the row-major layout.  slots < number of tasks: the least that a forward pass
+// without routing and request batching needs when the tasks run in turns of `slots`; only their final states are all kept.
+WsLayout layout_workspace(const mt_model* m, bool tiled, size_t slots)
+{
+    const mt_config& cfg = m->cfg;
+    const size_t H = cfg.hidden, F = cfg.ffn, T = m->tasks.size();
+    const size_t M = state_rows(tiled, (size_t)cfg.max_batch * cfg.max_seq), MB = state_rows(tiled, (size_t)cfg.max_batch);
+    const bool shared = slots < T;
+    WsLayout y;
+    Bump sb;
+    y.slots = slots;
+    for (int tap : m->tap_of_layer)
+        if (tap >= 0) {
+            y.tap_f.push_back(sb.take(M * H * 4));
+            y.tap_b.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
+        }
+    for (int i = 0; i < 2; ++i) {
+        y.pp_f[i] = sb.take(M * H * 4);
+        y.pp_b[i] = m->bf16 ? sb.take(M * H * 2) : 0;
+    }
+    y.trunk_scr = tiled ? layout_scratch_tiled(sb, M, H, F, 4) : layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
+    for (size_t t = 0; t < T; ++t) {
+        if (t >= slots) {
+            y.task_scr.push_back(y.task_scr[t - slots]);
+            y.task_cls.push_back(y.task_cls[t - slots]);
+            y.task_xf.push_back(y.task_xf[t - slots]);
+            y.task_xb.push_back(y.task_xb[t - slots]);
+            y.pooled.push_back(y.pooled[t - slots]);
+            y.split.push_back(y.split[t - slots]);
+            continue;
+        }
+        const bool layers = shared || m->tasks[t].n_layers > 0, first = shared || (layers && m->tasks[t].head == MT_HEAD_SEQUENCE);
+        Scratch scr{};
+        ClsScratch c;
+        const size_t scr_begin = sb.off;
+        if (layers) scr = tiled ? layout_scratch_tiled(sb, M, H, F, 1) : layout_scratch(sb, M, H, F, m->esz, m->bf16, 1);
+        if (first && tiled) {        // the first-token layer's buffers lie over those of the full layers before it
+            const size_t scr_end = sb.off;
+            sb.off = scr_begin;
+            c = layout_cls_tiled(sb, (size_t)cfg.max_batch, MB, H, F, (size_t)cfg.heads);
+            sb.off = std::max(sb.off, scr_end);
+        }
+        y.task_scr.push_back(scr);
+        y.task_xf.push_back(sb.take(M * H * 4));          // (without own layers only per-sequence routing uses it: the sub-batch's tap rows)
+        y.task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
+        if (first && !tiled) {
+            c.in_f = sb.take(MB * H * 4);
+            c.in_a = m->bf16 ? sb.take(MB * H * 2) : c.in_f;
+            c.q = sb.take(MB * H * m->esz);
+            c.ctx = sb.take(MB * H * m->esz);
+            c.y = sb.take(4 * MB * H * 4);
+            c.x1f = sb.take(MB * H * 4);
+            c.x1a = m->bf16 ? sb.take(MB * H * 2) : c.x1f;
+            c.u = sb.take(MB * F * m->esz);
+            c.out_f = sb.take(MB * H * 4);
+            if (m->bf16) {
+                const size_t A_pad = ((size_t)cfg.heads + 3) / 4 * 4;
+                c.qt = sb.take(MB * A_pad * H * 2);
+                c.scores = sb.take(M * A_pad * 4);
+                c.xbar = sb.take(MB * A_pad * H * 2);
+            }
+        }
+        y.task_cls.push_back(c);
+        y.pooled.push_back(sb.take(MB * H * 4));
+        y.split.push_back(sb.take(MB * H * 4));
+    }
+    for (size_t t = 0; shared && t < T; ++t)
+        if (m->tasks[t].n_layers > 0) y.task_cls[t].out_f = sb.take(MB * H * 4);
+    y.rm_n = sb.take(4);
+    y.rm_src = sb.take(M * 4);
+    y.rm_rowof = sb.take(M * 4);
+    y.rm_start = sb.take((size_t)cfg.max_batch * 4);
+    y.rm_len = sb.take((size_t)cfg.max_batch * 4);
+    if (!shared) {
+        for (size_t t = 0; t < T; ++t) {
+            RouteMapOff r;
+            r.n = sb.take(4);
+            r.src = sb.take(M * 4);
+            r.start = sb.take(MB * 4);
+            r.len = sb.take(MB * 4);
+            r.seq = sb.take(MB * 4);
+            r.rowof = sb.take(M * 4);
+            y.route.push_back(r);
+        }
+        y.chk_count = sb.take(4);
+        y.mr_ids = sb.take(M * 4);
+        y.mr_mask = sb.take(M * 4);
+        y.mr_logits = sb.take((size_t)cfg.max_batch * std::max(m->C_tot, 1) * 4);
+    }
+    y.bytes = sb.off;
+    return y;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1185,100 +1314,19 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->weight_bytes = wb.off;
 
     // ---- workspace
-    // (panel layout: row counts are whole panels)
-    auto rows = [&](size_t n) { return m->tiled ? (n + 31) / 32 * 32 : n; };
-    m->Mmax = rows((size_t)cfg->max_batch * cfg->max_seq);
-    m->MBmax = rows((size_t)cfg->max_batch);
-    const size_t M = m->Mmax;
-    Bump sb;
+    m->Mmax = state_rows(m->tiled, (size_t)cfg->max_batch * cfg->max_seq);
+    m->MBmax = state_rows(m->tiled, (size_t)cfg->max_batch);
     m->tap_of_layer.assign(D + 1, -1);
-    for (const auto& d : m->tasks) {
-        if (m->tap_of_layer[d.fork_layer] < 0) {
-            m->tap_of_layer[d.fork_layer] = (int)m->tap_f.size();
-            m->tap_f.push_back(sb.take(M * H * 4));
-            m->tap_b.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
-        }
-    }
-    for (int i = 0; i < 2; ++i) {
-        m->pp_f[i] = sb.take(M * H * 4);
-        m->pp_b[i] = m->bf16 ? sb.take(M * H * 2) : 0;
-    }
-    m->trunk_scr = m->tiled ? layout_scratch_tiled(sb, M, H, F, 4) : layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
-    const size_t MB = m->MBmax;
-    for (size_t t = 0; t < T; ++t) {
-        if (m->tasks[t].n_layers > 0 && m->tasks[t].head == MT_HEAD_TOKEN) {   // every layer runs on all rows
-            m->task_scr.push_back(m->tiled ? layout_scratch_tiled(sb, M, H, F, 1) : layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
-            m->task_xf.push_back(sb.take(M * H * 4));
-            m->task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
-            m->task_cls.push_back(ClsScratch{});
-        } else if (m->tasks[t].n_layers > 0) {
-            const size_t scr_begin = sb.off;
-            m->task_scr.push_back(m->tiled ? layout_scratch_tiled(sb, M, H, F, 1) : layout_scratch(sb, M, H, F, m->esz, m->bf16, 1));
-            const size_t scr_end = sb.off;
-            if (m->tiled) {        // the first-token layer's buffers lie over those of the full layers before it
-                sb.off = scr_begin;
-                ClsScratch c;
-                c.in_a = sb.take(MB * H * 2);
-                c.qt = sb.take(MB * 16 * H * 2);
-                c.xbar = sb.take((size_t)cfg->heads * MB * H * 2);
-                c.ctx = sb.take(MB * H * 2);
-                c.y = sb.take(4 * MB * H * 4);
-                c.x1f = sb.take(MB * H * 4);
-                c.x1a = sb.take(MB * H * 2);
-                c.u = sb.take(MB * F * 2);
-                c.out_f = sb.take(MB * H * 4);
-                sb.off = std::max(sb.off, scr_end);
-                m->task_cls.push_back(c);
-            }
-            m->task_xf.push_back(sb.take(M * H * 4));
-            m->task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
-            if (m->tiled) continue;
-            ClsScratch c;
-            c.in_f = sb.take(MB * H * 4);
-            c.in_a = m->bf16 ? sb.take(MB * H * 2) : c.in_f;
-            c.q = sb.take(MB * H * m->esz);
-            c.ctx = sb.take(MB * H * m->esz);
-            c.y = sb.take(4 * MB * H * 4);
-            c.x1f = sb.take(MB * H * 4);
-            c.x1a = m->bf16 ? sb.take(MB * H * 2) : c.x1f;
-            c.u = sb.take(MB * F * m->esz);
-            c.out_f = sb.take(MB * H * 4);
-            if (m->bf16) {
-                const size_t A_pad = ((size_t)cfg->heads + 3) / 4 * 4;
-                c.qt = sb.take(MB * A_pad * H * 2);
-                c.scores = sb.take(M * A_pad * 4);
-                c.xbar = sb.take(MB * A_pad * H * 2);
-            }
-            m->task_cls.push_back(c);
-        } else {
-            m->task_scr.push_back(Scratch{});
-            m->task_xf.push_back(sb.take(M * H * 4));          // only per-sequence routing uses it: the sub-batch's tap rows
-            m->task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
-            m->task_cls.push_back(ClsScratch{});
-        }
-    }
-    for (size_t t = 0; t < T; ++t) {
-        RouteMapOff r;
-        r.n = sb.take(4);
-        r.src = sb.take(M * 4);
-        r.start = sb.take(MB * 4);
-        r.len = sb.take(MB * 4);
-        r.seq = sb.take(MB * 4);
-        r.rowof = sb.take(M * 4);
-        m->route.push_back(r);
-    }
-    m->rm_n = sb.take(4);
-    m->rm_src = sb.take(M * 4);
-    m->rm_rowof = sb.take(M * 4);
-    m->rm_start = sb.take((size_t)cfg->max_batch * 4);
-    m->rm_len = sb.take((size_t)cfg->max_batch * 4);
-    m->pooled = sb.take(T * MB * H * 4);
-    m->cls_split = sb.take(T * MB * H * 4);   // [hi | lo] bf16 halves, or float32 rows in the validation mode
-    m->chk_count = sb.take(4);
-    m->mr_ids = sb.take(M * 4);
-    m->mr_mask = sb.take(M * 4);
-    m->mr_logits = sb.take((size_t)cfg->max_batch * std::max(m->C_tot, 1) * 4);
-    m->workspace_bytes = sb.off;
+    int n_taps = 0;
+    for (const auto& d : m->tasks)
+        if (m->tap_of_layer[d.fork_layer] < 0) m->tap_of_layer[d.fork_layer] = n_taps++;
+    m->bound = layout_workspace(m, m->tiled, T);
+    // mt_forward_static: where whole panels of rows are what makes the arena too large for its array (few sequences, many tasks), the
+    // tasks take turns at fewer sets of buffers
+    m->fixed = m->bound;
+    if (m->tiled && m->bound.bytes > MT_STATIC_SCRATCH_BYTES && layout_workspace(m, false, T).bytes <= MT_STATIC_SCRATCH_BYTES)
+        for (size_t slots = std::min<size_t>(T - 1, kMaxGroup); slots >= 1 && m->fixed.bytes > MT_STATIC_SCRATCH_BYTES; --slots)
+            m->fixed = layout_workspace(m, true, slots);
     m->task_loaded.assign(T, 0);
     m->last_enabled.assign(T, 0);
     *out = m;
@@ -1300,7 +1348,7 @@ void mt_destroy(mt_model* m)
 }
 
 size_t mt_weight_bytes(const mt_model* m) { return m ? m->weight_bytes : 0; }
-size_t mt_workspace_bytes(const mt_model* m) { return m ? m->workspace_bytes : 0; }
+size_t mt_workspace_bytes(const mt_model* m) { return m ? m->bound.bytes : 0; }
 int mt_logit_offset(const mt_model* m, int32_t task)
 {
     if (!m) return MT_ERR_NULL;
@@ -1341,9 +1389,9 @@ int mt_bind(mt_model* m, void* d_weights, size_t weight_bytes, void* d_workspace
 {
     if (!m) return MT_ERR_NULL;
     if (!d_weights || !d_workspace) return fail(m, MT_ERR_NULL, "mt_bind: null arena");
-    if (weight_bytes < m->weight_bytes || workspace_bytes < m->workspace_bytes)
+    if (weight_bytes < m->weight_bytes || workspace_bytes < m->bound.bytes)
         return fail(m, MT_ERR_SHAPE, "mt_bind: arenas too small (need %zu weight bytes, %zu workspace bytes)", m->weight_bytes,
-                    m->workspace_bytes);
+                    m->bound.bytes);
     if (((uintptr_t)d_weights | (uintptr_t)d_workspace) % kAlign)
         return fail(m, MT_ERR_SHAPE, "mt_bind: arenas must be %zu-byte aligned", kAlign);
     m->d_w = static_cast<unsigned char*>(d_weights);
@@ -1551,12 +1599,14 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     m->last_S = seq;
     m->last_depth = -1;                 // no trunk state of this call exists (yet)
     m->ws_act = ws_other ? ws_other : m->d_ws;
+    m->lay = ws_other ? &m->fixed : &m->bound;
     if (enabled.empty()) return MT_OK;
     m->last_depth = depth;
 
     const int B = batch, S = seq, H = m->cfg.hidden;
     unsigned char* W = m->d_w;
     unsigned char* ws = m->ws_act;
+    const WsLayout& y = *m->lay;
     const bool bf = m->bf16;
     Launcher L{m, static_cast<hipStream_t>(hip_stream)};
 
@@ -1564,16 +1614,15 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     auto trunk_out = [&](int layer, int pp, float*& of, void*& ob) {
         const int tap = m->tap_of_layer[layer];
         if (tap >= 0) {
-            of = (float*)(ws + m->tap_f[tap]);
-            ob = bf ? (void*)(ws + m->tap_b[tap]) : nullptr;
+            of = (float*)(ws + y.tap_f[tap]);
+            ob = bf ? (void*)(ws + y.tap_b[tap]) : nullptr;
         } else {
-            of = (float*)(ws + m->pp_f[pp]);
-            ob = bf ? (void*)(ws + m->pp_b[pp]) : nullptr;
+            of = (float*)(ws + y.pp_f[pp]);
+            ob = bf ? (void*)(ws + y.pp_b[pp]) : nullptr;
         }
     };
-    auto split_of = [&](int t) { return m->cls_split + (size_t)t * m->MBmax * H * 4; };
-    RowMap rm{(int32_t*)(ws + m->rm_n), (int32_t*)(ws + m->rm_src), (int32_t*)(ws + m->rm_rowof), (int32_t*)(ws + m->rm_start),
-              (int32_t*)(ws + m->rm_len)};
+    RowMap rm{(int32_t*)(ws + y.rm_n), (int32_t*)(ws + y.rm_src), (int32_t*)(ws + y.rm_rowof), (int32_t*)(ws + y.rm_start),
+              (int32_t*)(ws + y.rm_len)};
     float* cur_f;
     void* cur_b;
     trunk_out(0, 0, cur_f, cur_b);
@@ -1594,20 +1643,20 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     //      sequence: a branch starts as soon as its tap exists instead of waiting for the whole trunk, so the
     //      number of sequential layer steps is max(D, max_t(fork_t + layers_t)) instead of D + max_t layers_t.
     //      A task's last own layer takes the first-token-only path.
-    // routed mode: the trunk alone here, the branches follow per group of sequences
+    // Routed mode: the trunk alone, the branches follow per group of sequences.
     const int n_steps = h_route ? depth : mt_schedule_steps(m, h_task_mask);      // >= depth: every fork is a fork + 0 layers bound
     (void)max_y;
+    auto run_steps = [&](const std::vector<int>& tasks, bool trunk) {
     for (int step = 0; step < n_steps; ++step) {
         std::vector<LayerIO> full;
         std::vector<LastIO> last;
         float* nf = nullptr;
         void* nb = nullptr;
-        if (step < depth) {
+        if (trunk && step < depth) {
             trunk_out(step + 1, (step + 1) & 1, nf, nb);
-            full.push_back(LayerIO{cur_f, cur_b, &m->trunk[step], &m->trunk_scr, nf, nb});
+            full.push_back(LayerIO{cur_f, cur_b, &m->trunk[step], &y.trunk_scr, nf, nb});
         }
-        for (int t : enabled) {
-            if (h_route) break;
+        for (int t : tasks) {
             const mt_task_desc& d = m->tasks[t];
             const int stage = step - d.fork_layer;
             if (stage < 0 || stage >= d.n_layers) continue;
@@ -1615,17 +1664,17 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             const void* in_b;
             if (stage == 0) {
                 const int tap = m->tap_of_layer[d.fork_layer];
-                in_f = (const float*)(ws + m->tap_f[tap]);
-                in_b = bf ? (const void*)(ws + m->tap_b[tap]) : nullptr;
+                in_f = (const float*)(ws + y.tap_f[tap]);
+                in_b = bf ? (const void*)(ws + y.tap_b[tap]) : nullptr;
             } else {
-                in_f = (const float*)(ws + m->task_xf[t]);
-                in_b = bf ? (const void*)(ws + m->task_xb[t]) : nullptr;
+                in_f = (const float*)(ws + y.task_xf[t]);
+                in_b = bf ? (const void*)(ws + y.task_xb[t]) : nullptr;
             }
             if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE) {
-                last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t], split_of(t)});
+                last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &y.task_scr[t], &y.task_cls[t], y.split[t]});
             } else {
-                full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &m->task_scr[t], (float*)(ws + m->task_xf[t]),
-                                       bf ? (void*)(ws + m->task_xb[t]) : nullptr});
+                full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &y.task_scr[t], (float*)(ws + y.task_xf[t]),
+                                       bf ? (void*)(ws + y.task_xb[t]) : nullptr});
             }
         }
         for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
@@ -1636,11 +1685,12 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             std::vector<LastIO> part(last.begin() + lo, last.begin() + std::min(last.size(), lo + (size_t)kMaxGroup));
             (m->tiled ? run_last_layer_group_tiled : run_last_layer_group)(L, part, rm, B, S);
         }
-        if (step < depth) {
+        if (trunk && step < depth) {
             cur_f = nf;
             cur_b = nb;
         }
     }
+    };
 
     // ---- poolers and classifiers.  The pooler input stays float32-accurate in both modes: the bf16
     // path feeds the matrix cores with the [hi | lo] split of the first-token rows against [W | W].
@@ -1661,10 +1711,10 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         for (int i = 0; i < n; ++i) {
             const int t = list[lo + i];
             const mt_task_desc& d = m->tasks[t];
-            const float* z = d.n_layers > 0 ? (const float*)(ws + m->task_cls[t].out_f)     // one row per sequence already
-                             : gathered     ? (const float*)(ws + m->task_xf[t])          // the sub-batch's copy of the tap
-                                            : (const float*)(ws + m->tap_f[m->tap_of_layer[d.fork_layer]]);
-            float* pooled = (float*)(ws + m->pooled + (size_t)t * m->MBmax * H * 4);
+            const float* z = d.n_layers > 0 ? (const float*)(ws + y.task_cls[t].out_f)     // one row per sequence already
+                             : gathered     ? (const float*)(ws + y.task_xf[t])          // the sub-batch's copy of the tap
+                                            : (const float*)(ws + y.tap_f[m->tap_of_layer[d.fork_layer]]);
+            float* pooled = (float*)(ws + y.pooled[t]);
             cg.pooled[i] = pooled;
             cg.Wc[i] = W + m->taskw[t].Wc;
             cg.bc[i] = (const float*)(W + m->taskw[t].bc);
@@ -1674,9 +1724,9 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             if (m->tiled) {
                 if (d.n_layers == 0) {             // the others' operands were written with their last LayerNorm
                     sg.x[n_split] = z;
-                    sg.out[n_split++] = (bf16_t*)(ws + split_of(t));
+                    sg.out[n_split++] = (bf16_t*)(ws + y.split[t]);
                 }
-                tg.a[i] = units(split_of(t));
+                tg.a[i] = units(y.split[t]);
                 tg.w[i] = units(m->taskw[t].Wp);
                 tg.b[i] = units(m->taskw[t].bp);
                 tg.c[i] = units((const unsigned char*)pooled - ws);
@@ -1684,9 +1734,8 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             }
             sg.x[i] = z;
             sg.compact[i] = d.n_layers > 0 ? 1 : 0;
-            sg.out[i] = bf ? (bf16_t*)(ws + m->cls_split + (size_t)t * m->MBmax * 2 * H * 2)
-                           : (bf16_t*)(ws + m->cls_split + (size_t)t * m->MBmax * H * 4);   // fp32 mode: float32 rows
-            g.A[i] = bf ? (const void*)sg.out[i] : (const void*)(ws + m->cls_split + (size_t)t * m->MBmax * H * 4);
+            sg.out[i] = (bf16_t*)(ws + y.split[t]);          // (fp32 mode: float32 rows)
+            g.A[i] = sg.out[i];
             g.W[i] = W + m->taskw[t].Wp;
             g.bias[i] = (const float*)(W + m->taskw[t].bp);
             g.C[i] = pooled;
@@ -1726,8 +1775,8 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             for (int i = 0; i < n; ++i) {
                 const int t = list[lo + i];
                 const mt_task_desc& d = m->tasks[t];
-                tg.x[i] = (d.n_layers > 0 || gathered) ? (const float*)(ws + m->task_xf[t])
-                                                       : (const float*)(ws + m->tap_f[m->tap_of_layer[d.fork_layer]]);
+                tg.x[i] = (d.n_layers > 0 || gathered) ? (const float*)(ws + y.task_xf[t])
+                                                       : (const float*)(ws + y.tap_f[m->tap_of_layer[d.fork_layer]]);
                 tg.Wc[i] = W + m->taskw[t].Wc;
                 tg.bc[i] = (const float*)(W + m->taskw[t].bc);
                 tg.out[i] = d_out_token_logits + m->logit_off[t];
@@ -1739,10 +1788,21 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         }
     };
 
-    if (!h_route) {
+    if (!h_route && y.slots < (size_t)T) {          // the tasks take turns at `slots` sets of buffers
+        run_steps({}, true);
+        for (size_t lo = 0; lo < (size_t)T; lo += y.slots) {
+            std::vector<int> turn;
+            for (int t : enabled)
+                if ((size_t)t >= lo && (size_t)t < lo + y.slots) turn.push_back(t);
+            run_steps(turn, false);
+            run_heads(L, turn, rm, B, false, nullptr);
+        }
+    } else if (!h_route) {
+        run_steps(enabled, true);
         run_heads(L, enabled, rm, B, false, nullptr);
         run_token_heads(L, enabled, false, rm.row_of, rm.n_rows);
     } else {
+        run_steps({}, true);
         // ---- per-sequence routing: tasks wanted by the same set of sequences form a group; the group's sequences are
         // gathered from each task's tap into a padding-free row order of their own, on which the task's layers,
         // pooler and classifier run exactly as on a whole batch; logits land in the rows of the chosen sequences.
@@ -1786,7 +1846,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             int nb = 0;
             for (int b = 0; b < B; ++b)
                 if (h_route[(size_t)b * T + t0]) idx.seq[nb++] = (uint16_t)b;
-            const RouteMapOff& ro = m->route[t0];
+            const RouteMapOff& ro = y.route[t0];
             RowMap crm{(int32_t*)(ws + ro.n), (int32_t*)(ws + ro.src), nullptr, (int32_t*)(ws + ro.start), (int32_t*)(ws + ro.len)};
             int32_t* c_seq = (int32_t*)(ws + ro.seq);
             GL.begin(MT_K_EMBED);
@@ -1800,15 +1860,15 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             for (int t : grp_tasks) {
                 const int tap = m->tap_of_layer[m->tasks[t].fork_layer];
                 if (m->tiled) {
-                    rc.in_f[n_copy] = (const float*)(ws + m->tap_f[tap]);
-                    rc.in_b[n_copy] = ws + m->tap_b[tap];
-                    rc.out_f[n_copy] = (float*)(ws + m->task_xf[t]);
-                    rc.out_b[n_copy++] = ws + m->task_xb[t];
+                    rc.in_f[n_copy] = (const float*)(ws + y.tap_f[tap]);
+                    rc.in_b[n_copy] = ws + y.tap_b[tap];
+                    rc.out_f[n_copy] = (float*)(ws + y.task_xf[t]);
+                    rc.out_b[n_copy++] = ws + y.task_xb[t];
                     if (n_copy == kMaxGroup) flush_copies();
                     continue;
                 }
-                GL.check(launch_route_gather((const float*)(ws + m->tap_f[tap]), bf ? (const void*)(ws + m->tap_b[tap]) : nullptr,
-                                             (float*)(ws + m->task_xf[t]), bf ? (void*)(ws + m->task_xb[t]) : nullptr, crm.src, crm.n_rows,
+                GL.check(launch_route_gather((const float*)(ws + y.tap_f[tap]), bf ? (const void*)(ws + y.tap_b[tap]) : nullptr,
+                                             (float*)(ws + y.task_xf[t]), bf ? (void*)(ws + y.task_xb[t]) : nullptr, crm.src, crm.n_rows,
                                              nb * S, H, 2, GL.st));
             }
             flush_copies();
@@ -1821,13 +1881,13 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                 for (int t : grp_tasks) {
                     const mt_task_desc& d = m->tasks[t];
                     if (stage >= d.n_layers) continue;
-                    const float* in_f = (const float*)(ws + m->task_xf[t]);
-                    const void* in_b = bf ? (const void*)(ws + m->task_xb[t]) : nullptr;
+                    const float* in_f = (const float*)(ws + y.task_xf[t]);
+                    const void* in_b = bf ? (const void*)(ws + y.task_xb[t]) : nullptr;
                     if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE)
-                        last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &m->task_scr[t], &m->task_cls[t], split_of(t)});
+                        last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &y.task_scr[t], &y.task_cls[t], y.split[t]});
                     else
-                        full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &m->task_scr[t], (float*)(ws + m->task_xf[t]),
-                                               bf ? (void*)(ws + m->task_xb[t]) : nullptr});
+                        full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &y.task_scr[t], (float*)(ws + y.task_xf[t]),
+                                               bf ? (void*)(ws + y.task_xb[t]) : nullptr});
                 }
                 for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
                     std::vector<LayerIO> part(full.begin() + lo, full.begin() + std::min(full.size(), lo + (size_t)kMaxGroup));
@@ -1925,9 +1985,9 @@ int mt_forward_requests(mt_model* m, int32_t n_requests, const int32_t* const* h
         for (int c = m->logit_off[t]; c < m->logit_off[t] + m->tasks[t].n_classes; ++c) rq.col_on[c >> 5] |= 1u << (c & 31);
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    int32_t* ids_all = (int32_t*)(m->d_ws + m->mr_ids);
-    int32_t* mask_all = (int32_t*)(m->d_ws + m->mr_mask);
-    float* logits_all = (float*)(m->d_ws + m->mr_logits);
+    int32_t* ids_all = (int32_t*)(m->d_ws + m->bound.mr_ids);
+    int32_t* mask_all = (int32_t*)(m->d_ws + m->bound.mr_mask);
+    float* logits_all = (float*)(m->d_ws + m->bound.mr_logits);
     hipError_t e = launch_gather_requests(rq, n_requests, largest, seq, ids_all, mask_all, st);
     if (e != hipSuccess) return fail(m, MT_ERR_HIP, "mt_forward_requests: %s", hipGetErrorString(e));
     const int rc = forward_impl(m, ids_all, nullptr, mask_all, (int)total, seq, h_task_mask, nullptr, logits_all, nullptr, hip_stream);
@@ -1985,11 +2045,11 @@ int mt_forward_static(mt_model* m, const int32_t* d_input_ids, const int32_t* d_
                       const uint8_t* h_task_mask, float* d_out_logits, void* hip_stream)
 {
     if (!m) return MT_ERR_NULL;
-    if (m->workspace_bytes > (size_t)MT_STATIC_SCRATCH_BYTES)
+    if (m->fixed.bytes > (size_t)MT_STATIC_SCRATCH_BYTES)
         return fail(m, MT_ERR_SHAPE,
                     "mt_forward_static: this model's workspace (max_batch %d x max_seq %d: %zu bytes) exceeds the static scratch of %zu "
                     "bytes; create the model with smaller bounds or use mt_forward",
-                    m->cfg.max_batch, m->cfg.max_seq, m->workspace_bytes, (size_t)MT_STATIC_SCRATCH_BYTES);
+                    m->cfg.max_batch, m->cfg.max_seq, m->bound.bytes, (size_t)MT_STATIC_SCRATCH_BYTES);
     if (m->profiling) return fail(m, MT_ERR_STATE, "mt_forward_static: per-launch timing creates events; switch mt_profile_enable off");
     hipError_t e = hipSuccess;
     unsigned char* scratch = static_scratch_of_current_device(&e);
@@ -2022,7 +2082,7 @@ int mt_check_mask(mt_model* m, const int32_t* d_attn_mask, int32_t batch, int32_
     if (!m->d_ws) return fail(m, MT_ERR_STATE, "mt_check_mask: call mt_bind first");
     if (batch < 1 || seq < 1) return fail(m, MT_ERR_SHAPE, "mt_check_mask: batch %d x seq %d", batch, seq);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    int32_t* d_count = (int32_t*)(m->d_ws + m->chk_count);
+    int32_t* d_count = (int32_t*)(m->d_ws + m->bound.chk_count);
     hipError_t e = launch_count_bad_first_tokens(d_attn_mask, batch, seq, d_count, st);
     if (e == hipSuccess) e = hipMemcpyAsync(h_bad_sequences, d_count, 4, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -2047,23 +2107,23 @@ int mt_read_hidden(mt_model* m, int32_t task, int32_t layer, float* d_out, size_
         if (layer > m->last_depth)
             return fail(m, MT_ERR_STATE, "mt_read_hidden: the last forward pass ran the trunk to layer %d only, not to layer %d",
                         m->last_depth, layer);
-        src = m->ws_act + m->tap_f[m->tap_of_layer[layer]];
+        src = m->ws_act + m->lay->tap_f[m->tap_of_layer[layer]];
     } else {
         if (task >= (int)m->tasks.size()) return fail(m, MT_ERR_SHAPE, "mt_read_hidden: task %d out of range", task);
         if (!m->last_enabled[task]) return fail(m, MT_ERR_STATE, "mt_read_hidden: task %d was not computed", task);
         const mt_task_desc& d = m->tasks[task];
         if (d.n_layers > 0 && d.head == MT_HEAD_TOKEN) {
-            src = m->ws_act + m->task_xf[task];
+            src = m->ws_act + m->lay->task_xf[task];
         } else if (d.n_layers > 0) {   // only the first-token rows of a branch's final state exist
-            hipError_t e = launch_place_first_rows((const float*)(m->ws_act + m->task_cls[task].out_f), m->last_B, m->last_S,
+            hipError_t e = launch_place_first_rows((const float*)(m->ws_act + m->lay->task_cls[task].out_f), m->last_B, m->last_S,
                                                    m->cfg.hidden, d_out, static_cast<hipStream_t>(hip_stream), m->tiled ? 1 : 0);
             if (e != hipSuccess) return fail(m, MT_ERR_HIP, "mt_read_hidden: %s", hipGetErrorString(e));
             return MT_OK;
         } else {
-            src = m->ws_act + m->tap_f[m->tap_of_layer[d.fork_layer]];
+            src = m->ws_act + m->lay->tap_f[m->tap_of_layer[d.fork_layer]];
         }
     }
-    hipError_t e = launch_unpack_rows((const float*)src, (const int32_t*)(m->ws_act + m->rm_rowof), m->last_B * m->last_S, m->cfg.hidden,
+    hipError_t e = launch_unpack_rows((const float*)src, (const int32_t*)(m->ws_act + m->lay->rm_rowof), m->last_B * m->last_S, m->cfg.hidden,
                                       d_out, static_cast<hipStream_t>(hip_stream), m->tiled ? 1 : 0);
     if (e != hipSuccess) return fail(m, MT_ERR_HIP, "mt_read_hidden: %s", hipGetErrorString(e));
     return MT_OK;

@@ -392,3 +392,29 @@ def test_fp8_layer_precision_generator_and_configuration():
     assert n_layers * per_layer <= diff <= n_layers * (per_layer + 4 * 256)
     L.mt_destroy(h)
     L.mt_destroy(h2)
+
+
+# Models that one sequence's worth of rows per matrix lets into mt_forward_static's array: padding to whole panels of 32 rows must not keep them
+# out (many tasks, wide tasks, one row over a panel).
+@pytest.mark.parametrize("name,batch,seq", [("industrial", 1, 1), ("industrial", 1, 32), ("industrial", 4, 8), ("assistant", 1, 32), ("large", 1, 64),
+                                            ("large", 8, 8), ("large", 1, 100), ("base", 33, 1), ("latency", 1, 16), ("60 tasks", 1, 1),
+                                            ("60 tasks", 5, 1), ("200 tasks", 1, 1)])
+def test_small_models_fit_the_static_scratch(name, batch, seq):
+    if name.endswith("tasks"):
+        n = int(name.split()[0])
+        spec = dataclasses.replace(ms.get_config("base"), tasks=tuple(ms.TaskSpec(8, 1 + t % 2, 2) for t in range(n)))
+    else:
+        spec = ms.get_config(name)
+    rc, h, cfg = _create(spec, max_batch=batch, max_seq=seq)
+    assert rc == mt.MT_OK
+    # (the size is checked before anything else; without a device or with null pointers the call ends with another error)
+    assert mt.lib().mt_forward_static(h, None, None, batch, seq, None, None, None) in (mt.MT_ERR_HIP, mt.MT_ERR_NULL)
+    mt.lib().mt_destroy(h)
+
+
+@pytest.mark.parametrize("batch,seq", [(32, 128), (4, 128), (8, 64)])
+def test_large_models_do_not_fit_the_static_scratch(batch, seq):
+    rc, h, _ = _create(ms.get_config("base"), max_batch=batch, max_seq=seq)
+    assert rc == mt.MT_OK and mt.lib().mt_workspace_bytes(h) > mt.MT_STATIC_SCRATCH_BYTES
+    assert mt.lib().mt_forward_static(h, None, None, batch, seq, None, None, None) == mt.MT_ERR_SHAPE
+    mt.lib().mt_destroy(h)

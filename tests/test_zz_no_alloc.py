@@ -84,3 +84,33 @@ def test_static_scratch_forward_refuses_a_model_that_does_not_fit():
         model.forward_static(dev(ids), dev(mask), out)
     assert ei.value.code == mt.MT_ERR_SHAPE and "static scratch" in str(ei.value)
     model.close()
+
+
+def test_static_scratch_forward_of_many_tasks():
+    """The 21-task workload at the sizes that fit the array with every task's buffers side by side, and 100 tasks that take turns at fewer sets
+    (their arena is larger than the array): logits and the kept hidden states equal mt_forward's."""
+    many = ms.MTSpec("many", vocab=500, hidden=256, heads=4, ffn=512, max_pos=64, n_trunk_layers=2,
+                     tasks=tuple(ms.TaskSpec(2 if t == 0 else t % 3, (t * 7) % 3, 1 + t % 3) for t in range(100)),
+                     precision="bf16", batch=2, seq=17, len_lo=3, len_hi=17, input_seed=41)
+    for spec, sizes in ((dataclasses.replace(ms.get_config("industrial"), vocab=1000), ((1, 32), (1, 8))), (many, ((2, 17),))):
+        owner, _ = mt.load_synthetic(spec, max_batch=sizes[0][0], max_seq=sizes[0][1], std=0.05)
+        for batch, seq in sizes:
+            say(f"{spec.name}: {batch} x {seq}")
+            model = mt.Model(mt.make_config(spec, max_batch=batch, max_seq=seq), bind=False)
+            model.weights = owner.weights
+            model.workspace = torch.empty(model.workspace_bytes(), dtype=torch.uint8, device="cuda")
+            model._check(mt.lib().mt_bind(model.h, owner.weights.data_ptr(), owner.weights.numel(), model.workspace.data_ptr(), model.workspace.numel()))
+            model._check(mt.lib().mt_share_weights(model.h, owner.h))
+            assert (model.workspace_bytes() > mt.MT_STATIC_SCRATCH_BYTES) == (spec is many)
+            ids, mask, _ = ms.make_inputs(spec, batch=batch, seq=seq, len_hi=seq)
+            d_i, d_k = dev(ids), dev(mask)
+            for task_mask in (None, [t % 3 != 1 for t in range(spec.n_tasks)]):
+                want = model.forward(d_i, d_k, out=torch.full((batch, model.n_logits), 7.0, device="cuda"), task_mask=task_mask).cpu().numpy()
+                kept = [t for t in range(spec.n_tasks) if task_mask is None or task_mask[t]]
+                states = [model.read_hidden(t, 0, batch, seq).cpu().numpy() for t in kept]
+                got = model.forward_static(d_i, d_k, torch.full((batch, model.n_logits), 7.0, device="cuda"), task_mask=task_mask).cpu().numpy()
+                assert np.array_equal(got, want) and np.isfinite(got).all()
+                for t, state in zip(kept, states):
+                    assert np.array_equal(model.read_hidden(t, 0, batch, seq).cpu().numpy(), state)
+            model.close()
+        owner.close()
