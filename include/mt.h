@@ -360,6 +360,19 @@ int mt_op_linear_sub(const void* d_A, int64_t lda, const void* d_W, int64_t ldw,
 int mt_op_first_token_pool(const float* d_scores, const void* d_x, void* d_xbar, const int32_t* d_seq_start,
                            const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,
                            int32_t heads_pad, void* hip_stream);
+/* The same step in MT_BF16 mode with up to 16 heads, whose kernels hold matrices in the panel layout: 32 rows form a panel, inside a panel
+ * 8 consecutive columns of its 32 rows lie behind one another (element (r, c) of a matrix of `width` columns at
+ * (r / 32) 32 width + (c / 8) 256 + (r % 32) 8 + c % 8).  Rows are padded to whole panels, hidden = 64 heads, arrays are 256-byte aligned.
+ *   mt_op_panel_first_query:  q = Wq x + bq rounded to bf16, d_qt[b][a][:] = sum over the 64 rows of head a: Wk[row][:] q[row];
+ *     d_first [batch][hidden], d_Wq [hidden][hidden] and d_WkT (the transpose of Wk) bf16 panels, d_qt bf16 [batch][16][hidden];
+ *   mt_op_panel_first_attend: p = softmax_j(d_qt[b][a] . d_x[row_j] / 8), xbar = sum_j p_j d_x[row_j] over the rows d_seq_start[b] ..
+ *     + min(d_seq_len[b], seq) - 1; d_x bf16 panels of all rows, d_xbar per head a bf16 panel matrix [batch][hidden],
+ *     xbar_stride elements apart.  Rows of d_x that belong to no sequence may hold anything.
+ * Errors: NULL, SHAPE, HIP. */
+int mt_op_panel_first_query(const void* d_first, const void* d_Wq, const float* d_bq, const void* d_WkT, void* d_qt, int32_t batch,
+                            int32_t heads, void* hip_stream);
+int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                             const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream);
 /* ctx[b,s,a*d:(a+1)*d] = softmax(q k^T / sqrt(d) + mask) v per head; d_qkv is [B*S][3H] act
  * (columns Q | K | V), d_ctx [B*S][H] act. */
 int mt_op_attention(int32_t precision, const void* d_qkv, const int32_t* d_mask, void* d_ctx,

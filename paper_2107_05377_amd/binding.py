@@ -26,7 +26,7 @@ KERNEL_CLASSES = ["embed", "gemm_qkv", "attn", "gemm_out", "ln", "gemm_ffn1", "g
 EXPORTS = ["mt_create", "mt_destroy", "mt_weight_bytes", "mt_workspace_bytes", "mt_bind", "mt_load_weights",
            "mt_forward", "mt_logit_offset", "mt_n_logits", "mt_layer_count", "mt_last_error", "mt_error_name",
            "mt_read_hidden", "mt_profile_enable", "mt_profile_read", "mt_op_linear", "mt_op_attention",
-           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_schedule_steps", "mt_forward_routed",
+           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_schedule_steps", "mt_forward_routed",
            "mt_forward_tokens", "mt_token_logit_offset", "mt_n_token_logits", "mt_forward_static", "mt_forward_multi", "mt_forward_requests", "mt_forward_routed_tokens", "mt_op_linear_fp8", "mt_debug_e4m3_quantize", "mt_check_mask"]
 MT_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
@@ -97,6 +97,8 @@ def lib():
         L.mt_op_layernorm.argtypes = [vp, vp, vp, C.c_float, vp, vp, i32, i32, vp]
         L.mt_debug_set_gemm_tile.argtypes = [i32]
         L.mt_op_first_token_pool.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
+        L.mt_op_panel_first_query.argtypes = [vp, vp, vp, vp, vp, i32, i32, vp]
+        L.mt_op_panel_first_attend.argtypes = [vp, vp, vp, i64, vp, vp, i32, i32, i32, vp]
         L.mt_op_linear_sub.argtypes = [vp, i64, vp, i64, vp, vp, i64, i32, i32, i32, i32, i64, i64, i64, i64, vp, vp, i32, vp]
         L.mt_debug_set_gemm_tile.restype = i32
         _lib = L
@@ -354,6 +356,46 @@ def op_first_token_pool(scores, x, seq_start, seq_len, batch, seq, hidden, heads
     if rc != MT_OK:
         raise MTError(rc, "mt_op_first_token_pool")
     return xbar
+
+
+def to_panels(x, dtype):
+    """The panel layout (include/mt.h) of a CUDA tensor [rows][width], rows padded with NaN."""
+    import torch
+    rows, width = x.shape
+    full = torch.full(((rows + 31) // 32 * 32, width), float("nan"), dtype=dtype, device=x.device)
+    full[:rows] = x.to(dtype)
+    return full.view(-1, 32, width // 8, 8).transpose(1, 2).contiguous()
+
+
+def from_panels(p):
+    """[rows, whole panels][width] of a tensor in the panel layout ([panels][width / 8][32][8])."""
+    return p.transpose(1, 2).reshape(p.shape[0] * 32, p.shape[1] * 8)
+
+
+def _panels(rows, width, dtype, device):
+    import torch
+    return torch.full(((rows + 31) // 32, width // 8, 32, 8), float("nan"), dtype=dtype, device=device)
+
+
+def op_panel_first_query(first, Wq, bq, WkT, batch, heads):
+    """mt_op_panel_first_query; first, Wq, WkT in panels; returns q~ [batch][16][hidden] bf16 (heads beyond `heads` NaN)."""
+    import torch
+    qt = torch.full((batch, 16, heads * 64), float("nan"), dtype=torch.bfloat16, device=first.device)
+    rc = lib().mt_op_panel_first_query(_ptr(first), _ptr(Wq), _ptr(bq), _ptr(WkT), _ptr(qt), batch, heads, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_first_query")
+    return qt
+
+
+def op_panel_first_attend(x, qt, seq_start, seq_len, batch, seq, heads):
+    """mt_op_panel_first_attend; x in panels; returns xbar [batch][heads][hidden] bf16."""
+    import torch
+    H, panels = heads * 64, (batch + 31) // 32
+    xbar = torch.full((heads, panels, H // 8, 32, 8), float("nan"), dtype=torch.bfloat16, device=x.device)
+    rc = lib().mt_op_panel_first_attend(_ptr(x), _ptr(qt), _ptr(xbar), panels * 32 * H, _ptr(seq_start), _ptr(seq_len), batch, seq, heads, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_first_attend")
+    return torch.stack([from_panels(xbar[a])[:batch] for a in range(heads)], dim=1)
 
 
 def mfma_peak(iters=4000):

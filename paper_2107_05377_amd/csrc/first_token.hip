@@ -16,6 +16,10 @@ namespace mt {
 namespace {
 
 constexpr int kHeadsPad = 16;
+// The softmax weights are float32 quantities and enter the product as this many bfloat16 terms (the value, its remainder, ..: 16 bits of the
+// weight with two).  The row sums' error against float64 is that of float32 weights then, which one term exceeds 3 to 20 times where the
+// sum cancels.  Cost of the second term: 21 tasks x 272 short sequences 2810 -> 2822 us a pass, 8 tasks x 256 sequences nothing; of a third 1 %.
+constexpr int kTerms = 2;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, FirstTokenGroup g)
@@ -202,14 +206,18 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] *= alpha;
         }
-        bf16x8 pf;
+        bf16x8 pf[kTerms];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(sc[h][e], kScale, -m_run));
+                float p = __builtin_amdgcn_exp2f(fmaf(sc[h][e], kScale, -m_run));
                 l_run += p;
-                pf[h * 4 + e] = (__bf16)p;
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) {
+                    pf[t][h * 4 + e] = (__bf16)p;
+                    p -= (float)pf[t][h * 4 + e];
+                }
             }
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -221,7 +229,8 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
                 for (int e = 0; e < 4; ++e) xt[h * 4 + e] = (__bf16)t[e];
             }
             xt = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, xt) & keep);
-            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt, pf, acc[c], 0, 0, 0);                                    // row: column, column: head
+#pragma unroll
+            for (int t = kTerms - 1; t >= 0; --t) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt, pf[t], acc[c], 0, 0, 0);     // row: column, column: head
             if (c & 1) __builtin_amdgcn_sched_barrier(0);                    // (two at a time, for the registers)
         }
     };

@@ -140,7 +140,7 @@ struct FirstTokenGroup {
     const void* Wq[kMaxGroup];      // panels of the query matrix
     const float* bq[kMaxGroup];
     const void* WkT[kMaxGroup];     // panels of the transposed key matrix
-    void* qt[kMaxGroup];            // bf16 [B][H / 8][16][8]
+    void* qt[kMaxGroup];            // bf16 [B][16][H], rows from the number of heads on unused
     void* xbar[kMaxGroup];          // per head a bf16 [B][H] panel matrix, xbar_stride elements apart
 };
 hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream);

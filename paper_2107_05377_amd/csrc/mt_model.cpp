@@ -1224,6 +1224,12 @@ WsLayout layout_workspace(const mt_model* m, bool tiled, size_t slots)
     return y;
 }
 
+// single operations on the panel layout
+template <typename... P>
+bool aligned256(const P*... p) { return ((reinterpret_cast<uintptr_t>(p) | ...) & 255) == 0; }
+
+int op_result(hipError_t e) { return e == hipErrorInvalidValue ? MT_ERR_SHAPE : (e == hipSuccess ? MT_OK : MT_ERR_HIP); }
+
 }  // namespace
 
 extern "C" {
@@ -2275,6 +2281,32 @@ int mt_op_first_token_pool(const float* d_scores, const void* d_x, void* d_xbar,
                                            static_cast<hipStream_t>(hip_stream));
     if (e == hipErrorInvalidValue) return MT_ERR_SHAPE;
     return e == hipSuccess ? MT_OK : MT_ERR_HIP;
+}
+
+int mt_op_panel_first_query(const void* d_first, const void* d_Wq, const float* d_bq, const void* d_WkT, void* d_qt, int32_t batch,
+                            int32_t heads, void* hip_stream)
+{
+    if (!d_first || !d_Wq || !d_bq || !d_WkT || !d_qt) return MT_ERR_NULL;
+    if (batch < 1 || heads < 1 || !aligned256(d_first, d_Wq, d_bq, d_WkT, d_qt)) return MT_ERR_SHAPE;
+    FirstTokenGroup g;
+    g.first[0] = d_first;
+    g.Wq[0] = d_Wq;
+    g.bq[0] = d_bq;
+    g.WkT[0] = d_WkT;
+    g.qt[0] = d_qt;
+    return op_result(launch_first_query(g, 1, batch, heads * 64, heads, static_cast<hipStream_t>(hip_stream)));
+}
+
+int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                             const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream)
+{
+    if (!d_x || !d_qt || !d_xbar || !d_seq_start || !d_seq_len) return MT_ERR_NULL;
+    if (batch < 1 || seq < 1 || heads < 1 || xbar_stride < (int64_t)state_rows(true, batch) * heads * 64 || !aligned256(d_x, d_qt, d_xbar)) return MT_ERR_SHAPE;
+    FirstTokenGroup g;
+    g.x[0] = d_x;
+    g.qt[0] = const_cast<void*>(d_qt);
+    g.xbar[0] = d_xbar;
+    return op_result(launch_first_attend(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, xbar_stride, static_cast<hipStream_t>(hip_stream)));
 }
 
 int mt_op_linear_batched(int32_t precision, int32_t G, const void* d_A, int64_t strideA, int64_t lda, const void* d_W,

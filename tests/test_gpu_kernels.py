@@ -106,3 +106,59 @@ def test_weight_layout_does_not_depend_on_a_handles_bounds():
         assert np.abs(got - ref).max() <= bound
     small.close()
     owner.close()
+
+
+def ragged_rows(lens, gap, rng):
+    """(row0, total): sequences of these lengths behind one another with up to `gap` rows of no sequence between them."""
+    row0, at = [], 0
+    for n in lens:
+        at += int(rng.integers(0, gap + 1))
+        row0.append(at)
+        at += int(n)
+    return np.array(row0, np.int32), at + int(rng.integers(0, gap + 1))
+
+
+def bf16(x):
+    return torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(torch.bfloat16).double().numpy()
+
+
+# q~ and the weighted row sums against float64 on the same bf16 operands.  Rows of no sequence hold NaN; `late` puts each head's highest scores
+# into the last key panel, 20 above the first ones, so that the running maximum has to follow.
+# Bounds (bfloat16 rounds to 2^-8 of the value).  q~: the query (2^-8 of each q, so 2^-8 sum |Wk q|) and the result round once each.  Row sums:
+# the result rounds once; the weights are float32 quantities: 2^-14 sum p |x| is what scores of |s| <= 50 summed in float32 (2^-24 sqrt(H) |s|)
+# can shift them.
+@pytest.mark.parametrize("heads,lens,late", [(1, [1, 32, 33], False), (2, [31, 65, 64, 1], True), (3, [200, 7], True), (5, [97] * 33, True), (11, [40, 128, 3], False),
+                                             (12, [128, 127, 70], True), (16, [1, 257, 64], True)])
+def test_first_token_panels(heads, lens, late):
+    print(f"first token: {heads} heads, {lens}, late {late}", flush=True)
+    H, B, rng = 64 * heads, len(lens), np.random.default_rng(heads)
+    row0, rows = ragged_rows(lens, 5, rng)
+    first, Wq, Wk, bq = bf16(rng.standard_normal((B, H))), bf16(rng.standard_normal((H, H)) / H**0.5), bf16(rng.standard_normal((H, H)) / H**0.5), rng.standard_normal(H).astype(np.float32)
+    panels = lambda x: mt.to_panels(torch.from_numpy(x).cuda(), torch.bfloat16)
+    qt = mt.op_panel_first_query(panels(first), panels(Wq), dev(bq), panels(np.ascontiguousarray(Wk.T)), B, heads)
+    q = (first @ Wq.T + bq).reshape(B, heads, 64)
+    want = np.einsum("bad,adh->bah", q, Wk.reshape(heads, 64, H))
+    bound = 1.01 * 2.0**-8 * np.abs(want) + 2.0**-8 * np.einsum("bad,adh->bah", np.abs(q), np.abs(Wk).reshape(heads, 64, H)) + 1e-30
+    err = np.abs(qt[:, :heads].double().cpu().numpy() - want)
+    print(f"  q~: {(err / bound).max():.3f} of the bound", flush=True)
+    assert (err <= bound).all()
+
+    x = np.full((rows, H), np.nan)
+    qt16 = bf16(rng.standard_normal((B, 16, H)) * (60.0 / H**0.5 if late else 8.0 / H**0.5))
+    for b, n in enumerate(lens):
+        v = rng.standard_normal((n, H)) * 0.2
+        if late:                              # rows lean towards the mean of the heads' q~, further from key to key
+            d = qt16[b, :heads].sum(0)
+            v += np.linspace(0.0, 1.0, n)[:, None] * d / (d @ d) * heads * 160.0
+        x[row0[b]:row0[b] + n] = bf16(v)
+    got = mt.op_panel_first_attend(panels(x), dev(qt16, torch.bfloat16), dev(row0), dev(np.array(lens, np.int32)), B, max(lens), heads).double().cpu().numpy()
+    worst = 0.0
+    for b, n in enumerate(lens):
+        xb = x[row0[b]:row0[b] + n]
+        s = qt16[b, :heads] @ xb.T / 8
+        p = np.exp(s - s.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        want, bound = p @ xb, 1.01 * 2.0**-8 * np.abs(p @ xb) + 2.0**-14 * (p @ np.abs(xb))
+        worst = max(worst, (np.abs(got[b] - want) / bound).max())
+    print(f"  row sums: {worst:.3f} of the bound, scores of the last sequence up to {np.abs(s).max():.1f}, spread {np.ptp(s):.1f}", flush=True)
+    assert worst <= 1.0
