@@ -149,7 +149,9 @@ int mt_load_weights(mt_model* m, int32_t scope, const void* h_blob, size_t nbyte
  *               position 0 of every sequence must be a real token (the pooler reads it);
  *   h_task_mask host array [n_tasks] of 0/1, or NULL for all tasks.  Disabled tasks are not computed
  *               and their logit columns are left untouched; the trunk runs only as deep as the
- *               deepest enabled fork;
+ *               deepest enabled fork.  MT_BF16 with up to 16 heads: the logits of an enabled task are the same bits whichever
+ *               others are enabled (they do depend on batch x seq in the last bits: kernel forms are chosen by size, and
+ *               under per-sequence routing on the tasks of the same route);
  *   d_out_logits [batch][C_tot] float32 row-major, C_tot = sum of n_classes over the MT_HEAD_SEQUENCE tasks,
  *               task t's columns start at mt_logit_offset(m, t).  Raw logits (no softmax).
  * Hidden states at padded positions are unspecified and never influence a real token.

@@ -596,18 +596,22 @@ hipError_t launch_form(const TiledGroup& g, const TiledShape& s, int form, int f
 //   beyond: tiles.  Narrow outputs of fewer tiles than fill the chip twice take K2, which halves a workgroup's serial K loop (2318
 //     rows x 768 x 3072: 21.5 us, PAIR 31); long K with many tiles takes TALL (18.6 k rows x 768 x 3072: 75.5 us, PAIR 78), everything
 //     else PAIR, whose two workgroups per compute unit hide each other's epilogues (GELU: 84 us, TALL 100).
+// The few-row forms add K up in four quarters, K2 in two halves, PAIR and TALL in one run, and a task's result must not depend on which
+// others are enabled: which of the three it is goes by the number of problems with all tasks enabled (TiledShape::plan), and only
+// the choice among forms of one order by those that are there.
 int choose_form(const TiledShape& s)
 {
     const int pm = (s.M + 31) / 32, pn = s.N / 32;
-    const long blocks = (long)pm * pn * s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1);
+    const long sub = s.n_sub > 1 ? s.n_sub : 1, plan = s.plan > s.G ? s.plan : s.G;
+    const long blocks = (long)pm * pn * s.G * s.splits * sub, plan_blocks = (long)pm * pn * plan * s.splits * sub;
     const int slices = s.K / 64 / s.splits;
     if (s.n_sub > 1 || s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
-    if (blocks <= 1152 || !tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
-    if (blocks <= 3072 && !(k2_ok && pm >= 64 && pn <= 32)) return TILED_ROWS_2X1;
-    const long tiles4 = (long)((pm + 3) / 4) * ((pn + 7) / 8) * s.G * s.splits;     // 128 x 256
-    if (k2_ok && tiles4 <= 256) return TILED_K2;
-    if (s.K >= 2048 && s.act == ACT_NONE && slices % 2 == 0 && tiles4 >= 512) return TILED_TALL;
+    if (!tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
+    if (plan_blocks <= 1152 || (plan_blocks <= 3072 && !(k2_ok && pm >= 64 && pn <= 32))) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
+    const long tiles4 = (long)((pm + 3) / 4) * ((pn + 7) / 8) * s.splits;           // 128 x 256, of a problem
+    if (k2_ok && tiles4 * plan <= 256) return TILED_K2;
+    if (s.K >= 2048 && s.act == ACT_NONE && slices % 2 == 0 && tiles4 * s.G >= 512) return TILED_TALL;
     return TILED_PAIR;
 }
 

@@ -94,6 +94,8 @@ struct TiledShape {
     // bf16 results without activation: from this column panel on (0 = none) a 32x32 block is stored transposed, as the operand of a
     // product over its rows: [16 rows][half][32 columns][8 rows], rows of a (16, half) run: 4 half + 0..3, 8 + 4 half + 0..3
     int32_t vt_panel;
+    // problems that the launch has when every task is enabled (0 = G): decides the order in which K is added up, see choose_form
+    int32_t plan;
 };
 // The kernel forms (gemm_tiled.hip); TILED_AUTO chooses by shape.
 enum TiledForm : int { TILED_AUTO = 0, TILED_ROWS_1X1, TILED_ROWS_2X1, TILED_ROWS_2X2, TILED_K2, TILED_PAIR, TILED_TALL };

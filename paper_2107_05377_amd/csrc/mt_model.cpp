@@ -490,9 +490,11 @@ struct Launcher {
         else check(launch_gemm_f32(g, s, st));
         end();
     }
-    void tiled(int klass, const TiledGroup& g, const TiledShape& s)
+    int plan = 0;          // problems that the group's launches have with every task enabled (TiledShape::plan)
+    void tiled(int klass, const TiledGroup& g, TiledShape s)
     {
         begin(klass);
+        s.plan = plan;
         check(launch_gemm_tiled(g, s, st));
         end();
     }
@@ -915,7 +917,7 @@ TiledGroup tiled_group(const mt_model* m)
 
 // K ranges of a contraction with a float32 result: a long K over few output blocks (a row bound of up to 128 at 768 columns) leaves
 // most of the chip idle otherwise; 36 rows x 768 x 3072: 10 us whole, 4.4 us in 4 ranges that the LayerNorm adds up.  The number of
-// problems does not enter: a task's result does not depend on which others are enabled.
+// problems that are there does not enter: a task's result must not depend on which others are enabled.
 int tiled_splits(int M, int N, int K, int most)
 {
     if (K < 2048) return 1;
@@ -992,7 +994,8 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
     }
     L.tiled(MT_K_GEMM_FFN1, g, TiledShape{n, M, F, H, H, H, F, gelu_act, 0, rm.n_rows, 1, 0});
 
-    const int sp = n == 1 && io[0].scr->y_parts >= 4 ? tiled_splits(M, H, F, 4) : 1;      // (only the trunk has room for partial results)
+    // only the trunk has room for partial results, and takes them where it never shares the launch
+    const int sp = L.plan <= 1 && n == 1 && io[0].scr->y_parts >= 4 ? tiled_splits(M, H, F, 4) : 1;
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->u);
         g.w[i] = units(io[i].w->W2);
@@ -1653,6 +1656,8 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     const int n_steps = h_route ? depth : mt_schedule_steps(m, h_task_mask);      // >= depth: every fork is a fork + 0 layers bound
     (void)max_y;
     auto run_steps = [&](const std::vector<int>& tasks, bool trunk) {
+    // (routed: the trunk has its launches to itself, and a group of tasks goes by its own number)
+    const bool planned = !h_route;
     for (int step = 0; step < n_steps; ++step) {
         std::vector<LayerIO> full;
         std::vector<LastIO> last;
@@ -1661,6 +1666,11 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         if (trunk && step < depth) {
             trunk_out(step + 1, (step + 1) & 1, nf, nb);
             full.push_back(LayerIO{cur_f, cur_b, &m->trunk[step], &y.trunk_scr, nf, nb});
+        }
+        int all_full = step < m->cfg.n_trunk_layers ? 1 : 0, all_last = 0;        // with every task enabled
+        for (const mt_task_desc& d : m->tasks) {
+            const int stage = step - d.fork_layer;
+            if (stage >= 0 && stage < d.n_layers) ++(stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE ? all_last : all_full);
         }
         for (int t : tasks) {
             const mt_task_desc& d = m->tasks[t];
@@ -1683,10 +1693,13 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                                        bf ? (void*)(ws + y.task_xb[t]) : nullptr});
             }
         }
+        // (a launch takes up to kMaxGroup problems; all launches of a step go by the first one's number)
+        L.plan = planned ? std::min(all_full, kMaxGroup) : 0;
         for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
             std::vector<LayerIO> part(full.begin() + lo, full.begin() + std::min(full.size(), lo + (size_t)kMaxGroup));
             (m->tiled ? run_layer_group_tiled : run_layer_group)(L, part, rm, B, S);
         }
+        L.plan = planned ? std::min(all_last, kMaxGroup) : 0;
         for (size_t lo = 0; lo < last.size(); lo += kMaxGroup) {
             std::vector<LastIO> part(last.begin() + lo, last.begin() + std::min(last.size(), lo + (size_t)kMaxGroup));
             (m->tiled ? run_last_layer_group_tiled : run_last_layer_group)(L, part, rm, B, S);

@@ -525,6 +525,41 @@ def test_bf16_base_invariants_at_full_size(base_model):
         col += task.n_classes
 
 
+def check_masks_leave_logits_alone(spec, model, batch, seq, masks):
+    ids, mask, _ = ms.make_inputs(spec, batch=batch, seq=seq)
+    d_ids, d_mask = dev(ids), dev(mask)
+    full = model.forward(d_ids, d_mask).cpu().numpy()
+    for tm in masks:
+        got = model.forward(d_ids, d_mask, task_mask=tm).cpu().numpy()
+        for t, task in enumerate(spec.tasks):
+            lo = model.logit_offset(t)
+            if tm[t]:
+                assert np.array_equal(got[:, lo:lo + task.n_classes], full[:, lo:lo + task.n_classes]), (batch, seq, tm, t)
+
+
+@pytest.mark.parametrize("batch,seq", [(1, 40), (32, 128)])
+def test_bf16_base_logits_do_not_depend_on_the_enabled_tasks(base_model, batch, seq):
+    """Bit for bit, whichever kernel form the number of problems would suggest."""
+    spec, model, _, _ = base_model
+    T = spec.n_tasks
+    masks = [[int(t == i) for t in range(T)] for i in range(T)] + [[int(t < 2) for t in range(T)], [int(t > 1) for t in range(T)]]
+    check_masks_leave_logits_alone(spec, model, batch, seq, masks)
+
+
+@pytest.mark.parametrize("batch,seq", [(4, 37), (16, 128), (64, 128)])
+def test_bf16_logits_do_not_depend_on_the_enabled_tasks_when_they_share_the_trunks_launches(batch, seq):
+    """Branches that start below the top of the trunk: the trunk's own layers share launches with them, or not.  640 columns and K = 2048 put
+    these sizes on all three orders in which a contraction adds K up, and into the trunk's split of a long K."""
+    tasks = (ms.TaskSpec(1, 2, 3), ms.TaskSpec(1, 3, 2), ms.TaskSpec(0, 2, 2), ms.TaskSpec(2, 3, 4), ms.TaskSpec(3, 2, 2), ms.TaskSpec(1, 2, 5),
+             ms.TaskSpec(2, 1, 1), ms.TaskSpec(3, 0, 2), ms.TaskSpec(1, 3, 3))
+    spec = ms.MTSpec("masks", vocab=300, hidden=640, heads=10, ffn=2048, max_pos=128, n_trunk_layers=3, tasks=tasks, precision="bf16", batch=64,
+                     seq=128, len_lo=20, len_hi=128, input_seed=3)
+    model, _ = mt.load_synthetic(spec, std=0.05)
+    T = spec.n_tasks
+    check_masks_leave_logits_alone(spec, model, batch, seq, [[int(t == i) for t in range(T)] for i in range(T)] + [[int(t % 2 == 0) for t in range(T)]])
+    model.close()
+
+
 def test_bf16_base_task_isolation(base_model):
     """Reloading one task's checkpoint leaves every other task's logits bit-identical (Section 5.1)."""
     spec, model, _, tps = base_model
