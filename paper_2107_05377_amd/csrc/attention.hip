@@ -300,6 +300,14 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(AttnGroup g, co
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) vf[dt][e] = vrow[dt * 32];
         }
+        if (kb + 32 > S) {                                       // beyond the sequence: weight 0 times a repeat, which may be infinite
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (kb + (e >> 2) * 8 + half * 4 + (e & 3) >= S) {
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) vf[dt][e] = 0.f;
+                }
+        }
         f32x16 sc;
 #pragma unroll
         for (int e = 0; e < 16; ++e) sc[e] = 0.f;

@@ -52,6 +52,19 @@ def test_attention_f32_blocks(B, S, H, A):
     assert np.abs(ctx - oracle.attention(q, k, v, mask, A)).max() <= 2e-5
 
 
+@pytest.mark.parametrize("S,H", [(33, 64), (35, 32), (64, 64)])
+def test_attention_f32_infinite_value_of_the_last_key(S, H):
+    """An infinite value makes its own column infinite and no NaN, also where the last key block is not full."""
+    print(f"attention_f32 infinite value S={S} H={H}", flush=True)
+    rng = np.random.default_rng(S)
+    q, k, v = (rng.standard_normal((1, S, H)).astype(np.float32) for _ in range(3))
+    ref = oracle.attention(q, k, v, np.ones((1, S), np.int32), 1)
+    v[0, -1, 5] = np.inf
+    ctx = mt.op_attention(mt.MT_FP32_CHECK, dev(np.concatenate([q, k, v], axis=2)[0]), dev(np.ones((1, S), np.int32)), 1, S, H, 1).cpu().numpy().reshape(1, S, H)
+    rest = np.arange(H) != 5
+    assert (ctx[..., 5] == np.inf).all() and np.abs(ctx[..., rest] - ref[..., rest]).max() <= 2e-5
+
+
 # bfloat16 kernels of the panel layout through a whole model: ragged rows, both contractions' halves that a launch rule can choose.
 # Bound on the logits: bfloat16 operands (2^-9 each) through three layers give at most 2e-2 at logits of order 1.
 @pytest.mark.parametrize("heads,ffn,batch,seq,lo", [
