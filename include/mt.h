@@ -322,9 +322,10 @@ int mt_profile_enable(mt_model* m, int32_t on);
 int mt_profile_read(mt_model* m, float* h_ms /*[MT_K_COUNT]*/, int32_t* h_launches /*[MT_K_COUNT]*/);
 
 /*
- * Single operations on device buffers, the same kernels mt_forward launches, exposed so each can be
- * checked on its own.  `precision` selects the element type of activations/weights named "act":
- * MT_BF16 -> bfloat16, MT_FP32_CHECK -> float32.  All enqueue on hip_stream and return.
+ * Single operations on device buffers, exposed so that each of mt_forward's kernels can be checked on its own.  All enqueue on
+ * hip_stream and return.  mt_op_panel_* run the kernels of MT_BF16 with up to 16 heads (panel layout, below).  The others run the
+ * row-major kernels: with float32 those of MT_FP32_CHECK, with bfloat16 those of the FP8 precisions and of MT_BF16 with more than
+ * 16 heads.  `precision` selects the element type of activations/weights named "act": MT_BF16 -> bfloat16, MT_FP32_CHECK -> float32.
  */
 /* C[M,N] = epilogue(A[M,K] W[N,K]^T + bias[N]) ; act_kind: 0 none, 1 GELU(erf), 2 GELU(tanh), 3 tanh.
  * d_residual (float32 [M,N]) may be NULL; if given it is added after the activation (bf16 precision:
@@ -375,6 +376,38 @@ int mt_op_panel_first_query(const void* d_first, const void* d_Wq, const float* 
                             int32_t heads, void* hip_stream);
 int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
                              const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream);
+/* The other steps on the panel layout.  mt_op_panel_linear: `problems` equal-shaped contractions, each of `subs` equal parts (heads),
+ *   C = act(A W^T + bias) on A [M][lda], W [N][ldw], C [M][ldc], the widths being those of the matrices whose columns the operands are.
+ *   N % 32 == 0, K % (64 splits) == 0, lda and ldw multiples of 16, ldc of 8; at most 32 problems of at most 16 parts.
+ * splits > 1: float32 partial results of as many ranges of K, split_stride elements apart, the bias in the first.  transposed_from > 0 (a multiple of
+ * 64; bf16, no activation): from this output column on, every block of 32 rows x 32 columns is stored as an operand of a product over its rows,
+ * [rows in 16][half][32 columns][8 rows], the rows of a half h being 4 h + 0..3 and 8 + 4 h + 0..3 (the attention's values).
+ * form: 0 by shape, as mt_forward; 1, 2, 3 few rows in 1x1, 2x1, 2x2 blocks; 4 tiles with K in two halves; 5 pairs of tile workgroups; 6 tall tiles
+ * (no activation).  4 to 6 need K / splits >= 320 (4: 640, a multiple of 128; 6: a multiple of 128) and one part.  height: tile height of those in
+ * row panels (4, 5: 1..4; 6: 5..8; from 4 on an even number of K slices of 64 or, form 4, 128), 0 by shape.
+ * Errors: NULL, SHAPE, HIP. */
+typedef struct mt_panel_linear {
+    const void* d_A;
+    const void* d_W;
+    const float* d_bias;            /* or NULL */
+    void* d_C;
+    const int32_t* d_rows;          /* rows present, at most M; NULL: M */
+    int64_t stride_A, stride_W, stride_bias, stride_C;      /* bytes between problems, multiples of 256 below 16 GiB */
+    int64_t sub_A, sub_W, sub_bias, sub_C;                  /* bytes between the parts of a problem, likewise */
+    int64_t split_stride;
+    int32_t problems, subs, M, N, K, lda, ldw, ldc, act_kind, out_f32, splits, transposed_from, form, height;
+} mt_panel_linear;
+int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream);
+/* ctx = softmax(q k^T / 8) v per head over the rows d_seq_start[b] .. + min(d_seq_len[b], seq) - 1 of a sequence; d_qkv [rows][3 hidden] bf16 panels,
+ * the values as transposed_from = 2 hidden leaves them, d_ctx [rows][hidden] bf16 panels.  Rows of no sequence may hold anything and are not written. */
+int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq,
+                          int32_t heads, void* hip_stream);
+/* out = LayerNorm(sum of the n_parts (1, 2 or 4) matrices at d_x, part_stride elements apart, + residual) * gamma + beta; residual row i is row
+ * d_res_row[i] (below res_rows) if given, else row i.  d_out float32, d_out_b bf16: the rows, or with `split` [hi | lo] halves of 2 hidden columns.
+ * All but gamma and beta in panels.  hidden: a multiple of 64 up to 1024. */
+int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
+                          const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, const int32_t* d_rows,
+                          int32_t M, int32_t hidden, void* hip_stream);
 /* ctx[b,s,a*d:(a+1)*d] = softmax(q k^T / sqrt(d) + mask) v per head; d_qkv is [B*S][3H] act
  * (columns Q | K | V), d_ctx [B*S][H] act. */
 int mt_op_attention(int32_t precision, const void* d_qkv, const int32_t* d_mask, void* d_ctx,

@@ -26,7 +26,7 @@ KERNEL_CLASSES = ["embed", "gemm_qkv", "attn", "gemm_out", "ln", "gemm_ffn1", "g
 EXPORTS = ["mt_create", "mt_destroy", "mt_weight_bytes", "mt_workspace_bytes", "mt_bind", "mt_load_weights",
            "mt_forward", "mt_logit_offset", "mt_n_logits", "mt_layer_count", "mt_last_error", "mt_error_name",
            "mt_read_hidden", "mt_profile_enable", "mt_profile_read", "mt_op_linear", "mt_op_attention",
-           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_schedule_steps", "mt_forward_routed",
+           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_linear", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
            "mt_forward_tokens", "mt_token_logit_offset", "mt_n_token_logits", "mt_forward_static", "mt_forward_multi", "mt_forward_requests", "mt_forward_routed_tokens", "mt_op_linear_fp8", "mt_debug_e4m3_quantize", "mt_check_mask"]
 MT_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
@@ -42,6 +42,13 @@ class mt_config(C.Structure):
                 ("n_tasks", C.c_int32), ("tasks", C.POINTER(mt_task_desc)),
                 ("precision", C.c_int32), ("gelu", C.c_int32), ("ln_eps", C.c_float),
                 ("max_batch", C.c_int32), ("max_seq", C.c_int32)]
+
+
+class mt_panel_linear(C.Structure):
+    _fields_ = [("d_A", C.c_void_p), ("d_W", C.c_void_p), ("d_bias", C.c_void_p), ("d_C", C.c_void_p), ("d_rows", C.c_void_p)] + \
+               [(n, C.c_int64) for n in ("stride_A", "stride_W", "stride_bias", "stride_C", "sub_A", "sub_W", "sub_bias", "sub_C", "split_stride")] + \
+               [(n, C.c_int32) for n in ("problems", "subs", "M", "N", "K", "lda", "ldw", "ldc", "act_kind", "out_f32", "splits", "transposed_from",
+                                         "form", "height")]
 
 
 _lib = None
@@ -99,6 +106,9 @@ def lib():
         L.mt_op_first_token_pool.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
         L.mt_op_panel_first_query.argtypes = [vp, vp, vp, vp, vp, i32, i32, vp]
         L.mt_op_panel_first_attend.argtypes = [vp, vp, vp, i64, vp, vp, i32, i32, i32, vp]
+        L.mt_op_panel_linear.argtypes = [C.POINTER(mt_panel_linear), vp]
+        L.mt_op_panel_attention.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
+        L.mt_op_panel_layernorm.argtypes = [vp, i32, i64, vp, vp, i32, vp, vp, C.c_float, vp, vp, i32, vp, i32, i32, vp]
         L.mt_op_linear_sub.argtypes = [vp, i64, vp, i64, vp, vp, i64, i32, i32, i32, i32, i64, i64, i64, i64, vp, vp, i32, vp]
         L.mt_debug_set_gemm_tile.restype = i32
         _lib = L
@@ -396,6 +406,38 @@ def op_panel_first_attend(x, qt, seq_start, seq_len, batch, seq, heads):
     if rc != MT_OK:
         raise MTError(rc, "mt_op_panel_first_attend")
     return torch.stack([from_panels(xbar[a])[:batch] for a in range(heads)], dim=1)
+
+
+def op_panel_linear(A, W, bias, C_out, *, M, N, K, rows=None, **fields):
+    """mt_op_panel_linear on device tensors in the panel layout; `fields` are the struct's (lda, ldw, ldc default to K, K, N)."""
+    op = mt_panel_linear(d_A=A.data_ptr(), d_W=W.data_ptr(), d_bias=None if bias is None else bias.data_ptr(), d_C=C_out.data_ptr(),
+                         d_rows=None if rows is None else rows.data_ptr(), M=M, N=N, K=K,
+                         **{"problems": 1, "subs": 1, "lda": K, "ldw": K, "ldc": N, "splits": 1, **fields})
+    rc = lib().mt_op_panel_linear(C.byref(op), _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_linear")
+    return C_out
+
+
+def op_panel_attention(qkv, seq_start, seq_len, batch, seq, heads):
+    """mt_op_panel_attention; qkv in panels, values transposed; returns the context in panels (rows of no sequence NaN)."""
+    ctx = _panels(qkv.shape[0] * 32, heads * 64, qkv.dtype, qkv.device)
+    rc = lib().mt_op_panel_attention(_ptr(qkv), _ptr(ctx), _ptr(seq_start), _ptr(seq_len), batch, seq, heads, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_attention")
+    return ctx
+
+
+def op_panel_layernorm(x, residual, gamma, beta, eps, M, hidden, res_row=None, res_rows=0, split=False, rows=None):
+    """mt_op_panel_layernorm; x [parts][panels ..] float32 and residual in panels; returns the float32 state and its bf16 operand in panels."""
+    import torch
+    of = _panels(M, hidden, torch.float32, x.device)
+    ob = _panels(M, hidden * (2 if split else 1), torch.bfloat16, x.device)
+    rc = lib().mt_op_panel_layernorm(_ptr(x), x.shape[0], x.stride(0), _ptr(residual), _ptr(res_row), res_rows, _ptr(gamma), _ptr(beta), eps, _ptr(of),
+                                     _ptr(ob), 1 if split else 0, _ptr(rows), M, hidden, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_layernorm")
+    return of, ob
 
 
 def mfma_peak(iters=4000):

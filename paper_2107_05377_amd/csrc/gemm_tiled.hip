@@ -630,6 +630,9 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
     const int kw = form == TILED_K2 ? 2 : 1, slices = s.K / (64 * kw) / s.splits;
     if (form >= TILED_K2 && (s.n_sub > 1 || s.K % (64 * kw * s.splits) != 0 || slices < 5 || (form == TILED_TALL && slices % 2 != 0)))
         return hipErrorInvalidValue;
+    // a given height: one of the form's, and those with two weight buffers take an even number of slices
+    if (force && (form < TILED_K2 || force < (form == TILED_TALL ? 5 : 1) || force > (form == TILED_TALL ? 8 : 4) || (force >= 4 && slices % 2 != 0)))
+        return hipErrorInvalidValue;
     if (form < TILED_K2 && ((long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535 || s.lda / 16 > 65535 || s.ldw / 16 > 65535 || s.ldc / 8 > 65535 ||
                             s.N / 32 > 65535))
         return hipErrorInvalidValue;

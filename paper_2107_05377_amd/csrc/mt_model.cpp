@@ -2322,6 +2322,77 @@ int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, in
     return op_result(launch_first_attend(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, xbar_stride, static_cast<hipStream_t>(hip_stream)));
 }
 
+int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream)
+{
+    if (!op || !op->d_A || !op->d_W || !op->d_C) return MT_ERR_NULL;
+    const int64_t strides[] = {op->stride_A, op->stride_W, op->stride_bias, op->stride_C, op->sub_A, op->sub_W, op->sub_bias, op->sub_C};
+    if (op->problems < 1 || op->problems > kMaxGroup || op->subs < 1 || op->subs > 16 || op->M < 1 || op->N < 1 || op->ldc < op->N || op->K < 1 || op->splits < 1 || op->act_kind < 0 ||
+        op->act_kind > 3 || op->form < TILED_AUTO || op->form > TILED_TALL || op->transposed_from < 0 || op->transposed_from % 64 != 0 ||
+        !aligned256(op->d_A, op->d_W, op->d_bias, op->d_C))
+        return MT_ERR_SHAPE;
+    for (const int64_t v : strides)
+        if (v < 0 || v % 256 != 0 || v >= 1ll << 34) return MT_ERR_SHAPE;       // 32 problems and 16 parts: within 32 bits of 256-byte units
+    TiledGroup g;
+    g.A = op->d_A;
+    g.W = op->d_W;
+    g.C = op->d_C;
+    g.bias = op->d_bias;
+    for (int i = 0; i < op->problems; ++i) {
+        g.a[i] = units((size_t)i * op->stride_A);
+        g.w[i] = units((size_t)i * op->stride_W);
+        g.c[i] = units((size_t)i * op->stride_C);
+        g.b[i] = op->d_bias ? units((size_t)i * op->stride_bias) : kNoBias;
+    }
+    TiledShape s{op->problems, op->M, op->N, op->K, op->lda, op->ldw, op->ldc, op->act_kind, op->out_f32 ? 1 : 0, op->d_rows, op->splits, op->split_stride};
+    s.n_sub = op->subs;
+    s.sub_a = (int32_t)units(op->sub_A);
+    s.sub_w = (int32_t)units(op->sub_W);
+    s.sub_c = (int32_t)units(op->sub_C);
+    s.sub_b = (int32_t)units(op->sub_bias);
+    s.vt_panel = op->transposed_from / 32;
+    return op_result(launch_gemm_tiled(g, s, static_cast<hipStream_t>(hip_stream), op->form, op->height));
+}
+
+int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq,
+                          int32_t heads, void* hip_stream)
+{
+    if (!d_qkv || !d_ctx || !d_seq_start || !d_seq_len) return MT_ERR_NULL;
+    if (batch < 1 || seq < 1 || heads < 1 || heads > 16 || !aligned256(d_qkv, d_ctx)) return MT_ERR_SHAPE;
+    AttnTiledGroup g;
+    g.base_qkv = d_qkv;
+    g.base_ctx = d_ctx;
+    g.qkv[0] = g.ctx[0] = 0;
+    return op_result(launch_attention_tiled(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, static_cast<hipStream_t>(hip_stream)));
+}
+
+int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
+                          const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, const int32_t* d_rows,
+                          int32_t M, int32_t hidden, void* hip_stream)
+{
+    if (!d_x || !d_residual || !d_gamma || !d_beta || !d_out || !d_out_b) return MT_ERR_NULL;
+    if (M < 1 || hidden < 1 || part_stride < 0 || part_stride % 4 != 0 || (d_res_row && res_rows < 1) ||
+        !aligned256(d_x, d_residual, d_gamma, d_beta, d_out, d_out_b))
+        return MT_ERR_SHAPE;
+    // the launch takes offsets from a common base
+    auto at = [](const void* p, const void* base) { return (size_t)((uintptr_t)p - (uintptr_t)base); };
+    const void* ws = std::min({(const void*)d_x, (const void*)d_residual, (const void*)d_out, (const void*)d_out_b}, std::less<const void*>());
+    const void* wt = std::min<const void*>(d_gamma, d_beta, std::less<const void*>());
+    TiledLnGroup g;
+    g.ws = ws;
+    g.wt = wt;
+    const size_t off[] = {at(d_x, ws), at(d_residual, ws), at(d_out, ws), at(d_out_b, ws), at(d_gamma, wt), at(d_beta, wt)};
+    for (const size_t o : off)
+        if (o / 256 > 0xFFFFFFFFu) return MT_ERR_SHAPE;
+    g.x[0] = units(off[0]);
+    g.res[0] = units(off[1]);
+    g.out_f[0] = units(off[2]);
+    g.out_b[0] = units(off[3]);
+    g.gamma[0] = units(off[4]);
+    g.beta[0] = units(off[5]);
+    TiledLnShape s{1, M, hidden, d_rows, eps, n_parts, part_stride, d_res_row, res_rows, split ? 1 : 0};
+    return op_result(launch_layernorm_tiled(g, s, static_cast<hipStream_t>(hip_stream)));
+}
+
 int mt_op_linear_batched(int32_t precision, int32_t G, const void* d_A, int64_t strideA, int64_t lda, const void* d_W,
                          int64_t strideW, const float* d_bias, int64_t strideBias, const float* d_residual,
                          int64_t strideRes, void* d_C, int64_t strideC, int64_t ldc, int32_t M, int32_t N, int32_t K,

@@ -175,3 +175,190 @@ def test_first_token_panels(heads, lens, late):
         worst = max(worst, (np.abs(got[b] - want) / bound).max())
     print(f"  row sums: {worst:.3f} of the bound, scores of the last sequence up to {np.abs(s).max():.1f}, spread {np.ptp(s):.1f}", flush=True)
     assert worst <= 1.0
+
+
+def panels(x, dtype=None):
+    """A float array [rows][width] in the panel layout on the device, rows of the last panel beyond it NaN."""
+    return mt.to_panels(torch.from_numpy(np.ascontiguousarray(x)).cuda(), dtype or torch.bfloat16)
+
+
+def nan_panels(rows, width, dtype):
+    return torch.full(((rows + 31) // 32, width // 8, 32, 8), float("nan"), dtype=dtype, device="cuda")
+
+
+def rows_of(p):
+    return mt.from_panels(p).double().cpu().numpy()
+
+
+def transposed_columns(x, first):
+    """Columns from `first` on as an operand of a product over the rows: in blocks of 32 x 32, [16 rows][half][32 columns][8 rows]
+    instead of [8 columns][32 rows] chunks; the array that stands at such addresses of an ordinary panel matrix."""
+    rows, width = x.shape
+    order = np.array([16 * r + 4 * h + (j & 3) + 8 * (j >> 2) for r in range(2) for h in range(2) for j in range(8)])     # rows of a run [r][h]
+    out = x.copy()
+    for p in range(0, rows, 32):
+        for c in range(first, width, 32):
+            runs = x[p:p + 32, c:c + 32][order].reshape(4, 8, 32)                # [run][8 rows][32 columns]
+            out[p:p + 32, c:c + 32] = runs.transpose(2, 0, 1).reshape(32, 32)    # row of the chunk = column, chunk = run
+    return out
+
+
+ROWS_1X1, ROWS_2X1, ROWS_2X2, K2, PAIR, TALL = 1, 2, 3, 4, 5, 6
+
+
+# Every form of the panel contraction and every tile height at remainders of rows, columns and K, against float64 on the same bf16 operands.
+# `rows` of the M are present: what lies beyond is NaN.  Bound: K products summed in float32 in any order, K 2^-24 sum |a w| (+ bias), for
+# bfloat16 results their rounding, 2^-8 of the value; GELU: slope below 1.13, 3e-5 for its fit; tanh: slope 1 and 2^-21 for tanhf.
+@pytest.mark.parametrize("form,height,problems,M,rows,N,K,act,f32,splits", [
+    (ROWS_1X1, 0, 1, 1, 1, 32, 64, 0, 1, 1), (ROWS_1X1, 0, 1, 70, 33, 96, 832, 1, 0, 1), (ROWS_1X1, 0, 3, 33, 33, 96, 768, 3, 1, 1),
+    (ROWS_1X1, 0, 1, 40, 40, 64, 3072, 0, 1, 4), (ROWS_2X1, 0, 2, 97, 65, 96, 832, 2, 0, 1), (ROWS_2X1, 0, 1, 70, 70, 64, 1536, 0, 1, 2),
+    (ROWS_2X2, 0, 1, 97, 97, 96, 128, 0, 0, 1), (ROWS_2X2, 0, 2, 65, 40, 160, 192, 1, 0, 1),
+    (K2, 1, 1, 33, 33, 160, 640, 0, 1, 1), (K2, 2, 2, 97, 70, 288, 640, 1, 0, 1), (K2, 3, 1, 200, 193, 96, 896, 0, 0, 1), (K2, 4, 3, 290, 257, 160, 768, 0, 1, 1),
+    (K2, 4, 1, 130, 130, 160, 3072, 0, 1, 2), (K2, 1, 3, 1024, 1010, 512, 640, 0, 0, 1),
+    (PAIR, 1, 2, 65, 33, 288, 320, 2, 0, 1), (PAIR, 2, 1, 97, 97, 544, 448, 0, 1, 1), (PAIR, 3, 2, 200, 193, 96, 320, 1, 0, 1), (PAIR, 4, 1, 290, 257, 288, 384, 0, 0, 1),
+    (PAIR, 4, 1, 130, 130, 288, 1536, 0, 1, 4), (PAIR, 1, 10, 1024, 1001, 512, 320, 1, 0, 1),
+    (TALL, 5, 1, 170, 161, 288, 384, 0, 1, 1), (TALL, 6, 2, 390, 353, 96, 512, 0, 0, 1), (TALL, 7, 1, 230, 225, 288, 384, 0, 1, 1), (TALL, 8, 1, 300, 257, 544, 640, 0, 0, 1),
+    (TALL, 5, 8, 1312, 1300, 1024, 384, 0, 1, 1),
+    (0, 0, 1, 300, 171, 768, 768, 0, 0, 1), (0, 0, 8, 300, 171, 768, 768, 0, 1, 1), (0, 0, 1, 2080, 1900, 2304, 768, 1, 0, 1),
+])
+def test_panel_linear_forms(form, height, problems, M, rows, N, K, act, f32, splits):
+    print(f"panel linear: form {form} height {height}, {problems} x {rows}/{M} x {N} x {K}, act {act}, f32 {f32}, splits {splits}", flush=True)
+    from scipy.special import erf
+    rng = np.random.default_rng(M + N + K + height)
+    A, W = bf16(rng.standard_normal((problems, M, K))), bf16(rng.standard_normal((problems, N, K)) / K**0.5)
+    b = rng.standard_normal((problems, N)).astype(np.float32)
+    A[:, rows:] = np.nan
+    pa, pw = torch.stack([panels(a) for a in A]), torch.stack([panels(w) for w in W])
+    pc = torch.stack([nan_panels(M, N, torch.float32 if f32 else torch.bfloat16) for _ in range(problems * splits)])
+    bias = torch.zeros((problems, (N + 63) // 64 * 64), device="cuda")           # a problem's bias starts at a multiple of 256 bytes
+    bias[:, :N] = dev(b)
+    size = lambda t: t[0].numel() * t.element_size()
+    mt.op_panel_linear(pa, pw, bias, pc, M=M, N=N, K=K, rows=dev(np.array([rows], np.int32)), problems=problems, stride_A=size(pa), stride_W=size(pw),
+                       stride_bias=size(bias), stride_C=size(pc) * splits, split_stride=pc[0].numel(), splits=splits, act_kind=act, out_f32=f32, form=form,
+                       height=height)
+    for i in range(problems):
+        got = sum(rows_of(pc[i * splits + s])[:rows] for s in range(splits))
+        a, w = A[i, :rows], W[i]
+        x = a @ w.T + b[i]
+        bound = K * 2.0**-24 * (np.abs(a) @ np.abs(w).T + np.abs(b[i])) + 1e-30
+        if act in (1, 2):
+            want = x * 0.5 * (1 + (erf(x / 2**0.5) if act == 1 else np.tanh((2 / np.pi)**0.5 * (x + 0.044715 * x**3))))
+            bound = 1.13 * bound + 3e-5
+        else:
+            want, bound = (np.tanh(x), bound + 2.0**-21) if act == 3 else (x, bound)
+        if not f32:
+            bound = 1.01 * (bound + 2.0**-8 * np.abs(want))
+        err = np.abs(got - want)
+        assert (err <= bound).all(), (i, float((err / bound).max()))
+    untouched = (rows + 31) // 32
+    assert torch.isnan(pc[:, untouched:]).all()
+
+
+# the values' columns, stored transposed for the attention: the same numbers at other places
+@pytest.mark.parametrize("form,height,M,K", [(ROWS_1X1, 0, 40, 64), (ROWS_2X1, 0, 70, 832), (ROWS_2X2, 0, 97, 128), (K2, 3, 97, 640), (PAIR, 4, 160, 384), (PAIR, 1, 33, 320), (TALL, 5, 200, 384)])
+def test_panel_linear_transposed_columns(form, height, M, K):
+    print(f"panel linear, transposed columns: form {form} height {height}, {M} x {K}", flush=True)
+    rng, N, first = np.random.default_rng(M + K), 192, 128
+    A, W, b = panels(rng.standard_normal((M, K))), panels(rng.standard_normal((N, K)) / K**0.5), dev(rng.standard_normal(N).astype(np.float32))
+    full = (M + 31) // 32 * 32
+    A[-1, :, M % 32 or 32:] = 0                                                  # (every row of the last panel is compared)
+    plain, moved = (mt.op_panel_linear(A, W, b, nan_panels(M, N, torch.bfloat16), M=full, N=N, K=K, form=form, height=height, transposed_from=t) for t in (0, first))
+    assert np.array_equal(rows_of(moved), transposed_columns(rows_of(plain), first))
+
+
+def test_panel_linear_parts():
+    """Problems of equal parts with operands of their own, as the contexts of the heads: 3 heads over 2 problems."""
+    print("panel linear, parts", flush=True)
+    rng, heads, B, H = np.random.default_rng(5), 3, 37, 192
+    x, W, b = bf16(rng.standard_normal((2, heads, B, H))), bf16(rng.standard_normal((2, H, H)) / H**0.5), rng.standard_normal((2, H)).astype(np.float32)
+    px, pw = torch.stack([panels(v) for p in x for v in p]), torch.stack([panels(w) for w in W])
+    pc = torch.stack([nan_panels(B, H, torch.bfloat16) for _ in range(2)])
+    bias = torch.zeros((2, 256), device="cuda")
+    bias[:, :H] = dev(b)
+    size = lambda t: t[0].numel() * t.element_size()
+    mt.op_panel_linear(px, pw, bias, pc, M=B, N=64, K=H, ldc=H, problems=2, subs=heads, stride_A=size(px) * heads, stride_W=size(pw), stride_bias=1024,
+                       stride_C=size(pc), sub_A=size(px), sub_W=64 * H * 2, sub_bias=256, sub_C=8 * 512)
+    for p in range(2):
+        for h in range(heads):
+            w = W[p, h * 64:h * 64 + 64]
+            want = x[p, h] @ w.T + b[p, h * 64:h * 64 + 64]
+            bound = 1.01 * (2.0**-8 * np.abs(want) + H * 2.0**-24 * (np.abs(x[p, h]) @ np.abs(w).T + 3))
+            assert (np.abs(rows_of(pc[p])[:B, h * 64:h * 64 + 64] - want) <= bound).all(), (p, h)
+
+
+# heights, K and widths that no kernel takes are refused
+@pytest.mark.parametrize("bad", [dict(form=ROWS_1X1, height=1), dict(form=K2, K=576), dict(form=K2, height=5), dict(form=K2, K=640, height=4), dict(form=PAIR, K=256),
+                                 dict(form=PAIR, K=320, height=4), dict(form=TALL, K=320), dict(form=TALL, height=4), dict(form=TALL, act_kind=1), dict(form=TALL, height=9),
+                                 dict(form=PAIR, subs=2), dict(N=48), dict(K=96), dict(transposed_from=32), dict(transposed_from=64, out_f32=1), dict(splits=2), dict(ldc=32), dict(form=7)])
+def test_panel_linear_refuses(bad):
+    t = torch.zeros(1 << 18, dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(mt.MTError) as e:
+        mt.op_panel_linear(t, t, None, t, **{"M": 64, "N": 64, "K": 768, **bad})
+    assert e.value.code == mt.MT_ERR_SHAPE
+
+
+# Attention on the panels, each launch shape: one workgroup per sequence and head with up to four query panels, the fifth panel with and without
+# a wavefront of its own, several workgroups per sequence, two wavefronts per query panel.  Rows of no sequence hold NaN in every column and are
+# not written.  `late`: scores rise by 20 to the last key, so the running maximum follows panel after panel and the two halves of a query
+# panel's keys meet with different maxima.  Bound: a softmax weight is rounded to bfloat16 (2^-8 sum p |v|; 2^-14 for scores summed in
+# float32, as above) and so is the result.
+@pytest.mark.parametrize("heads,lens,seq,late", [
+    (1, [1, 2, 31, 32, 33], 33, False), (3, [64, 65, 63, 96], 96, True), (2, [128, 127, 97, 3], 128, True), (16, [128] + [97, 128, 66] * 21, 128, True),
+    (2, [200, 161, 5], 200, True), (5, [289, 288, 257, 4], 289, True), (1, [512, 509, 1], 512, False), (16, [289, 270, 33] * 4, 289, True), (2, [70, 64], 40, False),
+])
+def test_attention_panels(heads, lens, seq, late):
+    print(f"attention: {heads} heads, {len(lens)} sequences of up to {max(lens)}, bound {seq}, late {late}", flush=True)
+    H, rng = 64 * heads, np.random.default_rng(heads + seq)
+    row0, rows = ragged_rows(lens, 5, rng)
+    full = (rows + 31) // 32 * 32
+    x = np.full((full, 3, heads, 64), np.nan)
+    for r, n in zip(row0, lens):
+        x[r:r + n] = rng.standard_normal((n, 3, heads, 64)) * np.array([2.0, 1.0, 1.0])[:, None, None]
+        if late:
+            u = rng.standard_normal((heads, 64))
+            u /= np.linalg.norm(u, axis=1, keepdims=True)
+            x[r:r + n, 0] += 5.0 * u
+            x[r:r + n, 1] += 32.0 * u * np.linspace(0.0, 1.0, n)[:, None, None]
+    x = bf16(x)
+    qkv = panels(transposed_columns(x.reshape(full, 3 * H), 2 * H))
+    got = rows_of(mt.op_panel_attention(qkv, dev(row0), dev(np.array(lens, np.int32)), len(lens), seq, heads)).reshape(full, heads, 64)
+    worst, written = 0.0, np.zeros(full, bool)
+    for r, n in zip(row0, np.minimum(lens, seq)):
+        q, k, v = (x[r:r + n, i].transpose(1, 0, 2) for i in range(3))
+        s = q @ k.transpose(0, 2, 1) / 8
+        p = np.exp(s - s.max(2, keepdims=True))
+        p /= p.sum(2, keepdims=True)
+        want, bound = p @ v, 1.01 * 2.0**-8 * np.abs(p @ v) + (2.0**-8 + 2.0**-14) * (p @ np.abs(v))
+        worst = max(worst, (np.abs(got[r:r + n].transpose(1, 0, 2) - want) / bound).max())
+        written[r:r + n] = True
+    print(f"  {worst:.3f} of the bound, scores of the last sequence up to {np.abs(s).max():.1f}", flush=True)
+    assert worst <= 1.0 and np.isnan(got[~written]).all()
+
+
+# LayerNorm on the panels: remainders of the rows, each number of partial results, few rows and many (2048 divides the forms), a residual that is
+# looked up by row, the [hi | lo] operand.  Bound: float32 sums and a square root (2^-18 of the terms); the operand is the state rounded once, 2^-8
+# of the value, and as [hi | lo] twice, 2^-16.
+@pytest.mark.parametrize("M,rows,H,parts,look_up,split", [
+    (1, 1, 64, 1, False, False), (33, 30, 768, 4, False, False), (70, 70, 832, 2, True, True), (2080, 2049, 64, 2, False, False), (2100, 2051, 1024, 4, False, False),
+    (37, 37, 1024, 1, True, True), (2052, 2052, 128, 1, True, False), (64, 35, 320, 4, False, True),
+])
+def test_layernorm_panels(M, rows, H, parts, look_up, split):
+    print(f"layernorm: {rows}/{M} x {H}, {parts} parts, look-up {look_up}, split {split}", flush=True)
+    rng = np.random.default_rng(M + H)
+    x = rng.standard_normal((parts, M, H)).astype(np.float32)
+    x[:, rows:] = np.nan
+    res_rows = 50 if look_up else M
+    res = rng.standard_normal((res_rows, H)).astype(np.float32)
+    index = rng.integers(0, res_rows, M).astype(np.int32)
+    gamma, beta = 1 + 0.2 * rng.standard_normal(H).astype(np.float32), rng.standard_normal(H).astype(np.float32)
+    of, ob = mt.op_panel_layernorm(torch.stack([panels(p, torch.float32) for p in x]), panels(res, torch.float32), dev(gamma), dev(beta), 1e-12, M, H,
+                                   res_row=dev(index) if look_up else None, res_rows=res_rows if look_up else 0, split=split, rows=dev(np.array([rows], np.int32)))
+    v = x[:, :rows].astype(np.float64).sum(0) + (res[index[:rows]] if look_up else res[:rows])
+    n = (v - v.mean(1, keepdims=True)) / np.sqrt(v.var(1, keepdims=True) + 1e-12)
+    want = gamma * n + beta
+    got, operand = rows_of(of), rows_of(ob)
+    assert (np.abs(got[:rows] - want) <= 2.0**-18 * (np.abs(gamma) * (1 + np.abs(n)) + np.abs(beta))).all()
+    if split:
+        operand = operand[:, :H] + operand[:, H:]
+    assert (np.abs(operand[:rows] - got[:rows]) <= (2.0**-16 if split else 2.0**-8) * np.abs(got[:rows])).all()
+    assert np.isnan(got[rows:]).all() and np.isnan(operand[rows:]).all()
