@@ -22,7 +22,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_MFMA_TFLOPS = 2500.0     # MI355X dense bf16 matrix-core peak
 PEAK_FP8_MFMA_TFLOPS = 5000.0      # ... and dense FP8
-PEAK_FP32_VALU_TFLOPS = 157.3
+PEAK_FP32_TFLOPS = 157.3           # float32, matrix cores and vector units alike
 
 
 def layer_kinds(spec):
@@ -486,14 +486,15 @@ def main():
     n_full, n_first = layer_kinds(spec)
     assert n_full + n_first == n_layers
     bf16 = spec.precision == "bf16"
-    peak = PEAK_BF16_MFMA_TFLOPS if bf16 else PEAK_FP32_VALU_TFLOPS
+    peak = PEAK_BF16_MFMA_TFLOPS if bf16 else PEAK_FP32_TFLOPS
     flops, main_flops, gemm_ms, gemm_ms_raw, gemm_launches = gemm_summary(spec, B, rows, prof, dur, kernels, args.steps, peak)
     gemm_tflops = main_flops / (gemm_ms * 1e-3) / 1e12
-    kname = ("gemm_tiled_kernel" if rows * sv.R > 256 else "gemm_tiled_rows_kernel") if bf16 else "gemm_f32_kernel"
+    kname = ("gemm_tiled_kernel" if rows * sv.R > 256 else "gemm_tiled_rows_kernel") if bf16 else \
+        ("gemm_f32_mfma_kernel" if rows * sv.R > 32 else "gemm_f32_rows_kernel")
     traffic = stored_traffic(spec.name, sv.R) if (bf16 and B == spec.batch and rows * sv.R > 256) else None
     measured_peak = mt.mfma_peak() if bf16 else None
     # per LAUNCH: a launch serves the rows of all request batches of its call
-    roofline = {"kernel": kname, "bound": "mfma" if bf16 else "alu",
+    roofline = {"kernel": kname, "bound": "mfma",
                 "achieved": gemm_tflops, "peak": peak, "unit": "TFLOP/s", "frac": gemm_tflops / peak, "traffic": traffic,
                 "traffic_source": "stored rocprofv3 counter summary under profiles/ (null: none for this kernel source)",
                 "peak_measured_mfma_only": measured_peak,

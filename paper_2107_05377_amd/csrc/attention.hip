@@ -64,8 +64,6 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     const int l32 = lane & 31, half = lane >> 5;
     const size_t ld = (size_t)3 * H;
     const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (size_t)row0 * ld;
-    // element of row `row` of this sequence, column `col`
-    auto at = [&](int row, int col) { return (size_t)row * ld + col; };
     const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * S : nullptr;
     const int nblk = Sk / 32;
 
@@ -76,7 +74,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     bf16x8 qf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-        qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + at(qc, a * 64 + kk * 16 + half * 8));
+        qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qc * ld + a * 64 + kk * 16 + half * 8);
 
     // ---- stage K (rows = keys, 8 chunks of 8 elements) and V transposed (item = a pair of adjacent keys x one
     //      8-wide chunk of d).  All of a thread's global loads of a batch are issued before the first LDS write,
@@ -85,39 +83,41 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     for (int kb = 0; kb < Sk; kb += 128) {
         uint4 kv[KU], v0[VU], v1[VU];
         int m0[VU], m1[VU];
-        auto key_of = [&](int u) { return kb + ((u * 256 + tid) >> 3); };
-        auto kch_of = [&](int u) { return (u * 256 + tid) & 7; };
-        auto pair_of = [&](int u) { return kb / 2 + ((u * 256 + tid) >> 3); };
-        auto vch_of = [&](int u) { return (u * 256 + tid) & 7; };
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            const int key = key_of(u), ch = kch_of(u);
+            const int c = kb * 8 + u * 256 + tid;
+            const int key = c >> 3, ch = c & 7;
             kv[u] = make_uint4(0, 0, 0, 0);
-            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(qkv + at(key, H + a * 64 + ch * 8));
+            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)key * ld + H + a * 64 + ch * 8);
         }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
-            const int ch = vch_of(u), k0 = pair_of(u) * 2, k1 = k0 + 1;
+            const int c = kb * 4 + u * 256 + tid;
+            const int pair = c >> 3, ch = c & 7;
+            const int k0 = pair * 2, k1 = k0 + 1;
             v0[u] = make_uint4(0, 0, 0, 0);
             v1[u] = make_uint4(0, 0, 0, 0);
             m0[u] = 1;
             m1[u] = 1;
             if (k0 < n_tok) {
-                v0[u] = *reinterpret_cast<const uint4*>(qkv + at(k0, 2 * H + a * 64 + ch * 8));
+                v0[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k0 * ld + 2 * H + a * 64 + ch * 8);
                 if (mrow) m0[u] = mrow[k0];
             }
             if (k1 < n_tok) {
-                v1[u] = *reinterpret_cast<const uint4*>(qkv + at(k1, 2 * H + a * 64 + ch * 8));
+                v1[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k1 * ld + 2 * H + a * 64 + ch * 8);
                 if (mrow) m1[u] = mrow[k1];
             }
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            if (key_of(u) < Sk) *reinterpret_cast<uint4*>(Ks + k_chunk_off(key_of(u), kch_of(u))) = kv[u];
+            const int c = kb * 8 + u * 256 + tid;
+            if ((c >> 3) < Sk) *reinterpret_cast<uint4*>(Ks + k_chunk_off(c >> 3, c & 7)) = kv[u];
         }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
-            const int ch = vch_of(u), k0 = pair_of(u) * 2;
+            const int c = kb * 4 + u * 256 + tid;
+            const int pair = c >> 3, ch = c & 7;
+            const int k0 = pair * 2;
             if (k0 >= Sk) continue;
             if (m0[u] == 0) v0[u] = make_uint4(0, 0, 0, 0);       // a masked key's value row must not leak
             if (m1[u] == 0) v1[u] = make_uint4(0, 0, 0, 0);
@@ -627,7 +627,7 @@ hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask,
                       (size_t)(kAttnBf16MaxSeq + 32) * 260 + 512 > 160 * 1024,
                   "kAttnBf16MaxSeq is the largest multiple of 32 whose keys and values fit the LDS");
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static std::atomic<uint64_t> lds_raised;
+    static std::atomic<uint64_t> lds_raised{0};
     if (lds > 64 * 1024) {
         hipError_t e = ensure_dynamic_lds((const void*)attention_bf16_kernel, 160 * 1024, lds_raised);
         if (e != hipSuccess) return e;

@@ -306,18 +306,6 @@ hipError_t f_launch_one(const GemmGroup& g, const GemmShape& s, int n_wg, hipStr
     return hipGetLastError();
 }
 
-int f_cu_count()
-{
-    static std::atomic<int> cached[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cached[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
-    cached[dev].store(v, std::memory_order_relaxed);
-    return v;
-}
-
 }  // namespace
 
 hipError_t launch_gemm_fp8(const GemmGroup& g, const GemmShape& s, hipStream_t stream)
@@ -334,7 +322,7 @@ hipError_t launch_gemm_fp8(const GemmGroup& g, const GemmShape& s, hipStream_t s
     // (output and residual are addressed through 32-bit buffer offsets with 0x80000000 as the "nowhere" offset)
     if ((uint64_t)s.M * (uint64_t)s.ldc * 4 >= (1ull << 31) || (uint64_t)s.M * (uint64_t)s.ldr * 4 >= (1ull << 31)) return hipErrorInvalidValue;
     const long tiles = (long)s.G * ((s.M + F_BM - 1) / F_BM) * ((s.N + F_BN - 1) / F_BN);
-    const int n_wg = (int)std::min<long>(tiles, f_cu_count());
+    const int n_wg = (int)std::min<long>(tiles, device_cu_count());
     const bool gelu = s.act == ACT_GELU_ERF || s.act == ACT_GELU_TANH;
     if (s.act != ACT_NONE && !gelu) return hipErrorInvalidValue;
     switch (s.out_f32) {
