@@ -617,6 +617,24 @@ int choose_form(const TiledShape& s)
 
 }  // namespace
 
+int tiled_splits(int M, int N, int K, int most)
+{
+    if (K < 2048) return 1;
+    const long pm = (M + 31) / 32, blocks = pm * (N / 32);
+    int sp = 1;
+    while (sp < most && blocks * sp < 192 && K % (128 * sp) == 0) sp *= 2;
+    // One round of K2 tiles leaves a serial K loop on compute units that are not all busy: two ranges of K, where the launch takes that form
+    // with two, too, and fewer than 7/8 of the compute units had a tile.  Passes without and with: BERT-base widths 20 x 128 tokens 1147 and
+    // 1132 us, 32 x 128 1303 and 1294, 36 x 128 1360 and 1351, 9 x 509 1366 and 1353; BERT-large's 11 x 200 2462 and 2355, 15 x 200 2683 and
+    // 2615, 16 x 200 level (-1 to +1 %).  Beyond the line there is nothing to fill, and the few-row form, below it, loses (15 x 128: 905 and 923).
+    if (sp == 1 && most >= 4 && K % 128 == 0) {
+        const long tiles = (pm + 3) / 4 * ((N + 127) / 128);
+        TiledShape two{1, M, N, K, K, K, N, ACT_NONE, 1, nullptr, 2, 0};
+        if (8 * tiles < 7 * device_cu_count() && choose_form(two) == TILED_K2) sp = 2;
+    }
+    return sp;
+}
+
 hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream_t stream, int form, int force)
 {
     if (s.G <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;

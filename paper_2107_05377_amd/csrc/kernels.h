@@ -99,6 +99,10 @@ struct TiledShape {
 };
 // The kernel forms (gemm_tiled.hip); TILED_AUTO chooses by shape.
 enum TiledForm : int { TILED_AUTO = 0, TILED_ROWS_1X1, TILED_ROWS_2X1, TILED_ROWS_2X2, TILED_K2, TILED_PAIR, TILED_TALL };
+// K ranges (1, 2 or 4, at most `most`) of one contraction with a float32 result: a long K over few output blocks (a row bound of up to 128 at 768
+// columns) leaves most of the chip idle otherwise; 36 rows x 768 x 3072: 10 us whole, 4.4 us in 4 ranges that the LayerNorm adds up.  The number
+// of problems that are there does not enter: a task's result must not depend on which others are enabled.
+int tiled_splits(int M, int N, int K, int most);
 hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream_t stream, int form = TILED_AUTO, int force_height = 0);
 // compute units of the current device (cached per device)
 int device_cu_count();

@@ -257,7 +257,7 @@ ClsScratch layout_cls_tiled(Bump& b, size_t B, size_t MB, size_t H, size_t F, si
     c.xbar = b.take(heads * MB * H * 2);
     const size_t end_sums = b.off;
     b.off = c.xbar;
-    c.y = b.take(2 * MB * H * 4);          // (tiled_splits: at most two K ranges)
+    c.y = b.take(2 * MB * H * 4);          // (the second feed-forward contraction in at most two K ranges)
     c.x1f = b.take(MB * H * 4);
     c.x1a = b.take(MB * H * 2);
     c.u = b.take(MB * F * 2);
@@ -915,24 +915,6 @@ TiledGroup tiled_group(const mt_model* m)
     return g;
 }
 
-// K ranges of a contraction with a float32 result: a long K over few output blocks (a row bound of up to 128 at 768 columns) leaves
-// most of the chip idle otherwise; 36 rows x 768 x 3072: 10 us whole, 4.4 us in 4 ranges that the LayerNorm adds up.  The number of
-// problems that are there does not enter: a task's result must not depend on which others are enabled.
-int tiled_splits(int M, int N, int K, int most)
-{
-    if (K < 2048) return 1;
-    const long blocks = (long)((M + 31) / 32) * (N / 32);
-    int sp = 1;
-    while (sp < most && blocks * sp < 192 && K % (128 * sp) == 0) sp *= 2;
-    // One round of K2 tiles (gemm_tiled.hip) leaves a serial K loop on compute units that are not all busy: two ranges of K, where the
-    // launch then takes that form (choose_form: more than 3072 blocks, or 64 row panels) and fewer than 7/8 of 256 compute units had a
-    // tile.  A pass over 32 x 128 tokens at BERT-base widths 1265 -> 1248 us, 7 x 509 1312 -> 1293, 16 x 200 at BERT-large's 2680 -> 2617;
-    // 64 x 128, beyond the line, is the same either way, and the few-row form, below it, loses (15 x 128: 905 -> 923).
-    const long panels = (M + 31) / 32, tiles = (panels + 3) / 4 * ((N + 127) / 128);
-    if (sp == 1 && most >= 4 && K % 256 == 0 && tiles < 224 && 2 * blocks > 1152 && (panels >= 64 || 2 * blocks > 3072)) sp = 2;
-    return sp;
-}
-
 void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const RowMap& rm, int B, int S)
 {
     mt_model* m = L.m;
@@ -1076,14 +1058,13 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     s.sub_b = 1;
     L.tiled(MT_K_GEMM_FIRST, g, s);
 
-    const int sp_o = tiled_splits(B, H, H, 2);
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].cls->ctx);
         g.w[i] = units(io[i].w->Wo);
         g.b[i] = units(io[i].w->bo);
         g.c[i] = units(io[i].cls->y);
     }
-    L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, H, H, H, H, ACT_NONE, 1, nullptr, sp_o, part});
+    L.tiled(MT_K_GEMM_FIRST, g, TiledShape{n, B, H, H, H, H, H, ACT_NONE, 1, nullptr, 1, 0});
 
     TiledLnGroup lg;
     lg.ws = ws;
@@ -1096,7 +1077,7 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
         lg.gamma[i] = units(io[i].w->ln1g);
         lg.beta[i] = units(io[i].w->ln1b);
     }
-    TiledLnShape ls{n, B, H, nullptr, m->cfg.ln_eps, sp_o, part, rm.seq_start, M, 0};
+    TiledLnShape ls{n, B, H, nullptr, m->cfg.ln_eps, 1, part, rm.seq_start, M, 0};
     L.begin(MT_K_LN);
     L.check(launch_layernorm_tiled(lg, ls, L.st));
     L.end();
