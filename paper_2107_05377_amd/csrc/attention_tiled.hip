@@ -244,11 +244,12 @@ hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t*
     // Two wavefronts per query panel where one each would leave SIMDs idle over a long loop (7 sequences of up to 509 tokens, 12 heads:
     // 10.1 us, 12.0 with one, 10.6 with four).  Else a wavefront per panel that a sequence can touch, 3 or 4 to a workgroup (an idle
     // wavefront holds registers: 9 panels by 2 x 5 took 62 us, by 3 x 3 43); the fifth panel of a sequence of up to 128 tokens has
-    // one of its own only in a launch that does not fill the chip (384 workgroups: 8.6 us, 10.3 without; 3072: 34.6, 30 without).
+    // one of its own up to 2048 (sequence, head) pairs, where launches of 16 to 128 tokens cross: 384 pairs 8.9 us, 10.6 without; 1536 17.6
+    // and 18.6; 2052 21.1 and 21.2; 3072 36.6 and 33.8.  (100 to 128 tokens cross at 1500: 1152 19.0 and 19.9, 1536 28.3 and 27.1.)
     const int panels = (S + 31) / 32 + 1, groups = A * B * G;
     const int ks = panels > 8 && (long)groups * panels <= 2048 ? 2 : 1;
     int nq = panels <= 5 ? 1 : (panels + 3) / 4, nw = (panels + nq - 1) / nq;
-    if (panels == 5 && groups >= 1024) nw = 4;
+    if (panels == 5 && groups >= 2048) nw = 4;
     if (ks == 2) {
         nw = 4;
         nq = panels / 2;
