@@ -65,8 +65,9 @@ def test_attention_f32_infinite_value_of_the_last_key(S, H):
     assert (ctx[..., 5] == np.inf).all() and np.abs(ctx[..., rest] - ref[..., rest]).max() <= 2e-5
 
 
-# bfloat16 kernels of the panel layout through a whole model: ragged rows, both contractions' halves that a launch rule can choose.
-# Bound on the logits: bfloat16 operands (2^-9 each) through three layers give at most 2e-2 at logits of order 1.
+# The panel layout through a whole model: ragged rows and the launch shapes that a rule on sizes chooses, put together (the kernels one by one:
+# below).  Weights grow as the model gets narrower, so that a layer's output is of the size of its input at every width.
+# Bound on the logits: bfloat16 operands (2^-8 each) through three layers give at most 2e-2 at logits of order 1.
 @pytest.mark.parametrize("heads,ffn,batch,seq,lo", [
     (1, 64, 1, 1, 1),            # one row; K below one tile's ring
     (16, 192, 33, 65, 1),        # 16 heads; one sequence over a panel of first tokens; sequences that end one row into a key panel
@@ -81,14 +82,14 @@ def test_panel_layout_forms(heads, ffn, batch, seq, lo):
     spec = ms.MTSpec("panels", vocab=300, hidden=64 * heads, heads=heads, ffn=ffn, max_pos=seq + 1, n_trunk_layers=1,
                      tasks=(ms.TaskSpec(1, 2, 3), ms.TaskSpec(0, 1, 2), ms.TaskSpec(1, 0, 2)), precision="bf16", batch=batch, seq=seq,
                      len_lo=lo, len_hi=seq, input_seed=heads + seq)
-    model, (trunk, tasks) = mt.load_synthetic(spec, keep_params=True, std=0.03)
+    model, (trunk, tasks) = mt.load_synthetic(spec, keep_params=True, std=0.03 * max(1.0, (768 / spec.hidden)**0.5))
     ids, mask, _ = ms.make_inputs(spec)
     got = model.forward(dev(ids), dev(mask)).cpu().numpy()
     pick = np.unique(np.linspace(0, batch - 1, 7).astype(int))
     ref = oracle.Oracle(spec, trunk, tasks).mt_forward(ids[pick], mask[pick])
     err = np.abs(got[pick] - ref).max()
     print(f"  max |dlogit| {err:.3g}, logits up to {np.abs(ref).max():.3g}", flush=True)
-    assert np.isfinite(got).all() and err <= 2e-2
+    assert np.isfinite(got).all() and err <= 2e-2 * max(1.0, np.abs(ref).max())
     model.close()
 
 
