@@ -591,8 +591,11 @@ hipError_t launch_form(const TiledGroup& g, const TiledShape& s, int form, int f
 // about half of that in a padded batch).  Measured at BERT-base widths, 36 to 18.6 k rows, 1 and 8 problems:
 //   up to 1152 blocks (72 x 2 for 36 rows x 2304 columns): one block per workgroup; a launch is a chain of latencies there and
 //     more, smaller workgroups shorten it (36 rows: QKV 4.3 us, 2x1 4.4, 2x2 5.9, tiles 7.5);
-//   up to 3072: two row panels per workgroup (600 rows x 2304: 8.1 us, 1x1 8.5, K2 9.1), unless there are few column panels and
-//     enough rows for the K2 tiles (2318 rows x 768 x 768: 9.1 us);
+//   up to 3072: two row panels per workgroup (600 rows x 2304: 8.1 us, 1x1 8.5, K2 9.1).  For up to 1024 columns K2 takes over sooner: from 2048
+//     blocks on (8 problems of 288 rows x 768 x 768, 3072 blocks: K2 10.8 us, 2x1 14.3; 1920 blocks 10.3 both; with all rows of the bound
+//     present 13.1 and 15.2, 11.0 and 10.9), and where K is long at once for several problems (8 x 192 rows x 768 x 3072: 19.0 us, 24.2;
+//     3 x 288 rows 15.9 and 17.1; 8 x 288 rows 21.6 and 41.7) or 64 row panels of one (passes over 13 x 128 tokens, 52 panels, with K2 890 us,
+//     without 851; BERT-large 6 x 200, 38 panels, 1930 and 1839);
 //   beyond: tiles.  Narrow outputs of fewer tiles than fill the chip twice take K2, which halves a workgroup's serial K loop (2318
 //     rows x 768 x 3072: 21.5 us, PAIR 31); long K with many tiles takes TALL (18.6 k rows x 768 x 3072: 75.5 us, PAIR 78), everything
 //     else PAIR, whose two workgroups per compute unit hide each other's epilogues (GELU: 84 us, TALL 100).
@@ -608,7 +611,8 @@ int choose_form(const TiledShape& s)
     if (s.n_sub > 1 || s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
     if (!tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
-    if (plan_blocks <= 1152 || (plan_blocks <= 3072 && !(k2_ok && pm >= 64 && pn <= 32))) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
+    const long most_rows = !k2_ok || pn > 32 ? 3072 : s.K < 2048 ? 2047 : plan > 1 || pm >= 64 ? 1152 : 3072;
+    if (plan_blocks <= most_rows) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const long tiles4 = (long)((pm + 3) / 4) * ((pn + 7) / 8) * s.splits;           // 128 x 256, of a problem
     if (k2_ok && tiles4 * plan <= 256) return TILED_K2;
     if (s.K >= 2048 && s.act == ACT_NONE && slices % 2 == 0 && tiles4 * s.G >= 512) return TILED_TALL;
@@ -626,7 +630,8 @@ int tiled_splits(int M, int N, int K, int most)
     // One round of K2 tiles leaves a serial K loop on compute units that are not all busy: two ranges of K, where the launch takes that form
     // with two, too, and fewer than 7/8 of the compute units had a tile.  Passes without and with: BERT-base widths 20 x 128 tokens 1147 and
     // 1132 us, 32 x 128 1303 and 1294, 36 x 128 1360 and 1351, 9 x 509 1366 and 1353; BERT-large's 11 x 200 2462 and 2355, 15 x 200 2683 and
-    // 2615, 16 x 200 level (-1 to +1 %).  Beyond the line there is nothing to fill, and the few-row form, below it, loses (15 x 128: 905 and 923).
+    // 2615, 16 x 200 level (-1 to +1 %).  Of fewer rows the LayerNorm's second operand costs more than it saves (13 x 128: 861 and 882; 8 x 128:
+    // 734 and 748; BERT-large 6 x 200: 1842 and 1858).
     if (sp == 1 && most >= 4 && K % 128 == 0) {
         const long tiles = (pm + 3) / 4 * ((N + 127) / 128);
         TiledShape two{1, M, N, K, K, K, N, ACT_NONE, 1, nullptr, 2, 0};

@@ -220,6 +220,7 @@ ROWS_1X1, ROWS_2X1, ROWS_2X2, K2, PAIR, TALL = 1, 2, 3, 4, 5, 6
     (PAIR, 4, 1, 130, 130, 288, 1536, 0, 1, 4), (PAIR, 1, 10, 1024, 1001, 512, 320, 1, 0, 1),
     (TALL, 5, 1, 170, 161, 288, 384, 0, 1, 1), (TALL, 6, 2, 390, 353, 96, 512, 0, 0, 1), (TALL, 7, 1, 230, 225, 288, 384, 0, 1, 1), (TALL, 8, 1, 300, 257, 544, 640, 0, 0, 1),
     (TALL, 5, 8, 1312, 1300, 1024, 384, 0, 1, 1),
+    (0, 0, 3, 512, 290, 768, 3072, 0, 1, 1), (0, 0, 3, 384, 290, 768, 3072, 0, 1, 1), (0, 0, 2, 1376, 700, 768, 768, 0, 1, 1), (0, 0, 1, 2016, 1100, 768, 3072, 0, 1, 1),
     (0, 0, 1, 300, 171, 768, 768, 0, 0, 1), (0, 0, 8, 300, 171, 768, 768, 0, 1, 1), (0, 0, 1, 2080, 1900, 2304, 768, 1, 0, 1),
 ])
 def test_panel_linear_forms(form, height, problems, M, rows, N, K, act, f32, splits):
