@@ -323,9 +323,9 @@ int mt_profile_read(mt_model* m, float* h_ms /*[MT_K_COUNT]*/, int32_t* h_launch
 
 /*
  * Single operations on device buffers, exposed so that each of mt_forward's kernels can be checked on its own.  All enqueue on
- * hip_stream and return.  mt_op_panel_* run the kernels of MT_BF16 with up to 16 heads (panel layout, below).  The others run the
- * row-major kernels: with float32 those of MT_FP32_CHECK, with bfloat16 those of the FP8 precisions and of MT_BF16 with more than
- * 16 heads.  `precision` selects the element type of activations/weights named "act": MT_BF16 -> bfloat16, MT_FP32_CHECK -> float32.
+ * hip_stream and return.  mt_op_panel_* run the kernels of MT_BF16 with up to 16 heads and of MT_FP8_LAYER where hidden and ffn are
+ * multiples of 256 besides (panel layout, below).  The others run the row-major kernels: with float32 those of MT_FP32_CHECK, with
+ * bfloat16 those of all other models.  `precision` selects the element type of activations/weights named "act": MT_BF16 -> bfloat16, MT_FP32_CHECK -> float32.
  */
 /* C[M,N] = epilogue(A[M,K] W[N,K]^T + bias[N]) ; act_kind: 0 none, 1 GELU(erf), 2 GELU(tanh), 3 tanh.
  * d_residual (float32 [M,N]) may be NULL; if given it is added after the activation (bf16 precision:
@@ -398,6 +398,12 @@ typedef struct mt_panel_linear {
     int32_t problems, subs, M, N, K, lda, ldw, ldc, act_kind, out_f32, splits, transposed_from, form, height;
 } mt_panel_linear;
 int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream);
+/* The same on E4M3 operands (MT_FP8_LAYER with hidden and ffn multiples of 256): d_A and d_W one byte per element in panels whose chunks
+ * hold 16 columns (a 32 x 16 block is 512 bytes, row after row) and of every four chunks the middle two in each other's place; K, lda, ldw in elements,
+ * a multiple of 128; subs and splits 1; forms 1 and 5 (heights 1, 2, 4).  256 bytes in front of every
+ * problem's W stands what its values are multiplied by: an int32 that repeats the E8M0 exponent (127 + e for 2^e) in each byte.  out_f32: 0 bfloat16,
+ * 1 float32, 2 E4M3 (saturating, with a GELU). */
+int mt_op_panel_linear_fp8(const mt_panel_linear* op, void* hip_stream);
 /* ctx = softmax(q k^T / 8) v per head over the rows d_seq_start[b] .. + min(d_seq_len[b], seq) - 1 of a sequence; d_qkv [rows][3 hidden] bf16 panels,
  * the values as transposed_from = 2 hidden leaves them, d_ctx [rows][hidden] bf16 panels.  Rows of no sequence may hold anything and are not written. */
 int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq,

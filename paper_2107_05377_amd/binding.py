@@ -26,7 +26,7 @@ KERNEL_CLASSES = ["embed", "gemm_qkv", "attn", "gemm_out", "ln", "gemm_ffn1", "g
 EXPORTS = ["mt_create", "mt_destroy", "mt_weight_bytes", "mt_workspace_bytes", "mt_bind", "mt_load_weights",
            "mt_forward", "mt_logit_offset", "mt_n_logits", "mt_layer_count", "mt_last_error", "mt_error_name",
            "mt_read_hidden", "mt_profile_enable", "mt_profile_read", "mt_op_linear", "mt_op_attention",
-           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_linear", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
+           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_linear", "mt_op_panel_linear_fp8", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
            "mt_forward_tokens", "mt_token_logit_offset", "mt_n_token_logits", "mt_forward_static", "mt_forward_multi", "mt_forward_requests", "mt_forward_routed_tokens", "mt_op_linear_fp8", "mt_debug_e4m3_quantize", "mt_check_mask"]
 MT_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
@@ -107,6 +107,7 @@ def lib():
         L.mt_op_panel_first_query.argtypes = [vp, vp, vp, vp, vp, i32, i32, vp]
         L.mt_op_panel_first_attend.argtypes = [vp, vp, vp, i64, vp, vp, i32, i32, i32, vp]
         L.mt_op_panel_linear.argtypes = [C.POINTER(mt_panel_linear), vp]
+        L.mt_op_panel_linear_fp8.argtypes = [C.POINTER(mt_panel_linear), vp]
         L.mt_op_panel_attention.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
         L.mt_op_panel_layernorm.argtypes = [vp, i32, i64, vp, vp, i32, vp, vp, C.c_float, vp, vp, i32, vp, i32, i32, vp]
         L.mt_op_linear_sub.argtypes = [vp, i64, vp, i64, vp, vp, i64, i32, i32, i32, i32, i64, i64, i64, i64, vp, vp, i32, vp]
@@ -382,6 +383,22 @@ def from_panels(p):
     return p.transpose(1, 2).reshape(p.shape[0] * 32, p.shape[1] * 8)
 
 
+def to_panels_e4m3(x):
+    """The E4M3 panel layout (include/mt.h) of a CUDA float8_e4m3fn tensor [rows][width]: [panels][width / 16][32][16] bytes, rows padded with NaN."""
+    import torch
+    rows, width = x.shape
+    full = torch.full(((rows + 31) // 32 * 32, width), 0x7F, dtype=torch.uint8, device=x.device)
+    full[:rows] = x.view(torch.uint8)
+    return full.view(-1, 32, width // 64, 4, 16)[:, :, :, [0, 2, 1, 3]].reshape(-1, 32, width // 16, 16).transpose(1, 2).contiguous()
+
+
+def from_panels_e4m3(p):
+    """[rows, whole panels][width] float8_e4m3fn of a byte tensor in the E4M3 panel layout."""
+    import torch
+    rows, width = p.shape[0] * 32, p.shape[1] * 16
+    return p.transpose(1, 2).reshape(rows, width // 64, 4, 16)[:, :, [0, 2, 1, 3]].reshape(rows, width).contiguous().view(torch.float8_e4m3fn)
+
+
 def _panels(rows, width, dtype, device):
     import torch
     return torch.full(((rows + 31) // 32, width // 8, 32, 8), float("nan"), dtype=dtype, device=device)
@@ -408,12 +425,13 @@ def op_panel_first_attend(x, qt, seq_start, seq_len, batch, seq, heads):
     return torch.stack([from_panels(xbar[a])[:batch] for a in range(heads)], dim=1)
 
 
-def op_panel_linear(A, W, bias, C_out, *, M, N, K, rows=None, **fields):
-    """mt_op_panel_linear on device tensors in the panel layout; `fields` are the struct's (lda, ldw, ldc default to K, K, N)."""
+def op_panel_linear(A, W, bias, C_out, *, M, N, K, rows=None, fp8=False, **fields):
+    """mt_op_panel_linear (fp8: mt_op_panel_linear_fp8) on device tensors in the panel layout; `fields` are the struct's (lda, ldw, ldc default to
+    K, K, N)."""
     op = mt_panel_linear(d_A=A.data_ptr(), d_W=W.data_ptr(), d_bias=None if bias is None else bias.data_ptr(), d_C=C_out.data_ptr(),
                          d_rows=None if rows is None else rows.data_ptr(), M=M, N=N, K=K,
                          **{"problems": 1, "subs": 1, "lda": K, "ldw": K, "ldc": N, "splits": 1, **fields})
-    rc = lib().mt_op_panel_linear(C.byref(op), _stream())
+    rc = (lib().mt_op_panel_linear_fp8 if fp8 else lib().mt_op_panel_linear)(C.byref(op), _stream())
     if rc != MT_OK:
         raise MTError(rc, "mt_op_panel_linear")
     return C_out

@@ -43,6 +43,10 @@ __device__ inline int k_chunk_off(int row, int chunk) { return row * 128 + ((chu
 #define MT_ATTN_CB 2
 #endif
 constexpr int CB = MT_ATTN_CB;        // 32-key blocks per online-softmax chunk
+// PANELS: projections and context in the panel layout.  The staging loads of a wavefront are then 8 keys of 8 chunks, 128 contiguous bytes each.
+// (attention_tiled_kernel, which needs no staging, rounds its softmax weights to other bfloat16 values; E4M3 contexts amplify that to 5 % of the logits,
+// so the FP8 modes keep this kernel's arithmetic.)
+template <bool PANELS>
 __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnGroup g, const int32_t* __restrict__ mask,
                                                              const int32_t* __restrict__ seq_start,
                                                              const int32_t* __restrict__ seq_len, int B, int S, int H, int Sk_max,
@@ -63,7 +67,9 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const size_t ld = (size_t)3 * H;
-    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]) + (size_t)row0 * ld;
+    const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]);
+    // 8 columns (from a multiple of 8 on) of a row of the sequence
+    auto chunk_at = [&](int row, int col) { return qkv + (PANELS ? tiled_offset(row0 + row, col, ld) : (size_t)(row0 + row) * ld + col); };
     const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * S : nullptr;
     const int nblk = Sk / 32;
 
@@ -74,7 +80,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     bf16x8 qf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-        qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qc * ld + a * 64 + kk * 16 + half * 8);
+        qf[kk] = *reinterpret_cast<const bf16x8*>(chunk_at(qc, a * 64 + kk * 16 + half * 8));
 
     // ---- stage K (rows = keys, 8 chunks of 8 elements) and V transposed (item = a pair of adjacent keys x one
     //      8-wide chunk of d).  All of a thread's global loads of a batch are issued before the first LDS write,
@@ -88,7 +94,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
             const int c = kb * 8 + u * 256 + tid;
             const int key = c >> 3, ch = c & 7;
             kv[u] = make_uint4(0, 0, 0, 0);
-            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)key * ld + H + a * 64 + ch * 8);
+            if (key < n_tok) kv[u] = *reinterpret_cast<const uint4*>(chunk_at(key, H + a * 64 + ch * 8));
         }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
@@ -100,11 +106,11 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
             m0[u] = 1;
             m1[u] = 1;
             if (k0 < n_tok) {
-                v0[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k0 * ld + 2 * H + a * 64 + ch * 8);
+                v0[u] = *reinterpret_cast<const uint4*>(chunk_at(k0, 2 * H + a * 64 + ch * 8));
                 if (mrow) m0[u] = mrow[k0];
             }
             if (k1 < n_tok) {
-                v1[u] = *reinterpret_cast<const uint4*>(qkv + (size_t)k1 * ld + 2 * H + a * 64 + ch * 8);
+                v1[u] = *reinterpret_cast<const uint4*>(chunk_at(k1, 2 * H + a * 64 + ch * 8));
                 if (mrow) m1[u] = mrow[k1];
             }
         }
@@ -234,23 +240,25 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
 
     if (q < n_tok && ctx_fmt == 1) {             // E4M3 at unit scale: one byte per element
         const float inv = 1.0f / l_run;
-        unsigned char* out = static_cast<unsigned char*>(g.ctx[grp]) + ((size_t)row0 + q) * H + a * 64;
+        unsigned char* out = static_cast<unsigned char*>(g.ctx[grp]);
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq)
-                *reinterpret_cast<uint32_t*>(out + dt * 32 + qq * 8 + half * 4) =
+                *reinterpret_cast<uint32_t*>(out + (PANELS ? tiled_offset_e4m3(row0 + q, a * 64 + dt * 32 + qq * 8 + half * 4, H)
+                                                           : ((size_t)row0 + q) * H + a * 64 + dt * 32 + qq * 8 + half * 4)) =
                     pack_e4m3(o[dt][qq * 4 + 0] * inv, o[dt][qq * 4 + 1] * inv, o[dt][qq * 4 + 2] * inv, o[dt][qq * 4 + 3] * inv);
     } else if (q < n_tok) {
         const float inv = 1.0f / l_run;
-        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + ((size_t)row0 + q) * H + a * 64;
+        __bf16* out = static_cast<__bf16*>(g.ctx[grp]);
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq) {
                 bf16x4 v = {(__bf16)(o[dt][qq * 4 + 0] * inv), (__bf16)(o[dt][qq * 4 + 1] * inv),
                             (__bf16)(o[dt][qq * 4 + 2] * inv), (__bf16)(o[dt][qq * 4 + 3] * inv)};
-                *reinterpret_cast<bf16x4*>(out + dt * 32 + qq * 8 + half * 4) = v;
+                *reinterpret_cast<bf16x4*>(out + (PANELS ? tiled_offset(row0 + q, a * 64 + dt * 32 + qq * 8 + half * 4, H)
+                                                         : ((size_t)row0 + q) * H + a * 64 + dt * 32 + qq * 8 + half * 4)) = v;
             }
     }
 }
@@ -614,7 +622,7 @@ hipError_t launch_attention_cls(const AttnClsGroup& g, int G, int is_bf16, const
 }
 
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt)
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt, bool panels)
 {
     if (!mask && !(seq_start && seq_len)) return hipErrorInvalidValue;
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
@@ -627,14 +635,15 @@ hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask,
                       (size_t)(kAttnBf16MaxSeq + 32) * 260 + 512 > 160 * 1024,
                   "kAttnBf16MaxSeq is the largest multiple of 32 whose keys and values fit the LDS");
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static std::atomic<uint64_t> lds_raised{0};
+    auto kfn = panels ? attention_bf16_kernel<true> : attention_bf16_kernel<false>;
+    static std::atomic<uint64_t> lds_raised[2];
     if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)attention_bf16_kernel, 160 * 1024, lds_raised);
+        hipError_t e = ensure_dynamic_lds((const void*)kfn, 160 * 1024, lds_raised[panels]);
         if (e != hipSuccess) return e;
     }
     dim3 grid((S + 127) / 128, A, B * G), block(256);
     const float scale_log2e = (1.0f / sqrtf(64.0f)) * kLog2e;
-    hipLaunchKernelGGL(attention_bf16_kernel, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
+    hipLaunchKernelGGL(kfn, grid, block, lds, stream, g, mask, seq_start, seq_len, B, S, H, Sk, scale_log2e, ctx_fmt);
     return hipGetLastError();
 }
 

@@ -16,6 +16,11 @@
 // load path (32 bytes per clock at TMI = 8, 48 at TMI = 4) below their limits; with the weights in LDS as well, LDS was the limit.
 // A workgroup walks a list of tiles without draining: the loads of the next tile start during the last slices of a tile.
 //
+// FP8 operands (F8).  An E4M3 panel has 16 columns of its 32 rows in 512 bytes, as a bf16 panel has 8, so all of the above holds with a pair
+// of E4M3 values in the place of a bf16 value (K, lda and ldw count pairs): the same copies and the same fragments, of which two, 64 K
+// elements, make one v_mfma_scale_f32_32x32x64_f8f6f4 of twice the clocks.  The instruction also undoes the power of two that the weights were
+// stored with.  The sum starts from zero, the bias comes last, as in gemm_fp8.hip: E4M3 roundings of the results amplify any other order.
+//
 // The number of rows is on the device, so the tile height is chosen there (pick_height): the height with the smallest
 // (tiles per compute unit, rounded up) x (height + fixed cost).  18.6 k rows x 2304 columns are 5.1 tiles of 128 rows per compute
 // unit, i.e. 6 rounds, but 6.8 of 96 rows.
@@ -32,6 +37,8 @@ constexpr int kBand = 8;                // row-tiles per raster band
 typedef __attribute__((address_space(3))) void* lptr_t;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 template <int ACT>
 __device__ __forceinline__ float t_act(float v)
@@ -42,17 +49,53 @@ __device__ __forceinline__ float t_act(float v)
     else return v;
 }
 
+// A fragment: 32 rows x 16 bf16 columns (1 KB), or 32 rows x 64 E4M3 columns (two runs of 1 KB).
+template <bool F8> struct TFrag { typedef bf16x8 type; };
+template <> struct TFrag<true> { typedef i32x8 type; };
+// acc += first * second^T.  scale: of the first operand, an E8M0 exponent in every byte; the second one's is 1.
+__device__ __forceinline__ f32x16 t_mfma(const bf16x8& a, const bf16x8& b, const f32x16& c, int) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f32x16 t_mfma(const i32x8& a, const i32x8& b, const f32x16& c, int scale)
+{
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, scale, 0, 0x7F7F7F7F);
+}
+__device__ __forceinline__ i32x8 t_join(const i32x4& lo, const i32x4& hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); }
+// 32 E4M3 columns of a row, 16 each in the lanes of its two halves, from 4 of every 8 per lane (the accumulator's order)
+template <int ACT>
+__device__ __forceinline__ u32x4 t_pack_e4m3(const f32x16& v)
+{
+    uint32_t d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        d[q] = pack_e4m3(t_act<ACT>(v[q * 4]), t_act<ACT>(v[q * 4 + 1]), t_act<ACT>(v[q * 4 + 2]), t_act<ACT>(v[q * 4 + 3]));
+        __builtin_amdgcn_sched_barrier(0);           // (four at a time, for the registers)
+    }
+    const auto a = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+    return u32x4{a[0], a[1], b[0], b[1]};
+}
+// ... and where they are stored (tiled_offset_e4m3)
+__device__ __forceinline__ unsigned char* t_e4m3_at(unsigned char* c, int ldc, int pm, int pn, int lane)
+{
+    return c + (size_t)pm * 32 * ldc + (pn >> 1) * 2048 + (lane >> 5) * 1024 + (pn & 1) * 512 + (lane & 31) * 16;
+}
+// The exponent stands in front of an E4M3 matrix (kScaleSlot).  Read through the scalar cache.
+__device__ __forceinline__ int t_scale(const unsigned char* w)
+{
+    typedef const __attribute__((address_space(4))) int* cptr_t;
+    return *(cptr_t)(reinterpret_cast<uintptr_t>(w) - kScaleSlot);
+}
+
 // Scheduling of one K step: NM matrix instructions, PER fragment reads behind each of the first ones (the rest of the step covers
-// their latency), the step's two weight loads last.
-template <int NM, int NF, int PER>
+// their latency), the step's NV weight loads last.
+template <int NM, int NF, int PER, int NV>
 __device__ __forceinline__ void t_interleave()
 {
     if constexpr (NM > 0) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         if constexpr (NF > 0) __builtin_amdgcn_sched_group_barrier(0x100, NF < PER ? NF : PER, 0);
-        t_interleave<NM - 1, (NF > PER ? NF - PER : 0), PER>();
+        t_interleave<NM - 1, (NF > PER ? NF - PER : 0), PER, NV>();
     } else {
-        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, NV, 0);
     }
 }
 
@@ -63,7 +106,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t t_rsrc(const void* base, uint3
 
 // Ring depth and weight prefetch distance by tile height: as deep as two (KW = 1, TMI <= 4: 80 KB of LDS and 256 registers each)
 // or one workgroup per compute unit allow, and within the 63 loads that a wait can count.
-template <int TMI, int KW>
+template <int TMI, int KW, bool F8>
 struct TCfg {
     static constexpr int WN = 4 / KW;                                   // wavefronts along N
     static constexpr int AL = KW * TMI;                                 // activation loads per wavefront and slice
@@ -73,15 +116,19 @@ struct TCfg {
     static constexpr int XCHG = KW == 2 ? TMI * 4096 * 4 : 0;           // partial sums of the K halves
     static constexpr int LDS = S * STAGE + XCHG;
     // loads younger than the activation slice that must have landed at a slice's barrier, on every path (see below)
-    static constexpr int WAIT = (S - 2) * AL + 8 * (NB < S - 2 ? NB : S - 2) + 6;
+    static constexpr int STEPS = F8 ? 2 : 4;                            // matrix steps of a slice
+    static constexpr int WAIT = (S - 2) * AL + 8 * (NB < S - 2 ? NB : S - 2) + 8 - 8 / STEPS;
+    // activation fragments of two steps, or (where the registers of two workgroups do not hold two) each reloaded behind its last use
+    static constexpr bool IN_PLACE = F8 && KW == 1 && TMI == 4;
     static_assert(WAIT <= 63 && LDS <= 160 * 1024, "ring");
 };
 
-template <int TMI, int KW, bool OUT_F32, int ACT>
+template <int TMI, int KW, int OUT, int ACT, bool F8>
 __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const TiledShape& s, unsigned char* lds, int panels_m)
 {
-    using Cfg = TCfg<TMI, KW>;
-    constexpr int S = Cfg::S, NB = Cfg::NB, WN = Cfg::WN, AL = Cfg::AL, STAGE = Cfg::STAGE, KK = 4;
+    using Cfg = TCfg<TMI, KW, F8>;
+    static_assert(!F8 || KW == 1, "");
+    constexpr int S = Cfg::S, NB = Cfg::NB, WN = Cfg::WN, AL = Cfg::AL, STAGE = Cfg::STAGE, STEPS = Cfg::STEPS, STEP_BYTES = 4096 / STEPS;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave % WN, wk = wave / WN;
     const int panels_n = s.N >> 5;
@@ -100,8 +147,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         // A starts at the tile's first panel (the whole operand may exceed the 31 bits of an offset); a panel beyond the last one lies
         // beyond the buffer's end: reads as zero
         __amdgpu_buffer_rsrc_t A, W;
-        int ao, wo, grp, split, pm0, pn0;
+        int ao, wo, grp, split, pm0, pn0, scale;
     };
+    [[maybe_unused]] float bias_v = 0.f;       // F8: the bias of the wavefront's 64 columns, one per lane
     auto locate = [&](int j, Ref& t) {
         const int tile = lo + wi + j * wg_x;
         const int gs = tile / per_problem, tt = tile - gs * per_problem;
@@ -114,6 +162,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         const int k0 = t.split * KW * KT * 4096;                             // byte offset of the K range inside a panel
         t.A = t_rsrc(static_cast<const unsigned char*>(g.A) + (size_t)g.a[t.grp] * 256 + (size_t)t.pm0 * pa, min(panels_m - t.pm0, TMI) * pa);
         t.W = t_rsrc(static_cast<const unsigned char*>(g.W) + (size_t)g.w[t.grp] * 256, panels_n * pw);
+        t.scale = F8 ? t_scale(static_cast<const unsigned char*>(g.W) + (size_t)g.w[t.grp] * 256) : 0;
         t.ao = k0 + wave * 1024;
         t.wo = t.pn0 * (int)pw + k0 + wk * KT * 4096;
     };
@@ -128,21 +177,42 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
             __builtin_amdgcn_raw_ptr_buffer_load_lds(t.A, (lptr_t)(lds + stage * STAGE + (i * 4 + wave) * 1024), 16, voff,
                                                      t.ao + (i % TMI) * (int)pa + ((i / TMI) * KT + kt) * 4096, 0, 0);
     };
-    bf16x8 wf[NB][KK][2], af[2][TMI];
+    typename TFrag<F8>::type wf[NB][STEPS][2], af[Cfg::IN_PLACE ? 1 : 2][TMI];
     f32x16 acc[TMI][2];
-    auto loadW = [&](const Ref& t, int kt, int buf, int kk) {
+    auto loadW = [&](const Ref& t, int kt, int buf, int step) {
 #pragma unroll
-        for (int jn = 0; jn < 2; ++jn)
-            wf[buf][kk][jn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(t.W, voff + kk * 1024, t.wo + jn * (int)pw + kt * 4096, 0));
+        for (int jn = 0; jn < 2; ++jn) {
+            const auto lo = __builtin_amdgcn_raw_buffer_load_b128(t.W, voff + step * STEP_BYTES, t.wo + jn * (int)pw + kt * 4096, 0);
+            if constexpr (F8) {
+                const auto hi = __builtin_amdgcn_raw_buffer_load_b128(t.W, voff + step * STEP_BYTES + 1024, t.wo + jn * (int)pw + kt * 4096, 0);
+                wf[buf][step][jn] = t_join(__builtin_bit_cast(i32x4, lo), __builtin_bit_cast(i32x4, hi));
+            } else {
+                wf[buf][step][jn] = __builtin_bit_cast(bf16x8, lo);
+            }
+        }
     };
-    auto readA = [&](int buf, int stage, int kk) {
+    auto read1 = [&](int buf, int stage, int step, int i) {
+        const unsigned char* p = lds + stage * STAGE + (wk * TMI + i) * 4096 + step * STEP_BYTES + voff;
+        if constexpr (F8) af[buf][i] = t_join(*reinterpret_cast<const i32x4*>(p), *reinterpret_cast<const i32x4*>(p + 1024));
+        else af[buf][i] = *reinterpret_cast<const bf16x8*>(p);
+    };
+    auto readA = [&](int buf, int stage, int step) {
 #pragma unroll
-        for (int i = 0; i < TMI; ++i)
-            af[buf][i] = *reinterpret_cast<const bf16x8*>(lds + stage * STAGE + ((wk * TMI + i) * 4 + kk) * 1024 + voff);
+        for (int i = 0; i < TMI; ++i) read1(buf, stage, step, i);
     };
-    // accumulators start from the bias (the first K share's do)
+    // accumulators start from the bias (the first K share's do), with E4M3 operands from zero
     auto init_acc = [&](const Ref& t) {
         const uint32_t bo = t.split == 0 ? g.b[t.grp] : kNoBias;
+        if constexpr (F8) {
+            bias_v = bo == kNoBias ? 0.f : g.bias[(size_t)bo * 64 + min(t.pn0 * 32 + lane, s.N - 1)];
+#pragma unroll
+            for (int i = 0; i < TMI; ++i)
+#pragma unroll
+                for (int jn = 0; jn < 2; ++jn)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][jn][e] = 0.f;
+            return;
+        }
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) {
             f32x16 b0;
@@ -166,7 +236,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
     auto store_block = [&](const Ref& t, const f32x16& a, int pm, int pn) {
         if (pm >= panels_m || pn >= panels_n) return;                        // uniform
         unsigned char* Cb = static_cast<unsigned char*>(g.C) + (size_t)g.c[t.grp] * 256;
-        if constexpr (OUT_F32) {
+        if constexpr (OUT == TILED_E4M3) {
+            __builtin_nontemporal_store(t_pack_e4m3<ACT>(a), reinterpret_cast<u32x4*>(t_e4m3_at(Cb, s.ldc, pm, pn, lane)));
+        } else if constexpr (OUT == TILED_F32) {
             float* c = reinterpret_cast<float*>(Cb) + (size_t)t.split * s.split_stride + (size_t)pm * 32 * s.ldc + pn * 1024 + (lane & 31) * 8 + (lane >> 5) * 4;
 #pragma unroll
             for (int q = 0; q < 4; ++q) __builtin_nontemporal_store(f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]}, reinterpret_cast<f32x4*>(c + q * 256));
@@ -186,7 +258,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
                 const auto s0 = __builtin_amdgcn_permlane32_swap(xu[0], yu[0], false, false);
                 const auto s1 = __builtin_amdgcn_permlane32_swap(xu[1], yu[1], false, false);
                 const u32x4 r = u32x4{s0[0], s1[0], s0[1], s1[1]};
-                if constexpr (ACT == ACT_NONE) {
+                if constexpr (ACT == ACT_NONE && !F8) {
                     if (s.vt_panel && pn >= s.vt_panel) {
                         // transposed: the half block just formed is a matrix operand (32 rows x 16 columns); its product with the
                         // unit matrix moves the columns to the lanes, exactly (exchanging the operands of the whole tile instead
@@ -224,7 +296,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         else issueA(nxt, i + S - 1 - KT, i + S - 1);
         if (i + NB >= 0) {
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) loadW(i + NB < KT ? cur : nxt, i + NB < KT ? i + NB : i + NB - KT, (i + NB) % NB, kk);
+            for (int st = 0; st < STEPS; ++st) loadW(i + NB < KT ? cur : nxt, i + NB < KT ? i + NB : i + NB - KT, (i + NB) % NB, st);
         }
     }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * AL + 8 * (NB < S - 1 ? NB : S - 1) < 63 ? (S - 2) * AL + 8 * (NB < S - 1 ? NB : S - 1) : 63) : "memory");
@@ -241,31 +313,45 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         const int ps = st == 0 ? S - 1 : st - 1, ns = st + 1 == S ? 0 : st + 1;
         issueA(ta, ka < KT ? ka : ka - KT, ps);            // into the stage of the slice before, which everyone has read
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            if (kk + 1 < KK) {
-                readA((kk + 1) & 1, st, kk + 1);
-            } else {
+        for (int step = 0; step < STEPS; ++step) {
+            const bool last = step + 1 == STEPS;
+            if (last) {
                 // this slice is in registers and the next one must have landed, for every wavefront.  Loads return in order; those
-                // younger than the next slice's are S - 2 activation slices and at least min(NB, S - 2) weight slices and 3 of 4 steps.
+                // younger than the next slice's are S - 2 activation slices and at least min(NB, S - 2) weight slices and all steps but one.
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cfg::WAIT) : "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                readA(0, ns, 0);
             }
+            if constexpr (!Cfg::IN_PLACE) readA((step + 1) & 1, last ? ns : st, last ? 0 : step + 1);
 #pragma unroll
-            for (int i = 0; i < TMI; ++i)
+            for (int i = 0; i < TMI; ++i) {
 #pragma unroll
-                for (int jn = 0; jn < 2; ++jn)
-                    acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][kk][jn], af[kk & 1][i], acc[i][jn], 0, 0, 0);
-            loadW(tw, kw < KT ? kw : kw - KT, buf, kk);
-            t_interleave<TMI * 2, TMI, 2>();
+                for (int jn = 0; jn < 2; ++jn) acc[i][jn] = t_mfma(wf[buf][step][jn], af[Cfg::IN_PLACE ? 0 : step & 1][i], acc[i][jn], cur.scale);
+                if constexpr (Cfg::IN_PLACE) read1(0, last ? ns : st, last ? 0 : step + 1, i);
+            }
+            loadW(tw, kw < KT ? kw : kw - KT, buf, step);
+            if constexpr (!Cfg::IN_PLACE) t_interleave<TMI * 2, F8 ? 2 * TMI : TMI, F8 ? 4 : 2, 8 / STEPS>();
             __builtin_amdgcn_sched_barrier(0);
         }
         st = ns;
         ++kt;
     };
     auto epilogue = [&]() {
-        if constexpr (KW == 1) {
+        if constexpr (F8) {
+#pragma unroll
+            for (int jn = 0; jn < 2; ++jn) {
+                float b[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) b[e] = __shfl(bias_v, jn * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), 64);
+#pragma unroll
+                for (int i = 0; i < TMI; ++i) {
+                    f32x16 a;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) a[e] = acc[i][jn][e] + b[e];
+                    store_block(cur, a, cur.pm0 + i, cur.pn0 + jn);
+                }
+            }
+        } else if constexpr (KW == 1) {
 #pragma unroll
             for (int i = 0; i < TMI; ++i)
 #pragma unroll
@@ -335,7 +421,10 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
 
 // Tile height in panels, MINT .. MAXT: fewest rounds x cost of a tile.  Two workgroups on a compute unit share it, so rounds count
 // tiles per compute unit; the fixed cost of a tile (fill, epilogue) is about that of 0.7 panels at K = 768.
-template <int MINT, int MAXT>
+// E4M3 operands: half the slices for the same epilogue, so the fixed cost counts for more (it stands still in slices), and the
+// three-panel form, which has three copies of the epilogue, loses everywhere (18.6 k rows x 2304 x 768: 1 to 4 panels 64, 65, 71, 45 us; x 3072 83, 63, 61, 51;
+// 2.3 k rows x 2304 13.0, 16.1, 17.9, 12.6).
+template <int MINT, int MAXT, bool F8>
 __device__ __forceinline__ int pick_height(int panels_m, int tiles_per_row, int n_cu, int slices)
 {
     int best = MINT;
@@ -343,8 +432,9 @@ __device__ __forceinline__ int pick_height(int panels_m, int tiles_per_row, int 
 #pragma unroll
     for (int t = MAXT; t >= MINT; --t) {
         if (t >= 4 && (slices & 1)) continue;              // two weight buffers go with an even number of slices
+        if (F8 && t == 3) continue;
         const int tiles = (panels_m + t - 1) / t * tiles_per_row;
-        const float cost = (float)((tiles + n_cu - 1) / n_cu) * ((float)t + 0.7f);
+        const float cost = (float)((tiles + n_cu - 1) / n_cu) * ((float)t + (F8 ? 8.4f / (float)slices : 0.7f));
         if (cost < best_cost) {
             best_cost = cost;
             best = t;
@@ -353,7 +443,7 @@ __device__ __forceinline__ int pick_height(int panels_m, int tiles_per_row, int 
     return best;
 }
 
-template <int KW, int MAXT, bool OUT_F32, int ACT>
+template <int KW, int MAXT, int OUT, int ACT, bool F8>
 __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tiled_kernel(TiledGroup g, TiledShape s, int n_cu, int force)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -362,18 +452,20 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
     const int slices = s.K / (64 * KW) / s.splits;
     const int per_row = ((s.N >> 5) + 8 / KW - 1) / (8 / KW) * s.G * s.splits;
     if constexpr (MAXT == 8) {
-        switch (force ? force : pick_height<5, 8>(panels_m, per_row, n_cu, slices)) {
-            case 8: gemm_tiled_body<8, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            case 7: gemm_tiled_body<7, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            case 6: gemm_tiled_body<6, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            default: gemm_tiled_body<5, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+        switch (force ? force : pick_height<5, 8, F8>(panels_m, per_row, n_cu, slices)) {
+            case 8: gemm_tiled_body<8, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            case 7: gemm_tiled_body<7, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            case 6: gemm_tiled_body<6, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            default: gemm_tiled_body<5, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
         }
     } else {
-        switch (force ? force : pick_height<1, MAXT>(panels_m, per_row, n_cu, slices)) {
-            case 4: gemm_tiled_body<4, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            case 3: gemm_tiled_body<3, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            case 2: gemm_tiled_body<2, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
-            default: gemm_tiled_body<1, KW, OUT_F32, ACT>(g, s, lds, panels_m); break;
+        switch (force ? force : pick_height<1, MAXT, F8>(panels_m, per_row, n_cu, slices)) {
+            case 4: gemm_tiled_body<4, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            case 3:
+                if constexpr (!F8) gemm_tiled_body<3, KW, OUT, ACT, F8>(g, s, lds, panels_m);
+                break;
+            case 2: gemm_tiled_body<2, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            default: gemm_tiled_body<1, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
         }
     }
 }
@@ -387,7 +479,7 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
 // Packed: lda_ldw = widths in 16 columns, lda | ldw << 16; steps_pn = K steps of 16 per wavefront | column panels << 16; ldc_pm = width
 // of C in 8 columns | first row panel / 65536 << 16 (more row panels than a grid can have take several launches, see launch_rows).
 constexpr int kLaunchPanels = 65536;
-template <int TM, int TN, bool OUT_F32, int ACT>
+template <int TM, int TN, int OUT, int ACT>
 __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, const unsigned char* W, unsigned char* C, const float* bias,
                                                      const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn, uint32_t ldc_pm, int M, int split,
                                                      int64_t split_stride, int vt_panel)
@@ -414,7 +506,7 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     // blocks to store transposed are computed transposed (vt_panel is even: both column panels of a workgroup are, or none)
-    const bool vt = !OUT_F32 && ACT == ACT_NONE && vt_panel && pn0 >= vt_panel;
+    const bool vt = OUT == TILED_BF16 && ACT == ACT_NONE && vt_panel && pn0 >= vt_panel;
     float4 bv[TN];
     int panels_m = 0;
     // one batch of steps: all its loads are issued before its first product (a full batch without conditions: guarded loads are
@@ -458,7 +550,7 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
                         }
                 }
         };
-        if constexpr (!OUT_F32 && ACT == ACT_NONE) {
+        if constexpr (OUT == TILED_BF16 && ACT == ACT_NONE) {
             if (vt) {
                 products(std::true_type{});
                 return true;
@@ -498,7 +590,7 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
             v[2] = t_act<ACT>(v[2] + bv[j].z);
             v[3] = t_act<ACT>(v[3] + bv[j].w);
             const size_t at = pm * pc + pn * 1024 + (vt ? (wave >> 1) * 512 + lane * 8 + (wave & 1) * 4 : wave * 256 + (lane & 31) * 8 + (lane >> 5) * 4);
-            if constexpr (OUT_F32) {
+            if constexpr (OUT == TILED_F32) {
                 *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(C) + (size_t)split * split_stride + at) = v;
             } else {
                 const bf16x4 o = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
@@ -507,16 +599,16 @@ __device__ __forceinline__ void gemm_tiled_rows_body(const unsigned char* A, con
         }
 }
 
-template <int TM, int TN, bool OUT_F32, int ACT>
+template <int TM, int TN, int OUT, int ACT>
 __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_kernel(const unsigned char* A, const unsigned char* W, unsigned char* C,
                                                                                    const float* bias, const int32_t* d_M, uint32_t lda_ldw,
                                                                                    uint32_t steps_pn, uint32_t ldc_pm, int M, int vt_panel, int64_t split_stride)
 {
-    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(A, W, C, bias, d_M, lda_ldw, steps_pn, ldc_pm, M, blockIdx.z, split_stride, vt_panel);
+    gemm_tiled_rows_body<TM, TN, OUT, ACT>(A, W, C, bias, d_M, lda_ldw, steps_pn, ldc_pm, M, blockIdx.z, split_stride, vt_panel);
 }
 
 // several problems, and problems of n_sub equal ones
-template <int TM, int TN, bool OUT_F32, int ACT>
+template <int TM, int TN, int OUT, int ACT>
 __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_group_kernel(const int32_t* d_M, uint32_t lda_ldw, uint32_t steps_pn,
                                                                                          uint32_t ldc_pm, int M, TiledGroup g, TiledShape s)
 {
@@ -524,18 +616,90 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_grou
     const int sub = blockIdx.z % n_sub, gz = blockIdx.z / n_sub;
     const int grp = gz / s.splits, split = gz - grp * s.splits;
     const float* bias = g.b[grp] == kNoBias ? nullptr : g.bias + (size_t)(g.b[grp] + sub * s.sub_b) * 64;
-    gemm_tiled_rows_body<TM, TN, OUT_F32, ACT>(static_cast<const unsigned char*>(g.A) + (size_t)(g.a[grp] + sub * s.sub_a) * 256,
+    gemm_tiled_rows_body<TM, TN, OUT, ACT>(static_cast<const unsigned char*>(g.A) + (size_t)(g.a[grp] + sub * s.sub_a) * 256,
                                                      static_cast<const unsigned char*>(g.W) + (size_t)(g.w[grp] + sub * s.sub_w) * 256,
                                                      static_cast<unsigned char*>(g.C) + (size_t)(g.c[grp] + sub * s.sub_c) * 256, bias, d_M, lda_ldw,
                                                      steps_pn, ldc_pm, M, split, s.split_stride, s.vt_panel);
 }
 
-template <int KW, int MAXT, bool OUT_F32, int ACT>
+// Few rows of E4M3 operands: a wavefront has a block of 32 rows x 32 columns and all of K, which it adds up in the order of the tile forms (a result
+// is the same bits in either), operands straight from global memory to registers, the next batch of steps in flight while one is
+// multiplied.  290 rows x 2304 / 768 / 3072 x 768, x 768 x 3072: 5.4, 4.2, 5.8, 9.2 us, tiles 7.5, 7.4, 8.2, 13.3.
+template <int OUT, int ACT>
+__global__ __launch_bounds__(256, 2) void gemm_tiled_rows_fp8_kernel(const int32_t* d_M, TiledGroup g, TiledShape s)
+{
+    constexpr int U = 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = blockIdx.z;
+    const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(g.A));      // in flight with the first operands
+    const int panels_n = s.N >> 5, pn = blockIdx.x * 4 + wave, pm = blockIdx.y, steps = s.K >> 5;
+    if (pn >= panels_n) return;
+    const unsigned char* w = static_cast<const unsigned char*>(g.W) + (size_t)g.w[grp] * 256;
+    const int scale = t_scale(w);
+    const unsigned char* a = static_cast<const unsigned char*>(g.A) + (size_t)g.a[grp] * 256 + (size_t)pm * s.lda * 64 + lane * 16;
+    w += (size_t)pn * s.ldw * 64 + lane * 16;
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    i32x8 af[2][U], wf[2][U];
+    auto get = [](const unsigned char* p) { return t_join(*reinterpret_cast<const i32x4*>(p), *reinterpret_cast<const i32x4*>(p + 1024)); };
+    auto fetch = [&](int buf, int s0) {                  // steps beyond the last one repeat it
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            wf[buf][u] = get(w + (size_t)min(s0 + u, steps - 1) * 2048);
+            af[buf][u] = get(a + (size_t)min(s0 + u, steps - 1) * 2048);
+        }
+    };
+    auto multiply = [&](int buf, int s0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u < steps) acc = t_mfma(wf[buf][u], af[buf][u], acc, scale);
+    };
+    fetch(0, 0);
+    const uint32_t bo = g.b[grp];
+    float4 b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        b[q] = bo == kNoBias ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(g.bias + (size_t)bo * 64 + pn * 32 + q * 8 + (lane >> 5) * 4);
+    if (steps > U) fetch(1, U);
+    asm volatile("" ::: "memory");
+    if (pm * 32 >= (d_M ? min(s.M, rows_here) : s.M)) return;
+    for (int s0 = 0;; s0 += 2 * U) {
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0, s0);
+        if (s0 + U >= steps) break;
+        if (s0 + 2 * U < steps) fetch(0, s0 + 2 * U);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1, s0 + U);
+        if (s0 + 2 * U >= steps) break;
+        if (s0 + 3 * U < steps) fetch(1, s0 + 3 * U);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        acc[q * 4] += b[q].x;
+        acc[q * 4 + 1] += b[q].y;
+        acc[q * 4 + 2] += b[q].z;
+        acc[q * 4 + 3] += b[q].w;
+    }
+    unsigned char* c = static_cast<unsigned char*>(g.C) + (size_t)g.c[grp] * 256;
+    if constexpr (OUT == TILED_E4M3) {
+        *reinterpret_cast<u32x4*>(t_e4m3_at(c, s.ldc, pm, pn, lane)) = t_pack_e4m3<ACT>(acc);
+    } else if constexpr (OUT == TILED_F32) {
+        float* f = reinterpret_cast<float*>(c) + (size_t)pm * 32 * s.ldc + pn * 1024 + (lane & 31) * 8 + (lane >> 5) * 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(f + q * 256) = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+    } else {
+        __bf16* h = reinterpret_cast<__bf16*>(c) + (size_t)pm * 32 * s.ldc + pn * 1024 + (lane & 31) * 8 + (lane >> 5) * 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(h + q * 256) = bf16x4{(__bf16)acc[q * 4], (__bf16)acc[q * 4 + 1], (__bf16)acc[q * 4 + 2], (__bf16)acc[q * 4 + 3]};
+    }
+}
+
+template <int KW, int MAXT, int OUT, int ACT, bool F8>
 hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int force, hipStream_t stream)
 {
-    constexpr int b0 = TCfg<MAXT, KW>::LDS, b1 = TCfg<MAXT - 1, KW>::LDS, b2 = TCfg<MAXT - 2, KW>::LDS, b3 = TCfg<MAXT - 3, KW>::LDS;
+    constexpr int b0 = TCfg<MAXT, KW, F8>::LDS, b1 = TCfg<MAXT - 1, KW, F8>::LDS, b2 = TCfg<MAXT - 2, KW, F8>::LDS, b3 = TCfg<MAXT - 3, KW, F8>::LDS;
     constexpr int m0 = b0 > b1 ? b0 : b1, m1 = b2 > b3 ? b2 : b3, bytes = m0 > m1 ? m0 : m1;
-    auto kfn = gemm_tiled_kernel<KW, MAXT, OUT_F32, ACT>;
+    auto kfn = gemm_tiled_kernel<KW, MAXT, OUT, ACT, F8>;
     static std::atomic<uint64_t> lds_raised{0};
     if (bytes > 64 * 1024) {
         hipError_t e = ensure_dynamic_lds((const void*)kfn, bytes, lds_raised);
@@ -550,7 +714,7 @@ hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int 
     return hipGetLastError();
 }
 
-template <int TM, int TN, bool OUT_F32, int ACT>
+template <int TM, int TN, int OUT, int ACT>
 hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t stream)
 {
     const int n_sub = s.n_sub > 1 ? s.n_sub : 1, panels = (s.M + 31) / 32;
@@ -560,34 +724,45 @@ hipError_t launch_rows(const TiledGroup& g, const TiledShape& s, hipStream_t str
         dim3 grid((s.N / 32 + TN - 1) / TN, (std::min(panels - pm0, kLaunchPanels) + TM - 1) / TM, s.G * s.splits * n_sub), block(256);
         const uint32_t ldc_pm = (uint32_t)(s.ldc / 8) | (uint32_t)pm0;
         if (s.G == 1 && n_sub == 1)
-            hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream,
+            hipLaunchKernelGGL((gemm_tiled_rows_kernel<TM, TN, OUT, ACT>), grid, block, 0, stream,
                                static_cast<const unsigned char*>(g.A) + (size_t)g.a[0] * 256, static_cast<const unsigned char*>(g.W) + (size_t)g.w[0] * 256,
                                static_cast<unsigned char*>(g.C) + (size_t)g.c[0] * 256, g.b[0] == kNoBias ? nullptr : g.bias + (size_t)g.b[0] * 64, s.d_M,
                                lda_ldw, steps_pn, ldc_pm, s.M, s.vt_panel, s.split_stride);
         else
-            hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT_F32, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
+            hipLaunchKernelGGL((gemm_tiled_rows_group_kernel<TM, TN, OUT, ACT>), grid, block, 0, stream, s.d_M, lda_ldw, steps_pn, ldc_pm, s.M, g, s);
     }
     return hipGetLastError();
 }
 
-template <bool OUT_F32, int ACT>
+template <int OUT, int ACT>
 hipError_t launch_form(const TiledGroup& g, const TiledShape& s, int form, int force, hipStream_t stream)
 {
     const int n_cu = device_cu_count();
     switch (form) {
-        case TILED_ROWS_1X1: return launch_rows<1, 1, OUT_F32, ACT>(g, s, stream);
-        case TILED_ROWS_2X1: return launch_rows<2, 1, OUT_F32, ACT>(g, s, stream);
-        case TILED_ROWS_2X2: return launch_rows<2, 2, OUT_F32, ACT>(g, s, stream);
+        case TILED_ROWS_1X1: return launch_rows<1, 1, OUT, ACT>(g, s, stream);
+        case TILED_ROWS_2X1: return launch_rows<2, 1, OUT, ACT>(g, s, stream);
+        case TILED_ROWS_2X2: return launch_rows<2, 2, OUT, ACT>(g, s, stream);
     }
     if constexpr (ACT != ACT_TANH) {
         switch (form) {
-            case TILED_K2: return launch_tiles<2, 4, OUT_F32, ACT>(g, s, n_cu, force, stream);
-            case TILED_PAIR: return launch_tiles<1, 4, OUT_F32, ACT>(g, s, n_cu, force, stream);
+            case TILED_K2: return launch_tiles<2, 4, OUT, ACT, false>(g, s, n_cu, force, stream);
+            case TILED_PAIR: return launch_tiles<1, 4, OUT, ACT, false>(g, s, n_cu, force, stream);
             case TILED_TALL:
-                if constexpr (ACT == ACT_NONE) return launch_tiles<1, 8, OUT_F32, ACT>(g, s, n_cu, force, stream);
+                if constexpr (ACT == ACT_NONE) return launch_tiles<1, 8, OUT, ACT, false>(g, s, n_cu, force, stream);
         }
     }
     return hipErrorInvalidValue;
+}
+
+// E4M3 operands: one few-row form, and PAIR
+template <int OUT, int ACT>
+hipError_t launch_form_fp8(const TiledGroup& g, const TiledShape& s, int form, int force, hipStream_t stream)
+{
+    if (form == TILED_PAIR) return launch_tiles<1, 4, OUT, ACT, true>(g, s, device_cu_count(), force, stream);
+    const dim3 grid((s.N / 32 + 3) / 4, (s.M + 31) / 32, s.G);
+    if (form != TILED_ROWS_1X1 || grid.y > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_tiled_rows_fp8_kernel<OUT, ACT>), grid, dim3(256), 0, stream, s.d_M, g, s);
+    return hipGetLastError();
 }
 
 // The kernel form.  `blocks` counts the 32x32 outputs of the launch by its row bound (the rows present, known on the device, are
@@ -611,6 +786,13 @@ int choose_form(const TiledShape& s)
     const long sub = s.n_sub > 1 ? s.n_sub : 1, plan = s.plan > s.G ? s.plan : s.G;
     const long blocks = (long)pm * pn * s.G * s.splits * sub, plan_blocks = (long)pm * pn * plan * s.splits * sub;
     const int slices = s.K / 64 / s.splits;
+    if (s.f8) {
+        // Both forms add K up in one order, so the times alone decide (few-row form, tiles).  One problem: 580 rows x 2304 / 3072 x 768, 2304 and 3072
+        // blocks, 7.4, 7.7 us and 7.6, 8.5; 900 rows 9.4, 9.1; x 768 x 3072 1200 rows, 1584 blocks, 11.4, 13.9, 2318 rows, 3072 blocks, 18.0, 14.6.  8
+        // problems: 90 rows x 768 x 768, 960 blocks, 6.4, 7.5, x 2304, 2880 blocks, 12.0, 8.2.  (A tile of more than four panels: 44 and 46 us for 18.6 k
+        // rows x 768 x 3072.)
+        return slices < 5 || blocks <= (s.G > 1 ? 1536 : s.K < 1024 ? 3072 : 2304) ? TILED_ROWS_1X1 : TILED_PAIR;
+    }
     if (s.n_sub > 1 || s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
     if (!tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
@@ -647,7 +829,7 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
 {
     if (s.G <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
     if (s.G > kMaxGroup || s.splits < 1 || s.N % 32 != 0 || s.K % (64 * s.splits) != 0 || s.lda % 16 != 0 || s.ldw % 16 != 0 || s.ldc % 8 != 0 ||
-        s.lda < s.K || s.ldw < s.K || (s.vt_panel && (s.out_f32 || s.act != ACT_NONE || s.vt_panel % 2 != 0)) || (s.splits > 1 && (!s.out_f32 || s.act != ACT_NONE)))
+        s.lda < s.K || s.ldw < s.K || (s.f8 && (s.splits != 1 || s.n_sub > 1)) || (!s.f8 && s.out_f32 == TILED_E4M3) || (s.out_f32 == TILED_E4M3 && s.ldc % 64 != 0) || (s.vt_panel && (s.out_f32 || s.f8 || s.act != ACT_NONE || s.vt_panel % 2 != 0)) || (s.splits > 1 && (s.out_f32 != TILED_F32 || s.act != ACT_NONE)))
         return hipErrorInvalidValue;
     // byte offsets inside the weights, and inside the 8 row panels of a tile, are 31-bit
     if ((uint64_t)s.lda * 64 * 8 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;
@@ -657,20 +839,29 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
     if (form >= TILED_K2 && (s.n_sub > 1 || s.K % (64 * kw * s.splits) != 0 || slices < 5 || (form == TILED_TALL && slices % 2 != 0)))
         return hipErrorInvalidValue;
     // a given height: one of the form's, and those with two weight buffers take an even number of slices
-    if (force && (form < TILED_K2 || force < (form == TILED_TALL ? 5 : 1) || force > (form == TILED_TALL ? 8 : 4) || (force >= 4 && slices % 2 != 0)))
+    if (force && (form < TILED_K2 || force < (form == TILED_TALL ? 5 : 1) || force > (form == TILED_TALL ? 8 : 4) || (force >= 4 && slices % 2 != 0) || (s.f8 && force == 3)))
         return hipErrorInvalidValue;
-    if (form < TILED_K2 && ((long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535 || s.lda / 16 > 65535 || s.ldw / 16 > 65535 || s.ldc / 8 > 65535 ||
+    if (!s.f8 && form < TILED_K2 && ((long)s.G * s.splits * (s.n_sub > 1 ? s.n_sub : 1) > 65535 || s.lda / 16 > 65535 || s.ldw / 16 > 65535 || s.ldc / 8 > 65535 ||
                             s.N / 32 > 65535))
         return hipErrorInvalidValue;
+    if (s.f8) {
+        if (s.out_f32 == TILED_F32) return s.act == ACT_NONE ? launch_form_fp8<TILED_F32, ACT_NONE>(g, s, form, force, stream) : hipErrorInvalidValue;
+        if (s.out_f32 == TILED_BF16) return s.act == ACT_NONE ? launch_form_fp8<TILED_BF16, ACT_NONE>(g, s, form, force, stream) : hipErrorInvalidValue;
+        switch (s.act) {
+            case ACT_GELU_ERF: return launch_form_fp8<TILED_E4M3, ACT_GELU_ERF>(g, s, form, force, stream);
+            case ACT_GELU_TANH: return launch_form_fp8<TILED_E4M3, ACT_GELU_TANH>(g, s, form, force, stream);
+            default: return hipErrorInvalidValue;
+        }
+    }
     if (s.out_f32) {
-        if (s.act == ACT_TANH) return launch_form<true, ACT_TANH>(g, s, form, force, stream);
+        if (s.act == ACT_TANH) return launch_form<TILED_F32, ACT_TANH>(g, s, form, force, stream);
         if (s.act != ACT_NONE) return hipErrorInvalidValue;
-        return launch_form<true, ACT_NONE>(g, s, form, force, stream);
+        return launch_form<TILED_F32, ACT_NONE>(g, s, form, force, stream);
     }
     switch (s.act) {
-        case ACT_NONE: return launch_form<false, ACT_NONE>(g, s, form, force, stream);
-        case ACT_GELU_ERF: return launch_form<false, ACT_GELU_ERF>(g, s, form, force, stream);
-        case ACT_GELU_TANH: return launch_form<false, ACT_GELU_TANH>(g, s, form, force, stream);
+        case ACT_NONE: return launch_form<TILED_BF16, ACT_NONE>(g, s, form, force, stream);
+        case ACT_GELU_ERF: return launch_form<TILED_BF16, ACT_GELU_ERF>(g, s, form, force, stream);
+        case ACT_GELU_TANH: return launch_form<TILED_BF16, ACT_GELU_TANH>(g, s, form, force, stream);
         default: return hipErrorInvalidValue;
     }
 }

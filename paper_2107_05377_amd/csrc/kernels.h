@@ -85,7 +85,7 @@ struct TiledGroup {
 struct TiledShape {
     int32_t G, M, N, K;         // M: row bound; N % 32 == 0, K % (64 splits) == 0
     int32_t lda, ldw, ldc;      // widths of the matrices that the operands' columns are part of
-    int32_t act, out_f32;
+    int32_t act, out_f32;       // out_f32: TILED_BF16, TILED_F32, or TILED_E4M3 (f8 only)
     const int32_t* d_M;         // optional device scalar: rows present
     int32_t splits;             // K ranges, each with a float32 partial result, split_stride elements apart
     int64_t split_stride;
@@ -96,7 +96,21 @@ struct TiledShape {
     int32_t vt_panel;
     // problems that the launch has when every task is enabled (0 = G): decides the order in which K is added up, see choose_form
     int32_t plan;
+    // both operands are E4M3 in panels of their own (tiled_offset_e4m3); K, lda and ldw count pairs of elements, splits is 1, and
+    // kScaleSlot bytes in front of a weight matrix stands what its values are multiplied by, as an E8M0 exponent in each byte of an int32.
+    // E4M3 results at unit scale, saturating.
+    int32_t f8;
 };
+enum TiledOut : int { TILED_BF16 = 0, TILED_F32 = 1, TILED_E4M3 = 2 };
+constexpr size_t kScaleSlot = 256;
+// Byte offset of (row, col) in an E4M3 panel matrix (a multiple of 64 columns): as tiled_offset with chunks of 16 columns, of every four of
+// which the middle two change places: the two 16-byte loads of a lane then bring 32 consecutive columns, in which order the products of a
+// matrix instruction are added up as in the row-major kernel's (gemm_fp8.hip).
+__host__ __device__ inline size_t tiled_offset_e4m3(size_t row, size_t col, size_t width)
+{
+    const size_t c = col >> 4, place = (c & ~(size_t)3) | (c & 1) << 1 | (c >> 1 & 1);
+    return (row >> 5) * 32 * width + place * 512 + (row & 31) * 16 + (col & 15);
+}
 // The kernel forms (gemm_tiled.hip); TILED_AUTO chooses by shape.
 enum TiledForm : int { TILED_AUTO = 0, TILED_ROWS_1X1, TILED_ROWS_2X1, TILED_ROWS_2X2, TILED_K2, TILED_PAIR, TILED_TALL };
 // K ranges (1, 2 or 4, at most `most`) of one contraction with a float32 result: a long K over few output blocks (a row bound of up to 128 at 768
@@ -124,19 +138,27 @@ struct TiledLnShape {
     const int32_t* res_row;     // optional: residual row of row i is res_row[i] (below res_rows)
     int32_t res_rows;
     int32_t split;              // out_b: 0 the row as bf16, 1 as [hi | lo] bf16 halves of a matrix of 2H columns
+    // operand copies of problem i: bit i of want_b the one at out_b, of want_q one in E4M3 (unit scale, saturating) q_offset bytes behind out_b: of
+    // the bf16 values, or (q_offset 0: in its place) of the float32 ones
+    uint32_t want_b = ~0u, want_q = 0;
+    int64_t q_offset = 0;
+    // the order of the row-major kernel's sums, to the bit (H a multiple of 256, one part): layers whose operands are E4M3
+    int32_t whole_sums = 0;
 };
 hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream);
-// As launch_embed_ln (bf16 tables), states in the panel layout.
+// As launch_embed_ln (bf16 tables), states in the panel layout.  out_bf16, out_e4m3: operand copies, either may be null.
 hipError_t launch_embed_ln_tiled(const int32_t* ids, const int32_t* type_ids, int type_vocab, const int32_t* src, const int32_t* d_M, int B, int S,
                                  int H, int vocab, const void* word, const void* pos, const void* type, const float* gamma, const float* beta,
-                                 float eps, float* out_f32, void* out_bf16, hipStream_t stream);
+                                 float eps, float* out_f32, void* out_bf16, void* out_e4m3, hipStream_t stream);
 struct RowCopyGroup {
     const float* in_f[kMaxGroup];
     const void* in_b[kMaxGroup];
     float* out_f[kMaxGroup];
     void* out_b[kMaxGroup];
+    const void* in_q[kMaxGroup];
+    void* out_q[kMaxGroup];
 };
-// out row i = in row index[i] for i < *n (n_max if n is null), float32 and / or bf16 matrices of H columns
+// out row i = in row index[i] for i < *n (n_max if n is null), float32, bf16 and / or E4M3 matrices of H columns (a null input: not that kind)
 hipError_t launch_copy_rows_tiled(const RowCopyGroup& g, int G, const int32_t* index, const int32_t* n, int n_max, int max_rows, int H, hipStream_t stream);
 
 // First-token attention without projected keys and values (first_token.hip).
@@ -186,9 +208,10 @@ struct AttnGroup {
 };
 // Sequence b owns rows seq_start[b] .. +seq_len[b]-1 (all real tokens) when the two arrays are given;
 // otherwise rows b*S .. b*S+S-1 with `mask` ([B][S], 1 = real) marking the keys.  S bounds the length.
-// ctx_fmt 0: the context is written as bfloat16; 1: as E4M3 at unit scale (one byte per element, same row order)
+// ctx_fmt 0: the context is written as bfloat16; 1: as E4M3 at unit scale (one byte per element, same row order).  panels: both matrices in the
+// panel layout (values not transposed).
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
-                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0);
+                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0, bool panels = false);
 // Panel layout, packed sequences: projections with the values transposed (TiledShape::vt_panel), context as an operand; offsets in 256 bytes.
 struct AttnTiledGroup {
     const void* base_qkv;

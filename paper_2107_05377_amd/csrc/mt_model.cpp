@@ -120,7 +120,7 @@ struct mt_model {
     bool bf16 = true;
     bool fp8 = false;   // MT_FP8_FFN / MT_FP8_LAYER: bf16 everywhere, the two feed-forward contractions of every all-rows layer in E4M3
     bool fp8_attn = false;   // MT_FP8_LAYER: the QKV and attention output projections of such a layer too
-    bool tiled = false;      // MT_BF16 with up to 16 heads (mt_create has the rule): weights, operands and states in the panel layout (kernels.h)
+    bool tiled = false;      // MT_BF16 and MT_FP8_LAYER with up to 16 heads (mt_create has the rule): weights, operands and states in the panel layout (kernels.h)
     size_t esz = 2;   // bytes per matrix / activation element
     int C_tot = 0, C_tok = 0;            // widths of the per-sequence and of the per-token logit row
     std::vector<int> logit_off;          // task -> first column inside the row of its kind
@@ -185,9 +185,11 @@ struct Bump {
     }
 };
 
-LayerW layout_layer(Bump& b, size_t H, size_t F, size_t esz, bool fp8 = false, bool fp8_attn = false)
+// slot: bytes in front of every E4M3 matrix (panel layout: for its scale)
+LayerW layout_layer(Bump& b, size_t H, size_t F, size_t esz, bool fp8, bool fp8_attn, size_t slot)
 {
     LayerW L;
+    auto take_e4m3 = [&](size_t bytes) { return b.take(slot + bytes) + slot; };
     L.Wqkv = b.take(3 * H * H * esz);
     L.bqkv = b.take(3 * H * 4);
     L.Wo = b.take(H * H * esz);
@@ -201,12 +203,12 @@ LayerW layout_layer(Bump& b, size_t H, size_t F, size_t esz, bool fp8 = false, b
     L.ln2g = b.take(H * 4);
     L.ln2b = b.take(H * 4);
     if (fp8) {
-        L.W1q = b.take(F * H);
-        L.W2q = b.take(H * F);
+        L.W1q = take_e4m3(F * H);
+        L.W2q = take_e4m3(H * F);
     }
     if (fp8_attn) {
-        L.Wqkvq = b.take(3 * H * H);
-        L.Woq = b.take(H * H);
+        L.Wqkvq = take_e4m3(3 * H * H);
+        L.Woq = take_e4m3(H * H);
     }
     return L;
 }
@@ -364,6 +366,20 @@ void put_tiled(unsigned char* dst, const float* src, size_t N, size_t K, size_t 
     for (auto& t : th) t.join();
 }
 
+// [N][K] float32 times scale -> E4M3, row-major or (panel layout) in panels with its inverse in front: as an E8M0 exponent in each byte of an
+// int32.  row0 (a multiple of 32): first row that dst's matrix gets of a taller one.
+void put_e4m3(unsigned char* dst, const float* src, size_t N, size_t K, float scale, bool tiled, size_t row0 = 0)
+{
+    if (!tiled) {
+        for (size_t i = 0; i < N * K; ++i) dst[row0 * K + i] = f32_to_e4m3_rne(src[i] * scale);
+        return;
+    }
+    for (size_t r = 0; r < N; ++r)
+        for (size_t k = 0; k < K; ++k) dst[tiled_offset_e4m3(row0 + r, k, K)] = f32_to_e4m3_rne(src[r * K + k] * scale);
+    const uint32_t e = (uint32_t)(127 - ilogbf(scale)) * 0x01010101u;      // (the scale is a power of two between 2^-100 and 2^100)
+    memcpy(dst - kScaleSlot, &e, 4);
+}
+
 // Convert one encoder layer from the blob order into the arena image; returns floats consumed.
 size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* img, size_t img_base)
 {
@@ -393,11 +409,7 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
         float sc = e4m3_scale_for(p, H * H);
         sc = std::min(sc, e4m3_scale_for(p + (H * H + H), H * H));
         sc = std::min(sc, e4m3_scale_for(p + 2 * (H * H + H), H * H));
-        for (int i = 0; i < 3; ++i) {
-            const float* w = p + (size_t)i * (H * H + H);
-            uint8_t* q = at(L.Wqkvq) + (size_t)i * H * H;
-            for (size_t e = 0; e < H * H; ++e) q[e] = f32_to_e4m3_rne(w[e] * sc);
-        }
+        for (int i = 0; i < 3; ++i) put_e4m3(at(L.Wqkvq), p + (size_t)i * (H * H + H), H, H, sc, m->tiled, (size_t)i * H);
         L.inv_sqkv = 1.0f / sc;
     }
     for (int i = 0; i < 3; ++i) {   // Wq bq Wk bk Wv bv -> one [3H,H] matrix and one [3H] bias
@@ -409,26 +421,24 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
     put_linear(at(L.Wo), p, H, H);
     if (L.Woq) {
         const float sc = e4m3_scale_for(p, H * H);
-        uint8_t* q = at(L.Woq);
-        for (size_t e = 0; e < H * H; ++e) q[e] = f32_to_e4m3_rne(p[e] * sc);
+        put_e4m3(at(L.Woq), p, H, H, sc, m->tiled);
         L.inv_so = 1.0f / sc;
     }
     p += H * H;
     memcpy(at(L.bo), p, H * 4); p += H;
     memcpy(at(L.ln1g), p, H * 4); p += H;
     memcpy(at(L.ln1b), p, H * 4); p += H;
-    auto put_e4m3 = [&](size_t off, const float* w, size_t n) {
-        const float sc = e4m3_scale_for(w, n);
-        uint8_t* q = at(off);
-        for (size_t i = 0; i < n; ++i) q[i] = f32_to_e4m3_rne(w[i] * sc);
+    auto stage_e4m3 = [&](size_t off, const float* w, size_t N, size_t K) {
+        const float sc = e4m3_scale_for(w, N * K);
+        put_e4m3(at(off), w, N, K, sc, m->tiled);
         return 1.0f / sc;
     };
     put_linear(at(L.W1), p, F, H);
-    if (L.W1q) L.inv_s1 = put_e4m3(L.W1q, p, F * H);
+    if (L.W1q) L.inv_s1 = stage_e4m3(L.W1q, p, F, H);
     p += F * H;
     memcpy(at(L.b1), p, F * 4); p += F;
     put_linear(at(L.W2), p, H, F);
-    if (L.W2q) L.inv_s2 = put_e4m3(L.W2q, p, H * F);
+    if (L.W2q) L.inv_s2 = stage_e4m3(L.W2q, p, H, F);
     p += H * F;
     memcpy(at(L.b2), p, H * 4); p += H;
     memcpy(at(L.ln2g), p, H * 4); p += H;
@@ -508,6 +518,8 @@ struct LayerIO {
     const Scratch* scr;
     float* out_f;
     void* out_b;
+    // panel layout: the operand copies of the output that its readers take: bf16 at out_b, E4M3 behind it (state_q_offset)
+    bool want_b = true, want_q = false;
 };
 
 void run_layer_group(Launcher& L, const std::vector<LayerIO>& io, const RowMap& rm, int B, int S)
@@ -900,7 +912,10 @@ void run_last_layer_group(Launcher& L, const std::vector<LastIO>& io, const RowM
     L.end();
 }
 
-// ---- the bfloat16 path on the panel layout (MT_BF16, up to 16 heads)
+// ---- the panel layout (MT_BF16 and MT_FP8_LAYER; up to 16 heads)
+
+// MT_FP8_LAYER: a state's E4M3 copy lies behind its bf16 copy
+size_t state_q_offset(const mt_model* m) { return m->Mmax * (size_t)m->cfg.hidden * 2; }
 
 uint32_t units(size_t byte_offset) { return (uint32_t)(byte_offset / 256); }      // arena offsets are multiples of 256 bytes
 
@@ -924,14 +939,25 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
     auto off = [&](const void* p) { return units(static_cast<const unsigned char*>(p) - ws); };
     const int64_t part = (int64_t)m->Mmax * H;
 
+    // f8: operands E4M3, whose pairs are what K and the widths count
+    auto shape = [&](int N, int K, int act, int out, bool f8) {
+        const int k = f8 ? K / 2 : K;
+        TiledShape s{n, M, N, k, k, k, N, act, out, rm.n_rows, 1, 0};
+        s.f8 = f8;
+        return s;
+    };
+    const bool f8 = m->fp8_attn;
+
     TiledGroup g = tiled_group(m);
     for (int i = 0; i < n; ++i) {
-        g.a[i] = off(io[i].in_b);
-        g.w[i] = units(io[i].w->Wqkv);
+        g.a[i] = off(io[i].in_b) + (f8 ? units(state_q_offset(m)) : 0);
+        g.w[i] = units(f8 ? io[i].w->Wqkvq : io[i].w->Wqkv);
         g.b[i] = units(io[i].w->bqkv);
         g.c[i] = units(io[i].scr->qkv);
     }
-    L.tiled(MT_K_GEMM_QKV, g, TiledShape{n, M, 3 * H, H, H, H, 3 * H, ACT_NONE, 0, rm.n_rows, 1, 0, 0, 0, 0, 0, 0, 2 * H / 32});
+    TiledShape s = shape(3 * H, H, ACT_NONE, TILED_BF16, f8);
+    s.vt_panel = f8 ? 0 : 2 * H / 32;
+    L.tiled(MT_K_GEMM_QKV, g, s);
 
     AttnTiledGroup ag;
     ag.base_qkv = ws;
@@ -941,16 +967,26 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
         ag.ctx[i] = units(io[i].scr->ctx);
     }
     L.begin(MT_K_ATTN);
-    L.check(launch_attention_tiled(ag, n, rm.seq_start, rm.seq_len, B, S, H, A, L.st));
+    if (f8) {
+        AttnGroup fg;
+        memset(&fg, 0, sizeof fg);
+        for (int i = 0; i < n; ++i) {
+            fg.qkv[i] = ws + io[i].scr->qkv;
+            fg.ctx[i] = ws + io[i].scr->ctx;
+        }
+        L.check(launch_attention_bf16(fg, n, nullptr, rm.seq_start, rm.seq_len, B, S, H, A, L.st, 1, true));
+    } else {
+        L.check(launch_attention_tiled(ag, n, rm.seq_start, rm.seq_len, B, S, H, A, L.st));
+    }
     L.end();
 
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->ctx);
-        g.w[i] = units(io[i].w->Wo);
+        g.w[i] = units(f8 ? io[i].w->Woq : io[i].w->Wo);
         g.b[i] = units(io[i].w->bo);
         g.c[i] = units(io[i].scr->y);
     }
-    L.tiled(MT_K_GEMM_OUT, g, TiledShape{n, M, H, H, H, H, H, ACT_NONE, 1, rm.n_rows, 1, 0});
+    L.tiled(MT_K_GEMM_OUT, g, shape(H, H, ACT_NONE, TILED_F32, f8));
 
     TiledLnGroup lg;
     lg.ws = ws;
@@ -964,36 +1000,48 @@ void run_layer_group_tiled(Launcher& L, const std::vector<LayerIO>& io, const Ro
         lg.beta[i] = units(io[i].w->ln1b);
     }
     TiledLnShape ls{n, M, H, rm.n_rows, m->cfg.ln_eps, 1, part, nullptr, 0, 0};
+    if (f8) {                                    // the operand copy of x1 is E4M3, in the same buffer
+        ls.want_b = 0;
+        ls.want_q = ~0u;
+        ls.whole_sums = 1;
+    }
     L.begin(MT_K_LN);
     L.check(launch_layernorm_tiled(lg, ls, L.st));
     L.end();
 
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->x1b);
-        g.w[i] = units(io[i].w->W1);
+        g.w[i] = units(f8 ? io[i].w->W1q : io[i].w->W1);
         g.b[i] = units(io[i].w->b1);
         g.c[i] = units(io[i].scr->u);
     }
-    L.tiled(MT_K_GEMM_FFN1, g, TiledShape{n, M, F, H, H, H, F, gelu_act, 0, rm.n_rows, 1, 0});
+    L.tiled(MT_K_GEMM_FFN1, g, shape(F, H, gelu_act, f8 ? TILED_E4M3 : TILED_BF16, f8));
 
     // only the trunk has room for partial results, and takes them where it never shares the launch
-    const int sp = L.plan <= 1 && n == 1 && io[0].scr->y_parts >= 4 ? tiled_splits(M, H, F, 4) : 1;
+    const int sp = !f8 && L.plan <= 1 && n == 1 && io[0].scr->y_parts >= 4 ? tiled_splits(M, H, F, 4) : 1;
     for (int i = 0; i < n; ++i) {
         g.a[i] = units(io[i].scr->u);
-        g.w[i] = units(io[i].w->W2);
+        g.w[i] = units(f8 ? io[i].w->W2q : io[i].w->W2);
         g.b[i] = units(io[i].w->b2);
         g.c[i] = units(io[i].scr->y);
     }
-    L.tiled(MT_K_GEMM_FFN2, g, TiledShape{n, M, H, F, F, F, H, ACT_NONE, 1, rm.n_rows, sp, part});
+    s = shape(H, F, ACT_NONE, TILED_F32, f8);
+    s.splits = sp;
+    s.split_stride = part;
+    L.tiled(MT_K_GEMM_FFN2, g, s);
 
+    ls.want_b = ls.want_q = 0;
     for (int i = 0; i < n; ++i) {
         lg.res[i] = units(io[i].scr->x1f);
         lg.out_f[i] = off(io[i].out_f);
         lg.out_b[i] = off(io[i].out_b);
         lg.gamma[i] = units(io[i].w->ln2g);
         lg.beta[i] = units(io[i].w->ln2b);
+        ls.want_b |= (uint32_t)io[i].want_b << i;
+        ls.want_q |= (uint32_t)io[i].want_q << i;
     }
     ls.n_parts = sp;
+    ls.q_offset = (int64_t)state_q_offset(m);
     L.begin(MT_K_LN);
     L.check(launch_layernorm_tiled(lg, ls, L.st));
     L.end();
@@ -1024,6 +1072,7 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
         } else {
             fg.first[i] = rc.out_b[n_copy] = ws + io[i].cls->in_a;
             rc.in_b[n_copy] = io[i].in_a;
+            rc.in_q[n_copy] = nullptr;
             rc.in_f[n_copy++] = nullptr;
         }
         fg.Wq[i] = m->d_w + io[i].w->Wqkv;
@@ -1125,17 +1174,18 @@ WsLayout layout_workspace(const mt_model* m, bool tiled, size_t slots)
     const bool shared = slots < T;
     WsLayout y;
     Bump sb;
+    auto take_copies = [&] { return m->bf16 ? sb.take(M * H * (tiled && m->fp8_attn ? 3 : 2)) : 0; };      // of a state: operand copies
     y.slots = slots;
     for (int tap : m->tap_of_layer)
         if (tap >= 0) {
             y.tap_f.push_back(sb.take(M * H * 4));
-            y.tap_b.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
+            y.tap_b.push_back(take_copies());
         }
     for (int i = 0; i < 2; ++i) {
         y.pp_f[i] = sb.take(M * H * 4);
-        y.pp_b[i] = m->bf16 ? sb.take(M * H * 2) : 0;
+        y.pp_b[i] = take_copies();
     }
-    y.trunk_scr = tiled ? layout_scratch_tiled(sb, M, H, F, 4) : layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
+    y.trunk_scr = tiled ? layout_scratch_tiled(sb, M, H, F, m->fp8 ? 1 : 4) : layout_scratch(sb, M, H, F, m->esz, m->bf16, m->bf16 ? 4 : 1);
     for (size_t t = 0; t < T; ++t) {
         if (t >= slots) {
             y.task_scr.push_back(y.task_scr[t - slots]);
@@ -1159,7 +1209,7 @@ WsLayout layout_workspace(const mt_model* m, bool tiled, size_t slots)
         }
         y.task_scr.push_back(scr);
         y.task_xf.push_back(sb.take(M * H * 4));          // (without own layers only per-sequence routing uses it: the sub-batch's tap rows)
-        y.task_xb.push_back(m->bf16 ? sb.take(M * H * 2) : 0);
+        y.task_xb.push_back(take_copies());
         if (first && !tiled) {
             c.in_f = sb.take(MB * H * 4);
             c.in_a = m->bf16 ? sb.take(MB * H * 2) : c.in_f;
@@ -1270,9 +1320,11 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->fp8 = cfg->precision == MT_FP8_FFN || cfg->precision == MT_FP8_LAYER;
     m->fp8_attn = cfg->precision == MT_FP8_LAYER;
     // (nothing that handles on one weight arena may differ in decides its layout: neither max_batch nor max_seq, see mt_share_weights)
-    m->tiled = cfg->precision == MT_BF16 && cfg->heads <= 16;
+    // MT_FP8_LAYER: widths that the E4M3 panels and the LayerNorm's order of sums cover.  (MT_FP8_FFN: its bf16 contractions would add up in
+    // another order than the row-major kernels, and E4M3 roundings amplify the last bit of that to 5 % of the logits.)
+    m->tiled = cfg->heads <= 16 && (cfg->precision == MT_BF16 || (m->fp8_attn && cfg->hidden % 256 == 0 && cfg->ffn % 256 == 0));
     m->esz = m->bf16 ? 2 : 4;
-    const size_t H = cfg->hidden, F = cfg->ffn, T = cfg->n_tasks, D = cfg->n_trunk_layers;
+    const size_t H = cfg->hidden, F = cfg->ffn, T = cfg->n_tasks, D = cfg->n_trunk_layers, slot = m->tiled ? kScaleSlot : 0;
     for (const auto& d : m->tasks) {
         int& width = d.head == MT_HEAD_TOKEN ? m->C_tok : m->C_tot;
         m->logit_off.push_back(width);
@@ -1286,13 +1338,13 @@ int mt_create(const mt_config* cfg, mt_model** out)
     m->w_type = wb.take((size_t)cfg->type_vocab * H * m->esz);
     m->w_embg = wb.take(H * 4);
     m->w_embb = wb.take(H * 4);
-    for (size_t l = 0; l < D; ++l) m->trunk.push_back(layout_layer(wb, H, F, m->esz, m->fp8, m->fp8_attn));
+    for (size_t l = 0; l < D; ++l) m->trunk.push_back(layout_layer(wb, H, F, m->esz, m->fp8, m->fp8_attn, slot));
     m->w_trunk_end = wb.off;
     m->taskw.resize(T);
     for (size_t t = 0; t < T; ++t) {
         TaskW& tw = m->taskw[t];
         tw.begin = wb.off;
-        for (int l = 0; l < m->tasks[t].n_layers; ++l) tw.layers.push_back(layout_layer(wb, H, F, m->esz, m->fp8, m->fp8_attn));
+        for (int l = 0; l < m->tasks[t].n_layers; ++l) tw.layers.push_back(layout_layer(wb, H, F, m->esz, m->fp8, m->fp8_attn, slot));
         const bool seq_head = m->tasks[t].head == MT_HEAD_SEQUENCE;
         if (m->bf16 && seq_head && !tw.layers.empty()) tw.layers.back().WkT = wb.take(H * H * 2);
         tw.Wp = seq_head ? wb.take(H * H * m->esz * (m->bf16 ? 2 : 1)) : 0;
@@ -1613,15 +1665,34 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     };
     RowMap rm{(int32_t*)(ws + y.rm_n), (int32_t*)(ws + y.rm_src), (int32_t*)(ws + y.rm_rowof), (int32_t*)(ws + y.rm_start),
               (int32_t*)(ws + y.rm_len)};
+    // MT_FP8_LAYER on panels: a layer on all rows reads the E4M3 copy of a state, the first-token layer the bf16 copy
+    struct Copies {
+        bool b, q;
+    };
+    auto first_only = [&](const mt_task_desc& d, int stage) { return stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE; };
+    auto copies_of_trunk = [&](int layer) {
+        if (!m->fp8_attn) return Copies{true, false};
+        Copies c{false, layer < m->cfg.n_trunk_layers};
+        for (const mt_task_desc& d : m->tasks)
+            if (d.fork_layer == layer && d.n_layers > 0) (first_only(d, 0) ? c.b : c.q) = true;
+        return c;
+    };
+    auto copies_of_task = [&](int t, int stage) {                // of the output of its layer `stage`
+        if (!m->fp8_attn) return Copies{true, false};
+        const mt_task_desc& d = m->tasks[t];
+        const bool more = stage + 1 < d.n_layers, first = more && first_only(d, stage + 1);
+        return Copies{first, more && !first};
+    };
     float* cur_f;
     void* cur_b;
     trunk_out(0, 0, cur_f, cur_b);
+    const Copies emb = copies_of_trunk(0);
     L.begin(MT_K_EMBED);
     L.check(launch_build_row_map(d_attn_mask, B, S, rm, L.st));
     if (m->tiled)
         L.check(launch_embed_ln_tiled(d_input_ids, d_token_type_ids, m->cfg.type_vocab, rm.src, rm.n_rows, B, S, H, m->cfg.vocab, W + m->w_word,
                                       W + m->w_pos, W + m->w_type, (const float*)(W + m->w_embg), (const float*)(W + m->w_embb), m->cfg.ln_eps,
-                                      cur_f, cur_b, L.st));
+                                      cur_f, emb.b ? cur_b : nullptr, emb.q ? (unsigned char*)cur_b + state_q_offset(m) : nullptr, L.st));
     else
     L.check(launch_embed_ln(d_input_ids, d_token_type_ids, m->cfg.type_vocab, rm.src, rm.n_rows, B, S, H, m->cfg.vocab, W + m->w_word, W + m->w_pos, W + m->w_type, bf ? 1 : 0,
                             (const float*)(W + m->w_embg), (const float*)(W + m->w_embb), m->cfg.ln_eps, cur_f,
@@ -1646,7 +1717,8 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         void* nb = nullptr;
         if (trunk && step < depth) {
             trunk_out(step + 1, (step + 1) & 1, nf, nb);
-            full.push_back(LayerIO{cur_f, cur_b, &m->trunk[step], &y.trunk_scr, nf, nb});
+            const Copies c = copies_of_trunk(step + 1);
+            full.push_back(LayerIO{cur_f, cur_b, &m->trunk[step], &y.trunk_scr, nf, nb, c.b, c.q});
         }
         int all_full = step < m->cfg.n_trunk_layers ? 1 : 0, all_last = 0;        // with every task enabled
         for (const mt_task_desc& d : m->tasks) {
@@ -1667,11 +1739,12 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                 in_f = (const float*)(ws + y.task_xf[t]);
                 in_b = bf ? (const void*)(ws + y.task_xb[t]) : nullptr;
             }
-            if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE) {
+            if (first_only(d, stage)) {
                 last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &y.task_scr[t], &y.task_cls[t], y.split[t]});
             } else {
+                const Copies c = copies_of_task(t, stage);
                 full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &y.task_scr[t], (float*)(ws + y.task_xf[t]),
-                                       bf ? (void*)(ws + y.task_xb[t]) : nullptr});
+                                       bf ? (void*)(ws + y.task_xb[t]) : nullptr, c.b, c.q});
             }
         }
         // (a launch takes up to kMaxGroup problems; all launches of a step go by the first one's number)
@@ -1860,9 +1933,12 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             for (int t : grp_tasks) {
                 const int tap = m->tap_of_layer[m->tasks[t].fork_layer];
                 if (m->tiled) {
+                    const Copies c = copies_of_task(t, -1);
                     rc.in_f[n_copy] = (const float*)(ws + y.tap_f[tap]);
-                    rc.in_b[n_copy] = ws + y.tap_b[tap];
+                    rc.in_b[n_copy] = c.b ? ws + y.tap_b[tap] : nullptr;
+                    rc.in_q[n_copy] = c.q ? ws + y.tap_b[tap] + state_q_offset(m) : nullptr;
                     rc.out_f[n_copy] = (float*)(ws + y.task_xf[t]);
+                    rc.out_q[n_copy] = ws + y.task_xb[t] + state_q_offset(m);
                     rc.out_b[n_copy++] = ws + y.task_xb[t];
                     if (n_copy == kMaxGroup) flush_copies();
                     continue;
@@ -1883,11 +1959,12 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
                     if (stage >= d.n_layers) continue;
                     const float* in_f = (const float*)(ws + y.task_xf[t]);
                     const void* in_b = bf ? (const void*)(ws + y.task_xb[t]) : nullptr;
-                    if (stage == d.n_layers - 1 && d.head == MT_HEAD_SEQUENCE)
+                    const Copies c = copies_of_task(t, stage);
+                    if (first_only(d, stage))
                         last.push_back(LastIO{in_f, bf ? in_b : (const void*)in_f, &m->taskw[t].layers[stage], &y.task_scr[t], &y.task_cls[t], y.split[t]});
                     else
                         full.push_back(LayerIO{in_f, in_b, &m->taskw[t].layers[stage], &y.task_scr[t], (float*)(ws + y.task_xf[t]),
-                                               bf ? (void*)(ws + y.task_xb[t]) : nullptr});
+                                               bf ? (void*)(ws + y.task_xb[t]) : nullptr, c.b, c.q});
                 }
                 for (size_t lo = 0; lo < full.size(); lo += kMaxGroup) {
                     std::vector<LayerIO> part(full.begin() + lo, full.begin() + std::min(full.size(), lo + (size_t)kMaxGroup));
@@ -2303,7 +2380,7 @@ int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, in
     return op_result(launch_first_attend(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, xbar_stride, static_cast<hipStream_t>(hip_stream)));
 }
 
-int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream)
+static int op_panel_linear(const mt_panel_linear* op, bool f8, void* hip_stream)
 {
     if (!op || !op->d_A || !op->d_W || !op->d_C) return MT_ERR_NULL;
     const int64_t strides[] = {op->stride_A, op->stride_W, op->stride_bias, op->stride_C, op->sub_A, op->sub_W, op->sub_bias, op->sub_C};
@@ -2324,7 +2401,15 @@ int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream)
         g.c[i] = units((size_t)i * op->stride_C);
         g.b[i] = op->d_bias ? units((size_t)i * op->stride_bias) : kNoBias;
     }
-    TiledShape s{op->problems, op->M, op->N, op->K, op->lda, op->ldw, op->ldc, op->act_kind, op->out_f32 ? 1 : 0, op->d_rows, op->splits, op->split_stride};
+    TiledShape s{op->problems, op->M, op->N, op->K, op->lda, op->ldw, op->ldc, op->act_kind, op->out_f32 ? TILED_F32 : TILED_BF16, op->d_rows, op->splits, op->split_stride};
+    if (f8) {
+        if (op->out_f32 < 0 || op->out_f32 > 2 || op->K % 2 != 0 || op->lda % 2 != 0 || op->ldw % 2 != 0) return MT_ERR_SHAPE;
+        s.f8 = 1;
+        s.K /= 2;
+        s.lda /= 2;
+        s.ldw /= 2;
+        s.out_f32 = op->out_f32;
+    }
     s.n_sub = op->subs;
     s.sub_a = (int32_t)units(op->sub_A);
     s.sub_w = (int32_t)units(op->sub_W);
@@ -2333,6 +2418,9 @@ int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream)
     s.vt_panel = op->transposed_from / 32;
     return op_result(launch_gemm_tiled(g, s, static_cast<hipStream_t>(hip_stream), op->form, op->height));
 }
+
+int mt_op_panel_linear(const mt_panel_linear* op, void* hip_stream) { return op_panel_linear(op, false, hip_stream); }
+int mt_op_panel_linear_fp8(const mt_panel_linear* op, void* hip_stream) { return op_panel_linear(op, true, hip_stream); }
 
 int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq,
                           int32_t heads, void* hip_stream)

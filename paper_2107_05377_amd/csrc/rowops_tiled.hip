@@ -29,12 +29,36 @@ constexpr int kRowWaves = 4;                                                  //
 template <int NI, bool SPLIT>
 constexpr int rows_of_group = kRowWaves / (SPLIT ? row_shares(NI) : 1) * 4;
 
-// Normalise the NW x 4 values that a lane holds of its row, columns (wc NW + i) 64 .., and store: float32 state, bf16 operand copy, or
-// (split) the row as [hi | lo] bf16 halves of a matrix twice as wide.  STREAM: the float32 state is stored past the second-level
+// Where a row goes: the float32 state, and operand copies (each may be null): bf16, or (split) [hi | lo] bf16 halves of a matrix twice as
+// wide, and E4M3 (of the bf16 copy's values, or of the float32 ones: q_exact).
+struct RowOut {
+    float* f;
+    __bf16* b;
+    unsigned char* q;
+    int split;
+    bool q_exact;
+};
+
+// How the sums of a row are ordered.  SHARES: above.  WHOLE: one wavefront has the row, and the sums are those of the row-major kernels
+// (layernorm_fast: 64 partial sums of every 64th group of 4 columns, added up pairwise) to the bit, which the E4M3 roundings behind them amplify.
+enum RowSums : int { ROW_SHARES, ROW_WHOLE };
+
+// sum over the row of part[k], k = 0 .. 3: the partial sums 16 k + 2 c8 + half of 64
+__device__ __forceinline__ float row_sum_whole(const float (&part)[4])
+{
+    float v = (part[0] + part[2]) + (part[1] + part[3]);
+    v += __shfl_xor(v, 32, 64);
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 8, 64);
+    v += __shfl_xor(v, 1, 64);
+    return v;
+}
+
+// Normalise the NW x 4 values that a lane holds of its row, columns (wc NW + i) 64 .., and store.  STREAM: the float32 state is stored past the second-level
 // cache, since it is read again three launches later only (18.6 k rows 38.7 -> 38.2 us, 8 problems of them 278 -> 268).
-template <int NI, bool SPLIT, bool STREAM>
+template <int NI, bool SPLIT, bool STREAM, RowSums SUMS>
 __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(NI) : 1)], const float* __restrict__ gamma, const float* __restrict__ beta,
-                                           int row, int wave, bool live, float eps, float* of, __bf16* ob, int split)
+                                           int row, int wave, bool live, float eps, const RowOut& out)
 {
     constexpr int H = NI * 64, SH = row_shares(NI), W = SPLIT ? SH : 1, NW = NI / W, NS = NI / SH, N = NS * 64;
     const int lane = threadIdx.x & 63, half = lane & 1, c8 = lane >> 3, wc = wave % W;
@@ -45,6 +69,28 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
         b[i] = *reinterpret_cast<const float4*>(beta + ((wc * NW + i) * 8 + c8) * 8 + half * 4);
     }
     __builtin_amdgcn_sched_barrier(0);
+    float mean, q;                           // of the row: mean, sum of the squares about it
+    if constexpr (SUMS == ROW_WHOLE) {
+        static_assert(!SPLIT && NI % 4 == 0, "");
+        float part[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            part[k] = 0.f;
+#pragma unroll
+            for (int i = k; i < NI; i += 4) part[k] += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+        }
+        mean = row_sum_whole(part) / (float)H;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            part[k] = 0.f;
+#pragma unroll
+            for (int i = k; i < NI; i += 4) {
+                const float a = v[i].x - mean, bb = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
+                part[k] += (a * a + bb * bb) + (c * c + d * d);
+            }
+        }
+        q = row_sum_whole(part);
+    } else {
     float m[SH], d2[SH];                     // of the shares: mean, squares about it
 #pragma unroll
     for (int h = 0; h < SH / W; ++h) {
@@ -55,13 +101,13 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
     }
 #pragma unroll
     for (int h = 0; h < SH / W; ++h) {
-        float q = 0.f;
+        float s2 = 0.f;
 #pragma unroll
         for (int i = h * NS; i < (h + 1) * NS; ++i) {
             const float a = v[i].x - m[h], c = v[i].y - m[h], d = v[i].z - m[h], e = v[i].w - m[h];
-            q += fmaf(a, a, c * c) + fmaf(d, d, e * e);
+            s2 += fmaf(a, a, c * c) + fmaf(d, d, e * e);
         }
-        d2[h] = row_sum(q);
+        d2[h] = row_sum(s2);
     }
     if constexpr (W > 1) {
         __shared__ float2 share[kRowWaves / W][W][4];
@@ -76,7 +122,8 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
         }
     }
     // shares of equal size: the squares about the common mean are those about each share's + N (difference)^2
-    float mean = m[0], q = d2[0];
+    mean = m[0];
+    q = d2[0];
 #pragma unroll
     for (int h = 1; h < SH; ++h) {
         mean += m[h];
@@ -88,6 +135,7 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
 #pragma unroll
         for (int h = 0; h < SH; ++h) u = fmaf(m[h] - mean, m[h] - mean, u);
         q = fmaf(u, (float)N, q);
+    }
     }
     const float inv = 1.0f / sqrtf(q / (float)H + eps);
     if (!live) return;
@@ -101,13 +149,17 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
         o[1] = fmaf(g[i].y, (v[i].y - mean) * inv, b[i].y);
         o[2] = fmaf(g[i].z, (v[i].z - mean) * inv, b[i].z);
         o[3] = fmaf(g[i].w, (v[i].w - mean) * inv, b[i].w);
-        f32x4* f = reinterpret_cast<f32x4*>(of + panel * H + chunk * 256 + in_chunk);
+        f32x4* f = reinterpret_cast<f32x4*>(out.f + panel * H + chunk * 256 + in_chunk);
         if constexpr (STREAM) __builtin_nontemporal_store(o, f);
         else *f = o;
         const bf16x4 hi = {(__bf16)o[0], (__bf16)o[1], (__bf16)o[2], (__bf16)o[3]};
-        __bf16* p = ob + panel * (split ? 2 * H : H) + in_chunk;
+        if (out.q)
+            *reinterpret_cast<uint32_t*>(out.q + tiled_offset_e4m3(row, chunk * 8 + half * 4, H)) =
+                out.q_exact ? pack_e4m3(o[0], o[1], o[2], o[3]) : pack_e4m3((float)hi[0], (float)hi[1], (float)hi[2], (float)hi[3]);
+        if (!out.b) continue;
+        __bf16* p = out.b + panel * (out.split ? 2 * H : H) + in_chunk;
         *reinterpret_cast<bf16x4*>(p + chunk * 256) = hi;
-        if (split) {
+        if (out.split) {
             const bf16x4 lo = {(__bf16)(o[0] - (float)hi[0]), (__bf16)(o[1] - (float)hi[1]), (__bf16)(o[2] - (float)hi[2]), (__bf16)(o[3] - (float)hi[3])};
             *reinterpret_cast<bf16x4*>(p + (NI * 8 + chunk) * 256) = lo;
         }
@@ -118,10 +170,9 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
 // before the first use, in a launch of few rows (FEW) even before the row count has arrived: rows beyond it are memory of the
 // operands all the same, but of a large padded batch reading them would be real traffic.  The pointers are leading scalar arguments,
 // which the command processor preloads.
-template <int NI, int NP, bool FEW>
-__device__ __forceinline__ void layernorm_tiled_body(const float* x, const float* res, const float* gamma, const float* beta, float* of, __bf16* ob,
-                                                     const int32_t* d_M, int M, int64_t part_stride, const int32_t* res_row, int res_rows, float eps,
-                                                     int split)
+template <int NI, int NP, bool FEW, RowSums SUMS>
+__device__ __forceinline__ void layernorm_tiled_body(const float* x, const float* res, const float* gamma, const float* beta, const RowOut& out,
+                                                     const int32_t* d_M, int M, int64_t part_stride, const int32_t* res_row, int res_rows, float eps)
 {
     constexpr int H = NI * 64, W = FEW ? row_shares(NI) : 1, NW = NI / W;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -164,35 +215,37 @@ __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float
         v[0][i].z += r[i].z;
         v[0][i].w += r[i].w;
     }
-    finish_row<NI, FEW, !FEW>(v[0], gamma, beta, row, wave, row < M, eps, of, ob, split);
+    finish_row<NI, FEW, !FEW, SUMS>(v[0], gamma, beta, row, wave, row < M, eps, out);
 }
 
 template <int NI, int NP>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_kernel(const float* x, const float* res, const int32_t* d_M, const float* gamma,
                                                               const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps)
 {
-    layernorm_tiled_body<NI, NP, true>(x, res, gamma, beta, of, ob, d_M, M, part_stride, nullptr, 0, eps, 0);
+    layernorm_tiled_body<NI, NP, true, ROW_SHARES>(x, res, gamma, beta, RowOut{of, ob, nullptr, 0, false}, d_M, M, part_stride, nullptr, 0, eps);
 }
 
-template <int NI, int NP, bool FEW>
+template <int NI, int NP, bool FEW, RowSums SUMS>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_group_kernel(TiledLnGroup g, TiledLnShape s)
 {
     const int grp = blockIdx.y;
     const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
     unsigned char* ws = static_cast<unsigned char*>(const_cast<void*>(g.ws));
-    layernorm_tiled_body<NI, NP, FEW>(reinterpret_cast<const float*>(ws + (size_t)g.x[grp] * 256), reinterpret_cast<const float*>(ws + (size_t)g.res[grp] * 256),
-                                 reinterpret_cast<const float*>(wt + (size_t)g.gamma[grp] * 256), reinterpret_cast<const float*>(wt + (size_t)g.beta[grp] * 256),
-                                 reinterpret_cast<float*>(ws + (size_t)g.out_f[grp] * 256), reinterpret_cast<__bf16*>(ws + (size_t)g.out_b[grp] * 256), s.d_M,
-                                 s.M, s.part_stride, s.res_row, s.res_rows, s.eps, s.split);
+    unsigned char* ob = ws + (size_t)g.out_b[grp] * 256;
+    const RowOut out{reinterpret_cast<float*>(ws + (size_t)g.out_f[grp] * 256), s.want_b >> grp & 1 ? reinterpret_cast<__bf16*>(ob) : nullptr,
+                     s.want_q >> grp & 1 ? ob + s.q_offset : nullptr, s.split, s.q_offset == 0};
+    layernorm_tiled_body<NI, NP, FEW, SUMS>(reinterpret_cast<const float*>(ws + (size_t)g.x[grp] * 256), reinterpret_cast<const float*>(ws + (size_t)g.res[grp] * 256),
+                                      reinterpret_cast<const float*>(wt + (size_t)g.gamma[grp] * 256), reinterpret_cast<const float*>(wt + (size_t)g.beta[grp] * 256),
+                                      out, s.d_M, s.M, s.part_stride, s.res_row, s.res_rows, s.eps);
 }
 
 // Embedding sum + LayerNorm of the kept rows.
-template <int NI, bool SPLIT>
+template <int NI, bool SPLIT, RowSums SUMS>
 __global__ __launch_bounds__(kRowWaves * 64) void embed_ln_tiled_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ type_ids, int type_vocab,
                                                              const int32_t* __restrict__ src, const int32_t* __restrict__ d_M, int M, int S,
                                                              int vocab, const __bf16* __restrict__ word, const __bf16* __restrict__ pos,
                                                              const __bf16* __restrict__ type, const float* __restrict__ gamma,
-                                                             const float* __restrict__ beta, float eps, float* of, __bf16* ob)
+                                                             const float* __restrict__ beta, float eps, float* of, __bf16* ob, unsigned char* oq)
 {
     constexpr int H = NI * 64, W = SPLIT ? row_shares(NI) : 1, NW = NI / W;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -224,7 +277,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void embed_ln_tiled_kernel(const in
         v[i].z = ((float)a[i][2] + (float)b[i][2]) + (float)c[i][2];
         v[i].w = ((float)a[i][3] + (float)b[i][3]) + (float)c[i][3];
     }
-    finish_row<NI, SPLIT, false>(v, gamma, beta, row, wave, row < M, eps, of, ob, 0);
+    finish_row<NI, SPLIT, false, SUMS>(v, gamma, beta, row, wave, row < M, eps, RowOut{of, ob, oq, 0, false});
 }
 
 // Pooler operand of tasks without own layers: the tap's first-token row of every sequence as [hi | lo] bf16 halves.
@@ -261,6 +314,9 @@ __global__ __launch_bounds__(256) void copy_rows_tiled_kernel(RowCopyGroup g, co
             *reinterpret_cast<float4*>(g.out_f[grp] + b) = lo;
             *reinterpret_cast<float4*>(g.out_f[grp] + b + 4) = hi;
         }
+        if (g.in_q[grp])
+            *reinterpret_cast<uint2*>(static_cast<unsigned char*>(g.out_q[grp]) + tiled_offset_e4m3(r, chunk * 8, H)) =
+                *reinterpret_cast<const uint2*>(static_cast<const unsigned char*>(g.in_q[grp]) + tiled_offset_e4m3(from, chunk * 8, H));
         if (g.in_b[grp])
             *reinterpret_cast<uint4*>(reinterpret_cast<__bf16*>(g.out_b[grp]) + b) = *reinterpret_cast<const uint4*>(reinterpret_cast<const __bf16*>(g.in_b[grp]) + a);
     }
@@ -303,18 +359,24 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
     unsigned char* ws = static_cast<unsigned char*>(const_cast<void*>(g.ws));
     const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
     // with a row count on the device: less than a cached megabyte or two of padding.  Without, there is none.
-    const bool few = (long)s.G * s.M <= (s.d_M ? 2048 : 8192);
+    const bool few = !s.whole_sums && (long)s.G * s.M <= (s.d_M ? 2048 : 8192);
     const int rows = few ? rows_of_group<NI, true> : rows_of_group<NI, false>;
     const dim3 grid((s.M + rows - 1) / rows, s.G), block(kRowWaves * 64);
-    if (s.G == 1 && !s.res_row && !s.split && few)
+    if constexpr (NI % 4 == 0 && NP == 1) {
+        if (s.whole_sums) {
+            hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, ROW_WHOLE>), grid, block, 0, stream, g, s);
+            return;
+        }
+    }
+    if (s.G == 1 && !s.res_row && !s.split && few && (s.want_b & 1) && !(s.want_q & 1))
         hipLaunchKernelGGL((layernorm_tiled_kernel<NI, NP>), grid, block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
                            (const float*)(ws + (size_t)g.res[0] * 256), s.d_M, (const float*)(wt + (size_t)g.gamma[0] * 256),
                            (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
                            s.M, s.part_stride, s.eps);
     else if (few)
-        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true>), grid, block, 0, stream, g, s);
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, ROW_SHARES>), grid, block, 0, stream, g, s);
     else
-        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false>), grid, block, 0, stream, g, s);
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, ROW_SHARES>), grid, block, 0, stream, g, s);
 }
 
 }  // namespace
@@ -325,7 +387,7 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
 hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
 {
     if (s.G <= 0 || s.M <= 0) return hipSuccess;
-    if (s.G > kMaxGroup || s.H % 64 != 0 || s.n_parts < 1) return hipErrorInvalidValue;
+    if (s.G > kMaxGroup || s.H % 64 != 0 || s.n_parts < 1 || (s.whole_sums && (s.H % 256 != 0 || s.n_parts != 1))) return hipErrorInvalidValue;
     switch (s.H / 64) {
 #define X(NI)                                                    \
     case NI:                                                     \
@@ -345,19 +407,24 @@ hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, 
 
 hipError_t launch_embed_ln_tiled(const int32_t* ids, const int32_t* type_ids, int type_vocab, const int32_t* src, const int32_t* d_M, int B, int S,
                                  int H, int vocab, const void* word, const void* pos, const void* type, const float* gamma, const float* beta,
-                                 float eps, float* out_f32, void* out_bf16, hipStream_t stream)
+                                 float eps, float* out_f32, void* out_bf16, void* out_e4m3, hipStream_t stream)
 {
     const int M = B * S;
     if (M <= 0) return hipSuccess;
     if (H % 64 != 0 || !src || !d_M) return hipErrorInvalidValue;
-    const bool split = M <= 4096;            // 4096 x 768, 56 % of them kept: 7.6 -> 6.5 us; 8704: level; 32768: 33 us, 38 with the rows split
+    const bool whole = out_e4m3 != nullptr;  // (a model whose operands are E4M3)
+    const bool split = !whole && M <= 4096;  // 4096 x 768, 56 % of them kept: 7.6 -> 6.5 us; 8704: level; 32768: 33 us, 38 with the rows split
+    if (whole && H % 256 != 0) return hipErrorInvalidValue;
     switch (H / 64) {
 #define X(NI)                                                                                                                                \
     case NI: {                                                                                                                               \
+        constexpr RowSums kWhole = NI % 4 == 0 ? ROW_WHOLE : ROW_SHARES;                                                                     \
+        auto kfn = whole ? embed_ln_tiled_kernel<NI, false, kWhole>                                                                          \
+                         : split ? embed_ln_tiled_kernel<NI, true, ROW_SHARES> : embed_ln_tiled_kernel<NI, false, ROW_SHARES>;               \
         const int rows = split ? rows_of_group<NI, true> : rows_of_group<NI, false>;                                                         \
-        hipLaunchKernelGGL((split ? embed_ln_tiled_kernel<NI, true> : embed_ln_tiled_kernel<NI, false>), dim3((M + rows - 1) / rows),        \
-                           dim3(kRowWaves * 64), 0, stream, ids, type_ids, type_vocab, src, d_M, M, S, vocab, (const __bf16*)word,           \
-                           (const __bf16*)pos, (const __bf16*)type, gamma, beta, eps, out_f32, (__bf16*)out_bf16);                           \
+        hipLaunchKernelGGL(kfn, dim3((M + rows - 1) / rows), dim3(kRowWaves * 64), 0, stream, ids, type_ids, type_vocab, src, d_M, M, S,     \
+                           vocab, (const __bf16*)word, (const __bf16*)pos, (const __bf16*)type, gamma, beta, eps, out_f32,                   \
+                           (__bf16*)out_bf16, (unsigned char*)out_e4m3);                                                                     \
     } break;
         MT_FOR_WIDTH(X)
 #undef X

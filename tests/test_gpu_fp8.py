@@ -86,6 +86,47 @@ def test_fp8_contraction_vs_oracle(M, N, K):
     assert np.abs(o[:M, :N] - ref).max() <= 2e-4 * scale and (o[M] == 7.0).all() and (o[:, N:] == 7.0).all()
 
 
+ROWS_1X1, PAIR = 1, 5
+
+
+# Every form of the panel contraction on E4M3 operands and every tile height at remainders of rows, columns and K: the same bits as the row-major
+# kernel, which test_fp8_contraction_vs_oracle holds to the oracle.
+@pytest.mark.parametrize("form,height,problems,M,rows,N,K,act,out,w_std", [
+    (ROWS_1X1, 0, 1, 1, 1, 32, 256, 0, 1, 0.02), (ROWS_1X1, 0, 2, 70, 33, 192, 3328, 1, 2, 0.02), (ROWS_1X1, 0, 1, 40, 40, 64, 768, 0, 0, 1e-9),
+    (ROWS_1X1, 0, 2, 97, 65, 64, 896, 2, 2, 0.02), (ROWS_1X1, 0, 1, 70, 70, 160, 1536, 0, 1, 50.0), (ROWS_1X1, 0, 3, 33, 33, 96, 384, 0, 0, 0.02),
+    (PAIR, 1, 2, 65, 33, 320, 768, 2, 2, 0.02), (PAIR, 2, 1, 97, 97, 544, 1408, 0, 1, 0.02), (PAIR, 4, 1, 290, 257, 288, 768, 0, 0, 0.02),
+    (PAIR, 4, 2, 1024, 1001, 512, 1024, 1, 2, 0.02), (PAIR, 1, 3, 290, 257, 96, 640, 0, 0, 0.02),
+    (0, 0, 1, 300, 171, 768, 768, 0, 1, 0.02), (0, 0, 8, 300, 171, 768, 3072, 0, 1, 0.02), (0, 0, 1, 2080, 1900, 3072, 768, 1, 2, 0.02),
+])
+def test_fp8_panel_linear_forms(form, height, problems, M, rows, N, K, act, out, w_std):
+    say(f"fp8 panel linear: form {form} height {height}, {problems} x {rows}/{M} x {N} x {K}, act {act}, out {out}, weights {w_std}")
+    rng = np.random.default_rng(M + N + K + height)
+    bias = torch.zeros((problems, (N + 63) // 64 * 64), device="cuda")
+    pa, pw, want = [], [], []
+    for i in range(problems):
+        a = mt.e4m3_quantize((rng.standard_normal((M, K)) * 200).astype(np.float32))[1]
+        a[rows:] = 0x7F                                                          # NaN
+        scale, w = mt.e4m3_quantize((rng.standard_normal((N, K)) * w_std).astype(np.float32))
+        bias[i, :N] = dev((rng.standard_normal(N) * w_std).astype(np.float32))
+        pa.append(mt.to_panels_e4m3(dev(a).view(torch.float8_e4m3fn)))
+        slot = torch.full((256,), 127 - int(np.log2(scale)), dtype=torch.uint8, device="cuda")
+        pw.append(torch.cat([slot, mt.to_panels_e4m3(dev(w).view(torch.float8_e4m3fn)).flatten()]))
+        want.append(mt.op_linear_fp8(dev(a[:rows]), dev(w), 1.0 / scale, bias[i, :N].contiguous(), None, act, out).cpu())
+    pa, pw = torch.stack(pa), torch.stack(pw)
+    if out == 2:
+        pc = torch.full((problems, (M + 31) // 32, N // 16, 32, 16), 0x7F, dtype=torch.uint8, device="cuda")
+    else:
+        pc = torch.full((problems, (M + 31) // 32, N // 8, 32, 8), float("nan"), dtype=torch.float32 if out else torch.bfloat16, device="cuda")
+    size = lambda t: t[0].numel() * t.element_size()
+    mt.op_panel_linear(pa, pw.flatten()[256:], bias, pc, fp8=True, M=M, N=N, K=K, rows=dev(np.array([rows], np.int32)), problems=problems, stride_A=size(pa),
+                       stride_W=size(pw), stride_bias=size(bias), stride_C=size(pc), act_kind=act, out_f32=out, form=form, height=height)
+    for i in range(problems):
+        got = (mt.from_panels_e4m3(pc[i]).view(torch.uint8) if out == 2 else mt.from_panels(pc[i]))[:rows].cpu()
+        assert torch.equal(got, want[i].view(got.dtype)), (i, int((got != want[i].view(got.dtype)).sum()))
+    untouched = (rows + 31) // 32
+    assert (pc[:, untouched:] == 0x7F).all() if out == 2 else torch.isnan(pc[:, untouched:]).all()
+
+
 SMALL8 = ms.MTSpec("small_fp8", vocab=500, hidden=256, heads=4, ffn=512, max_pos=64, n_trunk_layers=3,
                    tasks=(ms.TaskSpec(3, 2, 2), ms.TaskSpec(1, 1, 3), ms.TaskSpec(2, 0, 1), ms.TaskSpec(0, 2, 4, token_level=True),
                           ms.TaskSpec(3, 2, 2)),
@@ -152,6 +193,38 @@ def test_fp8_small_model_whole_batches(stress, precision):
     say(f"  same checkpoints: bf16 mode {e_b:.4g}, {precision} mode {e_8:.4g}")
     assert e_b <= 2e-2 and e_8 > e_b
     mb.close()
+    model.close()
+
+
+@pytest.mark.parametrize("precision", ["fp8", "fp8_all"])
+@pytest.mark.parametrize("hidden,ffn,batch,seq", [(192, 320, 5, 40), (256, 256, 3, 300), (512, 768, 40, 70)])
+def test_fp8_layouts_and_attention_shapes(hidden, ffn, batch, seq, precision):
+    """MT_FP8_FFN, and hidden or ffn not a multiple of 256: the row-major kernels; otherwise the panel layout, with sequences of few and many
+    panels.  Plain and routed calls, a state that both an all-rows and a first-token layer read."""
+    spec = dataclasses.replace(SMALL8, hidden=hidden, heads=hidden // 64, ffn=ffn, max_pos=seq, batch=batch, seq=seq, len_lo=3, len_hi=seq, precision=precision,
+                               tasks=(ms.TaskSpec(3, 1, 2), ms.TaskSpec(1, 1, 3), ms.TaskSpec(1, 2, 5), ms.TaskSpec(2, 0, 1), ms.TaskSpec(0, 2, 4, token_level=True)))
+    say(f"fp8 layouts: hidden {hidden}, ffn {ffn}, {batch} x {seq}, {precision}")
+    model, orc = _model(spec, False, 0.05)
+    ids, mask, _ = ms.make_inputs(spec)
+    rows = np.arange(batch)[:6]
+    ref, ref_tok = orc.mt_forward(ids[rows], mask[rows], want_tokens=True)
+    got, tok = model.forward_tokens(dev(ids), dev(mask))
+    got, tok = got.cpu().numpy(), tok.cpu().numpy()
+    real = mask[rows].astype(bool)
+    bar = TOL[precision] * max(1.0, float(np.abs(ref).max()), float(np.abs(ref_tok[real]).max()))
+    err = max(float(np.abs(got[rows] - ref).max()), float(np.abs(tok[rows][real] - ref_tok[real]).max()))
+    say(f"  max |dlogit| {err:.4g} (bar {bar:.3g})")
+    assert err <= bar
+    route = (np.arange(batch)[:, None] + np.arange(spec.n_tasks)) % 2 == 0
+    route[:, 4] = False
+    out = torch.full((batch, spec.n_logits), 7.0, device="cuda")
+    model.forward_routed(dev(ids), dev(mask), route, out)
+    out, col = out.cpu().numpy(), 0
+    for t, task in enumerate(spec.tasks[:4]):
+        o = out[:, col:col + task.n_classes]
+        sel = route[rows, t]
+        assert np.abs(o[rows][sel] - ref[sel, col:col + task.n_classes]).max() <= bar and (o[~route[:, t]] == 7.0).all()
+        col += task.n_classes
     model.close()
 
 
