@@ -22,8 +22,10 @@ def dev(x, dtype=None):
     return t if dtype is None else t.to(dtype)
 
 
-# one row, full and one-over row blocks of the few-row kernel, of both tiles of the matrix-core kernel and of its large grid
-@pytest.mark.parametrize("M,N,K", [(1, 4, 64), (32, 100, 192), (33, 68, 64), (65, 64, 128), (31, 32, 832), (2113, 2052, 64)])
+# one row, full and one-over row blocks of the few-row kernel, of each tile of the matrix-core kernel (fewer K slices than ring stages, odd numbers of
+# them, and more), on both sides of the rule's lines
+@pytest.mark.parametrize("M,N,K", [(1, 4, 64), (32, 100, 192), (33, 68, 64), (65, 64, 128), (31, 32, 832), (2113, 2052, 64), (70, 100, 128), (161, 228, 640),
+                                   (385, 1056, 128), (700, 1000, 192)])
 @pytest.mark.parametrize("act", [0, 1])
 def test_gemm_f32_tiles(M, N, K, act):
     print(f"gemm_f32 {M}x{N}x{K} act {act}", flush=True)
