@@ -2,7 +2,8 @@
 // q~[b][a] = Wk_a^T (Wq_a x_b + bq_a) the score of key j is q~ . x_j up to a constant that the softmax drops, and the head's context
 // is Wv_a (sum_j p_j x_j) + bv_a.  Two launches per group of tasks (the contexts are one more, gemm_tiled_rows_kernel):
 //   first_query_kernel   one workgroup per (task, 32 sequences, head): query of the sequences' first rows (gathered before: in place, 16
-//                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences), then q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
+//                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences; of up to kInPlace
+//                        sequences that costs less than the launch), then q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
 //                        fragments are in flight at once.
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
 //                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
@@ -22,7 +23,7 @@ constexpr int kHeadsPad = 16;
 constexpr int kTerms = 2;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, FirstTokenGroup g)
+__global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, const int32_t* seq_start, int max_rows, FirstTokenGroup g)
 {
     constexpr int U = 12, MAXP = 8;
     __shared__ __attribute__((aligned(16))) float part[4][2][4][64][4];
@@ -46,7 +47,14 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A
     float4 bv[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const float4*>(g.bq[grp] + a * 64 + j * 32 + wave * 8 + half * 4);
-    const unsigned char* x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)yb * pw + (size_t)wave * steps * 1024 + lane * 16;
+    const unsigned char* x;
+    if (seq_start) {                         // in place: this lane's row of all rows
+        const int row = min(seq_start[min(b0 + l32, B - 1)], max_rows - 1);
+        x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)(row >> 5) * pw + half * 512 + (row & 31) * 16;
+    } else {
+        x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)yb * pw + lane * 16;
+    }
+    x += (size_t)wave * steps * 1024;
     f32x16 acc[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -257,12 +265,12 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
 
 }  // namespace
 
-hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream)
+hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream, const int32_t* seq_start, int max_rows)
 {
     if (G <= 0 || B <= 0) return hipSuccess;
     if (G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
     const int nb = (B + 31) / 32, pairs = A * G;
-    hipLaunchKernelGGL(first_query_kernel, dim3((pairs + 7) / 8 * 8 * nb), dim3(256), 0, stream, B, H, A, nb, pairs, g);
+    hipLaunchKernelGGL(first_query_kernel, dim3((pairs + 7) / 8 * 8 * nb), dim3(256), 0, stream, B, H, A, nb, pairs, seq_start, max_rows, g);
     return hipGetLastError();
 }
 

@@ -171,7 +171,9 @@ struct FirstTokenGroup {
     void* qt[kMaxGroup];            // bf16 [B][16][H], rows from the number of heads on unused
     void* xbar[kMaxGroup];          // per head a bf16 [B][H] panel matrix, xbar_stride elements apart
 };
-hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream);
+// up to so many sequences' first rows are read in place (seq_start given: `first` is not used, x has max_rows rows)
+constexpr int kInPlace = 8;
+hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream, const int32_t* seq_start = nullptr, int max_rows = 0);
 hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
                                int64_t xbar_stride, hipStream_t stream);
 

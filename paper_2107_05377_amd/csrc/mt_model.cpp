@@ -1081,11 +1081,14 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
         fg.qt[i] = ws + io[i].cls->qt;
         fg.xbar[i] = ws + io[i].cls->xbar;
     }
-    L.begin(MT_K_ATTN);
-    L.check(launch_copy_rows_tiled(rc, n_copy, rm.seq_start, nullptr, B, M, H, L.st));
-    L.end();
+    const bool in_place = B <= kInPlace;
+    if (!in_place) {
+        L.begin(MT_K_ATTN);
+        L.check(launch_copy_rows_tiled(rc, n_copy, rm.seq_start, nullptr, B, M, H, L.st));
+        L.end();
+    }
     L.begin(MT_K_GEMM_FIRST);
-    L.check(launch_first_query(fg, n, B, H, A, L.st));
+    L.check(launch_first_query(fg, n, B, H, A, L.st, in_place ? rm.seq_start : nullptr, M));
     L.end();
     L.begin(MT_K_ATTN);
     L.check(launch_first_attend(fg, n, rm.seq_start, rm.seq_len, B, S, H, A, xbar_stride, L.st));
