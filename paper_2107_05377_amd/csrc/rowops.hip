@@ -308,6 +308,43 @@ __global__ __launch_bounds__(256) void row_place_kernel(int B, int S, int32_t* _
     }
 }
 
+// Both passes in one launch, for batches of up to kMapOnce positions: every workgroup counts the real tokens before its sequence itself (8 x 64 tokens:
+// a pass 446 -> 444 us with the query's rows read in place; 32 x 128 level).
+constexpr int kMapOnce = 2048;
+__global__ __launch_bounds__(256) void row_map_kernel(const int32_t* __restrict__ mask, int B, int S, RowMap map)
+{
+    __shared__ int part[4], wave_cnt[4];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int acc = 0;
+#pragma unroll 8
+    for (int i = tid; i < b * S; i += 256) acc += mask[i] != 0;
+    acc = wave_sum_int(acc);
+    if (lane == 0) part[wave] = acc;
+    __syncthreads();
+    const int start = part[0] + part[1] + part[2] + part[3];
+    int base = start;
+    for (int c0 = 0; c0 < S; c0 += 256) {
+        const int s = c0 + tid, p = b * S + s;
+        const bool flag = s < S && mask[p] != 0;
+        const unsigned long long bal = __ballot(flag);
+        if (lane == 0) wave_cnt[wave] = __popcll(bal);
+        __syncthreads();
+        int row = base + __popcll(bal & ((1ull << lane) - 1ull));
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) row += wave_cnt[w];
+            base += wave_cnt[w];
+        }
+        if (s < S) map.row_of[p] = flag ? row : -1;
+        if (flag) map.src[row] = p;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        map.seq_start[b] = start;
+        map.seq_len[b] = base - start;
+        if (b == B - 1) *map.n_rows = base;
+    }
+}
+
 __global__ __launch_bounds__(256) void unpack_rows_kernel(const float* __restrict__ x, const int32_t* __restrict__ row_of, int n_pos,
                                                           int H, float* __restrict__ out, int tiled)
 {
@@ -434,9 +471,9 @@ __global__ __launch_bounds__(256) void token_classifier_kernel(TokGroup g, int n
 }
 
 // The same for H = NV * 256: one wavefront per position keeps its row in registers (NV float4 per lane) and takes
-// the classes four at a time, so the loads of four weight rows are in flight together.
+// the classes (blockIdx.z per_z ..) four at a time, so the loads of four weight rows are in flight together.
 template <typename TW, int NV, bool TILED>
-__global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, int n_pos, int64_t ldo,
+__global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, int n_pos, int per_z, int64_t ldo,
                                                                     const int32_t* __restrict__ row_of,
                                                                     const int32_t* __restrict__ n_rows)
 {
@@ -445,12 +482,13 @@ __global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, 
     const int lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (p >= n_pos) return;
-    const int C = g.C[grp];
+    const int first = blockIdx.z * per_z, C = min(g.C[grp], first + per_z);
+    if (first >= C) return;
     float* out = g.out[grp] + (size_t)p * ldo;
     const int r = row_of[p];
     if (r == kRowSkip) return;                        // not this launch's position: left untouched
     if (r < 0 || r >= *n_rows) {
-        for (int c = lane; c < C; c += 64) out[c] = 0.f;
+        for (int c = first + lane; c < C; c += 64) out[c] = 0.f;
         return;
     }
     const float* x = g.x[grp] + (TILED ? tiled_offset(r, 0, H) : (size_t)r * H);
@@ -461,7 +499,7 @@ __global__ __launch_bounds__(256) void token_classifier_rows_kernel(TokGroup g, 
         xv[v] = load4<float>(x + (TILED ? (col >> 3) * 256 + (col & 7) : col));
     }
     const TW* W = static_cast<const TW*>(g.Wc[grp]);
-    for (int c0 = 0; c0 < C; c0 += 4) {
+    for (int c0 = first; c0 < C; c0 += 4) {
         float acc[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -624,12 +662,17 @@ hipError_t launch_token_classifier(const TokGroup& g, int G, int n_pos, int H, i
     if (G <= 0 || n_pos <= 0) return hipSuccess;
     if (G > kMaxGroup || !row_of || !n_rows || H < 1 || (tiled && !w_bf16)) return hipErrorInvalidValue;
     if (H % 256 == 0 && H <= 1280) {          // classifier rows are then 16-byte aligned for either element type
-        const dim3 rgrid((n_pos + 3) / 4, G);
+        int most = 1;
+        for (int i = 0; i < G; ++i) most = std::max(most, g.C[i]);
+        // four classes are one memory round trip: few positions share theirs out (512 positions, 30, 16 and 9 classes: 17.4 -> 10.1 us)
+        const int per_z = (long)n_pos * G <= 8192 ? 4 : most;
+        const dim3 rgrid((n_pos + 3) / 4, G, (most + per_z - 1) / per_z);
+        if (rgrid.z > 65535) return hipErrorInvalidValue;
 #define MT_TOK_ROWS(NV)                                                                                                            \
     case NV:                                                                                                                       \
-        if (tiled) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, true>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows); \
-        else if (w_bf16) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows); \
-        else hipLaunchKernelGGL((token_classifier_rows_kernel<float, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, ldo, row_of, n_rows);       \
+        if (tiled) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, true>), rgrid, dim3(256), 0, stream, g, n_pos, per_z, ldo, row_of, n_rows); \
+        else if (w_bf16) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, per_z, ldo, row_of, n_rows); \
+        else hipLaunchKernelGGL((token_classifier_rows_kernel<float, NV, false>), rgrid, dim3(256), 0, stream, g, n_pos, per_z, ldo, row_of, n_rows);       \
         break;
         switch (H / 256) {
             MT_TOK_ROWS(1) MT_TOK_ROWS(2) MT_TOK_ROWS(3) MT_TOK_ROWS(4) MT_TOK_ROWS(5)
@@ -740,6 +783,10 @@ hipError_t launch_count_bad_first_tokens(const int32_t* mask, int B, int S, int3
 hipError_t launch_build_row_map(const int32_t* mask, int B, int S, const RowMap& map, hipStream_t stream)
 {
     if (B <= 0 || S <= 0) return hipSuccess;
+    if ((long)B * S <= kMapOnce) {
+        hipLaunchKernelGGL(row_map_kernel, dim3(B), dim3(256), 0, stream, mask, B, S, map);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(row_rank_kernel, dim3(B), dim3(256), 0, stream, mask, S, map.row_of, map.seq_len);
     hipLaunchKernelGGL(row_place_kernel, dim3(B), dim3(256), 0, stream, B, S, map.row_of, map.seq_len, map.seq_start, map.src,
                        map.n_rows);

@@ -394,3 +394,27 @@ def test_layernorm_panels_few_and_many_rows_give_the_same_bits(H, parts):
     # the sums of up to 5 float32 values round at 2^-24 of values up to 4 standard deviations of the row's offset
     bound = 2.0**-18 * (np.abs(gamma) * (1 + np.abs(n)) + np.abs(beta)) * np.maximum(1, np.abs(v).max(1, keepdims=True) / v.std(1, keepdims=True))
     assert (np.abs(got[0][0] - (gamma * n + beta)) <= bound).all()
+
+
+@pytest.mark.parametrize("batch,seq", [(9, 5), (60, 4), (70, 30)])
+def test_heads_of_many_unequal_tasks(batch, seq):
+    """18 tasks of 1 to 50 classes: the classifier's plain grid (9 sequences) and its list of classes; token heads of few and many positions; the row map in
+    one launch (up to 2048 positions) and in two; first-token rows read in place (up to 8 sequences wanted) and gathered."""
+    classes = (2, 3, 5, 8, 12, 1, 4, 30, 2, 6, 3, 2, 16, 4, 2, 9, 50, 7)
+    tasks = tuple(ms.TaskSpec(1, 1 + t % 2, c, token_level=t in (7, 12)) for t, c in enumerate(classes))
+    spec = ms.MTSpec("heads", vocab=300, hidden=256, heads=4, ffn=256, max_pos=64, n_trunk_layers=1, tasks=tasks, precision="bf16", batch=batch, seq=seq,
+                     len_lo=1, len_hi=seq, input_seed=3)
+    print(f"heads of 18 tasks: {batch} x {seq}", flush=True)
+    model, (trunk, params) = mt.load_synthetic(spec, keep_params=True, std=0.05)
+    ids, mask, _ = ms.make_inputs(spec)
+    got, tok = model.forward_tokens(dev(ids), dev(mask))
+    got, tok = got.cpu().numpy(), tok.cpu().numpy()
+    rows = np.arange(batch)[-7:]
+    ref, ref_tok = oracle.Oracle(spec, trunk, params).mt_forward(ids[rows], mask[rows], want_tokens=True)
+    real = mask[rows].astype(bool)
+    scale = max(1.0, np.abs(ref).max(), np.abs(ref_tok[real]).max())
+    assert np.abs(got[rows] - ref).max() <= 2e-2 * scale and np.abs(tok[rows][real] - ref_tok[real]).max() <= 2e-2 * scale
+    assert (tok[~mask.astype(bool)] == 0).all()
+    few = model.forward_tokens(dev(ids[:5].copy()), dev(mask[:5].copy()))[0].cpu().numpy()      # five sequences: in place
+    assert np.abs(few - got[:5]).max() <= 1e-2 * scale
+    model.close()
