@@ -626,12 +626,12 @@ __global__ __launch_bounds__(256, TM * TN > 1 ? 1 : 2) void gemm_tiled_rows_grou
 // is the same bits in either), operands straight from global memory to registers, the next batch of steps in flight while one is
 // multiplied.  290 rows x 2304 / 768 / 3072 x 768, x 768 x 3072: 5.4, 4.2, 5.8, 9.2 us, tiles 7.5, 7.4, 8.2, 13.3.
 template <int OUT, int ACT>
-__global__ __launch_bounds__(256, 2) void gemm_tiled_rows_fp8_kernel(const int32_t* d_M, TiledGroup g, TiledShape s)
+__global__ __launch_bounds__(256, 2) void gemm_tiled_rows_fp8_kernel(const int32_t* d_M, int pm0, TiledGroup g, TiledShape s)
 {
     constexpr int U = 6;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = blockIdx.z;
     const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(g.A));      // in flight with the first operands
-    const int panels_n = s.N >> 5, pn = blockIdx.x * 4 + wave, pm = blockIdx.y, steps = s.K >> 5;
+    const int panels_n = s.N >> 5, pn = blockIdx.x * 4 + wave, pm = pm0 + blockIdx.y, steps = s.K >> 5;
     if (pn >= panels_n) return;
     const unsigned char* w = static_cast<const unsigned char*>(g.W) + (size_t)g.w[grp] * 256;
     const int scale = t_scale(w);
@@ -759,9 +759,12 @@ template <int OUT, int ACT>
 hipError_t launch_form_fp8(const TiledGroup& g, const TiledShape& s, int form, int force, hipStream_t stream)
 {
     if (form == TILED_PAIR) return launch_tiles<1, 4, OUT, ACT, true>(g, s, device_cu_count(), force, stream);
-    const dim3 grid((s.N / 32 + 3) / 4, (s.M + 31) / 32, s.G);
-    if (form != TILED_ROWS_1X1 || grid.y > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((gemm_tiled_rows_fp8_kernel<OUT, ACT>), grid, dim3(256), 0, stream, s.d_M, g, s);
+    if (form != TILED_ROWS_1X1) return hipErrorInvalidValue;
+    const int panels = (s.M + 31) / 32;
+    constexpr int kPanels = kLaunchPanels / 2;                       // of a launch (a grid takes 65535)
+    for (int pm0 = 0; pm0 < panels; pm0 += kPanels)
+        hipLaunchKernelGGL((gemm_tiled_rows_fp8_kernel<OUT, ACT>), dim3((s.N / 32 + 3) / 4, std::min(panels - pm0, kPanels), s.G), dim3(256), 0, stream, s.d_M,
+                           pm0, g, s);
     return hipGetLastError();
 }
 

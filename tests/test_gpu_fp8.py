@@ -196,6 +196,21 @@ def test_fp8_small_model_whole_batches(stress, precision):
     model.close()
 
 
+def test_fp8_panel_linear_of_more_row_panels_than_a_grid_takes():
+    M, N, K = 65536 * 32 + 33, 32, 256
+    say(f"fp8 panel linear: few-row form, {M} x {N} x {K}")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    pa = torch.randint(0, 0x38, ((M + 31) // 32, K // 16, 32, 16), dtype=torch.uint8, device="cuda", generator=gen)      # values of 0 to 0.94
+    scale, w = mt.e4m3_quantize((np.random.default_rng(3).standard_normal((N, K)) * 0.02).astype(np.float32))
+    slot = torch.full((256,), 127 - int(np.log2(scale)), dtype=torch.uint8, device="cuda")
+    pw = torch.cat([slot, mt.to_panels_e4m3(dev(w).view(torch.float8_e4m3fn)).flatten()])
+    pc = torch.full(((M + 31) // 32, N // 8, 32, 8), float("nan"), device="cuda")
+    mt.op_panel_linear(pa, pw[256:], None, pc, fp8=True, M=M, N=N, K=K, out_f32=1, form=ROWS_1X1)
+    for lo in (0, 32767, 32768, 65535, pc.shape[0] - 2):                         # panels: the first and last of a launch
+        a = mt.from_panels_e4m3(pa[lo:lo + 2]).view(torch.uint8)
+        assert torch.equal(mt.from_panels(pc[lo:lo + 2]).cpu(), mt.op_linear_fp8(a, dev(w), 1.0 / scale, None, None, 0, 1).cpu()), lo
+
+
 @pytest.mark.parametrize("precision", ["fp8", "fp8_all"])
 @pytest.mark.parametrize("hidden,ffn,batch,seq", [(192, 320, 5, 40), (256, 256, 3, 300), (512, 768, 40, 70)])
 def test_fp8_layouts_and_attention_shapes(hidden, ffn, batch, seq, precision):
