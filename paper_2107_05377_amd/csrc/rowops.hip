@@ -665,9 +665,9 @@ hipError_t launch_token_classifier(const TokGroup& g, int G, int n_pos, int H, i
         int most = 1;
         for (int i = 0; i < G; ++i) most = std::max(most, g.C[i]);
         // four classes are one memory round trip: few positions share theirs out (512 positions, 30, 16 and 9 classes: 17.4 -> 10.1 us)
-        const int per_z = (long)n_pos * G <= 8192 ? 4 : most;
+        // as far as the grid's third dimension goes (4 x 65535 classes)
+        const int per_z = (long)n_pos * G <= 8192 && most <= 4 * 65535 ? 4 : most;
         const dim3 rgrid((n_pos + 3) / 4, G, (most + per_z - 1) / per_z);
-        if (rgrid.z > 65535) return hipErrorInvalidValue;
 #define MT_TOK_ROWS(NV)                                                                                                            \
     case NV:                                                                                                                       \
         if (tiled) hipLaunchKernelGGL((token_classifier_rows_kernel<__bf16, NV, true>), rgrid, dim3(256), 0, stream, g, n_pos, per_z, ldo, row_of, n_rows); \

@@ -518,19 +518,18 @@ hipError_t launch_classifier_tiled(const ClsGroup& g, int G, int B, int H, int m
     if (G > kMaxGroup || H % 8 != 0) return hipErrorInvalidValue;
     // Workgroups of the plain grid, of which those beyond a task's classes do nothing: 21 tasks of 2 to 50 classes, 16 sequences 4368 of them, 4.4 us
     // (the list 5.0); 272 sequences 74 thousand, 38 us (20).
+    // (a grid has room for 4 x 65535 groups of classes in the list.)
     const dim3 plain(B, G, (maxC + 3) / 4);
-    if ((long)plain.x * plain.y * plain.z <= 8192 || H > 512 * kClsChunks) {
+    ClsFirst first;
+    long total = 0;
+    for (int i = 0; i < kMaxGroup; ++i) {
+        first.at[i] = i < G ? (int32_t)total : 0;
+        if (i < G) total += (g.C[i] + kClsCols - 1) / kClsCols;
+    }
+    if ((long)plain.x * plain.y * plain.z <= 8192 || H > 512 * kClsChunks || total > 4 * 65535) {
         hipLaunchKernelGGL(classifier_tiled_kernel, plain, dim3(256), 0, stream, g, H, ldo, out_row);
         return hipGetLastError();
     }
-    ClsFirst first;
-    long total = 0;
-    for (int i = 0; i < G; ++i) {
-        first.at[i] = (int32_t)total;
-        total += (g.C[i] + kClsCols - 1) / kClsCols;
-    }
-    for (int i = G; i < kMaxGroup; ++i) first.at[i] = 0;
-    if (total > 4 * 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(classifier_list_kernel, dim3((B + kClsRows - 1) / kClsRows, (unsigned)((total + 3) / 4)), dim3(256), 0, stream, g, first, G, (int)total, B,
                        H, ldo, out_row);
     return hipGetLastError();
