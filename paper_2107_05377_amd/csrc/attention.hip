@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
                 for (int e = 0; e < 16; ++e) sc[j][e] = -INFINITY;
             }
         }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+        mloc = lane_pair_max<32>(mloc);
         const float m_new = fmaxf(m_run, mloc);
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);     // 0 on the first chunk (m_run = -inf)
         float lsum = 0.f;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
                 sc[j][e] = p;
                 lsum += p;
             }
-        lsum += __shfl_xor(lsum, 32, 64);
+        lsum = lane_pair_sum<32>(lsum);
         l_run = l_run * alpha + lsum;
         m_run = m_new;
 #pragma unroll
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(AttnGroup g, co
             sc[e] = t;
             mloc = fmaxf(mloc, t);
         }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));            // finite: the block's first key exists
+        mloc = lane_pair_max<32>(mloc);            // finite: the block's first key exists
         const float m_new = fmaxf(m_run, mloc);
         const float alpha = expf(m_run - m_new);
         float lsum = 0.f;

@@ -30,18 +30,6 @@ namespace {
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float other_half_max(float v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ __forceinline__ float halves_sum(float v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // two neighbouring chunks (8 columns each) of a context block: 4 of a chunk's columns per lane -> 8, the lower half wavefront the
 // first chunk, the upper the second
 __device__ __forceinline__ u32x4 pack_chunks(const float (&v)[8])
@@ -147,7 +135,7 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
                 float mx = sc[0];
 #pragma unroll
                 for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
-                mx = other_half_max(mx);
+                mx = lane_pair_max<32>(mx);
                 if (__any(q_real && mx * kScale > m_run)) {
                     const float m_new = fmaxf(m_run, mx * kScale), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                     m_run = m_new;
@@ -175,7 +163,7 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
                 kb = kn;
                 load_v(kb);
             }
-            l_run = halves_sum(l_run);
+            l_run = lane_pair_sum<32>(l_run);
         }
         unsigned char* ctx = base_ctx + (size_t)g.ctx[grp] * 256 + (size_t)qp * H * 64 + a * 4096 + lane * 16;
         if constexpr (KS == 1) {

@@ -29,24 +29,69 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
+// The values of a lane and of the lane whose number differs in the bit M, as two registers of every lane: one or two vector instructions, where a
+// shuffle is an LDS round trip of about 0.1 us in a chain that little else covers.  M = 4: only of values that agree in lanes 8 apart.
+template <int M>
+__device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& a, uint32_t& b)
+{
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "");
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        constexpr int ctrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x124 : 0x128;     // quad_perm [1,0,3,2], [2,3,0,1]; row_ror:4, :8
+        a = v;
+        b = __builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xF, 0xF, false);
+    }
+}
+template <int M>
+__device__ __forceinline__ float lane_pair_sum(float v)
+{
+    uint32_t a, b;
+    lane_pair<M>(__builtin_bit_cast(uint32_t, v), a, b);
+    return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+template <int M>
+__device__ __forceinline__ float lane_pair_max(float v)
+{
+    uint32_t a, b;
+    lane_pair<M>(__builtin_bit_cast(uint32_t, v), a, b);
+    return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+}
+template <int M>
+__device__ __forceinline__ int lane_pair_sum(int v)
+{
+    uint32_t a, b;
+    lane_pair<M>((uint32_t)v, a, b);
+    return (int)(a + b);
+}
+
 // Sum / max over the 64 lanes of a wavefront; every lane receives the result.
-__device__ inline float wave_sum(float v)
+template <typename T>
+__device__ __forceinline__ T wave_sum_any(T v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = lane_pair_sum<32>(v);
+    v = lane_pair_sum<16>(v);
+    v = lane_pair_sum<8>(v);
+    v = lane_pair_sum<4>(v);
+    v = lane_pair_sum<2>(v);
+    return lane_pair_sum<1>(v);
 }
-__device__ inline int wave_sum_int(int v)
+__device__ __forceinline__ float wave_sum(float v) { return wave_sum_any(v); }
+__device__ __forceinline__ int wave_sum_int(int v) { return wave_sum_any(v); }
+__device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ inline float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+    v = lane_pair_max<32>(v);
+    v = lane_pair_max<16>(v);
+    v = lane_pair_max<8>(v);
+    v = lane_pair_max<4>(v);
+    v = lane_pair_max<2>(v);
+    return lane_pair_max<1>(v);
 }
 
 // GELU(x) = x * Phi(x).  Exact form through erff; tanh form as the published approximation.

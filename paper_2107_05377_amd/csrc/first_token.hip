@@ -205,8 +205,8 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[h][e]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * kScale;
+        mx = lane_pair_max<16>(mx);
+        mx = lane_pair_max<32>(mx) * kScale;
         if (__any(l16 < A && mx > m_run + 8.f)) {                            // the maximum follows only when a score exceeds it by 2^8
             const float m_new = fmaxf(m_run, mx), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
@@ -250,8 +250,8 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
         if (kb + 2 < p1) fetch(xa, kb + 2);
         block(xb, kb + 1, 1);
     }
-    l_run += __shfl_xor(l_run, 16, 64);
-    l_run += __shfl_xor(l_run, 32, 64);
+    l_run = lane_pair_sum<16>(l_run);
+    l_run = lane_pair_sum<32>(l_run);
     if (l16 >= A) return;
     const float inv = 1.0f / l_run;
     __bf16* out = static_cast<__bf16*>(g.xbar[grp]) + l16 * xbar_stride + tiled_offset(b, wave * 128 + l4 * 4, H);

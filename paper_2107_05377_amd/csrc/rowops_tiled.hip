@@ -15,10 +15,10 @@ namespace {
 // Sum of a row's partial values over the 16 lanes that hold it.
 __device__ __forceinline__ float row_sum(float v)
 {
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
+    v = lane_pair_sum<1>(v);
+    v = lane_pair_sum<8>(v);
+    v = lane_pair_sum<16>(v);
+    v = lane_pair_sum<32>(v);
     return v;
 }
 
@@ -47,10 +47,10 @@ enum RowSums : int { ROW_SHARES, ROW_WHOLE };
 __device__ __forceinline__ float row_sum_whole(const float (&part)[4])
 {
     float v = (part[0] + part[2]) + (part[1] + part[3]);
-    v += __shfl_xor(v, 32, 64);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 1, 64);
+    v = lane_pair_sum<32>(v);
+    v = lane_pair_sum<16>(v);
+    v = lane_pair_sum<8>(v);
+    v = lane_pair_sum<1>(v);
     return v;
 }
 
