@@ -230,20 +230,25 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
             for (int i = 0; i < TMI; ++i) acc[i][jn] = b0;
         }
     };
-    // Results are stored past the second-level caches, whose 4 MB hold the operands that a compute unit's neighbours share: another die reads
-    // them, and a kernel ends by writing back what is dirty.  18.6 k rows, 768: QKV 67.5 -> 65.8 us, FFN1 87.0 -> 84.8, FFN2 78.8 -> 76.5, 8
-    // problems of 2318 rows 290 -> 278 for the four of a layer, one 68 -> 65.5 (without any store at all: 244, 264, 63).
+    // How results are stored, TiledShape::stream (launch_tiles has the rule): past the second-level caches, or written through them.  Either way a kernel does
+    // not end by writing back what is dirty (its readers run on other dies).
+    auto store16 = [&](const u32x4& v, __amdgpu_buffer_rsrc_t C, int at) {
+        if (s.stream) __builtin_amdgcn_raw_buffer_store_b128(v, C, at, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b128(v, C, at, 0, 16);
+    };
     auto store_block = [&](const Ref& t, const f32x16& a, int pm, int pn) {
         if (pm >= panels_m || pn >= panels_n) return;                        // uniform
         unsigned char* Cb = static_cast<unsigned char*>(g.C) + (size_t)g.c[t.grp] * 256;
         if constexpr (OUT == TILED_E4M3) {
-            __builtin_nontemporal_store(t_pack_e4m3<ACT>(a), reinterpret_cast<u32x4*>(t_e4m3_at(Cb, s.ldc, pm, pn, lane)));
+            const auto C = t_rsrc(t_e4m3_at(Cb, s.ldc, pm, pn, 0), 2048);
+            store16(t_pack_e4m3<ACT>(a), C, (lane >> 5) * 1024 + (lane & 31) * 16);
         } else if constexpr (OUT == TILED_F32) {
-            float* c = reinterpret_cast<float*>(Cb) + (size_t)t.split * s.split_stride + (size_t)pm * 32 * s.ldc + pn * 1024 + (lane & 31) * 8 + (lane >> 5) * 4;
+            const auto C = t_rsrc(reinterpret_cast<float*>(Cb) + (size_t)t.split * s.split_stride + (size_t)pm * 32 * s.ldc + pn * 1024, 4096);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) __builtin_nontemporal_store(f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]}, reinterpret_cast<f32x4*>(c + q * 256));
+            for (int q = 0; q < 4; ++q)
+                store16(__builtin_bit_cast(u32x4, f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]}), C, (lane & 31) * 32 + (lane >> 5) * 16 + q * 1024);
         } else {
-            __bf16* c = reinterpret_cast<__bf16*>(Cb) + (size_t)pm * 32 * s.ldc + pn * 1024 + lane * 8;
+            const auto C = t_rsrc(reinterpret_cast<__bf16*>(Cb) + (size_t)pm * 32 * s.ldc + pn * 1024, 2048);
             [[maybe_unused]] f32x16 tr;
 #pragma unroll
             for (int qp = 0; qp < 2; ++qp) {
@@ -278,13 +283,13 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
                                 bf16x8 v;
 #pragma unroll
                                 for (int e = 0; e < 8; ++e) v[e] = (__bf16)tr[h * 8 + e];
-                                __builtin_nontemporal_store(v, reinterpret_cast<bf16x8*>(c + h * 512));
+                                store16(__builtin_bit_cast(u32x4, v), C, lane * 16 + h * 1024);
                             }
                         }
                         continue;
                     }
                 }
-                __builtin_nontemporal_store(r, reinterpret_cast<u32x4*>(c + qp * 512));
+                store16(r, C, lane * 16 + qp * 1024);
             }
         }
     };
@@ -710,7 +715,13 @@ hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int 
     const long tiles = (long)(((s.M + 31) / 32 + low - 1) / low) * ((s.N / 32 + 8 / KW - 1) / (8 / KW)) * s.G * s.splits;
     const long slots = (long)n_cu * ((MAXT <= 4 && KW == 1) ? 2 : 1);
     const int n_wg = (int)(tiles < slots ? (tiles < kXcds ? kXcds : tiles) : slots);
-    hipLaunchKernelGGL(kfn, dim3(n_wg), dim3(256), bytes, stream, g, s, n_cu, force);
+    // Large results go past the second-level caches, whose 4 MB hold the operands that a compute unit's neighbours share, and pay for it in the kernels
+    // that read them (LayerNorm of 2.3 k rows 13.1 -> 14.0 us, attention 11.8 -> 12.6); small ones are written through.  Passes with ordinary stores,
+    // all past, all written through: base 8 x 32 x 128 6094, 5990, 6074 us; 32 x 128 1340, 1312, 1314; 7 x 509 1424, 1420, 1409; routed 32 x 128 1587, 1621,
+    // 1600.  The line, by the row bound: 32 x 128 rows of one problem have 13 to 25 MB, 8 problems of them or 256 x 128 rows 100 MB and more.
+    TiledShape t = s;
+    t.stream = (long)s.M * s.N * s.G * s.splits * (OUT == TILED_F32 ? 4 : OUT == TILED_BF16 ? 2 : 1) > (64l << 20);
+    hipLaunchKernelGGL(kfn, dim3(n_wg), dim3(256), bytes, stream, g, t, n_cu, force);
     return hipGetLastError();
 }
 

@@ -100,6 +100,7 @@ struct TiledShape {
     // kScaleSlot bytes in front of a weight matrix stands what its values are multiplied by, as an E8M0 exponent in each byte of an int32.
     // E4M3 results at unit scale, saturating.
     int32_t f8;
+    int32_t stream;             // set by the launch: results are stored past the second-level caches
 };
 enum TiledOut : int { TILED_BF16 = 0, TILED_F32 = 1, TILED_E4M3 = 2 };
 constexpr size_t kScaleSlot = 256;
