@@ -2,7 +2,7 @@
 // rows of a panel, lane = (chunk in 8, row in 4, half of the chunk), so that a load instruction covers 8 neighbouring chunks of 128
 // contiguous bytes of float32 (whole lines); the wavefronts of a workgroup complete the 128-byte lines of the bf16 copy.
 // A launch of many rows is bound by HBM (or the last-level cache): a row is read and written once, a wavefront has all columns of its
-// rows, and no barrier is needed.  A launch of few rows is a chain of latencies: there the columns are dealt out to as many wavefronts as
+// rows, and no barrier is needed.  A launch of few rows is a chain of latencies, one of some thousand has too few workgroups: there the columns are dealt out to as many wavefronts as
 // they have shares, each of which waits for a quarter of the loads (36 rows of 768, one and four partial results: 4.5 and 5.3 us a launch,
 // 3.4 and 3.6 so; 18.6 k rows the other way, 38 and 40 us).  Both form mean and variance from those of the shares: the same bits.
 #include "kernels.h"
@@ -167,21 +167,21 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
 }
 
 // out = LayerNorm(sum of NP partial products + residual) (the bias is already in the first product).  All loads of a lane are issued
-// before the first use, in a launch of few rows (FEW) even before the row count has arrived: rows beyond it are memory of the
+// before the first use, in a launch of few rows (EARLY) even before the row count has arrived: rows beyond it are memory of the
 // operands all the same, but of a large padded batch reading them would be real traffic.  The pointers are leading scalar arguments,
 // which the command processor preloads.
-template <int NI, int NP, bool FEW, RowSums SUMS>
+template <int NI, int NP, bool SPLIT, bool EARLY, RowSums SUMS>
 __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float* res, const float* gamma, const float* beta, const RowOut& out,
                                                      const int32_t* d_M, int M, int64_t part_stride, const int32_t* res_row, int res_rows, float eps)
 {
-    constexpr int H = NI * 64, W = FEW ? row_shares(NI) : 1, NW = NI / W;
+    constexpr int H = NI * 64, W = SPLIT ? row_shares(NI) : 1, NW = NI / W;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_here = *(d_M ? d_M : reinterpret_cast<const int32_t*>(x));
     const int last = (M + 31) / 32 * 32 - 1;                                  // rows of the last panel exist
-    if (!FEW && d_M) M = min(M, rows_here);
-    const int row0 = blockIdx.x * rows_of_group<NI, FEW>, row = row0 + wave / W * 4 + ((lane >> 1) & 3);
+    if (!EARLY && d_M) M = min(M, rows_here);
+    const int row0 = blockIdx.x * rows_of_group<NI, SPLIT>, row = row0 + wave / W * 4 + ((lane >> 1) & 3);
     const int at = (lane & 1) * 4 + (wave % W * NW * 8 + (lane >> 3)) * 256;
-    if (!FEW && row0 >= M) return;                                            // (the whole workgroup, here and below)
+    if (!EARLY && row0 >= M) return;                                            // (the whole workgroup, here and below)
     x += (size_t)(min(row, last) >> 5) * 32 * H + (row & 31) * 8 + at;
     // the residual row is the same row, or (first-token layers) the row that a sequence starts at
     const int rr = res_row ? (int)min((uint32_t)res_row[min(row, M - 1)], (uint32_t)(res_rows - 1)) : min(row, last);
@@ -194,7 +194,7 @@ __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float
         for (int i = 0; i < NW; ++i) v[p][i] = *reinterpret_cast<const float4*>(x + (size_t)p * part_stride + i * 2048);
 #pragma unroll
     for (int i = 0; i < NW; ++i) r[i] = *reinterpret_cast<const float4*>(res + i * 2048);
-    if constexpr (FEW) {
+    if constexpr (EARLY) {
         asm volatile("" ::: "memory");                                        // the loads stay in front of the exit
         if (d_M) M = min(M, rows_here);
         if (row0 >= M) return;
@@ -215,17 +215,17 @@ __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float
         v[0][i].z += r[i].z;
         v[0][i].w += r[i].w;
     }
-    finish_row<NI, FEW, !FEW, SUMS>(v[0], gamma, beta, row, wave, row < M, eps, out);
+    finish_row<NI, SPLIT, !SPLIT, SUMS>(v[0], gamma, beta, row, wave, row < M, eps, out);
 }
 
 template <int NI, int NP>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_kernel(const float* x, const float* res, const int32_t* d_M, const float* gamma,
                                                               const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps)
 {
-    layernorm_tiled_body<NI, NP, true, ROW_SHARES>(x, res, gamma, beta, RowOut{of, ob, nullptr, 0, false}, d_M, M, part_stride, nullptr, 0, eps);
+    layernorm_tiled_body<NI, NP, true, true, ROW_SHARES>(x, res, gamma, beta, RowOut{of, ob, nullptr, 0, false}, d_M, M, part_stride, nullptr, 0, eps);
 }
 
-template <int NI, int NP, bool FEW, RowSums SUMS>
+template <int NI, int NP, bool SPLIT, bool EARLY, RowSums SUMS>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_group_kernel(TiledLnGroup g, TiledLnShape s)
 {
     const int grp = blockIdx.y;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_group_kernel(T
     unsigned char* ob = ws + (size_t)g.out_b[grp] * 256;
     const RowOut out{reinterpret_cast<float*>(ws + (size_t)g.out_f[grp] * 256), s.want_b >> grp & 1 ? reinterpret_cast<__bf16*>(ob) : nullptr,
                      s.want_q >> grp & 1 ? ob + s.q_offset : nullptr, s.split, s.q_offset == 0};
-    layernorm_tiled_body<NI, NP, FEW, SUMS>(reinterpret_cast<const float*>(ws + (size_t)g.x[grp] * 256), reinterpret_cast<const float*>(ws + (size_t)g.res[grp] * 256),
+    layernorm_tiled_body<NI, NP, SPLIT, EARLY, SUMS>(reinterpret_cast<const float*>(ws + (size_t)g.x[grp] * 256), reinterpret_cast<const float*>(ws + (size_t)g.res[grp] * 256),
                                       reinterpret_cast<const float*>(wt + (size_t)g.gamma[grp] * 256), reinterpret_cast<const float*>(wt + (size_t)g.beta[grp] * 256),
                                       out, s.d_M, s.M, s.part_stride, s.res_row, s.res_rows, s.eps);
 }
@@ -423,11 +423,15 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
     const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
     // with a row count on the device: less than a cached megabyte or two of padding.  Without, there is none.
     const bool few = !s.whole_sums && (long)s.G * s.M <= (s.d_M ? 2048 : 8192);
-    const int rows = few ? rows_of_group<NI, true> : rows_of_group<NI, false>;
+    // 2.3 k rows are 144 workgroups of 16 rows, too few for 256 compute units: with the columns dealt out, but the row count read first, passes of 32 x
+    // 128 tokens 1294 -> 1267 us, 7 x 509 1394 -> 1379, routed 32 x 128 1597 -> 1552; a line at 8192 or 32768 rows was slower (1269, 1277; 8 x 32 x 128
+    // 5934 us, 5950, 6022).
+    const bool split = few || (!s.whole_sums && (long)s.G * s.M <= 16384);
+    const int rows = split ? rows_of_group<NI, true> : rows_of_group<NI, false>;
     const dim3 grid((s.M + rows - 1) / rows, s.G), block(kRowWaves * 64);
     if constexpr (NI % 4 == 0 && NP == 1) {
         if (s.whole_sums) {
-            hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, ROW_WHOLE>), grid, block, 0, stream, g, s);
+            hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, false, ROW_WHOLE>), grid, block, 0, stream, g, s);
             return;
         }
     }
@@ -437,9 +441,11 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
                            (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
                            s.M, s.part_stride, s.eps);
     else if (few)
-        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, ROW_SHARES>), grid, block, 0, stream, g, s);
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, true, ROW_SHARES>), grid, block, 0, stream, g, s);
+    else if (split)
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, false, ROW_SHARES>), grid, block, 0, stream, g, s);
     else
-        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, ROW_SHARES>), grid, block, 0, stream, g, s);
+        hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, false, false, ROW_SHARES>), grid, block, 0, stream, g, s);
 }
 
 }  // namespace

@@ -374,7 +374,8 @@ def test_layernorm_panels(M, rows, H, parts, look_up, split):
 
 @pytest.mark.parametrize("H,parts", [(64, 1), (128, 2), (192, 1), (256, 4), (704, 1), (768, 1), (768, 4), (1024, 2)])
 def test_layernorm_panels_few_and_many_rows_give_the_same_bits(H, parts):
-    """A launch of up to 2048 rows deals a row's columns out to several wavefronts (H / 64 a multiple of 4 or 2), a larger one does not."""
+    """A launch of up to 2048 rows deals a row's columns out to several wavefronts (H / 64 a multiple of 4 or 2) before it knows the row count, one of up to
+    16384 after, a larger one not."""
     rows = 1997
     print(f"layernorm, few and many rows: {rows} x {H}, {parts} parts", flush=True)
     rng = np.random.default_rng(H + parts)
@@ -382,13 +383,13 @@ def test_layernorm_panels_few_and_many_rows_give_the_same_bits(H, parts):
     x = (rng.standard_normal((parts, rows, H)) + 3 * rng.standard_normal((1, rows, 1))).astype(np.float32)
     res = rng.standard_normal((rows, H)).astype(np.float32)
     got = []
-    for M in (2048, 2080):
+    for M in (2048, 2080, 16384, 16416):
         xm, rm = np.full((parts, M, H), np.nan, np.float32), np.full((M, H), np.nan, np.float32)
         xm[:, :rows], rm[:rows] = x, res
         of, ob = mt.op_panel_layernorm(torch.stack([panels(p, torch.float32) for p in xm]), panels(rm, torch.float32), dev(gamma), dev(beta), 1e-12, M, H,
                                        rows=dev(np.array([rows], np.int32)))
         got.append((rows_of(of)[:rows], rows_of(ob)[:rows]))
-    assert (got[0][0] == got[1][0]).all() and (got[0][1] == got[1][1]).all()
+    assert all((got[0][0] == f).all() and (got[0][1] == b).all() for f, b in got[1:])
     v = x.astype(np.float64).sum(0) + res
     n = (v - v.mean(1, keepdims=True)) / np.sqrt(v.var(1, keepdims=True) + 1e-12)
     # the sums of up to 5 float32 values round at 2^-24 of values up to 4 standard deviations of the row's offset
