@@ -54,22 +54,15 @@ __device__ __forceinline__ float row_sum_whole(const float (&part)[4])
     return v;
 }
 
-// Normalise the NW x 4 values that a lane holds of its row, columns (wc NW + i) 64 .., and store.  STREAM: the float32 state is stored past the second-level
-// cache, since it is read again three launches later only (18.6 k rows 38.7 -> 38.2 us, 8 problems of them 278 -> 268).
-template <int NI, bool SPLIT, bool STREAM, RowSums SUMS>
-__device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(NI) : 1)], const float* __restrict__ gamma, const float* __restrict__ beta,
-                                           int row, int wave, bool live, float eps, const RowOut& out)
+// Mean of a row, and the sum of the squares about it.  SHARES: a share's sum, and its squares about its own mean, are what the wavefronts exchange (once); the
+// row's are put together from them in double.  In float, the mean one of four rounded means, 9 k rows of 768 values about 5 came out 2.2e-7 off
+// float64 (rms, of results of order 1); 1.6e-7 so, 1.8e-7 with one float sum over the whole row.  Time: passes of 1 to 32 k tokens within 0.3 %.
+// Nothing here may be contracted: a share's mean is kept in a register in one form and formed from LDS in the other.
+template <int NI, bool SPLIT, RowSums SUMS>
+__device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_shares(NI) : 1)], int wave, float& mean, float& q)
 {
-    constexpr int H = NI * 64, SH = row_shares(NI), W = SPLIT ? SH : 1, NW = NI / W, NS = NI / SH, N = NS * 64;
-    const int lane = threadIdx.x & 63, half = lane & 1, c8 = lane >> 3, wc = wave % W;
-    float4 g[NW], b[NW];                     // in flight during the reductions
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        g[i] = *reinterpret_cast<const float4*>(gamma + ((wc * NW + i) * 8 + c8) * 8 + half * 4);
-        b[i] = *reinterpret_cast<const float4*>(beta + ((wc * NW + i) * 8 + c8) * 8 + half * 4);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    float mean, q;                           // of the row: mean, sum of the squares about it
+#pragma clang fp contract(off)
+    constexpr int H = NI * 64;
     if constexpr (SUMS == ROW_WHOLE) {
         static_assert(!SPLIT && NI % 4 == 0, "");
         float part[4];
@@ -86,57 +79,86 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
 #pragma unroll
             for (int i = k; i < NI; i += 4) {
                 const float a = v[i].x - mean, bb = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-                part[k] += (a * a + bb * bb) + (c * c + d * d);
+                part[k] += fmaf(a, a, bb * bb) + fmaf(c, c, d * d);
             }
         }
         q = row_sum_whole(part);
     } else {
-    float m[SH], d2[SH];                     // of the shares: mean, squares about it
+        constexpr int SH = row_shares(NI), W = SPLIT ? SH : 1, NS = NI / SH, N = NS * 64;
+        float s[SH], d2[SH];                 // of the shares: sum, squares about its mean
+        auto mean_of = [](float sum) {
+#pragma clang fp contract(off)
+            return SH == 1 ? (float)((double)sum * (1.0 / H)) : sum * (1.0f / N);
+        };
 #pragma unroll
-    for (int h = 0; h < SH / W; ++h) {
-        float s = 0.f;
+        for (int h = 0; h < SH / W; ++h) {
+            float t = 0.f;
 #pragma unroll
-        for (int i = h * NS; i < (h + 1) * NS; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-        m[h] = row_sum(s) * (1.0f / N);
-    }
-#pragma unroll
-    for (int h = 0; h < SH / W; ++h) {
-        float s2 = 0.f;
-#pragma unroll
-        for (int i = h * NS; i < (h + 1) * NS; ++i) {
-            const float a = v[i].x - m[h], c = v[i].y - m[h], d = v[i].z - m[h], e = v[i].w - m[h];
-            s2 += fmaf(a, a, c * c) + fmaf(d, d, e * e);
+            for (int i = h * NS; i < (h + 1) * NS; ++i) t += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+            s[h] = row_sum(t);
         }
-        d2[h] = row_sum(s2);
-    }
-    if constexpr (W > 1) {
-        __shared__ float2 share[kRowWaves / W][W][4];
-        const int quad = wave / W, r = (lane >> 1) & 3;
-        if ((lane & 57) == 0) share[quad][wc][r] = make_float2(m[0], d2[0]);
-        __syncthreads();
 #pragma unroll
-        for (int h = 0; h < SH; ++h) {
-            const float2 t = share[quad][h][r];
-            m[h] = t.x;
-            d2[h] = t.y;
+        for (int h = 0; h < SH / W; ++h) {
+            const float m = mean_of(s[h]);
+            float t = 0.f;
+#pragma unroll
+            for (int i = h * NS; i < (h + 1) * NS; ++i) {
+                const float a = v[i].x - m, c = v[i].y - m, d = v[i].z - m, e = v[i].w - m;
+                t += fmaf(a, a, c * c) + fmaf(d, d, e * e);
+            }
+            d2[h] = row_sum(t);
+        }
+        if constexpr (W > 1) {
+            __shared__ float2 share[kRowWaves / W][W][4];
+            const int lane = threadIdx.x & 63, quad = wave / W, wc = wave % W, r = (lane >> 1) & 3;
+            if ((lane & 57) == 0) share[quad][wc][r] = make_float2(s[0], d2[0]);
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < SH; ++h) {
+                const float2 t = share[quad][h][r];
+                s[h] = t.x;
+                d2[h] = t.y;
+            }
+        }
+        if constexpr (SH == 1) {
+            mean = mean_of(s[0]);
+            q = d2[0];
+        } else {
+            // shares of equal size: the squares about the row's mean are those about each share's + N (difference)^2
+            double sum = s[0], squares = d2[0], u = 0.0;
+#pragma unroll
+            for (int h = 1; h < SH; ++h) {
+                sum += s[h];
+                squares += d2[h];
+            }
+            mean = (float)(sum * (1.0 / H));
+#pragma unroll
+            for (int h = 0; h < SH; ++h) {
+                const double d = (double)mean_of(s[h]) - mean;
+                u = fma(d, d, u);
+            }
+            q = (float)fma(u, (double)N, squares);
         }
     }
-    // shares of equal size: the squares about the common mean are those about each share's + N (difference)^2
-    mean = m[0];
-    q = d2[0];
+}
+
+// Normalise the NW x 4 values that a lane holds of its row, columns (wc NW + i) 64 .., and store.  STREAM: the float32 state is stored past the second-level
+// cache, since it is read again three launches later only (18.6 k rows 38.7 -> 38.2 us, 8 problems of them 278 -> 268).
+template <int NI, bool SPLIT, bool STREAM, RowSums SUMS>
+__device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(NI) : 1)], const float* __restrict__ gamma, const float* __restrict__ beta,
+                                           int row, int wave, bool live, float eps, const RowOut& out)
+{
+    constexpr int H = NI * 64, W = SPLIT ? row_shares(NI) : 1, NW = NI / W;
+    const int lane = threadIdx.x & 63, half = lane & 1, c8 = lane >> 3, wc = wave % W;
+    float4 g[NW], b[NW];                     // in flight during the reductions
 #pragma unroll
-    for (int h = 1; h < SH; ++h) {
-        mean += m[h];
-        q += d2[h];
+    for (int i = 0; i < NW; ++i) {
+        g[i] = *reinterpret_cast<const float4*>(gamma + ((wc * NW + i) * 8 + c8) * 8 + half * 4);
+        b[i] = *reinterpret_cast<const float4*>(beta + ((wc * NW + i) * 8 + c8) * 8 + half * 4);
     }
-    mean *= 1.0f / SH;
-    if constexpr (SH > 1) {
-        float u = 0.f;
-#pragma unroll
-        for (int h = 0; h < SH; ++h) u = fmaf(m[h] - mean, m[h] - mean, u);
-        q = fmaf(u, (float)N, q);
-    }
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    float mean, q;
+    row_moments<NI, SPLIT, SUMS>(v, wave, mean, q);
     const float inv = 1.0f / sqrtf(q / (float)H + eps);
     if (!live) return;
     const size_t panel = (size_t)(row >> 5) * 32;

@@ -372,7 +372,7 @@ def test_layernorm_panels(M, rows, H, parts, look_up, split):
     assert np.isnan(got[rows:]).all() and np.isnan(operand[rows:]).all()
 
 
-@pytest.mark.parametrize("H,parts", [(64, 1), (128, 2), (192, 1), (256, 4), (704, 1), (768, 1), (768, 4), (1024, 2)])
+@pytest.mark.parametrize("H,parts", [(64, 1), (128, 2), (192, 1), (256, 4), (384, 1), (640, 2), (704, 1), (768, 1), (768, 4), (896, 1), (1024, 2)])
 def test_layernorm_panels_few_and_many_rows_give_the_same_bits(H, parts):
     """A launch of up to 2048 rows deals a row's columns out to several wavefronts (H / 64 a multiple of 4 or 2) before it knows the row count, one of up to
     16384 after, a larger one not."""
@@ -395,6 +395,26 @@ def test_layernorm_panels_few_and_many_rows_give_the_same_bits(H, parts):
     # the sums of up to 5 float32 values round at 2^-24 of values up to 4 standard deviations of the row's offset
     bound = 2.0**-18 * (np.abs(gamma) * (1 + np.abs(n)) + np.abs(beta)) * np.maximum(1, np.abs(v).max(1, keepdims=True) / v.std(1, keepdims=True))
     assert (np.abs(got[0][0] - (gamma * n + beta)) <= bound).all()
+
+
+@pytest.mark.parametrize("M", [1500, 9000, 16500])
+@pytest.mark.parametrize("H", [128, 192, 256, 384, 640, 768, 896, 1024])
+def test_layernorm_panels_error_of_rows_far_from_zero(H, M):
+    """Rows about 5: the error is that of the mean, whose parts are independent.  Its own rounding (values from 4 to 8 lie 2^-21 apart), and the last few
+    additions of each share's sum, sqrt(1 + 1/2 + 1/4 + ..) roundings at the sum's size (a quarter of the columns where that is a multiple of 64, or
+    half, or all); the result rounds at 2^-24 of itself.  A seventh more for the squares and the many smaller additions."""
+    print(f"layernorm of rows about 5: {M} x {H}", flush=True)
+    rng = np.random.default_rng(H + M)
+    v = (rng.standard_normal((M, H)) + 5).astype(np.float32)
+    of, _ = mt.op_panel_layernorm(panels(np.zeros_like(v), torch.float32)[None], panels(v, torch.float32), dev(np.ones(H, np.float32)), dev(np.zeros(H, np.float32)),
+                                  1e-12, M, H)
+    w = v.astype(np.float64)
+    want = (w - w.mean(1, keepdims=True)) / w.std(1, keepdims=True)
+    err = np.sqrt(((rows_of(of)[:M] - want)**2).mean())
+    shares = 4 if H % 256 == 0 else 2 if H % 128 == 0 else 1
+    cols = H // shares
+    rounding = np.array([2.0**-21, np.sqrt(2.0) * np.spacing(np.float32(5 * cols)) / cols / np.sqrt(shares), 2.0**-23]) / np.sqrt(12)
+    assert err <= 8 / 7 * np.sqrt((rounding**2).sum()), (err, rounding)
 
 
 @pytest.mark.parametrize("batch,seq", [(9, 5), (60, 4), (70, 30)])
