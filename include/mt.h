@@ -370,12 +370,15 @@ int mt_op_first_token_pool(const float* d_scores, const void* d_x, void* d_xbar,
  *     d_first [batch][hidden], d_Wq [hidden][hidden] and d_WkT (the transpose of Wk) bf16 panels, d_qt bf16 [batch][16][hidden];
  *   mt_op_panel_first_attend: p = softmax_j(d_qt[b][a] . d_x[row_j] / 8), xbar = sum_j p_j d_x[row_j] over the rows d_seq_start[b] ..
  *     + min(d_seq_len[b], seq) - 1; d_x bf16 panels of all rows, d_xbar per head a bf16 panel matrix [batch][hidden],
- *     xbar_stride elements apart.  Rows of d_x that belong to no sequence may hold anything.
+ *     xbar_stride elements apart.  Rows of d_x that belong to no sequence may hold anything.  The weights p enter the sums with 16 bits;
+ *   mt_op_panel_first_attend_fp8: the same as MT_FP8_LAYER runs it, with all bits of float32 weights.
  * Errors: NULL, SHAPE, HIP. */
 int mt_op_panel_first_query(const void* d_first, const void* d_Wq, const float* d_bq, const void* d_WkT, void* d_qt, int32_t batch,
                             int32_t heads, void* hip_stream);
 int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
                              const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream);
+int mt_op_panel_first_attend_fp8(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                                 const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream);
 /* The other steps on the panel layout.  mt_op_panel_linear: `problems` equal-shaped contractions, each of `subs` equal parts (heads),
  *   C = act(A W^T + bias) on A [M][lda], W [N][ldw], C [M][ldc], the widths being those of the matrices whose columns the operands are.
  *   N % 32 == 0, K % (64 splits) == 0, lda and ldw multiples of 16, ldc of 8; at most 32 problems of at most 16 parts.

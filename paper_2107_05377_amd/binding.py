@@ -26,7 +26,7 @@ KERNEL_CLASSES = ["embed", "gemm_qkv", "attn", "gemm_out", "ln", "gemm_ffn1", "g
 EXPORTS = ["mt_create", "mt_destroy", "mt_weight_bytes", "mt_workspace_bytes", "mt_bind", "mt_load_weights",
            "mt_forward", "mt_logit_offset", "mt_n_logits", "mt_layer_count", "mt_last_error", "mt_error_name",
            "mt_read_hidden", "mt_profile_enable", "mt_profile_read", "mt_op_linear", "mt_op_attention",
-           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_linear", "mt_op_panel_linear_fp8", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
+           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_first_attend_fp8", "mt_op_panel_linear", "mt_op_panel_linear_fp8", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
            "mt_forward_tokens", "mt_token_logit_offset", "mt_n_token_logits", "mt_forward_static", "mt_forward_multi", "mt_forward_requests", "mt_forward_routed_tokens", "mt_op_linear_fp8", "mt_debug_e4m3_quantize", "mt_check_mask"]
 MT_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
@@ -105,7 +105,7 @@ def lib():
         L.mt_debug_set_gemm_tile.argtypes = [i32]
         L.mt_op_first_token_pool.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
         L.mt_op_panel_first_query.argtypes = [vp, vp, vp, vp, vp, i32, i32, vp]
-        L.mt_op_panel_first_attend.argtypes = [vp, vp, vp, i64, vp, vp, i32, i32, i32, vp]
+        L.mt_op_panel_first_attend.argtypes = L.mt_op_panel_first_attend_fp8.argtypes = [vp, vp, vp, i64, vp, vp, i32, i32, i32, vp]
         L.mt_op_panel_linear.argtypes = [C.POINTER(mt_panel_linear), vp]
         L.mt_op_panel_linear_fp8.argtypes = [C.POINTER(mt_panel_linear), vp]
         L.mt_op_panel_attention.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
@@ -414,12 +414,13 @@ def op_panel_first_query(first, Wq, bq, WkT, batch, heads):
     return qt
 
 
-def op_panel_first_attend(x, qt, seq_start, seq_len, batch, seq, heads):
-    """mt_op_panel_first_attend; x in panels; returns xbar [batch][heads][hidden] bf16."""
+def op_panel_first_attend(x, qt, seq_start, seq_len, batch, seq, heads, fp8=False):
+    """mt_op_panel_first_attend (fp8: mt_op_panel_first_attend_fp8); x in panels; returns xbar [batch][heads][hidden] bf16."""
     import torch
     H, panels = heads * 64, (batch + 31) // 32
     xbar = torch.full((heads, panels, H // 8, 32, 8), float("nan"), dtype=torch.bfloat16, device=x.device)
-    rc = lib().mt_op_panel_first_attend(_ptr(x), _ptr(qt), _ptr(xbar), panels * 32 * H, _ptr(seq_start), _ptr(seq_len), batch, seq, heads, _stream())
+    op = lib().mt_op_panel_first_attend_fp8 if fp8 else lib().mt_op_panel_first_attend
+    rc = op(_ptr(x), _ptr(qt), _ptr(xbar), panels * 32 * H, _ptr(seq_start), _ptr(seq_len), batch, seq, heads, _stream())
     if rc != MT_OK:
         raise MTError(rc, "mt_op_panel_first_attend")
     return torch.stack([from_panels(xbar[a])[:batch] for a in range(heads)], dim=1)

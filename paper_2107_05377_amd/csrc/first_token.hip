@@ -17,10 +17,11 @@ namespace mt {
 namespace {
 
 constexpr int kHeadsPad = 16;
-// The softmax weights are float32 quantities and enter the product as this many bfloat16 terms (the value, its remainder, ..: 16 bits of the
-// weight with two).  The row sums' error against float64 is that of float32 weights then, which one term exceeds 3 to 20 times where the
-// sum cancels.  Cost of the second term: 21 tasks x 272 short sequences 2810 -> 2822 us a pass, 8 tasks x 256 sequences nothing; of a third 1 %.
-constexpr int kTerms = 2;
+// The softmax weights are float32 quantities and enter the product as TERMS bfloat16 terms (the value, its remainder, ..).  Three are the whole
+// float32 weight: MT_FP8_LAYER, whose row-major kernels hold float32 weights.  Two, 16 bits of it, are what MT_BF16 takes: the row sums' error
+// against float64 is then that of float32 weights unless the sum cancels to less than about 2^-8 of its terms (one term exceeds it 3 to 20 times
+// where the sum cancels at all).  Cost of the second term: 21 tasks x 272 short sequences 2810 -> 2822 us a pass, 8 tasks x 256 sequences nothing;
+// of the third 1 % of the former; MT_FP8_LAYER with it 8 tasks x 4 sequences 504 -> 508 us, x 256 sequences 4.25 -> 4.28 ms.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, const int32_t* seq_start, int max_rows, FirstTokenGroup g)
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A
 // operands (16 x 32, straight from global memory), forms its share of the scores with q~ and leaves it in LDS; after the only barrier all
 // wavefronts add the shares, each for itself, and have the weights of all heads in the operand order of the next product.  For that the
 // rows are needed transposed: a product with the unit matrix, exact, moves the columns to the lanes.
-template <int NW>
+template <int NW, int TERMS>
 __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(const int32_t* __restrict__ seq_start,
                                                                                     const int32_t* __restrict__ seq_len, int B, int Smax, int H,
                                                                                     int A, int64_t xbar_stride, FirstTokenGroup g)
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] *= alpha;
         }
-        bf16x8 pf[kTerms];
+        bf16x8 pf[TERMS];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
                 float p = __builtin_amdgcn_exp2f(fmaf(sc[h][e], kScale, -m_run));
                 l_run += p;
 #pragma unroll
-                for (int t = 0; t < kTerms; ++t) {
+                for (int t = 0; t < TERMS; ++t) {
                     pf[t][h * 4 + e] = (__bf16)p;
                     p -= (float)pf[t][h * 4 + e];
                 }
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
             }
             xt = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, xt) & keep);
 #pragma unroll
-            for (int t = kTerms - 1; t >= 0; --t) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt, pf[t], acc[c], 0, 0, 0);     // row: column, column: head
+            for (int t = TERMS - 1; t >= 0; --t) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt, pf[t], acc[c], 0, 0, 0);     // row: column, column: head
             if (c & 1) __builtin_amdgcn_sched_barrier(0);                    // (two at a time, for the registers)
         }
     };
@@ -275,11 +276,15 @@ hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int
 }
 
 hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
-                               int64_t xbar_stride, hipStream_t stream)
+                               int64_t xbar_stride, hipStream_t stream, bool whole_weights)
 {
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
     if (!seq_start || !seq_len || G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-#define MT_ATTEND(N) case N: hipLaunchKernelGGL(first_attend_kernel<N>, dim3((B + 7) / 8 * 8, G), dim3(N * 64), 0, stream, seq_start, seq_len, B, S, H, A, xbar_stride, g); break
+#define MT_ATTEND(N)                                                                                                                          \
+    case N: {                                                                                                                                 \
+        auto kfn = whole_weights ? first_attend_kernel<N, 3> : first_attend_kernel<N, 2>;                                                     \
+        hipLaunchKernelGGL(kfn, dim3((B + 7) / 8 * 8, G), dim3(N * 64), 0, stream, seq_start, seq_len, B, S, H, A, xbar_stride, g);           \
+    } break
     switch ((H + 127) / 128) {
         MT_ATTEND(1);
         MT_ATTEND(2);

@@ -175,8 +175,9 @@ struct FirstTokenGroup {
 // up to so many sequences' first rows are read in place (seq_start given: `first` is not used, x has max_rows rows)
 constexpr int kInPlace = 8;
 hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int A, hipStream_t stream, const int32_t* seq_start = nullptr, int max_rows = 0);
+// whole_weights: the softmax weights enter with all their float32 bits instead of 16
 hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
-                               int64_t xbar_stride, hipStream_t stream);
+                               int64_t xbar_stride, hipStream_t stream, bool whole_weights = false);
 
 // float32 operands, products and sums; any shape.
 hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t stream);

@@ -1091,7 +1091,7 @@ void run_last_layer_group_tiled(Launcher& L, const std::vector<LastIO>& io, cons
     L.check(launch_first_query(fg, n, B, H, A, L.st, in_place ? rm.seq_start : nullptr, M));
     L.end();
     L.begin(MT_K_ATTN);
-    L.check(launch_first_attend(fg, n, rm.seq_start, rm.seq_len, B, S, H, A, xbar_stride, L.st));
+    L.check(launch_first_attend(fg, n, rm.seq_start, rm.seq_len, B, S, H, A, xbar_stride, L.st, m->fp8_attn));
     L.end();
 
     // contexts: per head, [B x H] row sums against the head's 64 rows of Wv
@@ -2371,8 +2371,8 @@ int mt_op_panel_first_query(const void* d_first, const void* d_Wq, const float* 
     return op_result(launch_first_query(g, 1, batch, heads * 64, heads, static_cast<hipStream_t>(hip_stream)));
 }
 
-int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
-                             const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream)
+static int op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                                 const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, bool whole_weights, void* hip_stream)
 {
     if (!d_x || !d_qt || !d_xbar || !d_seq_start || !d_seq_len) return MT_ERR_NULL;
     if (batch < 1 || seq < 1 || heads < 1 || xbar_stride < (int64_t)state_rows(true, batch) * heads * 64 || !aligned256(d_x, d_qt, d_xbar)) return MT_ERR_SHAPE;
@@ -2380,7 +2380,20 @@ int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, in
     g.x[0] = d_x;
     g.qt[0] = const_cast<void*>(d_qt);
     g.xbar[0] = d_xbar;
-    return op_result(launch_first_attend(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, xbar_stride, static_cast<hipStream_t>(hip_stream)));
+    return op_result(launch_first_attend(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, xbar_stride, static_cast<hipStream_t>(hip_stream),
+                                         whole_weights));
+}
+
+int mt_op_panel_first_attend(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                             const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream)
+{
+    return op_panel_first_attend(d_x, d_qt, d_xbar, xbar_stride, d_seq_start, d_seq_len, batch, seq, heads, false, hip_stream);
+}
+
+int mt_op_panel_first_attend_fp8(const void* d_x, const void* d_qt, void* d_xbar, int64_t xbar_stride, const int32_t* d_seq_start,
+                                 const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads, void* hip_stream)
+{
+    return op_panel_first_attend(d_x, d_qt, d_xbar, xbar_stride, d_seq_start, d_seq_len, batch, seq, heads, true, hip_stream);
 }
 
 static int op_panel_linear(const mt_panel_linear* op, bool f8, void* hip_stream)

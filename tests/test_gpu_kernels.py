@@ -180,6 +180,38 @@ def test_first_token_panels(heads, lens, late):
     assert worst <= 1.0
 
 
+# Row sums that cancel to 2^-18 of their terms show the bits of the weights: two keys of every sequence are chosen, column by column, against the
+# sum of the others under one head's weights.  Weights of 24 bits from an exponential good to 2^-23 leave at most 2^-23 of sum p |x| (rms over the
+# columns, independent from key to key); weights of 16 bits leave 2^-22 to 2^-20.  Scores come from one column alone, exactly.
+@pytest.mark.parametrize("heads", [1, 5, 12, 16])
+def test_first_token_panels_whole_weights(heads):
+    lens = [4, 9, 33, 100]
+    print(f"first token, whole weights: {heads} heads", flush=True)
+    H, B, rng = 64 * heads, len(lens), np.random.default_rng(heads)
+    row0, rows = ragged_rows(lens, 5, rng)
+    qt = np.zeros((B, 16, H))
+    qt[:, :, 0] = bf16(rng.uniform(2, 8, (B, 16)))
+    x, ps = np.full((rows, H), np.nan), []
+    for b, n in enumerate(lens):
+        v = bf16(rng.standard_normal((n, H))).astype(np.float64)
+        v[:, 0] = bf16(rng.uniform(-1, 1, n))
+        s = qt[b, :heads, :1] * v[:, 0] / 8
+        p = np.exp(s - s.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        own = p[np.arange(H) % heads]                      # [H][n]: the weights that column c is to cancel under
+        v[n - 2:, 1:] = 0
+        for k in (n - 2, n - 1):
+            v[k, 1:] = bf16(-(own[1:] * v[:, 1:].T).sum(1) / own[1:, k])
+        x[row0[b]:row0[b] + n] = v
+        ps.append(own)
+    got = mt.op_panel_first_attend(panels(x), dev(qt, torch.bfloat16), dev(row0), dev(np.array(lens, np.int32)), B, max(lens), heads, fp8=True).double().cpu().numpy()
+    for b, n in enumerate(lens):
+        terms = ps[b][1:] * x[row0[b]:row0[b] + n, 1:].T
+        err = (got[b, np.arange(H) % heads, np.arange(H)][1:] - terms.sum(1)) / np.abs(terms).sum(1)
+        print(f"  {n} keys: {np.sqrt((err**2).mean()) * 2**23:.3f} of the bound", flush=True)
+        assert np.sqrt((err**2).mean()) <= 2.0**-23
+
+
 def panels(x, dtype=None):
     """A float array [rows][width] in the panel layout on the device, rows of the last panel beyond it NaN."""
     return mt.to_panels(torch.from_numpy(np.ascontiguousarray(x)).cuda(), dtype or torch.bfloat16)
