@@ -16,6 +16,8 @@
 // Measured at 576 rows against the any-shape kernel, which did everything before: 768 x 3072 and 768 x 768 columns x K 223 -> 25 us
 // on average, 3072 x 768 136 -> 38 us, 8 problems of 768 x 3072 / 768 x 768 501 -> 163 us on average (83 TFLOP/s), 8 rows x 8
 // problems 148 -> 18 us.
+#include <algorithm>
+
 #include "kernels.h"
 #include "device_util.h"
 
@@ -278,7 +280,8 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
     }
     // Blocks of 32 x 32 that are about as many as the compute units, or fewer: one per workgroup, its wavefronts a quarter of K each (300 rows x 768 x
     // 768: 9.2 us, 12.0 with two blocks and half of K; x 3072: 20.9, 34.1; of 576 rows, 432 blocks, 14.4 and 12.4, 39.2 and 35.8).
-    const long blocks = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32);
+    // By the problems with all tasks enabled: a task's logits are the same bits whichever others are.
+    const long blocks = (long)std::max(s.plan, s.G) * ((s.M + 31) / 32) * ((s.N + 31) / 32);
     if (blocks <= 400 && s.K % 128 == 0) return launch_mfma<1, 1, 4, 2>(g, s, stream);
     const long tiles64 = (long)s.G * ((s.M + 63) / 64) * ((s.N + 63) / 64);
     if (tiles64 >= 1024) return launch_mfma<2, 2, 1, 4>(g, s, stream);

@@ -560,6 +560,20 @@ def test_bf16_logits_do_not_depend_on_the_enabled_tasks_when_they_share_the_trun
     model.close()
 
 
+@pytest.mark.parametrize("batch,seq,n_tasks", [(1, 33, 8), (1, 128, 8), (3, 50, 8), (5, 64, 8), (40, 2, 26)])
+def test_fp32_logits_of_small_calls_do_not_depend_on_the_enabled_tasks(batch, seq, n_tasks):
+    """One task alone has a fraction of the output blocks, in the layers and (more than 32 sequences) in the poolers: the number of K shares goes by
+    those of all tasks."""
+    spec = ms.MTSpec("f32_masks", vocab=300, hidden=256, heads=4, ffn=512, max_pos=128, n_trunk_layers=2,
+                     tasks=tuple(ms.TaskSpec(2, 2 if n_tasks == 8 else 1, 2 + t % 5) for t in range(n_tasks)), precision="fp32", batch=batch, seq=seq,
+                     len_lo=max(1, seq // 2), len_hi=seq, input_seed=5)
+    say(f"fp32, enabled tasks: {n_tasks} tasks, {batch} x {seq}")
+    model, _ = mt.load_synthetic(spec, std=0.05)
+    T = range(n_tasks)
+    check_masks_leave_logits_alone(spec, model, batch, seq, [[int(t == i) for t in T] for i in T] + [[int(t < 3) for t in T]])
+    model.close()
+
+
 def test_bf16_base_task_isolation(base_model):
     """Reloading one task's checkpoint leaves every other task's logits bit-identical (Section 5.1)."""
     spec, model, _, tps = base_model
