@@ -278,11 +278,13 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
         hipLaunchKernelGGL(gemm_f32_rows_kernel, grid, block, 0, stream, g, s);
         return hipGetLastError();
     }
-    // Blocks of 32 x 32 that are about as many as the compute units, or fewer: one per workgroup, its wavefronts a quarter of K each (300 rows x 768 x
-    // 768: 9.2 us, 12.0 with two blocks and half of K; x 3072: 20.9, 34.1; of 576 rows, 432 blocks, 14.4 and 12.4, 39.2 and 35.8).
+    // Blocks of 32 x 32, one per workgroup, its wavefronts a quarter of K each; otherwise two blocks and half of K.  While every block has a compute unit
+    // that is 1.3 to 1.8 times as fast (240 blocks of one problem, K = 768: 8.8 and 12.1 us, 3072: 20.5 and 35.8; 256 blocks of 8 problems 8.7 and
+    // 12.2, 24.1 and 35.8; K = 256 level).  Up to one and a half times as many it is a little ahead for one problem (264 to 384 blocks, K = 768: 11.7
+    // to 12.0 and 12.1 to 12.2, 3072: 33.9 to 34.5 and 35.8), while several problems at K = 768 lose (320 and 384 blocks of 8: 12.6 and 12.2, 12.9 and 12.3).
     // By the problems with all tasks enabled: a task's logits are the same bits whichever others are.
-    const long blocks = (long)std::max(s.plan, s.G) * ((s.M + 31) / 32) * ((s.N + 31) / 32);
-    if (blocks <= 400 && s.K % 128 == 0) return launch_mfma<1, 1, 4, 2>(g, s, stream);
+    const long plan = std::max(s.plan, s.G), blocks = plan * ((s.M + 31) / 32) * ((s.N + 31) / 32), n_cu = device_cu_count();
+    if (blocks <= (plan == 1 ? n_cu * 3 / 2 : n_cu) && s.K % 128 == 0) return launch_mfma<1, 1, 4, 2>(g, s, stream);
     const long tiles64 = (long)s.G * ((s.M + 63) / 64) * ((s.N + 63) / 64);
     if (tiles64 >= 1024) return launch_mfma<2, 2, 1, 4>(g, s, stream);
     return launch_mfma<1, 2, 2, 3>(g, s, stream);
