@@ -417,6 +417,15 @@ int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_s
 int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
                           const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, const int32_t* d_rows,
                           int32_t M, int32_t hidden, void* hip_stream);
+/* The same for the layers of MT_FP8_LAYER (hidden a multiple of 256), whose sums have the order of mt_op_layernorm's: the same bits.  d_out_b: the
+ * bf16 copy or NULL; d_out_q: NULL or a copy in E4M3 panels (unit scale, saturating) of the bf16 copy's values or, without one, of the float32
+ * ones.  At least one of the two copies. */
+int mt_op_panel_layernorm_fp8(const float* d_x, const float* d_residual, const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b,
+                              void* d_out_q, const int32_t* d_rows, int32_t M, int32_t hidden, void* hip_stream);
+/* The attention of MT_FP8_LAYER: as mt_op_panel_attention, values not transposed, the context rounded to E4M3 (unit scale, saturating); both matrices
+ * in panels, or row-major (panels == 0; the same values), 256-byte aligned. */
+int mt_op_attention_fp8(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq, int32_t heads,
+                        int32_t panels, void* hip_stream);
 /* ctx[b,s,a*d:(a+1)*d] = softmax(q k^T / sqrt(d) + mask) v per head; d_qkv is [B*S][3H] act
  * (columns Q | K | V), d_ctx [B*S][H] act. */
 int mt_op_attention(int32_t precision, const void* d_qkv, const int32_t* d_mask, void* d_ctx,

@@ -26,7 +26,7 @@ KERNEL_CLASSES = ["embed", "gemm_qkv", "attn", "gemm_out", "ln", "gemm_ffn1", "g
 EXPORTS = ["mt_create", "mt_destroy", "mt_weight_bytes", "mt_workspace_bytes", "mt_bind", "mt_load_weights",
            "mt_forward", "mt_logit_offset", "mt_n_logits", "mt_layer_count", "mt_last_error", "mt_error_name",
            "mt_read_hidden", "mt_profile_enable", "mt_profile_read", "mt_op_linear", "mt_op_attention",
-           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_first_attend_fp8", "mt_op_panel_linear", "mt_op_panel_linear_fp8", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_schedule_steps", "mt_forward_routed",
+           "mt_op_layernorm", "mt_op_linear_batched", "mt_debug_set_gemm_tile", "mt_share_weights", "mt_debug_mfma_peak", "mt_forward_typed", "mt_op_linear_sub", "mt_op_first_token_pool", "mt_op_panel_first_query", "mt_op_panel_first_attend", "mt_op_panel_first_attend_fp8", "mt_op_panel_linear", "mt_op_panel_linear_fp8", "mt_op_panel_attention", "mt_op_panel_layernorm", "mt_op_panel_layernorm_fp8", "mt_op_attention_fp8", "mt_schedule_steps", "mt_forward_routed",
            "mt_forward_tokens", "mt_token_logit_offset", "mt_n_token_logits", "mt_forward_static", "mt_forward_multi", "mt_forward_requests", "mt_forward_routed_tokens", "mt_op_linear_fp8", "mt_debug_e4m3_quantize", "mt_check_mask"]
 MT_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
@@ -109,6 +109,8 @@ def lib():
         L.mt_op_panel_linear.argtypes = [C.POINTER(mt_panel_linear), vp]
         L.mt_op_panel_linear_fp8.argtypes = [C.POINTER(mt_panel_linear), vp]
         L.mt_op_panel_attention.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
+        L.mt_op_panel_layernorm_fp8.argtypes = [vp, vp, vp, vp, C.c_float, vp, vp, vp, vp, i32, i32, vp]
+        L.mt_op_attention_fp8.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, vp]
         L.mt_op_panel_layernorm.argtypes = [vp, i32, i64, vp, vp, i32, vp, vp, C.c_float, vp, vp, i32, vp, i32, i32, vp]
         L.mt_op_linear_sub.argtypes = [vp, i64, vp, i64, vp, vp, i64, i32, i32, i32, i32, i64, i64, i64, i64, vp, vp, i32, vp]
         L.mt_debug_set_gemm_tile.restype = i32
@@ -457,6 +459,26 @@ def op_panel_layernorm(x, residual, gamma, beta, eps, M, hidden, res_row=None, r
     if rc != MT_OK:
         raise MTError(rc, "mt_op_panel_layernorm")
     return of, ob
+
+
+def op_panel_layernorm_fp8(x, residual, gamma, beta, eps, M, hidden, want_b, want_q, rows=None):
+    """mt_op_panel_layernorm_fp8; x and residual in panels; returns the float32 state, and its bf16 and E4M3 copies (or None) in panels."""
+    import torch
+    of = _panels(M, hidden, torch.float32, x.device)
+    ob = _panels(M, hidden, torch.bfloat16, x.device) if want_b else None
+    oq = torch.full(((M + 31) // 32, hidden // 16, 32, 16), 0x7F, dtype=torch.uint8, device=x.device) if want_q else None
+    rc = lib().mt_op_panel_layernorm_fp8(_ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), eps, _ptr(of), _ptr(ob), _ptr(oq), _ptr(rows), M, hidden, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_panel_layernorm_fp8")
+    return of, ob, oq
+
+
+def op_attention_fp8(qkv, ctx, seq_start, seq_len, batch, seq, heads, panels):
+    """mt_op_attention_fp8; qkv bf16 in panels or row-major, ctx (written in place) E4M3 bytes in the same layout."""
+    rc = lib().mt_op_attention_fp8(_ptr(qkv), _ptr(ctx), _ptr(seq_start), _ptr(seq_len), batch, seq, heads, 1 if panels else 0, _stream())
+    if rc != MT_OK:
+        raise MTError(rc, "mt_op_attention_fp8")
+    return ctx
 
 
 def mfma_peak(iters=4000):

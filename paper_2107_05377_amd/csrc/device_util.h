@@ -94,6 +94,21 @@ __device__ __forceinline__ float wave_max(float v)
     return lane_pair_max<1>(v);
 }
 
+// LayerNorm's arithmetic on a lane's four values, contractions written out: the row-major and the panel kernels give the same bits (E4M3 roundings
+// behind them amplify a last bit to 5 % of the logits), whatever the compiler would fuse in either.
+__device__ __forceinline__ float ln_squares(const float4& v, float mean)
+{
+#pragma clang fp contract(off)
+    const float a = v.x - mean, b = v.y - mean, c = v.z - mean, d = v.w - mean;
+    return fmaf(a, a, b * b) + fmaf(c, c, d * d);
+}
+__device__ __forceinline__ float4 ln_normalise(const float4& v, float mean, float inv, const float4& g, const float4& b)
+{
+#pragma clang fp contract(off)
+    return make_float4(fmaf(g.x, (v.x - mean) * inv, b.x), fmaf(g.y, (v.y - mean) * inv, b.y), fmaf(g.z, (v.z - mean) * inv, b.z),
+                       fmaf(g.w, (v.w - mean) * inv, b.w));
+}
+
 // GELU(x) = x * Phi(x).  Exact form through erff; tanh form as the published approximation.
 __device__ inline float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 // The erf form for bf16 epilogues.  GELU(x) = x * Phi(x) and Phi(x) = 1 / (1 + exp(-z(x))) with z = ln(Phi(x) / Phi(-x)),

@@ -2452,22 +2452,37 @@ int mt_op_panel_attention(const void* d_qkv, void* d_ctx, const int32_t* d_seq_s
     return op_result(launch_attention_tiled(g, 1, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, static_cast<hipStream_t>(hip_stream)));
 }
 
-int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
-                          const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, const int32_t* d_rows,
-                          int32_t M, int32_t hidden, void* hip_stream)
+int mt_op_attention_fp8(const void* d_qkv, void* d_ctx, const int32_t* d_seq_start, const int32_t* d_seq_len, int32_t batch, int32_t seq,
+                        int32_t heads, int32_t panels, void* hip_stream)
 {
-    if (!d_x || !d_residual || !d_gamma || !d_beta || !d_out || !d_out_b) return MT_ERR_NULL;
-    if (M < 1 || hidden < 1 || part_stride < 0 || part_stride % 4 != 0 || (d_res_row && res_rows < 1) ||
-        !aligned256(d_x, d_residual, d_gamma, d_beta, d_out, d_out_b))
+    if (!d_qkv || !d_ctx || !d_seq_start || !d_seq_len) return MT_ERR_NULL;
+    if (batch < 1 || seq < 1 || heads < 1 || !aligned256(d_qkv, d_ctx)) return MT_ERR_SHAPE;
+    AttnGroup g;
+    memset(&g, 0, sizeof g);
+    g.qkv[0] = d_qkv;
+    g.ctx[0] = d_ctx;
+    return op_result(launch_attention_bf16(g, 1, nullptr, d_seq_start, d_seq_len, batch, seq, heads * 64, heads, static_cast<hipStream_t>(hip_stream), 1,
+                                           panels != 0));
+}
+
+// d_out_q: the E4M3 copy; fp8: the order of sums of the layers with E4M3 operands
+static int op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
+                              const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, void* d_out_q, bool fp8,
+                              const int32_t* d_rows, int32_t M, int32_t hidden, void* hip_stream)
+{
+    if (!d_x || !d_residual || !d_gamma || !d_beta || !d_out || (!d_out_b && !d_out_q)) return MT_ERR_NULL;
+    if (M < 1 || hidden < 1 || part_stride < 0 || part_stride % 4 != 0 || (d_res_row && res_rows < 1) || (d_out_b && d_out_b == d_out_q) ||
+        !aligned256(d_x, d_residual, d_gamma, d_beta, d_out, d_out_b, d_out_q))
         return MT_ERR_SHAPE;
+    const void* copy = d_out_b ? d_out_b : d_out_q;
     // the launch takes offsets from a common base
     auto at = [](const void* p, const void* base) { return (size_t)((uintptr_t)p - (uintptr_t)base); };
-    const void* ws = std::min({(const void*)d_x, (const void*)d_residual, (const void*)d_out, (const void*)d_out_b}, std::less<const void*>());
+    const void* ws = std::min({(const void*)d_x, (const void*)d_residual, (const void*)d_out, copy}, std::less<const void*>());
     const void* wt = std::min<const void*>(d_gamma, d_beta, std::less<const void*>());
     TiledLnGroup g;
     g.ws = ws;
     g.wt = wt;
-    const size_t off[] = {at(d_x, ws), at(d_residual, ws), at(d_out, ws), at(d_out_b, ws), at(d_gamma, wt), at(d_beta, wt)};
+    const size_t off[] = {at(d_x, ws), at(d_residual, ws), at(d_out, ws), at(copy, ws), at(d_gamma, wt), at(d_beta, wt)};
     for (const size_t o : off)
         if (o / 256 > 0xFFFFFFFFu) return MT_ERR_SHAPE;
     g.x[0] = units(off[0]);
@@ -2477,7 +2492,26 @@ int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride
     g.gamma[0] = units(off[4]);
     g.beta[0] = units(off[5]);
     TiledLnShape s{1, M, hidden, d_rows, eps, n_parts, part_stride, d_res_row, res_rows, split ? 1 : 0};
+    s.want_b = d_out_b ? 1 : 0;
+    s.want_q = d_out_q ? 1 : 0;
+    s.q_offset = d_out_b && d_out_q ? (int64_t)((uintptr_t)d_out_q - (uintptr_t)d_out_b) : 0;
+    s.whole_sums = fp8 ? 1 : 0;
     return op_result(launch_layernorm_tiled(g, s, static_cast<hipStream_t>(hip_stream)));
+}
+
+int mt_op_panel_layernorm(const float* d_x, int32_t n_parts, int64_t part_stride, const float* d_residual, const int32_t* d_res_row, int32_t res_rows,
+                          const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b, int32_t split, const int32_t* d_rows,
+                          int32_t M, int32_t hidden, void* hip_stream)
+{
+    if (!d_out_b) return MT_ERR_NULL;
+    return op_panel_layernorm(d_x, n_parts, part_stride, d_residual, d_res_row, res_rows, d_gamma, d_beta, eps, d_out, d_out_b, split, nullptr, false, d_rows, M,
+                              hidden, hip_stream);
+}
+
+int mt_op_panel_layernorm_fp8(const float* d_x, const float* d_residual, const float* d_gamma, const float* d_beta, float eps, float* d_out, void* d_out_b,
+                              void* d_out_q, const int32_t* d_rows, int32_t M, int32_t hidden, void* hip_stream)
+{
+    return op_panel_layernorm(d_x, 1, 0, d_residual, nullptr, 0, d_gamma, d_beta, eps, d_out, d_out_b, 0, d_out_q, true, d_rows, M, hidden, hip_stream);
 }
 
 int mt_op_linear_batched(int32_t precision, int32_t G, const void* d_A, int64_t strideA, int64_t lda, const void* d_W,

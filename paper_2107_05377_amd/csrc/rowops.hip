@@ -37,19 +37,12 @@ __device__ inline void ln_finish_store(float4 (&v)[NV], const float4 (&g)[NV], c
     const float mean = wave_sum(s) / (float)H;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        float a = v[i].x - mean, bb = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-        q += (a * a + bb * bb) + (c * c + d * d);
-    }
+    for (int i = 0; i < NV; ++i) q += ln_squares(v[i], mean);
     const float inv = 1.0f / sqrtf(wave_sum(q) / (float)H + eps);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int col = (i * 64 + lane) * 4;
-        float4 o;
-        o.x = g[i].x * ((v[i].x - mean) * inv) + b[i].x;
-        o.y = g[i].y * ((v[i].y - mean) * inv) + b[i].y;
-        o.z = g[i].z * ((v[i].z - mean) * inv) + b[i].z;
-        o.w = g[i].w * ((v[i].w - mean) * inv) + b[i].w;
+        const float4 o = ln_normalise(v[i], mean, inv, g[i], b[i]);
         if (out_f32) *reinterpret_cast<float4*>(out_f32 + col) = o;
         if (out_bf16 && low_fmt == 1) {                   // E4M3, one byte per element
             *reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(out_bf16) + col) = pack_e4m3(o.x, o.y, o.z, o.w);

@@ -77,10 +77,7 @@ __device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_
         for (int k = 0; k < 4; ++k) {
             part[k] = 0.f;
 #pragma unroll
-            for (int i = k; i < NI; i += 4) {
-                const float a = v[i].x - mean, bb = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-                part[k] += fmaf(a, a, bb * bb) + fmaf(c, c, d * d);
-            }
+            for (int i = k; i < NI; i += 4) part[k] += ln_squares(v[i], mean);
         }
         q = row_sum_whole(part);
     } else {
@@ -102,10 +99,7 @@ __device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_
             const float m = mean_of(s[h]);
             float t = 0.f;
 #pragma unroll
-            for (int i = h * NS; i < (h + 1) * NS; ++i) {
-                const float a = v[i].x - m, c = v[i].y - m, d = v[i].z - m, e = v[i].w - m;
-                t += fmaf(a, a, c * c) + fmaf(d, d, e * e);
-            }
+            for (int i = h * NS; i < (h + 1) * NS; ++i) t += ln_squares(v[i], m);
             d2[h] = row_sum(t);
         }
         if constexpr (W > 1) {
@@ -166,11 +160,8 @@ __device__ __forceinline__ void finish_row(float4 (&v)[NI / (SPLIT ? row_shares(
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
         const int chunk = (wc * NW + i) * 8 + c8;
-        f32x4 o;
-        o[0] = fmaf(g[i].x, (v[i].x - mean) * inv, b[i].x);
-        o[1] = fmaf(g[i].y, (v[i].y - mean) * inv, b[i].y);
-        o[2] = fmaf(g[i].z, (v[i].z - mean) * inv, b[i].z);
-        o[3] = fmaf(g[i].w, (v[i].w - mean) * inv, b[i].w);
+        const float4 n = ln_normalise(v[i], mean, inv, g[i], b[i]);
+        const f32x4 o = {n.x, n.y, n.z, n.w};
         f32x4* f = reinterpret_cast<f32x4*>(out.f + panel * H + chunk * 256 + in_chunk);
         if constexpr (STREAM) __builtin_nontemporal_store(o, f);
         else *f = o;

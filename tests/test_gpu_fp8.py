@@ -127,6 +127,77 @@ def test_fp8_panel_linear_forms(form, height, problems, M, rows, N, K, act, out,
     assert (pc[:, untouched:] == 0x7F).all() if out == 2 else torch.isnan(pc[:, untouched:]).all()
 
 
+def to_e4m3(x):
+    """E4M3 codes of a CPU tensor, saturating."""
+    return x.float().clamp(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8)
+
+
+# LayerNorm of the layers with E4M3 operands: the row-major kernel's bits (test_layernorm_vs_oracle holds that one to the oracle), whose E4M3 copy is of
+# the bf16 values (a layer's output) or of the float32 ones (between the two halves of a layer).  Remainders of the rows, values that saturate.
+@pytest.mark.parametrize("M,rows,H", [(1, 1, 256), (37, 33, 768), (300, 290, 1024), (2100, 2049, 512), (16500, 16401, 256)])
+@pytest.mark.parametrize("want_b,want_q", [(True, True), (True, False), (False, True)])
+def test_fp8_panel_layernorm_gives_the_row_major_bits(M, rows, H, want_b, want_q):
+    say(f"fp8 panel layernorm: {rows}/{M} x {H}, bf16 {want_b}, E4M3 {want_q}")
+    rng = np.random.default_rng(M + H)
+    x, r = rng.standard_normal((2, M, H)).astype(np.float32)
+    x += 2 * rng.standard_normal((M, 1)).astype(np.float32)
+    x[rows:] = np.nan
+    gamma, beta = 1 + 0.5 * rng.standard_normal(H).astype(np.float32), rng.standard_normal(H).astype(np.float32)
+    gamma[::7] *= 200
+    of, ob, oq = mt.op_panel_layernorm_fp8(mt.to_panels(dev(x), torch.float32), mt.to_panels(dev(r), torch.float32), dev(gamma), dev(beta), 1e-12, M, H, want_b, want_q,
+                                           rows=dev(np.array([rows], np.int32)))
+    wf, wb = mt.op_layernorm(dev(x[:rows] + r[:rows]), dev(gamma), dev(beta), 1e-12, want_bf16=True)
+    assert torch.equal(mt.from_panels(of)[:rows], wf)
+    assert not want_b or torch.equal(mt.from_panels(ob)[:rows].view(torch.int16), wb.view(torch.int16))
+    if want_q:
+        got, want = mt.from_panels_e4m3(oq).view(torch.uint8)[:rows].cpu(), to_e4m3((wb if want_b else wf).cpu())
+        assert torch.equal(got, want), int((got != want).sum())
+        assert (got & 0x7F).max() == 0x7E                                        # something saturates
+        assert (oq[(rows + 31) // 32:] == 0x7F).all()
+
+
+# The attention with an E4M3 context on panels: the row-major kernel's bits, and those are roundings of the bf16 form's values (which
+# test_attention_bf16_vs_oracle holds to the oracle).  Sequences of part of a panel, of several, of more than one block of queries; rows of none hold NaN.
+@pytest.mark.parametrize("heads,lens", [(4, [1, 33, 300]), (12, [128, 127, 2, 31]), (16, [65, 200]), (1, [32] * 9)])
+def test_fp8_panel_attention_gives_the_row_major_bits(heads, lens):
+    say(f"fp8 panel attention: {heads} heads, {lens}")
+    rng, H = np.random.default_rng(heads), 64 * heads
+    row0 = np.cumsum([3] + [n + 5 for n in lens[:-1]]).astype(np.int32)
+    rows = int(row0[-1] + lens[-1] + 7)
+    real = np.zeros(rows, bool)
+    for a, n in zip(row0, lens):
+        real[a:a + n] = True
+    qkv = torch.full((rows, 3 * H), float("nan"), dtype=torch.bfloat16)
+    qkv[torch.from_numpy(real)] = torch.from_numpy(rng.standard_normal((int(real.sum()), 3 * H)).astype(np.float32) * 2).to(torch.bfloat16)
+    start, length, seq = dev(row0), dev(np.array(lens, np.int32)), max(lens)
+    flat = mt.op_attention_fp8(qkv.cuda(), torch.full((rows, H), 0x7F, dtype=torch.uint8, device="cuda"), start, length, len(lens), seq, heads, False).cpu()
+    ctx = torch.full(((rows + 31) // 32, H // 16, 32, 16), 0x7F, dtype=torch.uint8, device="cuda")
+    mt.op_attention_fp8(mt.to_panels(qkv.cuda(), torch.bfloat16), ctx, start, length, len(lens), seq, heads, True)
+    got = mt.from_panels_e4m3(ctx).view(torch.uint8)[:rows].cpu()
+    assert torch.equal(got, flat), int((got != flat).sum())
+    assert (flat[torch.from_numpy(~real)] == 0x7F).all()
+    for b, n in enumerate(lens):
+        alone = qkv[row0[b]:row0[b] + n].contiguous().cuda()
+        want = mt.op_attention(mt.MT_BF16, alone, torch.ones((1, n), dtype=torch.int32, device="cuda"), 1, n, H, heads).float().cpu().view(n, H)
+        have = flat[row0[b]:row0[b] + n].view(torch.float8_e4m3fn).float()
+        assert ((have - want).abs() <= (2.0**-4 + 2.0**-8) * want.abs() + 2.0**-10).all()      # half a step of E4M3, half of the bf16 value
+
+
+@pytest.mark.parametrize("hidden", [256, 768])
+def test_fp8_embedding_gives_the_row_major_bits(hidden):
+    """MT_FP8_FFN embeds with the row-major kernel."""
+    states = []
+    for precision in ("fp8", "fp8_all"):
+        spec = dataclasses.replace(SMALL8, hidden=hidden, heads=hidden // 64, precision=precision)
+        model, _ = mt.load_synthetic(spec, std=0.05)
+        ids, mask, _ = ms.make_inputs(spec)
+        model.forward_tokens(dev(ids), dev(mask))
+        states.append(model.read_hidden(-1, 0, *ids.shape).cpu())
+        model.close()
+    say(f"fp8 embedding: {hidden} columns")
+    assert states[0].abs().max() > 0 and torch.equal(*states)
+
+
 SMALL8 = ms.MTSpec("small_fp8", vocab=500, hidden=256, heads=4, ffn=512, max_pos=64, n_trunk_layers=3,
                    tasks=(ms.TaskSpec(3, 2, 2), ms.TaskSpec(1, 1, 3), ms.TaskSpec(2, 0, 1), ms.TaskSpec(0, 2, 4, token_level=True),
                           ms.TaskSpec(3, 2, 2)),
