@@ -43,7 +43,8 @@ __device__ inline int k_chunk_off(int row, int chunk) { return row * 128 + ((chu
 #define MT_ATTN_CB 2
 #endif
 constexpr int CB = MT_ATTN_CB;        // 32-key blocks per online-softmax chunk
-// PANELS: projections and context in the panel layout.  The staging loads of a wavefront are then 8 keys of 8 chunks, 128 contiguous bytes each.
+// PANELS: projections and context in the panel layout, packed sequences (no mask) and an E4M3 context only, as MT_FP8_LAYER calls it.  The staging loads of a
+// wavefront are then 8 keys of 8 chunks, 128 contiguous bytes each.
 // (attention_tiled_kernel, which needs no staging, rounds its softmax weights to other bfloat16 values; E4M3 contexts amplify that to 5 % of the logits,
 // so the FP8 modes keep this kernel's arithmetic.)
 template <bool PANELS>
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
     const __bf16* __restrict__ qkv = static_cast<const __bf16*>(g.qkv[grp]);
     // 8 columns (from a multiple of 8 on) of a row of the sequence
     auto chunk_at = [&](int row, int col) { return qkv + (PANELS ? tiled_offset(row0 + row, col, ld) : (size_t)(row0 + row) * ld + col); };
-    const int32_t* __restrict__ mrow = mask ? mask + (size_t)b * S : nullptr;
+    const int32_t* __restrict__ mrow = !PANELS && mask ? mask + (size_t)b * S : nullptr;
     const int nblk = Sk / 32;
 
     // ---- this wavefront's 32 queries: their fragments are fetched first, so that the round trip overlaps the staging
@@ -238,27 +239,27 @@ __global__ __launch_bounds__(256, MT_ATTN_MINW) void attention_bf16_kernel(AttnG
         }
     }
 
-    if (q < n_tok && ctx_fmt == 1) {             // E4M3 at unit scale: one byte per element
-        const float inv = 1.0f / l_run;
+    if (q >= n_tok) return;
+    const float inv = 1.0f / l_run;
+    if (PANELS || ctx_fmt == 1) {                // E4M3 at unit scale: one byte per element
         unsigned char* out = static_cast<unsigned char*>(g.ctx[grp]);
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-            for (int qq = 0; qq < 4; ++qq)
-                *reinterpret_cast<uint32_t*>(out + (PANELS ? tiled_offset_e4m3(row0 + q, a * 64 + dt * 32 + qq * 8 + half * 4, H)
-                                                           : ((size_t)row0 + q) * H + a * 64 + dt * 32 + qq * 8 + half * 4)) =
+            for (int qq = 0; qq < 4; ++qq) {
+                const int col = a * 64 + dt * 32 + qq * 8 + half * 4;
+                *reinterpret_cast<uint32_t*>(out + (PANELS ? tiled_offset_e4m3(row0 + q, col, H) : ((size_t)row0 + q) * H + col)) =
                     pack_e4m3(o[dt][qq * 4 + 0] * inv, o[dt][qq * 4 + 1] * inv, o[dt][qq * 4 + 2] * inv, o[dt][qq * 4 + 3] * inv);
-    } else if (q < n_tok) {
-        const float inv = 1.0f / l_run;
-        __bf16* out = static_cast<__bf16*>(g.ctx[grp]);
+            }
+    } else {
+        __bf16* out = static_cast<__bf16*>(g.ctx[grp]) + ((size_t)row0 + q) * H + a * 64;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq) {
                 bf16x4 v = {(__bf16)(o[dt][qq * 4 + 0] * inv), (__bf16)(o[dt][qq * 4 + 1] * inv),
                             (__bf16)(o[dt][qq * 4 + 2] * inv), (__bf16)(o[dt][qq * 4 + 3] * inv)};
-                *reinterpret_cast<bf16x4*>(out + (PANELS ? tiled_offset(row0 + q, a * 64 + dt * 32 + qq * 8 + half * 4, H)
-                                                         : ((size_t)row0 + q) * H + a * 64 + dt * 32 + qq * 8 + half * 4)) = v;
+                *reinterpret_cast<bf16x4*>(out + dt * 32 + qq * 8 + half * 4) = v;
             }
     }
 }
@@ -626,7 +627,7 @@ hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask,
 {
     if (!mask && !(seq_start && seq_len)) return hipErrorInvalidValue;
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
-    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1)) return hipErrorInvalidValue;
+    if (H != A * 64 || G > kMaxGroup || S > kAttnBf16MaxSeq || (ctx_fmt != 0 && ctx_fmt != 1) || (panels && (mask || ctx_fmt != 1))) return hipErrorInvalidValue;
     const int Sk = (S + 31) / 32 * 32;
     const size_t lds = (size_t)Sk * 128 + (size_t)64 * (Sk + 4) * 2 + (size_t)Sk * 4 + (size_t)(Sk / 32) * 4;
     static_assert(kAttnBf16MaxSeq % 32 == 0 &&

@@ -215,7 +215,7 @@ struct AttnGroup {
 // Sequence b owns rows seq_start[b] .. +seq_len[b]-1 (all real tokens) when the two arrays are given;
 // otherwise rows b*S .. b*S+S-1 with `mask` ([B][S], 1 = real) marking the keys.  S bounds the length.
 // ctx_fmt 0: the context is written as bfloat16; 1: as E4M3 at unit scale (one byte per element, same row order).  panels: both matrices in the
-// panel layout (values not transposed).
+// panel layout (values not transposed); packed sequences and E4M3 only.
 hipError_t launch_attention_bf16(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
                                  const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream, int ctx_fmt = 0, bool panels = false);
 // Panel layout, packed sequences: projections with the values transposed (TiledShape::vt_panel), context as an operand; offsets in 256 bytes.
