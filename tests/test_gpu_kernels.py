@@ -375,12 +375,14 @@ def test_attention_panels(heads, lens, seq, late):
     assert worst <= 1.0 and np.isnan(got[~written]).all()
 
 
-# LayerNorm on the panels: remainders of the rows, each number of partial results, few rows and many (2048 divides the forms), a residual that is
-# looked up by row, the [hi | lo] operand.  Bound: float32 sums and a square root (2^-18 of the terms); the operand is the state rounded once, 2^-8
+# LayerNorm on the panels: remainders of the rows, each number of partial results, the three forms (up to 2048 rows, up to 16384, more), a residual
+# that is looked up by row, the [hi | lo] operand.  Bound: float32 sums and a square root (2^-18 of the terms); the operand is the state rounded once, 2^-8
 # of the value, and as [hi | lo] twice, 2^-16.
 @pytest.mark.parametrize("M,rows,H,parts,look_up,split", [
     (1, 1, 64, 1, False, False), (33, 30, 768, 4, False, False), (70, 70, 832, 2, True, True), (2080, 2049, 64, 2, False, False), (2100, 2051, 1024, 4, False, False),
     (37, 37, 1024, 1, True, True), (2052, 2052, 128, 1, True, False), (64, 35, 320, 4, False, True),
+    (2080, 2070, 768, 1, True, True), (16384, 16383, 256, 1, False, True), (16417, 16401, 768, 1, True, False), (16385, 16385, 256, 2, False, True),
+    (16400, 16390, 384, 4, True, True),
 ])
 def test_layernorm_panels(M, rows, H, parts, look_up, split):
     print(f"layernorm: {rows}/{M} x {H}, {parts} parts, look-up {look_up}, split {split}", flush=True)
@@ -468,6 +470,11 @@ def test_heads_of_many_unequal_tasks(batch, seq):
     scale = max(1.0, np.abs(ref).max(), np.abs(ref_tok[real]).max())
     assert np.abs(got[rows] - ref).max() <= 2e-2 * scale and np.abs(tok[rows][real] - ref_tok[real]).max() <= 2e-2 * scale
     assert (tok[~mask.astype(bool)] == 0).all()
+    for t, task in enumerate(tasks):             # alone, a task's classes are few enough for the plain grid; all of them go through the list from 60 sequences on
+        if not task.token_level:
+            at = slice(spec.logit_offset(t), spec.logit_offset(t) + task.n_classes)
+            one = model.forward(dev(ids), dev(mask), task_mask=[u == t for u in range(len(tasks))]).cpu().numpy()
+            assert np.array_equal(one[:, at], got[:, at]), t
     few = model.forward_tokens(dev(ids[:5].copy()), dev(mask[:5].copy()))[0].cpu().numpy()      # five sequences: in place
     assert np.abs(few - got[:5]).max() <= 1e-2 * scale
     model.close()
