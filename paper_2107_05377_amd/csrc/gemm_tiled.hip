@@ -53,10 +53,11 @@ __device__ __forceinline__ float t_act(float v)
 template <bool F8> struct TFrag { typedef bf16x8 type; };
 template <> struct TFrag<true> { typedef i32x8 type; };
 // acc += first * second^T.  scale: of the first operand, an E8M0 exponent in every byte; the second one's is 1.
-__device__ __forceinline__ f32x16 t_mfma(const bf16x8& a, const bf16x8& b, const f32x16& c, int) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f32x16 t_mfma(const i32x8& a, const i32x8& b, const f32x16& c, int scale)
+template <bool F8>
+__device__ __forceinline__ f32x16 t_mfma(const typename TFrag<F8>::type& a, const typename TFrag<F8>::type& b, const f32x16& c, int scale)
 {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, scale, 0, 0x7F7F7F7F);
+    if constexpr (F8) return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, scale, 0, 0x7F7F7F7F);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ i32x8 t_join(const i32x4& lo, const i32x4& hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); }
 // 32 E4M3 columns of a row, 16 each in the lanes of its two halves, from 4 of every 8 per lane (the accumulator's order)
@@ -331,7 +332,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
 #pragma unroll
             for (int i = 0; i < TMI; ++i) {
 #pragma unroll
-                for (int jn = 0; jn < 2; ++jn) acc[i][jn] = t_mfma(wf[buf][step][jn], af[Cfg::IN_PLACE ? 0 : step & 1][i], acc[i][jn], cur.scale);
+                for (int jn = 0; jn < 2; ++jn) acc[i][jn] = t_mfma<F8>(wf[buf][step][jn], af[Cfg::IN_PLACE ? 0 : step & 1][i], acc[i][jn], cur.scale);
                 if constexpr (Cfg::IN_PLACE) read1(0, last ? ns : st, last ? 0 : step + 1, i);
             }
             loadW(tw, kw < KT ? kw : kw - KT, buf, step);
@@ -657,7 +658,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_rows_fp8_kernel(const int32
     auto multiply = [&](int buf, int s0) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (s0 + u < steps) acc = t_mfma(wf[buf][u], af[buf][u], acc, scale);
+            if (s0 + u < steps) acc = t_mfma<true>(wf[buf][u], af[buf][u], acc, scale);
     };
     fetch(0, 0);
     const uint32_t bo = g.b[grp];
@@ -715,10 +716,11 @@ hipError_t launch_tiles(const TiledGroup& g, const TiledShape& s, int n_cu, int 
     const long tiles = (long)(((s.M + 31) / 32 + low - 1) / low) * ((s.N / 32 + 8 / KW - 1) / (8 / KW)) * s.G * s.splits;
     const long slots = (long)n_cu * ((MAXT <= 4 && KW == 1) ? 2 : 1);
     const int n_wg = (int)(tiles < slots ? (tiles < kXcds ? kXcds : tiles) : slots);
-    // Large results go past the second-level caches, whose 4 MB hold the operands that a compute unit's neighbours share, and pay for it in the kernels
-    // that read them (LayerNorm of 2.3 k rows 13.1 -> 14.0 us, attention 11.8 -> 12.6); small ones are written through.  Passes with ordinary stores,
-    // all past, all written through: base 8 x 32 x 128 6094, 5990, 6074 us; 32 x 128 1340, 1312, 1314; 7 x 509 1424, 1420, 1409; routed 32 x 128 1587, 1621,
-    // 1600.  The line, by the row bound: 32 x 128 rows of one problem have 13 to 25 MB, 8 problems of them or 256 x 128 rows 100 MB and more.
+    // Large results go past the second-level caches, whose 4 MB hold the operands that a compute unit's neighbours share; small ones are written through:
+    // their readers follow at once and find them in the last-level cache.  Passes with ordinary stores, all past, all written through, this rule: base
+    // 8 x 32 x 128 5777, 5724, 5779, 5721 us; 4 x 32 x 128 3304, 3301, 3275, 3223; 32 x 128 1287, 1261, 1249, 1247; 7 x 509 1211, 1209, 1187, 1191;
+    // eight different forks, 64 x 128 2542, 2615, 2510, 2537; routed 32 x 128 1522, 1567, 1537, 1537.  The line, by the row bound: 32 x 128 rows of one
+    // problem have 13 to 25 MB, 8 problems of them or 256 x 128 rows 100 MB and more.
     TiledShape t = s;
     t.stream = (long)s.M * s.N * s.G * s.splits * (OUT == TILED_F32 ? 4 : OUT == TILED_BF16 ? 2 : 1) > (64l << 20);
     hipLaunchKernelGGL(kfn, dim3(n_wg), dim3(256), bytes, stream, g, t, n_cu, force);
