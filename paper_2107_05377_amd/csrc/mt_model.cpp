@@ -339,12 +339,27 @@ void put_matrix(unsigned char* dst, const float* src, size_t n, bool bf16)
     for (auto& t : th) t.join();
 }
 
+// f(first, past the last) over the n_panels row panels of a matrix, on several threads if it is large.
+template <typename F>
+void over_panels(size_t n_panels, size_t elements, const F& f)
+{
+    const size_t nthreads = elements > (1u << 19) ? std::min<size_t>({8, n_panels, std::max(1u, std::thread::hardware_concurrency())}) : 1;
+    if (nthreads <= 1) {
+        f(0, n_panels);
+        return;
+    }
+    std::vector<std::thread> th;
+    const size_t per = (n_panels + nthreads - 1) / nthreads;
+    for (size_t t = 0; t < nthreads && t * per < n_panels; ++t) th.emplace_back(f, t * per, std::min(n_panels, (t + 1) * per));
+    for (auto& t : th) t.join();
+}
+
 // [N][K] float32 -> the panel layout in bf16 (N a multiple of 32, K of 8).
 void put_tiled(unsigned char* dst, const float* src, size_t N, size_t K, size_t width = 0, size_t col0 = 0)
 {
     uint16_t* d = reinterpret_cast<uint16_t*>(dst);
     if (!width) width = K;
-    auto panels = [=](size_t lo, size_t hi) {
+    over_panels(N / 32, N * K, [=](size_t lo, size_t hi) {
         for (size_t p = lo; p < hi; ++p)
             for (size_t r = 0; r < 32; ++r) {
                 const float* row = src + (p * 32 + r) * K;
@@ -353,30 +368,25 @@ void put_tiled(unsigned char* dst, const float* src, size_t N, size_t K, size_t 
                     for (size_t e = 0; e < 8; ++e) o[e] = f32_to_bf16_rne(row[k + e]);
                 }
             }
-    };
-    const size_t n_panels = N / 32;
-    const size_t nthreads = N * K > (1u << 19) ? std::min<size_t>({8, n_panels, std::max(1u, std::thread::hardware_concurrency())}) : 1;
-    if (nthreads <= 1) {
-        panels(0, n_panels);
-        return;
-    }
-    std::vector<std::thread> th;
-    const size_t per = (n_panels + nthreads - 1) / nthreads;
-    for (size_t t = 0; t < nthreads && t * per < n_panels; ++t) th.emplace_back(panels, t * per, std::min(n_panels, (t + 1) * per));
-    for (auto& t : th) t.join();
+    });
 }
 
-// [N][K] float32 times scale -> E4M3, row-major or (panel layout) in panels with its inverse in front: as an E8M0 exponent in each byte of an
-// int32.  row0 (a multiple of 32): first row that dst's matrix gets of a taller one.
+// [N][K] float32 times scale -> E4M3, row-major or (panel layout: N a multiple of 32, K of 64) in panels with its inverse in front: as an E8M0 exponent
+// in each byte of an int32.  row0 (a multiple of 32): first row that dst's matrix gets of a taller one.
 void put_e4m3(unsigned char* dst, const float* src, size_t N, size_t K, float scale, bool tiled, size_t row0 = 0)
 {
     if (!tiled) {
         for (size_t i = 0; i < N * K; ++i) dst[row0 * K + i] = f32_to_e4m3_rne(src[i] * scale);
         return;
     }
-    for (size_t r = 0; r < N; ++r)
-        for (size_t k = 0; k < K; ++k) dst[tiled_offset_e4m3(row0 + r, k, K)] = f32_to_e4m3_rne(src[r * K + k] * scale);
-    const uint32_t e = (uint32_t)(127 - ilogbf(scale)) * 0x01010101u;      // (the scale is a power of two between 2^-100 and 2^100)
+    over_panels(N / 32, N * K, [=](size_t lo, size_t hi) {
+        for (size_t r = lo * 32; r < hi * 32; ++r)
+            for (size_t k = 0; k < K; k += 16) {
+                unsigned char* o = dst + tiled_offset_e4m3(row0 + r, k, K);
+                for (size_t e = 0; e < 16; ++e) o[e] = f32_to_e4m3_rne(src[r * K + k + e] * scale);
+            }
+    });
+    const uint32_t e = (uint32_t)(127 - ilogbf(scale)) * 0x01010101u;      // (the scale is a power of two from 2^-120 to 2^127)
     memcpy(dst - kScaleSlot, &e, 4);
 }
 
