@@ -1,7 +1,7 @@
 // Row kernels: the padding-free row map, embedding sum + LayerNorm, LayerNorm of a pre-summed row,
 // pooler input split and classifier.
 // One 64-lane wavefront owns one row; statistics are float32 with a two-pass variance taken from
-// registers, reductions are wavefront shuffles.  Both kernels are HBM-bound: each row is read once
+// registers, reductions are exchanges between lanes without LDS (device_util.h).  Both kernels are HBM-bound: each row is read once
 // and written once (float32 and, for the matrix-core path, a bfloat16 copy).
 #include <algorithm>
 
