@@ -56,7 +56,7 @@ __device__ __forceinline__ float row_sum_whole(const float (&part)[4])
 
 // Mean of a row, and the sum of the squares about it.  SHARES: a share's sum, and its squares about its own mean, are what the wavefronts exchange (once); the
 // row's are put together from them in double.  In float, the mean one of four rounded means, 9 k rows of 768 values about 5 came out 2.2e-7 off
-// float64 (rms, of results of order 1); 1.6e-7 so, 1.8e-7 with one float sum over the whole row.  Time: passes of 1 to 32 k tokens within 0.3 %.
+// float64 (rms, of results of order 1); 1.6e-7 so, 1.8e-7 with one float sum over the whole row.  Time: passes of 40 to 32 k tokens within 0.4 %.
 // Nothing here may be contracted: a share's mean is kept in a register in one form and formed from LDS in the other.
 template <int NI, bool SPLIT, RowSums SUMS>
 __device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_shares(NI) : 1)], int wave, float& mean, float& q)
@@ -118,7 +118,8 @@ __device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_
             mean = mean_of(s[0]);
             q = d2[0];
         } else {
-            // shares of equal size: the squares about the row's mean are those about each share's + N (difference)^2
+            // the squares of a share about the row's mean, from those about its own mean c, d = c - mean: + N d^2 + 2 d (sum - N c).  The last term is there because
+            // c is rounded: without it rows of 896 values, 4e6 of their deviations from zero, came out twice as far off as with one sum (1.03 times with it).
             double sum = s[0], squares = d2[0], u = 0.0;
 #pragma unroll
             for (int h = 1; h < SH; ++h) {
@@ -128,10 +129,10 @@ __device__ __forceinline__ void row_moments(const float4 (&v)[NI / (SPLIT ? row_
             mean = (float)(sum * (1.0 / H));
 #pragma unroll
             for (int h = 0; h < SH; ++h) {
-                const double d = (double)mean_of(s[h]) - mean;
-                u = fma(d, d, u);
+                const double c = mean_of(s[h]), d = c - mean;
+                u = fma(d, fma((double)N, d, 2.0 * fma(-(double)N, c, (double)s[h])), u);
             }
-            q = (float)fma(u, (double)N, squares);
+            q = (float)(squares + u);
         }
     }
 }

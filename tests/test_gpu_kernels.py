@@ -451,6 +451,35 @@ def test_layernorm_panels_error_of_rows_far_from_zero(H, M):
     assert err <= 8 / 7 * np.sqrt((rounding**2).sum()), (err, rounding)
 
 
+@pytest.mark.parametrize("mean", [0.0, 1e2, 1e4, 1e6, 4e6])
+@pytest.mark.parametrize("H", [128, 384, 768, 896, 1024])
+def test_layernorm_panels_error_against_one_float32_sum_over_the_row(H, mean):
+    """Shares of a row put together are to be no further from float64 than one float32 sum over it (16 lanes, their values one after another, then pairwise),
+    however far the row is from zero.  Two such orders differ by a few percent over 3000 rows: a tenth is allowed."""
+    print(f"layernorm against one sum: rows about {mean:g}, {H} columns", flush=True)
+    rng = np.random.default_rng(int(H + mean))
+    v = (rng.standard_normal((3000, H)) + mean).astype(np.float32)
+    w = v.astype(np.float64)
+    want = (w - w.mean(1, keepdims=True)) / w.std(1, keepdims=True)
+
+    def one_sum(x):
+        x = x.reshape(len(x), H // 64, 16, 4)
+        s = np.zeros((len(x), 16), np.float32)
+        for i in range(H // 64):
+            s = s + ((x[:, i, :, 0] + x[:, i, :, 1]) + (x[:, i, :, 2] + x[:, i, :, 3]))
+        while s.shape[1] > 1:
+            s = s[:, ::2] + s[:, 1::2]
+        return s / np.float32(H)
+
+    d = v - one_sum(v)
+    ref = d * (np.float32(1) / np.sqrt(one_sum(d * d)))
+    of, _ = mt.op_panel_layernorm(panels(np.zeros_like(v), torch.float32)[None], panels(v, torch.float32), dev(np.ones(H, np.float32)), dev(np.zeros(H, np.float32)),
+                                  1e-12, len(v), H)
+    err, bar = (np.sqrt(((x - want)**2).mean()) for x in (rows_of(of)[:len(v)], ref.astype(np.float64)))
+    print(f"  {err:.3g}, one sum {bar:.3g}", flush=True)
+    assert err <= 1.1 * bar
+
+
 @pytest.mark.parametrize("batch,seq", [(9, 5), (60, 4), (70, 30)])
 def test_heads_of_many_unequal_tasks(batch, seq):
     """18 tasks of 1 to 50 classes: the classifier's plain grid (9 sequences) and its list of classes; token heads of few and many positions; the row map in
