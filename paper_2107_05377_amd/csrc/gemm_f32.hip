@@ -2,20 +2,26 @@
 // every linear layer.  Products and sums are float32 throughout (v_mfma_f32_32x32x2_f32; plain FMAs in the any-shape kernel).
 //
 // Three kernels, chosen by shape in launch_gemm_f32:
-//   gemm_f32_mfma_kernel  operands through an LDS ring, 32x32 outputs per wavefront.  A K slice is 32 floats = 128 bytes per row, so
-//                         the ring has the geometry of the bf16 kernel's 64-wide slices: global_load_lds of 16-byte chunks, chunk c of
-//                         row r in slot c ^ (r & 7).  A lane reads 4 consecutive k of its row at once; since the order of k is
-//                         free as long as both operands agree, MFMA i of a step takes k = i from the lower and k = 4 + i from
-//                         the upper half wavefront.
+//   gemm_f32_tile_kernel  32x32 blocks, a quarter of K per wavefront, operands through an LDS ring of each wavefront's own.  A K slice is
+//                         32 floats = 128 bytes per row: buffer loads to LDS of 16-byte chunks, chunk c of row r in slot c ^ (r & 7).  A
+//                         lane reads 4 consecutive k of its row at once; since the order of k is free as long as both operands agree, MFMA i
+//                         of a step takes k = i from the lower and k = 4 + i from the upper half wavefront.
 //   gemm_f32_rows_kernel  few rows: bound by streaming the weights, which go straight from global memory to registers, each of
 //                         the 4 wavefronts a quarter of K.
 //   gemm_f32_any_kernel   any M, N, K and strides.
-// The matrix cores' float32 rate is 256 FLOP per clock and compute unit, i.e. a 32x32x2 instruction takes 64 clocks while its
-// operands are 512 bytes: the tile kernel is bound by the matrix cores and by how evenly the tiles divide over the compute
-// units, so the smaller tile with K split over two wavefronts is taken until there are two rounds of the larger one.
-// Measured at 576 rows against the any-shape kernel, which did everything before: 768 x 3072 and 768 x 768 columns x K 223 -> 25 us
-// on average, 3072 x 768 136 -> 38 us, 8 problems of 768 x 3072 / 768 x 768 501 -> 163 us on average (83 TFLOP/s), 8 rows x 8
-// problems 148 -> 18 us.
+// The matrix cores' float32 rate is 256 FLOP per clock and compute unit: a 32x32x2 instruction takes 64 clocks.  What the tile kernel has to do is to
+// keep them coming.
+//   - One block per workgroup is the finest split that needs no second pass: 753 rows x 768 columns are 576 blocks, 2.25 for each compute unit, so the
+//     busiest has 3, where pairs of blocks (264 to 288 workgroups) or 64x64 tiles leave the time of 4 (768 x 3072: 43 us, 63 us before).
+//   - A wavefront issues in order, and a load whose issue is held up holds up its matrix instructions: loads and LDS reads go one by one between
+//     them (all of a slice's loads at its start: 53 us), and nothing in the loop branches, divides or waits for another wavefront (no barrier: a
+//     wavefront reads what it has loaded itself).  1190 clocks a slice with one wavefront per SIMD, 1024 being the matrix instructions; two
+//     workgroups per compute unit fill the rest.
+//   - Workgroups walk a list of blocks; the first slices of the next block are under way during the last ones of a block, whose sums are put together
+//     and stored behind the next one's matrix instructions.
+// 753 rows x 2304 / 768 / 3072 (GELU) x 768, x 768 x 3072: 32, 14, 42, 43 us (82 TFLOP/s); the ring shared by a workgroup, fragments read behind its
+// barrier and multiplied at once, 40, 20, 56, 63.  8 problems: 213, 72, 307, 263 us (101 TFLOP/s at a clock of 1.95 GHz), before 212, 92, 303, 330.
+// 8 problems of 75 rows 29, 15, 39, 44; 38, 20, 60, 62.
 #include <algorithm>
 
 #include "kernels.h"
@@ -56,84 +62,206 @@ __device__ __forceinline__ void store_block_f32(const f32x16& acc, int m, int n_
     }
 }
 
-// WM x WN wavefronts of 32x32 outputs, each with WK wavefronts that share its K range.
-template <int WM, int WN, int WK, int STAGES>
-__global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, GemmShape s)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t f_rsrc(const void* base, uint32_t bytes)
 {
-    constexpr int BM = 32 * WM, BN = 32 * WN, SUB = BM + BN, ROWS = SUB * WK;          // rows of 128 bytes per stage
-    constexpr int STAGE = ROWS * 128, LPS = ROWS / 8 / 4;                               // load instructions per wavefront and slice
-    static_assert(WM * WN * WK == 4 && ROWS % 32 == 0, "four wavefronts");
-    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    const int grp = blockIdx.z;
-    const int N = g.N[grp];
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
+constexpr int kRing = 2, kStage = 64 * 128, kExchange = 16 * 1024;      // stages, bytes of one (32 rows of A, 32 of W), exchanged partial sums
+constexpr int kTileLds = 4 * kRing * kStage + kExchange;
+
+// One 32x32 block at a time, a quarter of K per wavefront, two workgroups per compute unit.
+__device__ __forceinline__ void gemm_f32_tile_body(const GemmGroup& g, const GemmShape& s, unsigned char* lds)
+{
     const int M = s.d_M ? min(s.M, *s.d_M) : s.M;      // rows actually present; the grid covers the bound s.M
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    if (n0 >= N || m0 >= M) return;
-    const unsigned char* A = static_cast<const unsigned char*>(g.A[grp]);
-    const unsigned char* W = static_cast<const unsigned char*>(g.W[grp]);
+    const int tiles_n = (s.N + 31) >> 5, per_problem = ((M + 31) >> 5) * tiles_n, total = per_problem * s.G;
+    if ((int)blockIdx.x >= total) return;
     const uint32_t lda_b = (uint32_t)s.lda * 4, ldw_b = (uint32_t)(s.ldw ? s.ldw : s.K) * 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / WK / WN;
+    // this wavefront's slices of 32 k: a quarter of them, the first wavefronts one more where four do not divide them
+    const int slices = s.K >> 5, KT = (slices >> 2) + (wave < (slices & 3) ? 1 : 0);
+    const int k0 = ((slices >> 2) * wave + min(wave, slices & 3)) * 128;
 
-    // load i of a wavefront fills stage rows (wave + 4 i) * 8 .. + 7: sub-slice row / SUB, in it BM rows of A, then BN of W
-    const unsigned char* src[LPS];
-#pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-        const int row = (wave + i * 4) * 8 + (lane >> 3);
-        const int sub = row / SUB, r = row - sub * SUB;
-        const int off = sub * 128 + (((lane & 7) ^ (row & 7)) << 4);
-        src[i] = r < BM ? A + (size_t)min(m0 + r, M - 1) * lda_b + off : W + (size_t)min(n0 + r - BM, N - 1) * ldw_b + off;
-    }
-    const int KT = s.K / (32 * WK);
-    auto issue = [&](int kt) {
-        unsigned char* base = lds + (kt % STAGES) * STAGE;
-#pragma unroll
-        for (int i = 0; i < LPS; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (size_t)kt * (128 * WK)), (lptr_t)(base + (wave + i * 4) * 1024), 16, 0, 0);
+    struct Ref {
+        __amdgpu_buffer_rsrc_t A, W;                   // from the block's first row on; rows beyond the last one read as zero
+        int grp, m0, n0;
     };
-    const int a_row = wk * SUB + wm * 32 + l32, w_row = wk * SUB + BM + wn * 32 + l32;
+    auto locate = [&](int tile) {
+        Ref t;
+        t.grp = tile / per_problem;
+        const int tt = tile - t.grp * per_problem, tm = tt / tiles_n;
+        t.m0 = tm * 32;
+        t.n0 = (tt - tm * tiles_n) * 32;
+        const int rows_w = g.N[t.grp] - t.n0;          // none: a problem of fewer columns than the widest
+        t.A = f_rsrc(static_cast<const unsigned char*>(g.A[t.grp]) + (size_t)t.m0 * lda_b, (min(32, M - t.m0) - 1) * lda_b + s.K * 4);
+        t.W = f_rsrc(static_cast<const unsigned char*>(g.W[t.grp]) + (size_t)t.n0 * ldw_b, rows_w > 0 ? (min(32, rows_w) - 1) * ldw_b + s.K * 4 : 0);
+        return t;
+    };
+    // load i of a slice fills 8 rows of 128 bytes, chunk c of row r in slot c ^ (r & 7)
+    int va[4], vw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = i * 8 + (lane >> 3), off = ((lane & 7) ^ (r & 7)) << 4;
+        va[i] = r * lda_b + off;
+        vw[i] = r * ldw_b + off;
+    }
+    unsigned char* mine = lds + wave * (kRing * kStage);
+    auto issue = [&](const Ref& t, int kt, int st, int i) {
+        unsigned char* to = mine + st * kStage + i * 1024;
+        if (i < 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(t.A, (lptr_t)to, 16, va[i & 3], k0 + kt * 128, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(t.W, (lptr_t)to, 16, vw[i & 3], k0 + kt * 128, 0, 0);
+    };
+    f32x4 af[4], wf[4];
+    int ro[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ro[c] = l32 * 128 + (((c * 2 + half) ^ (l32 & 7)) << 4);
+    auto read = [&](int st, int c) {
+        const unsigned char* p = mine + st * kStage + ro[c];
+        af[c] = *reinterpret_cast<const f32x4*>(p);
+        wf[c] = *reinterpret_cast<const f32x4*>(p + 4096);
+    };
     f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-    for (int p = 0; p < STAGES - 1; ++p)
-        if (p < KT) issue(p);
-    for (int kt = 0; kt < KT; ++kt) {
-        // slice kt has landed when at most the slices after it are outstanding; the fragments of slice kt - 1 are in registers
-        if (kt + STAGES - 2 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPS * (STAGES - 2)) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();                   // ... for every wavefront
+    auto mul = [&](int c, int i) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[c][i], af[c][i], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // A finished block's partial sums wait in LDS until the second slice of the next block, whose matrix instructions cover the sum, the activation and the store.
+    float* const part = reinterpret_cast<float*>(lds + 4 * kRing * kStage);
+    struct Out {
+        int grp, m, n;
+        bool ok;
+        f32x4 bias;
+    };
+    f32x4 v;
+    auto exchange = [&]() {                                              // this wavefront's share
         asm volatile("" ::: "memory");
-        if (kt + STAGES - 1 < KT) issue(kt + STAGES - 1);
-        const unsigned char* sb = lds + (kt % STAGES) * STAGE;
-        f32x4 af[4], wf[4];
+        __builtin_amdgcn_s_barrier();                                    // everyone has read the block before
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            af[c] = *reinterpret_cast<const f32x4*>(sb + a_row * 128 + (((c * 2 + half) ^ (a_row & 7)) << 4));
-            wf[c] = *reinterpret_cast<const f32x4*>(sb + w_row * 128 + (((c * 2 + half) ^ (w_row & 7)) << 4));
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(part + ((wave * 4 + q) * 64 + lane) * 4) = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+    };
+    auto gather = [&]() {                                                // columns 8 wave .. + 7 of the block, added in a fixed order
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        f32x4 p[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) p[w] = *reinterpret_cast<const f32x4*>(part + ((w * 4 + wave) * 64 + lane) * 4);
+        v = p[0] + p[1] + p[2] + p[3];
+    };
+    auto store = [&](const Out& o) {
+        if (!o.ok) return;
+        if (g.residual[o.grp]) v += *reinterpret_cast<const f32x4*>(g.residual[o.grp] + (size_t)o.m * s.ldr + o.n);
+        *reinterpret_cast<f32x4*>(static_cast<float*>(g.C[o.grp]) + (size_t)o.m * s.ldc + o.n) = v;
+    };
+    int st = 0;
+    // A slice: the loads two slices ahead (left = 2) and the fragments of the next one (left > 0) between its products, and extra(i) behind product i.
+    auto slice = [&](const Ref& t, int kn, auto left, auto extra) {
+        constexpr int L = decltype(left)::value;
+        auto next = [&](int c) {
+            if constexpr (L > 0) read(st, c);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        __builtin_amdgcn_sched_barrier(0);
+        mul(0, 0);
+        extra(0);
+        mul(0, 1);
+        extra(1);
+        mul(0, 2);
+        extra(2);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // this slice is in registers, its stage is free
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if constexpr (L == kRing) issue(t, kn, st, i);
+            __builtin_amdgcn_sched_barrier(0);
+            mul((3 + i) >> 2, (3 + i) & 3);
+            extra(3 + i);
         }
+        st ^= 1;
+        if constexpr (L > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (L - 1)) : "memory");      // the next slice has landed
+        next(0);
+        mul(2, 3);
+        extra(11);
+        next(1);
+        mul(3, 0);
+        extra(12);
+        next(2);
+        mul(3, 1);
+        extra(13);
+        mul(3, 2);
+        mul(3, 3);
+        next(3);
+    };
+    auto nothing = [](int) {};
+
+    Ref cur = locate(blockIdx.x);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+    for (int p = 0; p < kRing; ++p)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[c][i], af[c][i], acc, 0, 0, 0);
-    }
-    if constexpr (WK > 1) {                             // partial sums of the other K shares, added in a fixed order
-        __syncthreads();
-        float* part = reinterpret_cast<float*>(lds);
-        if (wk > 0) {
+        for (int i = 0; i < 8; ++i) issue(cur, p, p, i);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
 #pragma unroll
-            for (int e = 0; e < 16; ++e) part[(((wm * WN + wn) * (WK - 1) + wk - 1) * 16 + e) * 64 + lane] = acc[e];
+    for (int c = 0; c < 4; ++c) read(0, c);
+    Out prev;
+    prev.ok = false;
+    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+        // The last slices of a block fetch the next one's first.  Without a next one they fetch nothing, or (of so few slices that these are also the first
+        // ones) this block's again, never read.
+        const bool more = tile + (int)gridDim.x < total;
+        const Ref nxt = more ? locate(tile + gridDim.x) : cur;
+        Out out;
+        out.grp = cur.grp;
+        out.m = cur.m0 + l32;
+        out.n = cur.n0 + wave * 8 + half * 4;
+        out.ok = out.m < M && out.n < g.N[cur.grp];
+        out.bias = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (g.bias[cur.grp] && out.ok) out.bias = *reinterpret_cast<const f32x4*>(g.bias[cur.grp] + out.n);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        auto ahead = [&](int kt, auto extra) {
+            const bool here = kt + kRing < KT;
+            const Ref t = here ? cur : nxt;
+            slice(t, here ? kt + kRing : kt + kRing - KT, std::integral_constant<int, kRing>{}, extra);
+        };
+        ahead(0, [&](int i) {
+            if (i == 11) asm volatile("" : "+v"(out.bias));               // here its load is awaited anyway; later the wait would be for the ring's too
+        });
+        if (tile != (int)blockIdx.x) {
+            gather();
+            ahead(1, [&](int i) {
+                if (i == 0) v += prev.bias;
+                if (s.act != ACT_NONE && i >= 1 && i <= 10 && i % 3 == 1) v[i / 3] = apply_act(v[i / 3], s.act);
+                if (i == 12) store(prev);
+            });
+        } else {
+            ahead(1, nothing);
         }
-        __syncthreads();
-        if (wk > 0) return;
-#pragma unroll
-        for (int w = 0; w < WK - 1; ++w)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[e] += part[(((wm * WN + wn) * (WK - 1) + w) * 16 + e) * 64 + lane];
+        const bool drain = !more && KT >= 2 * kRing;
+        for (int kt = 2; kt < (drain ? KT - kRing : KT); ++kt) ahead(kt, nothing);
+        if (drain) {
+            slice(cur, 0, std::integral_constant<int, 1>{}, nothing);
+            slice(cur, 0, std::integral_constant<int, 0>{}, nothing);
+        }
+        exchange();
+        prev = out;
+        cur = nxt;
     }
-    store_block_f32(acc, m0 + wm * 32 + l32, n0 + wn * 32 + half * 4, M, N, g.bias[grp], g.residual[grp], s.ldr,
-                    static_cast<float*>(g.C[grp]), s.ldc, s.act);
+    gather();
+    v += prev.bias;
+    if (s.act != ACT_NONE)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = apply_act(v[e], s.act);
+    store(prev);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // loads must land before the LDS is released
+}
+
+__global__ __launch_bounds__(256, 2) void gemm_f32_tile_kernel(GemmGroup g, GemmShape s)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    gemm_f32_tile_body(g, s, lds);
 }
 
 // 32 rows x 32 columns per workgroup, a quarter of K per wavefront, operands straight into registers.
@@ -244,50 +372,34 @@ __global__ __launch_bounds__(256) void gemm_f32_any_kernel(GemmGroup g, GemmShap
     }
 }
 
-template <int WM, int WN, int WK, int STAGES>
-hipError_t launch_mfma(const GemmGroup& g, const GemmShape& s, hipStream_t stream)
-{
-    constexpr int bytes = STAGES * 32 * (WM + WN) * WK * 128;
-    static std::atomic<uint64_t> lds_raised{0};
-    if (bytes > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)gemm_f32_mfma_kernel<WM, WN, WK, STAGES>, bytes, lds_raised);
-        if (e != hipSuccess) return e;
-    }
-    dim3 grid((s.N + 32 * WN - 1) / (32 * WN), (s.M + 32 * WM - 1) / (32 * WM), s.G), block(256);
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<WM, WN, WK, STAGES>), grid, block, bytes, stream, g, s);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t stream)
 {
     if (s.G <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
-    // the matrix-core kernels move 16-byte chunks of whole 128-byte (64 for two K shares: 256-byte) slices
+    // the matrix-core kernels move 16-byte chunks of whole slices; offsets inside a block's 32 rows are 31-bit
     bool chunks = s.K % 64 == 0 && s.N % 4 == 0 && s.lda % 4 == 0 && s.ldw % 4 == 0 && s.ldc % 4 == 0 && s.ldr % 4 == 0 &&
-                  (uint64_t)s.lda * 4 < (1ull << 32) && (uint64_t)s.ldw * 4 < (1ull << 32);
+                  (uint64_t)s.lda * 128 < (1ull << 31) && (uint64_t)(s.ldw ? s.ldw : s.K) * 128 < (1ull << 31);
     for (int i = 0; chunks && i < s.G; ++i)
         chunks = g.N[i] % 4 == 0 && (((uintptr_t)g.A[i] | (uintptr_t)g.W[i] | (uintptr_t)g.C[i] | (uintptr_t)g.bias[i] | (uintptr_t)g.residual[i]) & 15) == 0;
-    if (!chunks) {
+    // each wavefront's quarter has as many slices as the ring; fewer: the few-row kernel, whose blocks are rows of the grid
+    const bool rows = s.M <= 32 || s.K < 4 * 32 * kRing;
+    if (!chunks || (rows && (s.M + 31) / 32 > 65535)) {
         dim3 grid((s.N + TN - 1) / TN, (s.M + TM - 1) / TM, s.G), block(256);
         hipLaunchKernelGGL(gemm_f32_any_kernel, grid, block, 0, stream, g, s);
         return hipGetLastError();
     }
-    if (s.M <= 32) {
+    if (rows) {
         dim3 grid((s.N + 31) / 32, (s.M + 31) / 32, s.G), block(256);
         hipLaunchKernelGGL(gemm_f32_rows_kernel, grid, block, 0, stream, g, s);
         return hipGetLastError();
     }
-    // Blocks of 32 x 32, one per workgroup, its wavefronts a quarter of K each; otherwise two blocks and half of K.  While every block has a compute unit
-    // that is 1.3 to 1.8 times as fast (240 blocks of one problem, K = 768: 8.8 and 12.1 us, 3072: 20.5 and 35.8; 256 blocks of 8 problems 8.7 and
-    // 12.2, 24.1 and 35.8; K = 256 level).  Up to one and a half times as many it is a little ahead for one problem (264 to 384 blocks, K = 768: 11.7
-    // to 12.0 and 12.1 to 12.2, 3072: 33.9 to 34.5 and 35.8), while several problems at K = 768 lose (320 and 384 blocks of 8: 12.6 and 12.2, 12.9 and 12.3).
-    // By the problems with all tasks enabled: a task's logits are the same bits whichever others are.
-    const long plan = std::max(s.plan, s.G), blocks = plan * ((s.M + 31) / 32) * ((s.N + 31) / 32), n_cu = device_cu_count();
-    if (blocks <= (plan == 1 ? n_cu * 3 / 2 : n_cu) && s.K % 128 == 0) return launch_mfma<1, 1, 4, 2>(g, s, stream);
-    const long tiles64 = (long)s.G * ((s.M + 63) / 64) * ((s.N + 63) / 64);
-    if (tiles64 >= 1024) return launch_mfma<2, 2, 1, 4>(g, s, stream);
-    return launch_mfma<1, 2, 2, 3>(g, s, stream);
+    static std::atomic<uint64_t> lds_raised{0};
+    hipError_t e = ensure_dynamic_lds((const void*)gemm_f32_tile_kernel, kTileLds, lds_raised);
+    if (e != hipSuccess) return e;
+    const long tiles = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32);
+    hipLaunchKernelGGL(gemm_f32_tile_kernel, dim3((unsigned)std::min(tiles, 2l * device_cu_count())), dim3(256), kTileLds, stream, g, s);
+    return hipGetLastError();
 }
 
 }  // namespace mt

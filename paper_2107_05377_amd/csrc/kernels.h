@@ -46,8 +46,6 @@ struct GemmShape {
     const int32_t* d_sub_row0;
     const int32_t* d_sub_rows;
     float out_scale;        // FP8 path, out_f32 == 2: the value is multiplied by this before it is rounded to E4M3
-    int32_t plan;           // float32 path: problems that the launch has when every task is enabled (0 = G): decides into how many shares few
-                            // output blocks cut K
 };
 
 // bf16 x bf16 -> fp32 accumulate on the matrix cores.  Needs K % 64 == 0, lda % 8 == 0, 16-byte aligned A/W rows.

@@ -503,11 +503,10 @@ struct Launcher {
         if (first_err == hipSuccess && e != hipSuccess) first_err = e;
     }
 
-    int plan = 0;          // problems that the group's launches have with every task enabled (GemmShape::plan, TiledShape::plan)
-    void gemm(int klass, const GemmGroup& g, GemmShape s)
+    int plan = 0;          // problems that the group's launches have with every task enabled (TiledShape::plan)
+    void gemm(int klass, const GemmGroup& g, const GemmShape& s)
     {
         begin(klass);
-        s.plan = plan;
         if (m->bf16) check(launch_gemm_bf16(g, s, st));
         else check(launch_gemm_f32(g, s, st));
         end();
@@ -1843,7 +1842,6 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         } else {
             L.check(launch_gather_rows(sg, n, HB, H, hrm.seq_start, S, HB * S, L.st));
             GemmShape s{n, HB, H, H, H, H, 0, ACT_TANH, 1, nullptr, 1, 0};
-            s.plan = h_route ? 0 : std::min((int)std::count_if(m->tasks.begin(), m->tasks.end(), [](const mt_task_desc& d) { return d.head == MT_HEAD_SEQUENCE; }), kMaxGroup);
             L.check(launch_gemm_f32(g, s, L.st));
         }
         L.check(launch_classifier(cg, n, HB, H, maxC, bf ? 1 : 0, m->C_tot, out_row, L.st));

@@ -40,6 +40,24 @@ def test_gemm_f32_tiles(M, N, K, act):
     assert np.abs(out - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
 
 
+# the block list of the float32 tile kernel: one block and several per workgroup (more than two per compute unit of 256), remainders of rows, columns and of the
+# four K shares (equal and not), as few slices as the ring has and more, one problem and several
+@pytest.mark.parametrize("G,M,N,K", [(1, 33, 36, 256), (1, 64, 96, 320), (3, 97, 100, 448), (1, 1500, 1028, 256), (8, 130, 516, 320), (2, 700, 800, 768), (5, 40, 64, 3072)])
+def test_gemm_f32_block_list(G, M, N, K):
+    print(f"gemm_f32, {G} x {M} x {N} x {K}", flush=True)
+    rng = np.random.default_rng(G + M + N + K)
+    A, W = rng.standard_normal((G, M, K)).astype(np.float32), rng.standard_normal((G, N, K)).astype(np.float32)
+    b = rng.standard_normal((G, N)).astype(np.float32)
+    out = torch.full((G * M + 1, N), 7.0, dtype=torch.float32, device="cuda")
+    mt.op_linear_batched(mt.MT_FP32_CHECK, dev(A), dev(W), dev(b), out=out[:G * M].view(G, M, N))
+    ref = A.astype(np.float64) @ W.astype(np.float64).transpose(0, 2, 1) + b[:, None]
+    # a quarter of K one after another, the four shares, the bias: each addition rounds at most by 2^-24 of the sum of magnitudes
+    bound = (K / 4 + 8) * 2.0**-24 * (np.abs(A) @ np.abs(W).transpose(0, 2, 1) + np.abs(b[:, None]))
+    got = out.cpu().numpy()
+    assert (np.abs(got[:G * M].reshape(G, M, N) - ref) <= bound).all()
+    assert (got[G * M:] == 7.0).all()                    # nothing beyond the last row
+
+
 @pytest.mark.parametrize("B,S,H,A", [(2, 1, 64, 1), (3, 31, 64, 2), (2, 33, 128, 2), (1, 130, 64, 1), (2, 257, 64, 2)])
 def test_attention_f32_blocks(B, S, H, A):
     print(f"attention_f32 B={B} S={S} H={H} A={A}", flush=True)
