@@ -7,7 +7,10 @@
 //                        fragments are in flight at once.
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
 //                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
-//                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509, now 117 and 34); bound by reading the rows.
+//                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509); bound by reading the rows.
+//                        Four wavefronts: six of 128 columns, placed 2, 2, 1, 1 on the SIMDs, left no room for a second workgroup of theirs at 168
+//                        registers (200 workgroups in flight, now 450), and a compute unit stood still while its one waited for rows or stored.
+//                        21 tasks x 272 short sequences 62 + 77 -> 41 + 52 us, 8 tasks x 256 112 -> 73, x 7 of up to 509 tokens 33 -> 26.
 // Scores and sums were two kernels that read the rows once each (85 + 107 us for 8 tasks x 256 sequences).
 #include "kernels.h"
 #include "device_util.h"
@@ -22,6 +25,7 @@ constexpr int kHeadsPad = 16;
 // against float64 is then that of float32 weights unless the sum cancels to less than about 2^-8 of its terms (one term exceeds it 3 to 20 times
 // where the sum cancels at all).  Cost of the second term: 21 tasks x 272 short sequences 2810 -> 2822 us a pass, 8 tasks x 256 sequences nothing;
 // of the third 1 % of the former; MT_FP8_LAYER with it 8 tasks x 4 sequences 504 -> 508 us, x 256 sequences 4.25 -> 4.28 ms.
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, const int32_t* seq_start, int max_rows, FirstTokenGroup g)
@@ -120,12 +124,12 @@ __global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A
     }
 }
 
-// NW wavefronts, each 128 of the H columns (the last one perhaps 64).  Per key panel: a wavefront loads its columns of the 32 rows as matrix
+// NW wavefronts, each STEPS x 32 of the H columns (the last ones perhaps fewer, or none).  Per key panel: a wavefront loads its columns of the 32 rows as matrix
 // operands (16 x 32, straight from global memory), forms its share of the scores with q~ and leaves it in LDS; after the only barrier all
 // wavefronts add the shares, each for itself, and have the weights of all heads in the operand order of the next product.  For that the
 // rows are needed transposed: a product with the unit matrix, exact, moves the columns to the lanes.
-template <int NW, int TERMS>
-__global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(const int32_t* __restrict__ seq_start,
+template <int NW, int STEPS, int TERMS>
+__global__ __launch_bounds__(NW * 64, 2) void first_attend_kernel(const int32_t* __restrict__ seq_start,
                                                                                     const int32_t* __restrict__ seq_len, int B, int Smax, int H,
                                                                                     int A, int64_t xbar_stride, FirstTokenGroup g)
 {
@@ -139,19 +143,19 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, l4 = lane >> 4;
     const int p0 = row0 >> 5, p1 = (end + 31) >> 5;                          // panels of the sequence
-    const int steps = min(4, (H - wave * 128) / 32);                         // of 32 columns: 4 or 2
+    const int c0 = wave * STEPS, steps = min(STEPS, (H >> 5) - c0), c_max = (H >> 5) - 1;          // columns in units of 32
     const size_t pitch = (size_t)H * 64;                                     // bytes of a panel
-    const unsigned char* x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)wave * 16 * 512 + l4 * 512 + l16 * 16;
-    const __bf16* qt = static_cast<const __bf16*>(g.qt[grp]) + ((size_t)b * kHeadsPad + min(l16, A - 1)) * H + wave * 128 + l4 * 8;
-    bf16x8 qf[4];
-    f32x4 acc[8];                                                            // 16 columns x 16 heads each; lane: head l16, columns 4 l4 + 0..3
+    const unsigned char* x = static_cast<const unsigned char*>(g.x[grp]) + l4 * 512 + l16 * 16;
+    const __bf16* qt = static_cast<const __bf16*>(g.qt[grp]) + ((size_t)b * kHeadsPad + min(l16, A - 1)) * H + l4 * 8;
+    bf16x8 qf[STEPS];
+    f32x4 acc[2 * STEPS];                                                            // 16 columns x 16 heads each; lane: head l16, columns 4 l4 + 0..3
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        qf[k] = *reinterpret_cast<const bf16x8*>(qt + min(k, steps - 1) * 32);
+    for (int k = 0; k < STEPS; ++k) {
+        qf[k] = *reinterpret_cast<const bf16x8*>(qt + min(c0 + k, c_max) * 32);
         if (k >= steps) qf[k] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});          // columns beyond H repeat others, to no effect
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < 2 * STEPS; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     bf16x8 unit[2];                                                          // [16 columns][32]: the first and the second 16 of a step
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -162,31 +166,29 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
         unit[c] = __builtin_bit_cast(bf16x8, u);
     }
     float m_run = -INFINITY, l_run = 0.f;
-    bf16x8 xa[2][4], xb[2][4];                                               // [upper or lower 16 keys][step]
-    auto fetch = [&](bf16x8 (&v)[2][4], int kb) {
+    bf16x8 xa[2][STEPS], xb[2][STEPS];                                               // [upper or lower 16 keys][step]
+    auto fetch = [&](bf16x8 (&v)[2][STEPS], int kb) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < STEPS; ++k)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) v[h][k] = *reinterpret_cast<const bf16x8*>(x + (size_t)kb * pitch + min(k, steps - 1) * 2048 + h * 256);
+            for (int h = 0; h < 2; ++h) v[h][k] = *reinterpret_cast<const bf16x8*>(x + (size_t)kb * pitch + min(c0 + k, c_max) * 2048 + h * 256);
     };
-    auto block = [&](const bf16x8 (&v)[2][4], int kb, int buf) {
+    auto block = [&](const bf16x8 (&v)[2][STEPS], int kb, int buf) {
         f32x4 sc[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             sc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], sc[h], 0, 0, 0);    // row: key, column: head
-            if constexpr (NW > 1) *reinterpret_cast<f32x4*>(part[buf][wave][h][lane]) = sc[h];
+            for (int k = 0; k < STEPS; ++k) sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], sc[h], 0, 0, 0);    // row: key, column: head
+            *reinterpret_cast<f32x4*>(part[buf][wave][h][lane]) = sc[h];
         }
-        if constexpr (NW > 1) {
-            __syncthreads();
+        __syncthreads();
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                sc[h] = *reinterpret_cast<const f32x4*>(part[buf][0][h][lane]);
+        for (int h = 0; h < 2; ++h) {
+            sc[h] = *reinterpret_cast<const f32x4*>(part[buf][0][h][lane]);
 #pragma unroll
-                for (int w = 1; w < NW; ++w) sc[h] += *reinterpret_cast<const f32x4*>(part[buf][w][h][lane]);
-                __builtin_amdgcn_sched_barrier(0);                           // (fewer of the shares in registers at a time)
-            }
+            for (int w = 1; w < NW; ++w) sc[h] += *reinterpret_cast<const f32x4*>(part[buf][w][h][lane]);
+            if constexpr (NW > 4) __builtin_amdgcn_sched_barrier(0);         // (fewer of the shares in registers at a time)
         }
         // keys 16 h + 4 l4 + e of this panel; what belongs to a neighbouring sequence counts as nothing, whatever it is
         const bool edge = kb * 32 < row0 || kb * 32 + 32 > end;
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
             m_run = m_new;
             l_run *= alpha;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+            for (int c = 0; c < 2 * STEPS; ++c) acc[c] *= alpha;
         }
         bf16x8 pf[TERMS];
 #pragma unroll
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
                 }
             }
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
+        for (int c = 0; c < 2 * STEPS; ++c) {
             bf16x8 xt;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -243,25 +245,42 @@ __global__ __launch_bounds__(NW * 64, NW <= 6 ? 3 : 2) void first_attend_kernel(
             if (c & 1) __builtin_amdgcn_sched_barrier(0);                    // (two at a time, for the registers)
         }
     };
+    // A panel is on its way while the one before it is worked on.  Written so that each wait has one possible number of loads behind it: after a
+    // conditional fetch the compiler waits for everything, the next panel included.
     fetch(xa, p0);
-    for (int kb = p0; kb < p1; kb += 2) {
-        if (kb + 1 < p1) fetch(xb, kb + 1);
+    int kb = p0;
+    for (; kb + 2 < p1; kb += 2) {
+        fetch(xb, kb + 1);
         block(xa, kb, 0);
-        if (kb + 1 >= p1) break;
-        if (kb + 2 < p1) fetch(xa, kb + 2);
+        fetch(xa, kb + 2);
         block(xb, kb + 1, 1);
+    }
+    if (kb + 1 < p1) {
+        fetch(xb, kb + 1);
+        block(xa, kb, 0);
+        block(xb, kb + 1, 1);
+    } else {
+        block(xa, kb, 0);
     }
     l_run = lane_pair_sum<16>(l_run);
     l_run = lane_pair_sum<32>(l_run);
-    if (l16 >= A) return;
     const float inv = 1.0f / l_run;
-    __bf16* out = static_cast<__bf16*>(g.xbar[grp]) + l16 * xbar_stride + tiled_offset(b, wave * 128 + l4 * 4, H);
+    // 4 columns of each of two blocks per lane; lanes 16 apart exchange, so that each has a chunk's 8 columns of one
+    __bf16* out = static_cast<__bf16*>(g.xbar[grp]) + l16 * xbar_stride + tiled_offset(b, c0 * 32 + (l4 & 1) * 16 + (l4 >> 1) * 8, H);
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
-        if (c < 4 || steps == 4) {
-            const bf16x4 o = {(__bf16)(acc[c][0] * inv), (__bf16)(acc[c][1] * inv), (__bf16)(acc[c][2] * inv), (__bf16)(acc[c][3] * inv)};
-            *reinterpret_cast<bf16x4*>(out + c * 512) = o;
+    for (int k = 0; k < STEPS; ++k) {
+        uint32_t d[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const f32x4& a = acc[2 * k + j];
+            const bf16x4 o = {(__bf16)(a[0] * inv), (__bf16)(a[1] * inv), (__bf16)(a[2] * inv), (__bf16)(a[3] * inv)};
+            const u32x2 u = __builtin_bit_cast(u32x2, o);
+            d[j][0] = u[0];
+            d[j][1] = u[1];
         }
+        const auto lo = __builtin_amdgcn_permlane16_swap(d[0][0], d[1][0], false, false), hi = __builtin_amdgcn_permlane16_swap(d[0][1], d[1][1], false, false);
+        if (k < steps && l16 < A) *reinterpret_cast<u32x4*>(out + k * 1024) = u32x4{lo[0], hi[0], lo[1], hi[1]};
+    }
 }
 
 }  // namespace
@@ -280,20 +299,20 @@ hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* s
 {
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
     if (!seq_start || !seq_len || G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-#define MT_ATTEND(N)                                                                                                                          \
-    case N: {                                                                                                                                 \
-        auto kfn = whole_weights ? first_attend_kernel<N, 3> : first_attend_kernel<N, 2>;                                                     \
+#define MT_ATTEND(N, STEPS)                                                                                                                   \
+    {                                                                                                                                         \
+        auto kfn = whole_weights ? first_attend_kernel<N, STEPS, 3> : first_attend_kernel<N, STEPS, 2>;                                       \
         hipLaunchKernelGGL(kfn, dim3((B + 7) / 8 * 8, G), dim3(N * 64), 0, stream, seq_start, seq_len, B, S, H, A, xbar_stride, g);           \
-    } break
+    }                                                                                                                                         \
+    break
     switch ((H + 127) / 128) {
-        MT_ATTEND(1);
-        MT_ATTEND(2);
-        MT_ATTEND(3);
-        MT_ATTEND(4);
-        MT_ATTEND(5);
-        MT_ATTEND(6);
-        MT_ATTEND(7);
-        MT_ATTEND(8);
+        case 1: MT_ATTEND(4, 1);
+        case 2: MT_ATTEND(4, 2);
+        case 3: MT_ATTEND(4, 3);
+        case 4: MT_ATTEND(4, 4);
+        case 5: MT_ATTEND(4, 5);
+        case 6: MT_ATTEND(4, 6);
+        default: MT_ATTEND(8, 4);
     }
 #undef MT_ATTEND
     return hipGetLastError();
