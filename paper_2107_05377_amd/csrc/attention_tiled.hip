@@ -16,7 +16,8 @@
 //
 // Bound by memory when the batch is large: 18.6 k rows of 12 heads are 114 MB in 29 us (staging keys and values in LDS 32, on 7
 // sequences of up to 509 tokens 23.5 instead of 10.1, on 128 of up to 256 with 16 heads 79 instead of 43), by the chain of its loads
-// when it is small (one sequence: 4.1 us, 6.3).  Loads run one block ahead: a block's keys are fetched after the scores of the one before, its values after the product.  The four
+// when it is small (one sequence: 4.1 us, 6.3).  Loads run one block ahead: a block's keys are fetched after the scores of the one before, its values after the product, and
+// no wait is for what the next block needs (before: for all of it at every product; 32 x 128 tokens 9.4 -> 8.8 us a layer, 7 x 509 a pass 0.5 %).  The four
 // wavefronts of a workgroup take neighbouring query panels of a head, so that keys and values come from the first-level cache for
 // three of them; where that gives too few wavefronts (long sequences of a small batch), KS of them share a query panel and take
 // every KS-th key panel each, merged through LDS.
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
     const int p0 = row0 >> 5, p1 = (end + 31) >> 5;                          // panels of the sequence
     const int H = A * 64;
     const size_t pitch = (size_t)H * 192;                                    // bytes of a panel of projections
-    const unsigned char* qkv = base_qkv + (size_t)g.qkv[grp] * 256 + a * 4096 + lane * 16;
+    const unsigned char* qkv = base_qkv + (size_t)g.qkv[grp] * 256 + a * 4096;
 
     for (int pb = p0 + qg * QW; pb < p1; pb += nq * QW) {
         const int qp = pb + qi;
@@ -89,32 +90,38 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
         const bool q_real = (unsigned)(qp * 32 + l32 - row0) < (unsigned)n;
         if (active && p0 + ks < p1) {
             bf16x8 qf[4], kf[4], vf[2][2];
-            auto load_k = [&](int kb) {
-                const unsigned char* kp = qkv + (size_t)kb * pitch + (size_t)H * 64;
+            // Behind the last block (not real) the loads are issued but read nothing: after a conditional fetch the compiler waits for everything under way
+            // before a block's values are used, the next block's keys included.
+            auto load_k = [&](int kb, bool real) {
+                const auto kp = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(qkv + (size_t)kb * pitch + (size_t)H * 64), 0, real ? 4096 : 0, 0x00020000);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(kp + kk * 1024);
+                for (int kk = 0; kk < 4; ++kk) kf[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kp, lane * 16 + kk * 1024, 0, 0));
             };
-            auto load_v = [&](int kb) {
-                const unsigned char* vp = qkv + (size_t)kb * pitch + (size_t)H * 128;
+            auto load_v = [&](int kb, bool real) {
+                const auto vp = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(qkv + (size_t)kb * pitch + (size_t)H * 128), 0, real ? 4096 : 0, 0x00020000);
 #pragma unroll
-                for (int dt = 0; dt < 2; ++dt)
+                for (int mf = 0; mf < 2; ++mf)
 #pragma unroll
-                    for (int mf = 0; mf < 2; ++mf) vf[mf][dt] = *reinterpret_cast<const bf16x8*>(vp + dt * 2048 + mf * 1024);
+                    for (int dt = 0; dt < 2; ++dt)
+                        vf[mf][dt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vp, lane * 16 + dt * 2048 + mf * 1024, 0, 0));
             };
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qp * pitch + kk * 1024);
+            for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qp * pitch + lane * 16 + kk * 1024);
             int kb = p0 + ks;
-            load_k(kb);
-            load_v(kb);
-            for (;;) {
+            load_k(kb, true);
+            load_v(kb, true);
+            bool more;
+            do {
                 f32x16 sc;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sc, 0, 0, 0);
                 const int kn = kb + KS;
-                const bool more = kn < p1;
-                if (more) load_k(kn);
+                more = kn < p1;
+                __builtin_amdgcn_sched_barrier(0);                           // (into the registers that the scores have used)
+                load_k(kn, more);
+                __builtin_amdgcn_sched_barrier(0);
                 if (kb * 32 < row0 || kb * 32 + 32 > end) {                  // a panel shared with a neighbour
                     const int r0 = kb * 32 + half * 4 - row0;
 #pragma unroll
@@ -159,10 +166,10 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
 #pragma unroll
                     for (int dt = 0; dt < 2; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mf][dt], pf, o[dt], 0, 0, 0);
                 }
-                if (!more) break;
+                __builtin_amdgcn_sched_barrier(0);
                 kb = kn;
-                load_v(kb);
-            }
+                load_v(kb, more);
+            } while (more);
             l_run = lane_pair_sum<32>(l_run);
         }
         unsigned char* ctx = base_ctx + (size_t)g.ctx[grp] * 256 + (size_t)qp * H * 64 + a * 4096 + lane * 16;
