@@ -1,10 +1,12 @@
 // First-token attention of a branch's last layer on the panel layout, keys and values not projected (bfloat16 path): with
 // q~[b][a] = Wk_a^T (Wq_a x_b + bq_a) the score of key j is q~ . x_j up to a constant that the softmax drops, and the head's context
 // is Wv_a (sum_j p_j x_j) + bv_a.  Two launches per group of tasks (the contexts are one more, gemm_tiled_rows_kernel):
-//   first_query_kernel   one workgroup per (task, 32 sequences, head): query of the sequences' first rows (gathered before: in place, 16
+//   first_query_kernel   per (task, head) one workgroup, or as many as there are compute units for, that keep the two weight slices (98 KB each) in
+//                        registers and walk over panels of 32 sequences: query of the sequences' first rows (gathered before: in place, 16
 //                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences; of up to kInPlace
-//                        sequences that costs less than the launch), then q~, the 64 columns between them staying in LDS.  Bound by the two weight slices (98 KB each), all of whose
-//                        fragments are in flight at once.
+//                        sequences that costs less than the launch), then q~, the 64 columns between them staying in LDS.  A chain of latencies: 10 us
+//                        for the first panel, 3 for each further one (a workgroup per panel, each with weights to load: 10 and 11 tasks x 272
+//                        sequences 43 + 52 us, now 25 + 33, 8 tasks x 256 35, 19).
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
 //                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
 //                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509); bound by reading the rows.
@@ -12,6 +14,8 @@
 //                        registers (200 workgroups in flight, now 450), and a compute unit stood still while its one waited for rows or stored.
 //                        21 tasks x 272 short sequences 62 + 77 -> 41 + 52 us, 8 tasks x 256 112 -> 73, x 7 of up to 509 tokens 33 -> 26.
 // Scores and sums were two kernels that read the rows once each (85 + 107 us for 8 tasks x 256 sequences).
+#include <algorithm>
+
 #include "kernels.h"
 #include "device_util.h"
 
@@ -28,100 +32,113 @@ constexpr int kHeadsPad = 16;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int H, int A, int nb, int pairs, const int32_t* seq_start, int max_rows, FirstTokenGroup g)
+// NS = H / 64: K steps of 16 of a wavefront.  A workgroup has its (task, head)'s two weight slices in registers and walks over panels of 32
+// sequences, gy workgroups dealing them out.
+template <int NS>
+__global__ __launch_bounds__(256, 1) void first_query_kernel(int B, int A, int nb, int gy, int pairs, const int32_t* seq_start, int max_rows, FirstTokenGroup g)
 {
-    constexpr int U = 12, MAXP = 8;
+    constexpr int H = NS * 64, PANELS = 2 * NS, P = (PANELS + 3) / 4;        // panels of the hidden columns; of a wavefront (wave, wave + 4, ..)
     __shared__ __attribute__((aligned(16))) float part[4][2][4][64][4];
     __shared__ __attribute__((aligned(16))) __bf16 qs[8 * 256];              // 64 columns of 32 rows, panel layout
-    // the nb workgroups of a (task, head), which share its weight slices, follow one another on one XCD
-    const int i8 = blockIdx.x >> 3, pi = nb == 1 ? i8 : i8 / nb, pair = pi * 8 + (blockIdx.x & 7), yb = i8 - pi * nb;
+    // the gy workgroups of a (task, head), which share its weight slices, follow one another on one XCD
+    const int i8 = blockIdx.x >> 3, pi = gy == 1 ? i8 : i8 / gy, pair = pi * 8 + (blockIdx.x & 7);
+    int yb = i8 - pi * gy;
     if (pair >= pairs) return;
     const int grp = pair / A, a = pair - grp * A, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int b0 = yb * 32, panels = H >> 5;
-    const size_t pw = (size_t)H * 64;                                        // bytes per panel
-    const int steps = H / 64;                                                // K steps of 16 of a wavefront
-    const unsigned char* wq = static_cast<const unsigned char*>(g.Wq[grp]) + (size_t)a * 2 * pw + (size_t)wave * steps * 1024 + lane * 16;
+    constexpr size_t pw = (size_t)H * 64;                                    // bytes per panel
+    const unsigned char* wq = static_cast<const unsigned char*>(g.Wq[grp]) + (size_t)a * 2 * pw + (size_t)wave * NS * 1024 + lane * 16;
     const unsigned char* wk = static_cast<const unsigned char*>(g.WkT[grp]) + (size_t)a * 4096 + lane * 16;
-    // the key matrix's fragments for this wavefront's panels of q~ (wave, wave + 4, ..): needed last, in flight first
-    bf16x8 kf[MAXP][4];
+    auto rows = [&](int y) {
+        const unsigned char* x;
+        if (seq_start) {                     // in place: this lane's row of all rows
+            const int row = min(seq_start[min(y * 32 + l32, B - 1)], max_rows - 1);
+            x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)(row >> 5) * pw + half * 512 + (row & 31) * 16;
+        } else {
+            x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)y * pw + lane * 16;
+        }
+        return x + (size_t)wave * NS * 1024;
+    };
+    bf16x8 wf[NS][2], kf[P][4], xf[NS];
 #pragma unroll
-    for (int i = 0; i < MAXP; ++i)
+    for (int u = 0; u < NS; ++u) {
+        wf[u][0] = *reinterpret_cast<const bf16x8*>(wq + (size_t)u * 1024);
+        wf[u][1] = *reinterpret_cast<const bf16x8*>(wq + pw + (size_t)u * 1024);
+    }
+    auto fetch = [&](int y) {
+        const unsigned char* x = rows(y);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kf[i][kk] = *reinterpret_cast<const bf16x8*>(wk + (size_t)min(wave + 4 * i, panels - 1) * pw + kk * 1024);
+        for (int u = 0; u < NS; ++u) xf[u] = *reinterpret_cast<const bf16x8*>(x + (size_t)u * 1024);
+    };
+    fetch(yb);
+    // the key matrix's fragments for this wavefront's panels of q~
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) kf[i][kk] = *reinterpret_cast<const bf16x8*>(wk + (size_t)min(wave + 4 * i, PANELS - 1) * pw + kk * 1024);
     float4 bv[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const float4*>(g.bq[grp] + a * 64 + j * 32 + wave * 8 + half * 4);
-    const unsigned char* x;
-    if (seq_start) {                         // in place: this lane's row of all rows
-        const int row = min(seq_start[min(b0 + l32, B - 1)], max_rows - 1);
-        x = static_cast<const unsigned char*>(g.x[grp]) + (size_t)(row >> 5) * pw + half * 512 + (row & 31) * 16;
-    } else {
-        x = static_cast<const unsigned char*>(g.first[grp]) + (size_t)yb * pw + lane * 16;
-    }
-    x += (size_t)wave * steps * 1024;
-    f32x16 acc[2];
+    __builtin_amdgcn_sched_barrier(0);
+    auto panel = [&](auto more) {
+        f32x16 acc[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-    auto batch = [&](int s0, int nb, auto full) {
-        bf16x8 af[U], wf[U][2];
+            for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (full || u < nb) {
-                wf[u][0] = *reinterpret_cast<const bf16x8*>(wq + (size_t)(s0 + u) * 1024);
-                wf[u][1] = *reinterpret_cast<const bf16x8*>(wq + pw + (size_t)(s0 + u) * 1024);
-                af[u] = *reinterpret_cast<const bf16x8*>(x + (size_t)(s0 + u) * 1024);
-            }
+        for (int u = 0; u < NS; ++u) {
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][0], xf[u], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][1], xf[u], acc[1], 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) fetch(yb + gy);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (full || u < nb) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][0], af[u], acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][1], af[u], acc[1], 0, 0, 0);
-            }
-    };
-    int s0 = 0;
-    for (; s0 + U <= steps; s0 += U) batch(s0, U, std::true_type{});
-    if (s0 < steps) batch(s0, steps - s0, std::false_type{});
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(part[wave][j][q][lane]) = f32x4{acc[j][q * 4], acc[j][q * 4 + 1], acc[j][q * 4 + 2], acc[j][q * 4 + 3]};
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<f32x4*>(part[wave][j][q][lane]) = f32x4{acc[j][q * 4], acc[j][q * 4 + 1], acc[j][q * 4 + 2], acc[j][q * 4 + 3]};
-    __syncthreads();
+        for (int j = 0; j < 2; ++j) {                                        // this wavefront finishes chunk `wave` of both blocks
+            f32x4 v = *reinterpret_cast<const f32x4*>(part[0][j][wave][lane]);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {                                            // this wavefront finishes chunk `wave` of both blocks
-        f32x4 v = *reinterpret_cast<const f32x4*>(part[0][j][wave][lane]);
+            for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(part[p][j][wave][lane]);
+            const bf16x4 o = {(__bf16)(v[0] + bv[j].x), (__bf16)(v[1] + bv[j].y), (__bf16)(v[2] + bv[j].z), (__bf16)(v[3] + bv[j].w)};
+            *reinterpret_cast<bf16x4*>(qs + (j * 4 + wave) * 256 + l32 * 8 + half * 4) = o;
+        }
+        __syncthreads();
+        bf16x8 qf[4];
 #pragma unroll
-        for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(part[p][j][wave][lane]);
-        const bf16x4 o = {(__bf16)(v[0] + bv[j].x), (__bf16)(v[1] + bv[j].y), (__bf16)(v[2] + bv[j].z), (__bf16)(v[3] + bv[j].w)};
-        *reinterpret_cast<bf16x4*>(qs + (j * 4 + wave) * 256 + l32 * 8 + half * 4) = o;
-    }
-    __syncthreads();
-    bf16x8 qf[4];
+        for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qs + kk * 512 + lane * 8);
+        // q~: [sequence][16 heads][H], so that a workgroup writes whole lines; the half wavefronts exchange for 8 columns per lane
+        const int b = yb * 32 + l32;
+        __bf16* qt = static_cast<__bf16*>(g.qt[grp]) + ((size_t)b * kHeadsPad + a) * H + half * 8;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qs + kk * 512 + lane * 8);
-    // q~: [sequence][16 heads][H], so that a workgroup writes whole lines
-    __bf16* qt = static_cast<__bf16*>(g.qt[grp]) + ((size_t)(b0 + l32) * kHeadsPad + a) * H + half * 4;
+        for (int i = 0; i < P; ++i) {
+            const int p = wave + 4 * i;
+            if (PANELS % 4 != 0 && p >= PANELS) break;
+            f32x16 c;
 #pragma unroll
-    for (int i = 0; i < MAXP; ++i) {
-        const int p = wave + 4 * i;
-        if (p >= panels) break;
-        f32x16 c;
+            for (int e = 0; e < 16; ++e) c[e] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) c[e] = 0.f;
+            for (int kk = 0; kk < 4; ++kk) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i][kk], qf[kk], c, 0, 0, 0);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i][kk], qf[kk], c, 0, 0, 0);
-        if (b0 + l32 < B) {
+            for (int q = 0; q < 4; q += 2) {
+                bf16x4 lo, hi;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bf16x4 o = {(__bf16)c[q * 4], (__bf16)c[q * 4 + 1], (__bf16)c[q * 4 + 2], (__bf16)c[q * 4 + 3]};
-                *reinterpret_cast<bf16x4*>(qt + (p * 4 + q) * 8) = o;
+                for (int e = 0; e < 4; ++e) {
+                    lo[e] = (__bf16)c[q * 4 + e];
+                    hi[e] = (__bf16)c[q * 4 + 4 + e];
+                }
+                const u32x2 lu = __builtin_bit_cast(u32x2, lo), hu = __builtin_bit_cast(u32x2, hi);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(lu[0], hu[0], false, false), s1 = __builtin_amdgcn_permlane32_swap(lu[1], hu[1], false, false);
+                if (b < B) *reinterpret_cast<u32x4*>(qt + (p * 4 + q) * 8) = u32x4{s0[0], s1[0], s0[1], s1[1]};
             }
         }
-    }
+    };
+    for (; yb + gy < nb; yb += gy) panel(std::true_type{});
+    panel(std::false_type{});
 }
 
 // NW wavefronts, each STEPS x 32 of the H columns (the last ones perhaps fewer, or none).  Per key panel: a wavefront loads its columns of the 32 rows as matrix
@@ -289,8 +306,31 @@ hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int
 {
     if (G <= 0 || B <= 0) return hipSuccess;
     if (G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-    const int nb = (B + 31) / 32, pairs = A * G;
-    hipLaunchKernelGGL(first_query_kernel, dim3((pairs + 7) / 8 * 8 * nb), dim3(256), 0, stream, B, H, A, nb, pairs, seq_start, max_rows, g);
+    // One workgroup fills a compute unit's registers: as many per (task, head) as there are compute units for (8 tasks x 256 sequences, 96 pairs, 1 to 5:
+    // 36, 26, 34, 32, 31 us; 11 tasks x 272, 132 pairs: 42, 49, 39, 48, 43).
+    const int nb = (B + 31) / 32, pairs = A * G, gy = std::max(1, std::min(nb, device_cu_count() / pairs));
+    const dim3 grid((pairs + 7) / 8 * 8 * gy);
+#define MT_QUERY(NS)                                                                                                                          \
+    case NS: hipLaunchKernelGGL(first_query_kernel<NS>, grid, dim3(256), 0, stream, B, A, nb, gy, pairs, seq_start, max_rows, g); break
+    switch (A) {                             // H = A * 64
+        MT_QUERY(1);
+        MT_QUERY(2);
+        MT_QUERY(3);
+        MT_QUERY(4);
+        MT_QUERY(5);
+        MT_QUERY(6);
+        MT_QUERY(7);
+        MT_QUERY(8);
+        MT_QUERY(9);
+        MT_QUERY(10);
+        MT_QUERY(11);
+        MT_QUERY(12);
+        MT_QUERY(13);
+        MT_QUERY(14);
+        MT_QUERY(15);
+        MT_QUERY(16);
+    }
+#undef MT_QUERY
     return hipGetLastError();
 }
 

@@ -162,7 +162,8 @@ def bf16(x):
 # the result rounds once; the weights are float32 quantities: 2^-14 sum p |x| is what scores of |s| <= 50 summed in float32 (2^-24 sqrt(H) |s|)
 # can shift them.
 @pytest.mark.parametrize("heads,lens,late", [(1, [1, 32, 33], False), (2, [31, 65, 64, 1], True), (3, [200, 7], True), (5, [97] * 33, True), (11, [40, 128, 3], False),
-                                             (12, [128, 127, 70], True), (16, [1, 257, 64], True)])
+                                             (12, [128, 127, 70], True), (16, [1, 257, 64], True)] + [(h, [33, 2, 70], True) for h in (4, 6, 7, 8, 9, 10, 13, 14, 15)] +
+                         [(16, [2] * 545, False)])           # every width, and more panels of sequences than workgroups
 def test_first_token_panels(heads, lens, late):
     print(f"first token: {heads} heads, {lens}, late {late}", flush=True)
     H, B, rng = 64 * heads, len(lens), np.random.default_rng(heads)
