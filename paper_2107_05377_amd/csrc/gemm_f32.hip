@@ -6,8 +6,9 @@
 //                         32 floats = 128 bytes per row: buffer loads to LDS of 16-byte chunks, chunk c of row r in slot c ^ (r & 7).  A
 //                         lane reads 4 consecutive k of its row at once; since the order of k is free as long as both operands agree, MFMA i
 //                         of a step takes k = i from the lower and k = 4 + i from the upper half wavefront.
-//   gemm_f32_rows_kernel  few rows: bound by streaming the weights, which go straight from global memory to registers, each of
-//                         the 4 wavefronts a quarter of K.
+//   gemm_f32_rows_kernel  short K (of up to 7 slices, too few for four rings): operands straight from global memory to registers, each of the 4
+//                         wavefronts a quarter of K.  (It did all launches of up to 32 rows, whose weights it reads 32 bytes of a row at a time: 8 problems
+//                         of 8 rows x 768 / 3072 x 768, x 768 x 3072 13, 34, 31 us, the tile kernel 8, 19, 21; one of 20 rows 12, 17, 31 and 8, 9, 18.)
 //   gemm_f32_any_kernel   any M, N, K and strides.
 // The matrix cores' float32 rate is 256 FLOP per clock and compute unit: a 32x32x2 instruction takes 64 clocks.  What the tile kernel has to do is to
 // keep them coming.
@@ -382,8 +383,8 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
                   (uint64_t)s.lda * 128 < (1ull << 31) && (uint64_t)(s.ldw ? s.ldw : s.K) * 128 < (1ull << 31);
     for (int i = 0; chunks && i < s.G; ++i)
         chunks = g.N[i] % 4 == 0 && (((uintptr_t)g.A[i] | (uintptr_t)g.W[i] | (uintptr_t)g.C[i] | (uintptr_t)g.bias[i] | (uintptr_t)g.residual[i]) & 15) == 0;
-    // each wavefront's quarter has as many slices as the ring; fewer: the few-row kernel, whose blocks are rows of the grid
-    const bool rows = s.M <= 32 || s.K < 4 * 32 * kRing;
+    // each wavefront's quarter has as many slices as the ring; fewer: the short-K kernel, whose blocks are rows of the grid
+    const bool rows = s.K < 4 * 32 * kRing;
     if (!chunks || (rows && (s.M + 31) / 32 > 65535)) {
         dim3 grid((s.N + TN - 1) / TN, (s.M + TM - 1) / TM, s.G), block(256);
         hipLaunchKernelGGL(gemm_f32_any_kernel, grid, block, 0, stream, g, s);

@@ -42,7 +42,7 @@ def test_gemm_f32_tiles(M, N, K, act):
 
 # the block list of the float32 tile kernel: one block and several per workgroup (more than two per compute unit of 256), remainders of rows, columns and of the
 # four K shares (equal and not), as few slices as the ring has and more, one problem and several
-@pytest.mark.parametrize("G,M,N,K", [(1, 33, 36, 256), (1, 64, 96, 320), (3, 97, 100, 448), (1, 1500, 1028, 256), (8, 130, 516, 320), (2, 700, 800, 768), (5, 40, 64, 3072)])
+@pytest.mark.parametrize("G,M,N,K", [(1, 33, 36, 256), (1, 64, 96, 320), (3, 97, 100, 448), (1, 3, 36, 256), (8, 20, 100, 416), (1, 1500, 1028, 256), (8, 130, 516, 320), (2, 700, 800, 768), (5, 40, 64, 3072)])
 def test_gemm_f32_block_list(G, M, N, K):
     print(f"gemm_f32, {G} x {M} x {N} x {K}", flush=True)
     rng = np.random.default_rng(G + M + N + K)
