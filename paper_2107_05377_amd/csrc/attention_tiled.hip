@@ -53,8 +53,12 @@ __device__ __forceinline__ u32x4 pack_chunks(const float (&v)[8])
 template <int KS>
 __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attention_tiled_kernel(const unsigned char* base_qkv, unsigned char* base_ctx,
                                                               const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len, int B, int S,
-                                                              int A, int nq_nw, int pairs, AttnTiledGroup g)
+                                                              int A, int nq_nw, int pairs, int G, AttnTiledGroup g, ReadAhead ahead)
 {
+    if (!pairs && (int)blockIdx.z >= G) {
+        read_ahead(ahead, ((blockIdx.z - G) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+        return;
+    }
     const int nq = nq_nw & 0xFFFF, QW = KS == 1 ? nq_nw >> 16 : 4 / KS;      // query panels of a workgroup at a time
     constexpr float kScale = 0.125f * 1.4426950408889634f;                   // exponents of two
     __shared__ __attribute__((aligned(16))) float s_o[KS > 1 ? 4 : 1][8][KS > 1 ? 64 : 1][4];
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
 }  // namespace
 
 hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
-                                  hipStream_t stream)
+                                  hipStream_t stream, AheadQueue* queue)
 {
     if (G <= 0 || B <= 0 || S <= 0) return hipSuccess;
     if (!seq_start || !seq_len || H != A * 64 || G > kMaxGroup || (long)A * B * G > (1 << 24)) return hipErrorInvalidValue;
@@ -251,12 +255,14 @@ hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t*
     }
     // a small launch saves the divisions of the flat order
     const bool flat = nq > 1 || groups >= 1024;
-    const dim3 grid = flat ? dim3((groups * nq + 7) / 8 * 8) : dim3(A, B, G), block(nw * 64);
+    ReadAhead ahead;
+    if (!flat && queue) ahead = queue->take();
+    const dim3 grid = flat ? dim3((groups * nq + 7) / 8 * 8) : dim3(A, B, G + (ahead.blocks() + A * B - 1) / (A * B)), block(nw * 64);
     const int pairs = flat ? groups : 0, nq_nw = nq | nw << 16;
     const unsigned char* q = static_cast<const unsigned char*>(g.base_qkv);
     unsigned char* c = static_cast<unsigned char*>(g.base_ctx);
-    if (ks == 2) hipLaunchKernelGGL(attention_tiled_kernel<2>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, g);
-    else hipLaunchKernelGGL(attention_tiled_kernel<1>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, g);
+    if (ks == 2) hipLaunchKernelGGL(attention_tiled_kernel<2>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
+    else hipLaunchKernelGGL(attention_tiled_kernel<1>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
     return hipGetLastError();
 }
 

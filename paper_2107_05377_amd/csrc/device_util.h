@@ -6,6 +6,8 @@
 #include <atomic>
 #include <cstdint>
 
+#include "kernels.h"
+
 namespace mt {
 
 // Host: raise a kernel's dynamic-LDS limit once per device (the attribute belongs to the function ON a device).
@@ -92,6 +94,29 @@ __device__ __forceinline__ float wave_max(float v)
     v = lane_pair_max<4>(v);
     v = lane_pair_max<2>(v);
     return lane_pair_max<1>(v);
+}
+
+// Block w of what is to be read ahead.
+__device__ __forceinline__ void read_ahead(const ReadAhead& r, uint32_t w)
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t n = (r.bytes[i] + kAheadBlock - 1) / kAheadBlock;
+        if (w < n) {
+            const unsigned char* p = static_cast<const unsigned char*>(r.base) + (size_t)r.at[i] * 256 + (size_t)w * kAheadBlock;
+            const uint32_t end = min(r.bytes[i] - w * kAheadBlock, kAheadBlock), step = blockDim.x * 16;
+            for (uint32_t o = threadIdx.x * 16; o < end; o += 8 * step) {
+                u32x4 v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(p + min(o + k * step, end - 16));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) asm volatile("" ::"v"(v[k]));
+            }
+            return;
+        }
+        w -= n;
+    }
 }
 
 // LayerNorm's arithmetic on a lane's four values, contractions written out: the row-major and the panel kernels give the same bits (E4M3 roundings

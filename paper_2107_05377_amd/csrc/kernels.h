@@ -5,6 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <vector>
+
 namespace mt {
 
 typedef uint16_t bf16_t;   // raw bfloat16 bits in host-visible interfaces
@@ -72,6 +75,55 @@ __host__ __device__ inline size_t tiled_offset(size_t row, size_t col, size_t wi
 {
     return (row >> 5) * 32 * width + (col >> 3) * 256 + (row & 31) * 8 + (col & 7);
 }
+// Weights that later launches of a small call will need, read ahead by additional workgroups of its launches that leave most of the chip and all of the
+// memory's bandwidth unused (LayerNorm and attention of the trunk): a contraction of few rows waits for its weights, which then come from the last-level
+// cache (36 rows x 2304 / 3072 x 768, x 768 x 3072: 3.8 us each from memory, 3.0 from that cache).  Blocks of kAheadBlock bytes, one per workgroup, of up to
+// four pieces (offsets from base in 256 bytes).
+constexpr uint32_t kAheadBlock = 32768;
+struct ReadAhead {
+    const void* base = nullptr;
+    uint32_t at[4] = {}, bytes[4] = {};
+    int blocks() const
+    {
+        int n = 0;
+        for (int i = 0; i < 4; ++i) n += (int)((bytes[i] + kAheadBlock - 1) / kAheadBlock);
+        return n;
+    }
+};
+// ... in the order of their use.  A launch takes kAheadBytes: two MB more or less are level, 8 MB and what contractions of few rows could carry lengthen
+// the launches by as much as the later ones gain (one request, 0 / 4 / 8 MB by each: 312, 305, 308 us; with 4 MB by each contraction as well 320).
+constexpr uint32_t kAheadBytes = 4u << 20;
+struct AheadQueue {
+    struct Piece {
+        uint32_t at, bytes;
+    };
+    const void* base = nullptr;
+    std::vector<Piece> piece;
+    size_t next = 0, used = 0;      // the next piece to read, pieces whose launches have been made
+    uint32_t done = 0;              // bytes of the next piece that have been read
+    ReadAhead take()
+    {
+        ReadAhead r;
+        uint32_t budget = kAheadBytes;
+        if (next < used) {
+            next = used;
+            done = 0;
+        }
+        r.base = base;
+        for (int i = 0; i < 4 && budget >= kAheadBlock && next < piece.size(); ++i) {
+            const uint32_t n = std::min(piece[next].bytes - done, budget / kAheadBlock * kAheadBlock);
+            r.at[i] = piece[next].at + done / 256;
+            r.bytes[i] = n;
+            budget -= n;
+            done += n;
+            if (done == piece[next].bytes) {
+                ++next;
+                done = 0;
+            }
+        }
+        return r;
+    }
+};
 // Grouped problems as byte offsets from common bases, in units of 256 bytes (all buffers of the arenas are so aligned): a third of the
 // kernel arguments that pointers would be, which the host writes on every launch (4.1 -> 2.9 us of host time a launch).
 constexpr uint32_t kNoBias = 0xFFFFFFFFu;
@@ -146,7 +198,7 @@ struct TiledLnShape {
     // the order of the row-major kernel's sums, to the bit (H a multiple of 256, one part): layers whose operands are E4M3
     int32_t whole_sums = 0;
 };
-hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream);
+hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream, AheadQueue* ahead = nullptr);
 // As launch_embed_ln (bf16 tables), states in the panel layout.  out_bf16, out_e4m3: operand copies, either may be null.
 hipError_t launch_embed_ln_tiled(const int32_t* ids, const int32_t* type_ids, int type_vocab, const int32_t* src, const int32_t* d_M, int B, int S,
                                  int H, int vocab, const void* word, const void* pos, const void* type, const float* gamma, const float* beta,
@@ -223,7 +275,7 @@ struct AttnTiledGroup {
     uint32_t qkv[kMaxGroup], ctx[kMaxGroup];
 };
 hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t* seq_start, const int32_t* seq_len, int B, int S, int H, int A,
-                                  hipStream_t stream);
+                                  hipStream_t stream, AheadQueue* ahead = nullptr);
 hipError_t launch_attention_f32(const AttnGroup& g, int G, const int32_t* mask, const int32_t* seq_start,
                                 const int32_t* seq_len, int B, int S, int H, int A, hipStream_t stream);
 

@@ -234,8 +234,12 @@ __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float
 
 template <int NI, int NP>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_kernel(const float* x, const float* res, const int32_t* d_M, const float* gamma,
-                                                              const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps)
+                                                              const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps, int groups, ReadAhead ahead)
 {
+    if ((int)blockIdx.x >= groups) {
+        read_ahead(ahead, blockIdx.x - groups);
+        return;
+    }
     layernorm_tiled_body<NI, NP, true, true, ROW_SHARES>(x, res, gamma, beta, RowOut{of, ob, nullptr, 0, false}, d_M, M, part_stride, nullptr, 0, eps);
 }
 
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(256) void classifier_list_kernel(ClsGroup g, ClsFir
 namespace {
 
 template <int NI, int NP>
-void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
+void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream, AheadQueue* queue)
 {
     unsigned char* ws = static_cast<unsigned char*>(const_cast<void*>(g.ws));
     const unsigned char* wt = static_cast<const unsigned char*>(g.wt);
@@ -449,12 +453,13 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
             return;
         }
     }
-    if (s.G == 1 && !s.res_row && !s.split && few && (s.want_b & 1) && !(s.want_q & 1))
-        hipLaunchKernelGGL((layernorm_tiled_kernel<NI, NP>), grid, block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
+    if (s.G == 1 && !s.res_row && !s.split && few && (s.want_b & 1) && !(s.want_q & 1)) {
+        const ReadAhead ahead = queue ? queue->take() : ReadAhead{};
+        hipLaunchKernelGGL((layernorm_tiled_kernel<NI, NP>), dim3(grid.x + ahead.blocks()), block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
                            (const float*)(ws + (size_t)g.res[0] * 256), s.d_M, (const float*)(wt + (size_t)g.gamma[0] * 256),
                            (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
-                           s.M, s.part_stride, s.eps);
-    else if (few)
+                           s.M, s.part_stride, s.eps, (int)grid.x, ahead);
+    } else if (few)
         hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, true, ROW_SHARES>), grid, block, 0, stream, g, s);
     else if (split)
         hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, false, ROW_SHARES>), grid, block, 0, stream, g, s);
@@ -467,7 +472,7 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
 #define MT_FOR_WIDTH(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
-hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream)
+hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream, AheadQueue* ahead)
 {
     if (s.G <= 0 || s.M <= 0) return hipSuccess;
     if (s.G > kMaxGroup || s.H % 64 != 0 || s.n_parts < 1 || (s.whole_sums && (s.H % 256 != 0 || s.n_parts != 1))) return hipErrorInvalidValue;
@@ -475,9 +480,9 @@ hipError_t launch_layernorm_tiled(const TiledLnGroup& g, const TiledLnShape& s, 
 #define X(NI)                                                    \
     case NI:                                                     \
         switch (s.n_parts) {                                     \
-            case 1: ln_launch<NI, 1>(g, s, stream); break; \
-            case 2: ln_launch<NI, 2>(g, s, stream); break; \
-            case 4: ln_launch<NI, 4>(g, s, stream); break; \
+            case 1: ln_launch<NI, 1>(g, s, stream, ahead); break; \
+            case 2: ln_launch<NI, 2>(g, s, stream, ahead); break; \
+            case 4: ln_launch<NI, 4>(g, s, stream, ahead); break; \
             default: return hipErrorInvalidValue;                \
         }                                                        \
         break;
