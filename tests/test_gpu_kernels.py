@@ -274,7 +274,7 @@ ROWS_1X1, ROWS_2X1, ROWS_2X2, K2, PAIR, TALL = 1, 2, 3, 4, 5, 6
     (TALL, 5, 1, 170, 161, 288, 384, 0, 1, 1), (TALL, 6, 2, 390, 353, 96, 512, 0, 0, 1), (TALL, 7, 1, 230, 225, 288, 384, 0, 1, 1), (TALL, 8, 1, 300, 257, 544, 640, 0, 0, 1),
     (TALL, 5, 8, 1312, 1300, 1024, 384, 0, 1, 1),
     (0, 0, 3, 512, 290, 768, 3072, 0, 1, 1), (0, 0, 3, 384, 290, 768, 3072, 0, 1, 1), (0, 0, 2, 1376, 700, 768, 768, 0, 1, 1), (0, 0, 1, 2016, 1100, 768, 3072, 0, 1, 1),
-    (0, 0, 1, 300, 171, 768, 768, 0, 0, 1), (0, 0, 8, 300, 171, 768, 768, 0, 1, 1), (0, 0, 1, 2080, 1900, 2304, 768, 1, 0, 1),
+    (0, 0, 12, 270, 257, 1024, 448, 3, 1, 1), (0, 0, 12, 288, 33, 1024, 256, 3, 1, 1), (0, 0, 1, 300, 171, 768, 768, 0, 0, 1), (0, 0, 8, 300, 171, 768, 768, 0, 1, 1), (0, 0, 1, 2080, 1900, 2304, 768, 1, 0, 1),
 ])
 def test_panel_linear_forms(form, height, problems, M, rows, N, K, act, f32, splits):
     print(f"panel linear: form {form} height {height}, {problems} x {rows}/{M} x {N} x {K}, act {act}, f32 {f32}, splits {splits}", flush=True)
@@ -321,17 +321,18 @@ def test_panel_linear_transposed_columns(form, height, M, K):
     assert np.array_equal(rows_of(moved), transposed_columns(rows_of(plain), first))
 
 
-def test_panel_linear_parts():
-    """Problems of equal parts with operands of their own, as the contexts of the heads: 3 heads over 2 problems."""
-    print("panel linear, parts", flush=True)
-    rng, heads, B, H = np.random.default_rng(5), 3, 37, 192
+@pytest.mark.parametrize("heads,B", [(3, 37), (12, 200)])               # one block per workgroup, and two by two
+def test_panel_linear_parts(heads, B):
+    """Problems of equal parts with operands of their own, as the contexts of the heads, over 2 problems."""
+    print(f"panel linear, parts: {heads} heads, {B} rows", flush=True)
+    rng, H = np.random.default_rng(5), heads * 64
     x, W, b = bf16(rng.standard_normal((2, heads, B, H))), bf16(rng.standard_normal((2, H, H)) / H**0.5), rng.standard_normal((2, H)).astype(np.float32)
     px, pw = torch.stack([panels(v) for p in x for v in p]), torch.stack([panels(w) for w in W])
     pc = torch.stack([nan_panels(B, H, torch.bfloat16) for _ in range(2)])
-    bias = torch.zeros((2, 256), device="cuda")
+    bias = torch.zeros((2, max(256, H)), device="cuda")
     bias[:, :H] = dev(b)
     size = lambda t: t[0].numel() * t.element_size()
-    mt.op_panel_linear(px, pw, bias, pc, M=B, N=64, K=H, ldc=H, problems=2, subs=heads, stride_A=size(px) * heads, stride_W=size(pw), stride_bias=1024,
+    mt.op_panel_linear(px, pw, bias, pc, M=B, N=64, K=H, ldc=H, problems=2, subs=heads, stride_A=size(px) * heads, stride_W=size(pw), stride_bias=size(bias),
                        stride_C=size(pc), sub_A=size(px), sub_W=64 * H * 2, sub_bias=256, sub_C=8 * 512)
     for p in range(2):
         for h in range(heads):
