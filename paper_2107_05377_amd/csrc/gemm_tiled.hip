@@ -118,7 +118,9 @@ struct TCfg {
     static constexpr int LDS = S * STAGE + XCHG;
     // loads younger than the activation slice that must have landed at a slice's barrier, on every path (see below)
     static constexpr int STEPS = F8 ? 2 : 4;                            // matrix steps of a slice
-    static constexpr int WAIT = (S - 2) * AL + 8 * (NB < S - 2 ? NB : S - 2) + 8 - 8 / STEPS;
+    // A tall tile has one wavefront per SIMD: its loads go one by one between the matrix instructions (slice_spread).
+    static constexpr bool SPREAD = TMI >= 5;
+    static constexpr int WAIT = (S - 2) * AL + 8 - 8 / STEPS + 8 * (NB < S - 2 ? NB : S - 2) - (SPREAD && NB >= S - 2 ? 8 - 8 / STEPS : 0);
     // activation fragments of two steps, or (where the registers of two workgroups do not hold two) each reloaded behind its last use
     static constexpr bool IN_PLACE = F8 && KW == 1 && TMI == 4;
     static_assert(WAIT <= 63 && LDS <= 160 * 1024, "ring");
@@ -172,14 +174,20 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
     if (n_mine > 1) locate(1, nxt);
     else nxt = cur;                        // no next tile: its loads are repeats of this one, never read
 
+    auto issueA1 = [&](const Ref& t, int kt, int stage, int i) {          // wavefront w fetches K step w of every panel
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(t.A, (lptr_t)(lds + stage * STAGE + (i * 4 + wave) * 1024), 16, voff,
+                                                 t.ao + (i % TMI) * (int)pa + ((i / TMI) * KT + kt) * 4096, 0, 0);
+    };
     auto issueA = [&](const Ref& t, int kt, int stage) {
 #pragma unroll
-        for (int i = 0; i < AL; ++i)       // wavefront w fetches K step w of every panel
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(t.A, (lptr_t)(lds + stage * STAGE + (i * 4 + wave) * 1024), 16, voff,
-                                                     t.ao + (i % TMI) * (int)pa + ((i / TMI) * KT + kt) * 4096, 0, 0);
+        for (int i = 0; i < AL; ++i) issueA1(t, kt, stage, i);
     };
     typename TFrag<F8>::type wf[NB][STEPS][2], af[Cfg::IN_PLACE ? 1 : 2][TMI];
     f32x16 acc[TMI][2];
+    [[maybe_unused]] auto loadW1 = [&](const Ref& t, int kt, int buf, int step, int jn) {
+        if constexpr (!F8)
+            wf[buf][step][jn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(t.W, voff + step * STEP_BYTES, t.wo + jn * (int)pw + kt * 4096, 0));
+    };
     auto loadW = [&](const Ref& t, int kt, int buf, int step) {
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) {
@@ -343,6 +351,53 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         st = ns;
         ++kt;
     };
+    // The same with the loads spread: a wavefront whose load waits for the load path issues no matrix instruction either, and a tall tile's compute unit
+    // has no other.  18.6 k rows x 768 x 3072 78.5 -> 75.8 us, 8 problems of 20 k rows x 1024 x 4096 1130 -> 1070.  (Where two workgroups share a compute
+    // unit, and with K halved between wavefronts, it was level to 14 % slower.)  A step has its share of the activation slice (the last one none) and the
+    // weight registers that the step before has used.
+    [[maybe_unused]] auto slice_spread = [&](auto bufc) {
+        constexpr int buf = decltype(bufc)::value;
+        const int ka = kt + S - 1, kw = kt + NB, kp = kw - 1;
+        const Ref ta = ka < KT ? cur : nxt, tw = kw < KT ? cur : nxt, tp = kp < KT ? cur : nxt;
+        const int ps = st == 0 ? S - 1 : st - 1, ns = st + 1 == S ? 0 : st + 1;
+        auto one_step = [&](auto stepc) {
+            constexpr int step = decltype(stepc)::value, NM = 2 * TMI;
+            constexpr bool last = step + 1 == STEPS;
+            if constexpr (last) {
+                // as above; of the slice that issued the awaited one, only the last step's weight loads are certainly younger (in the fill: all 8)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cfg::WAIT) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            constexpr int a0 = last ? AL : AL * step / (STEPS - 1), a1 = last ? AL : AL * (step + 1) / (STEPS - 1), NL = a1 - a0 + 2, M0 = (TMI + 1) / 2;
+            int l = 0, f = 0;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int i = m >> 1, jn = m & 1;
+                acc[i][jn] = t_mfma<F8>(wf[buf][step][jn], af[step & 1][i], acc[i][jn], cur.scale);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    if (f < TMI) read1((step + 1) & 1, last ? ns : st, last ? 0 : step + 1, f++);
+                const int due = m == NM - 1 ? NL : (m < M0 ? 0 : NL * (m - M0 + 1) / (NM - M0));
+#pragma unroll
+                for (int k = 0; k < NL; ++k)
+                    if (l < due) {
+                        const int w = l - (a1 - a0);
+                        if (w < 0) issueA1(ta, ka < KT ? ka : ka - KT, ps, a0 + l);
+                        else if (step == 0) loadW1(tp, kp < KT ? kp : kp - KT, (buf + NB - 1) % NB, STEPS - 1, w);
+                        else loadW1(tw, kw < KT ? kw : kw - KT, buf, step - 1, w);
+                        ++l;
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        one_step(std::integral_constant<int, 0>{});
+        one_step(std::integral_constant<int, 1>{});
+        one_step(std::integral_constant<int, 2>{});
+        one_step(std::integral_constant<int, 3>{});
+        st = ns;
+        ++kt;
+    };
     auto epilogue = [&]() {
         if constexpr (F8) {
 #pragma unroll
@@ -403,8 +458,13 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         while (j < n_mine) {
             init_acc(cur);
             while (kt < KT) {
-                slice(std::integral_constant<int, 0>{});
-                slice(std::integral_constant<int, 1>{});
+                if constexpr (Cfg::SPREAD) {
+                    slice_spread(std::integral_constant<int, 0>{});
+                    slice_spread(std::integral_constant<int, 1>{});
+                } else {
+                    slice(std::integral_constant<int, 0>{});
+                    slice(std::integral_constant<int, 1>{});
+                }
             }
             epilogue();
         }
