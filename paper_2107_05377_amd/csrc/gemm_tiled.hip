@@ -255,8 +255,7 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
             const auto C = t_rsrc(reinterpret_cast<float*>(Cb) + (size_t)t.split * s.split_stride + (size_t)pm * 32 * s.ldc + pn * 1024, 4096);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                store16(__builtin_bit_cast(u32x4, f32x4{t_act<ACT>(a[q * 4]), t_act<ACT>(a[q * 4 + 1]), t_act<ACT>(a[q * 4 + 2]), t_act<ACT>(a[q * 4 + 3])}), C,
-                        (lane & 31) * 32 + (lane >> 5) * 16 + q * 1024);
+                store16(__builtin_bit_cast(u32x4, f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]}), C, (lane & 31) * 32 + (lane >> 5) * 16 + q * 1024);
         } else {
             const auto C = t_rsrc(reinterpret_cast<__bf16*>(Cb) + (size_t)pm * 32 * s.ldc + pn * 1024, 2048);
             [[maybe_unused]] f32x16 tr;
@@ -817,9 +816,7 @@ hipError_t launch_form(const TiledGroup& g, const TiledShape& s, int form, int f
         case TILED_ROWS_2X1: return launch_rows<2, 1, OUT, ACT>(g, s, stream);
         case TILED_ROWS_2X2: return launch_rows<2, 2, OUT, ACT>(g, s, stream);
     }
-    if constexpr (ACT == ACT_TANH) {
-        if (form == TILED_PAIR) return launch_tiles<1, 4, OUT, ACT, false>(g, s, n_cu, force, stream);
-    } else {
+    if constexpr (ACT != ACT_TANH) {
         switch (form) {
             case TILED_K2: return launch_tiles<2, 4, OUT, ACT, false>(g, s, n_cu, force, stream);
             case TILED_PAIR: return launch_tiles<1, 4, OUT, ACT, false>(g, s, n_cu, force, stream);
@@ -875,9 +872,9 @@ int choose_form(const TiledShape& s)
     // Contexts (parts of 64 columns): one block per workgroup reads its rows twice.  8 problems of 12 heads x 768, 32 / 64 / 128 / 256 rows, 192 to 1536 blocks:
     // 1x1 5.4, 7.5, 13.3, 18.2 us, 2x1 5.5, 6.0, 11.1, 18.8, 2x2 6.3, 7.0, 8.1, 15.9; 11 problems, 272 rows 25.9, 26.7, 22.9.
     if (s.n_sub > 1) return blocks <= 288 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
-    // Poolers, K = 1536: 8 problems of 272 rows, 1728 blocks, 2x1 20.5 us, PAIR 24.6; 512 rows, 3072 blocks, 28.8 and 25.7; 21 problems of 128 rows, 2016
-    // blocks, 25.1 and 26.8, 272 rows 44.4 and 32.1; 24 of 128 rows x 1024 x 2048, 3072 blocks, 43.2 and 37.7.
-    if (s.act == ACT_TANH) return plan_blocks >= 3072 && slices >= 5 ? TILED_PAIR : blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
+    // Poolers: the few-row forms at any size.  PAIR would be faster from 3072 blocks on (21 problems of 272 rows x 768 x 1536 32 us, 2x1 44) but adds K up in
+    // one run instead of four quarters: error against float64 2.2e-7 instead of 1.1e-7 there, 2.4e-7 and 1.2e-7 for 24 of 128 rows x 1024 x 2048.
+    if (s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
     if (!tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
     const long most_rows = !k2_ok || pn > 32 ? 3072 : s.K < 2048 ? 2047 : plan > 1 || pm >= 64 ? 1152 : 3072;
@@ -917,7 +914,6 @@ hipError_t launch_gemm_tiled(const TiledGroup& g, const TiledShape& s, hipStream
         return hipErrorInvalidValue;
     // byte offsets inside the weights, and inside the 8 row panels of a tile, are 31-bit
     if ((uint64_t)s.lda * 64 * 8 >= (1ull << 31) || (uint64_t)s.N / 32 * s.ldw * 64 >= (1ull << 31)) return hipErrorInvalidValue;
-    if (form >= TILED_K2 && s.act == ACT_TANH) return hipErrorInvalidValue;
     if (form == TILED_AUTO) form = choose_form(s);
     // the tile forms: a tile's loads reach at most into the next tile, so it has at least as many slices as the ring holds ahead
     const int kw = form == TILED_K2 ? 2 : 1, slices = s.K / (64 * kw) / s.splits;

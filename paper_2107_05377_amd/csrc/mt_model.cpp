@@ -1866,9 +1866,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         L.begin(MT_K_POOL);
         if (m->tiled) {
             L.check(launch_split_first_rows_tiled(sg, n_split, HB, H, hrm.seq_start, HB * S, L.st));
-            TiledShape s{n, HB, H, 2 * H, 2 * H, 2 * H, H, ACT_TANH, 1, nullptr, 1, 0};
-            s.plan = h_route ? 0 : std::min((int)std::count_if(m->tasks.begin(), m->tasks.end(), [](const mt_task_desc& d) { return d.head == MT_HEAD_SEQUENCE; }), kMaxGroup);
-            L.check(launch_gemm_tiled(tg, s, L.st));
+            L.check(launch_gemm_tiled(tg, TiledShape{n, HB, H, 2 * H, 2 * H, 2 * H, H, ACT_TANH, 1, nullptr, 1, 0}, L.st));
             L.check(launch_classifier_tiled(cg, n, HB, H, maxC, m->C_tot, out_row, L.st));
             L.end();
             continue;

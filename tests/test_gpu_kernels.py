@@ -309,6 +309,22 @@ def test_panel_linear_forms(form, height, problems, M, rows, N, K, act, f32, spl
     assert torch.isnan(pc[:, untouched:]).all()
 
 
+# Poolers add K up in four quarters at any size (of the forms that take tanh): the same bits as one block per workgroup, on both sides of that form's line and
+# far beyond it, K of both model widths.
+@pytest.mark.parametrize("problems,M,N,K", [(3, 384, 1024, 2048), (4, 300, 1024, 2048), (21, 272, 768, 1536), (24, 128, 1024, 2048), (32, 33, 768, 1536)])
+def test_panel_linear_poolers_sum_in_one_order(problems, M, N, K):
+    print(f"panel linear, poolers: {problems} x {M} x {N} x {K}", flush=True)
+    rng = np.random.default_rng(problems + M)
+    pa = torch.stack([panels(rng.standard_normal((M, K)).astype(np.float32)) for _ in range(problems)])
+    pw = torch.stack([panels(rng.standard_normal((N, K)).astype(np.float32) / K**0.5) for _ in range(problems)])
+    bias = dev(rng.standard_normal((problems, N)).astype(np.float32))
+    size = lambda t: t[0].numel() * t.element_size()
+    auto, one = (mt.op_panel_linear(pa, pw, bias, torch.stack([nan_panels(M, N, torch.float32) for _ in range(problems)]), M=M, N=N, K=K, problems=problems, stride_A=size(pa),
+                                    stride_W=size(pw), stride_bias=size(bias), stride_C=pa.shape[1] * 32 * N * 4, act_kind=3, out_f32=1, form=form) for form in (0, ROWS_1X1))
+    for i in range(problems):
+        assert np.array_equal(rows_of(auto[i])[:M], rows_of(one[i])[:M]), i
+
+
 # the values' columns, stored transposed for the attention: the same numbers at other places
 @pytest.mark.parametrize("form,height,M,K", [(ROWS_1X1, 0, 40, 64), (ROWS_2X1, 0, 70, 832), (ROWS_2X2, 0, 97, 128), (K2, 3, 97, 640), (PAIR, 4, 160, 384), (PAIR, 1, 33, 320), (TALL, 5, 200, 384)])
 def test_panel_linear_transposed_columns(form, height, M, K):
