@@ -6,9 +6,9 @@
 //                         32 floats = 128 bytes per row: buffer loads to LDS of 16-byte chunks, chunk c of row r in slot c ^ (r & 7).  A
 //                         lane reads 4 consecutive k of its row at once; since the order of k is free as long as both operands agree, MFMA i
 //                         of a step takes k = i from the lower and k = 4 + i from the upper half wavefront.
-//   gemm_f32_rows_kernel  short K (of up to 7 slices, too few for four rings): operands straight from global memory to registers, each of the 4
-//                         wavefronts a quarter of K.  (It did all launches of up to 32 rows, whose weights it reads 32 bytes of a row at a time: 8 problems
-//                         of 8 rows x 768 / 3072 x 768, x 768 x 3072 13, 34, 31 us, the tile kernel 8, 19, 21; one of 20 rows 12, 17, 31 and 8, 9, 18.)
+//   gemm_f32_short_kernel short K (of 2, 4 or 6 slices, too few for four rings): all or most slices of a workgroup's operands in LDS at once.  Operands
+//                         straight from global memory to registers instead, 32 bytes of a row at a time: 2048 rows x 4 K columns, 8 problems,
+//                         K = 64 / 128 / 192 21, 51, 99 us, here 12, 31, 55.
 //   gemm_f32_any_kernel   any M, N, K and strides.
 // The matrix cores' float32 rate is 256 FLOP per clock and compute unit: a 32x32x2 instruction takes 64 clocks.  What the tile kernel has to do is to
 // keep them coming.
@@ -265,53 +265,98 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tile_kernel(GemmGroup g, Gemm
     gemm_f32_tile_body(g, s, lds);
 }
 
-// 32 rows x 32 columns per workgroup, a quarter of K per wavefront, operands straight into registers.
-__global__ __launch_bounds__(256) void gemm_f32_rows_kernel(GemmGroup g, GemmShape s)
+// K = 32 Q, Q = 2, 4 or 6: WM x WN wavefronts of 32 x 32 outputs, each with WK that share its K, slices of 32 k through a shared LDS ring.  Quarters of K are
+// summed apart and added up in their order however many wavefronts they belong to: the same bits in every form.
+template <int Q, int WM, int WN, int WK>
+__global__ __launch_bounds__(256, 2) void gemm_f32_short_kernel(GemmGroup g, GemmShape s)
 {
-    __shared__ __attribute__((aligned(16))) float part[3 * 16 * 64];
-    constexpr int U = 12;                               // steps of 8 k in flight
+    constexpr int BM = 32 * WM, BN = 32 * WN, SUB = BM + BN, STAGE = SUB * WK * 128;     // 128-byte rows: BM of A, BN of W, of every share
+    constexpr int KT = Q / WK, STAGES = KT * STAGE <= 65536 ? KT : 65536 / STAGE;
+    constexpr int LPS = SUB * WK / 32, QUARTERS = 4 / WK, PART = QUARTERS * 16 * 64;     // loads of a wavefront and slice; floats of its partial sums
+    static_assert(WM * WN * WK == 4 && Q % WK == 0 && WM * WN * (WK - 1) * PART * 4 <= STAGES * STAGE, "four wavefronts, whole slices");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * STAGE];
     const int grp = blockIdx.z;
     const int N = g.N[grp];
     const int M = s.d_M ? min(s.M, *s.d_M) : s.M;
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     if (n0 >= N || m0 >= M) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int k_len = s.K / 4;
-    const float* __restrict__ a = static_cast<const float*>(g.A[grp]) + (size_t)min(m0 + l32, M - 1) * s.lda + wave * k_len + half * 4;
-    const float* __restrict__ w = static_cast<const float*>(g.W[grp]) + (size_t)min(n0 + l32, N - 1) * (s.ldw ? s.ldw : s.K) + wave * k_len + half * 4;
-    f32x16 acc;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5, wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
+    const size_t lda = s.lda, ldw = s.ldw ? s.ldw : s.K;
+    // load i of a slice: 32 rows, 8 per wavefront, chunk c of row r in slot c ^ (r & 7); rows beyond the last one repeat it
+    const int r8 = wave * 8 + (lane >> 3), off = ((lane & 7) ^ (lane >> 3)) * 4;
+    const float* src[LPS];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int steps = k_len / 8;
-    for (int st = 0; st < steps; st += U) {
-        f32x4 af[U], wf[U];
-        const int nb = steps - st;                      // uniform over the workgroup
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (u < nb) {
-                af[u] = *reinterpret_cast<const f32x4*>(a + (st + u) * 8);
-                wf[u] = *reinterpret_cast<const f32x4*>(w + (st + u) * 8);
-            }
-        __builtin_amdgcn_sched_barrier(0);              // all loads of the batch are in flight before the first product
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (u < nb) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][i], af[u][i], acc, 0, 0, 0);
-            }
+    for (int i = 0; i < LPS; ++i) {
+        const int share = i * 32 / SUB, r = i * 32 % SUB, k0 = share * (KT * 32) + off;
+        src[i] = r < BM ? static_cast<const float*>(g.A[grp]) + min(m0 + r + r8, M - 1) * lda + k0 : static_cast<const float*>(g.W[grp]) + min(n0 + r - BM + r8, N - 1) * ldw + k0;
     }
-    if (wave > 0) {
+    auto issue = [&](int kt) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part[((wave - 1) * 16 + e) * 64 + lane] = acc[e];
+        for (int i = 0; i < LPS; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + kt * 32), (lptr_t)(lds + (kt % STAGES) * STAGE + (i * 4 + wave) * 1024), 16, 0, 0);
+    };
+#pragma unroll
+    for (int kt = 0; kt < STAGES; ++kt) issue(kt);
+    const int a_row = wk * SUB + wm * 32 + l32, w_row = wk * SUB + BM + wn * 32 + l32;
+    f32x16 acc[QUARTERS];
+    auto slice = [&](auto ktc) {
+        constexpr int kt = decltype(ktc)::value;
+        if constexpr (kt < KT) {
+            // it has landed when at most the slices issued after it are outstanding; the fragments of the slice before are in registers
+            constexpr int issued = kt < 2 || STAGES == KT ? STAGES : (KT < STAGES + kt - 1 ? KT : STAGES + kt - 1);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPS * (issued - kt - 1)) : "memory");
+            __builtin_amdgcn_s_barrier();                   // ... for every wavefront
+            asm volatile("" ::: "memory");
+            if constexpr (kt > 0 && kt - 1 + STAGES < KT) issue(kt - 1 + STAGES);
+            const unsigned char* sb = lds + (kt % STAGES) * STAGE;
+            f32x4 af[4], wf[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                af[c] = *reinterpret_cast<const f32x4*>(sb + a_row * 128 + (((c * 2 + half) ^ (a_row & 7)) << 4));
+                wf[c] = *reinterpret_cast<const f32x4*>(sb + w_row * 128 + (((c * 2 + half) ^ (w_row & 7)) << 4));
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                constexpr int step0 = kt * 4;               // steps of 8 k, Q to a quarter
+                f32x16& q = acc[(step0 + c) / Q];
+                if ((step0 + c) % Q == 0) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) q[e] = 0.f;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[c][i], af[c][i], q, 0, 0, 0);
+            }
+        }
+    };
+    slice(std::integral_constant<int, 0>{});
+    slice(std::integral_constant<int, 1>{});
+    slice(std::integral_constant<int, 2>{});
+    slice(std::integral_constant<int, 3>{});
+    slice(std::integral_constant<int, 4>{});
+    slice(std::integral_constant<int, 5>{});
+    if constexpr (WK > 1) {
+        float* part = reinterpret_cast<float*>(lds) + (wm * WN + wn) * (WK - 1) * PART + lane;
+        __syncthreads();
+        if (wk > 0) {
+#pragma unroll
+            for (int q = 0; q < QUARTERS; ++q)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) part[(wk - 1) * PART + (q * 16 + e) * 64] = acc[q][e];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int q = 1; q < QUARTERS; ++q) acc[0] += acc[q];
+#pragma unroll
+        for (int q = 0; q < (WK - 1) * QUARTERS; ++q)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[0][e] += part[(q * 16 + e) * 64];
+    } else {
+#pragma unroll
+        for (int q = 1; q < QUARTERS; ++q) acc[0] += acc[q];
     }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int v = 0; v < 3; ++v)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] += part[(v * 16 + e) * 64 + lane];
-    store_block_f32(acc, m0 + l32, n0 + half * 4, M, N, g.bias[grp], g.residual[grp], s.ldr, static_cast<float*>(g.C[grp]), s.ldc, s.act);
+    store_block_f32(acc[0], m0 + wm * 32 + l32, n0 + wn * 32 + half * 4, M, N, g.bias[grp], g.residual[grp], s.ldr, static_cast<float*>(g.C[grp]), s.ldc, s.act);
 }
 
 // Any M, N, K, strides: 64x64 outputs per workgroup, 4x4 per thread, K staged through LDS in slices of 16, loads outside the
@@ -383,17 +428,26 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
                   (uint64_t)s.lda * 128 < (1ull << 31) && (uint64_t)(s.ldw ? s.ldw : s.K) * 128 < (1ull << 31);
     for (int i = 0; chunks && i < s.G; ++i)
         chunks = g.N[i] % 4 == 0 && (((uintptr_t)g.A[i] | (uintptr_t)g.W[i] | (uintptr_t)g.C[i] | (uintptr_t)g.bias[i] | (uintptr_t)g.residual[i]) & 15) == 0;
-    // each wavefront's quarter has as many slices as the ring; fewer: the short-K kernel, whose blocks are rows of the grid
-    const bool rows = s.K < 4 * 32 * kRing;
-    if (!chunks || (rows && (s.M + 31) / 32 > 65535)) {
+    if (!chunks) {
         dim3 grid((s.N + TN - 1) / TN, (s.M + TM - 1) / TM, s.G), block(256);
         hipLaunchKernelGGL(gemm_f32_any_kernel, grid, block, 0, stream, g, s);
         return hipGetLastError();
     }
-    if (rows) {
-        dim3 grid((s.N + 31) / 32, (s.M + 31) / 32, s.G), block(256);
-        hipLaunchKernelGGL(gemm_f32_rows_kernel, grid, block, 0, stream, g, s);
-        return hipGetLastError();
+    // Each wavefront's quarter has as many slices as the ring of the tile kernel; fewer: the short-K forms.  Up to 512 blocks (two for each compute unit; K = 192:
+    // 1536) a launch is a chain of latencies, which K dealt out to wavefronts shortens (3 problems of 128 rows x 4 K columns, K = 128 / 192 4.8, 5.5 us, 64 x
+    // 64 outputs 5.8, 7.0; 8 problems of 200 rows x 576 x 192 9.6 and 10.9).  Beyond, 64 x 64 outputs read the operands half as often (8 problems of 2048
+    // rows, K = 64 / 128 / 192 12, 31, 55 us, with K dealt out 14, 40, 62).
+    if (s.K < 4 * 32 * kRing) {
+        const bool few = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32) <= (s.K == 192 ? 1536 : 512);
+        auto launch = [&](auto kernel, int bm, int bn) {
+            hipLaunchKernelGGL(kernel, dim3((s.N + bn - 1) / bn, (s.M + bm - 1) / bm, s.G), dim3(256), 0, stream, g, s);
+            return hipGetLastError();
+        };
+        switch (s.K) {
+            case 64: return few ? launch(gemm_f32_short_kernel<2, 1, 2, 2>, 32, 64) : launch(gemm_f32_short_kernel<2, 2, 2, 1>, 64, 64);
+            case 128: return few ? launch(gemm_f32_short_kernel<4, 1, 1, 4>, 32, 32) : launch(gemm_f32_short_kernel<4, 2, 2, 1>, 64, 64);
+            default: return few ? launch(gemm_f32_short_kernel<6, 1, 2, 2>, 32, 64) : launch(gemm_f32_short_kernel<6, 2, 2, 1>, 64, 64);
+        }
     }
     static std::atomic<uint64_t> lds_raised{0};
     hipError_t e = ensure_dynamic_lds((const void*)gemm_f32_tile_kernel, kTileLds, lds_raised);

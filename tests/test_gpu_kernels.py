@@ -40,6 +40,34 @@ def test_gemm_f32_tiles(M, N, K, act):
     assert np.abs(out - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
 
 
+# Short K: few blocks have K dealt out to wavefronts, many have not (the line is 512 blocks of 32 x 32, K = 192: 1536).  Quarters are added up in one order, so rows of a large launch
+# are the bits of a small one; remainders of rows and columns on both sides.
+@pytest.mark.parametrize("K", [64, 128, 192])
+@pytest.mark.parametrize("G,M,N,act", [(1, 1, 4, 0), (1, 33, 36, 1), (2, 300, 804, 0), (1, 993, 516, 1), (8, 130, 420, 2), (3, 650, 804, 0)])
+def test_gemm_f32_short_k(K, G, M, N, act):
+    print(f"gemm_f32, short K, {G} x {M} x {N} x {K} act {act}", flush=True)
+    from scipy.special import erf
+    rng = np.random.default_rng(G + M + N + K)
+    A, W = rng.standard_normal((G, M, K)).astype(np.float32), rng.standard_normal((G, N, K)).astype(np.float32)
+    b, r = rng.standard_normal((G, N)).astype(np.float32), rng.standard_normal((G, M, N)).astype(np.float32)
+    out = torch.full((G * M + 1, N), 7.0, dtype=torch.float32, device="cuda")
+    mt.op_linear_batched(mt.MT_FP32_CHECK, dev(A), dev(W), dev(b), residual=dev(r), act=act, out=out[:G * M].view(G, M, N))
+    got = out.cpu().numpy()
+    assert (got[G * M:] == 7.0).all()
+    got = got[:G * M].reshape(G, M, N)
+    few = min(M, 40)                                     # at most 512 blocks of each problem
+    for i in range(G):
+        one = mt.op_linear(mt.MT_FP32_CHECK, dev(A[i, -few:]), dev(W[i]), dev(b[i]), residual=dev(r[i, -few:]), act=act)
+        assert np.array_equal(got[i, -few:], one.cpu().numpy()), i
+    x = A.astype(np.float64) @ W.astype(np.float64).transpose(0, 2, 1) + b[:, None]
+    # as below; GELU: slope below 1.13, 1e-6 for erff and tanhf
+    bound = (K / 4 + 8) * 2.0**-24 * (np.abs(A) @ np.abs(W).transpose(0, 2, 1) + np.abs(b[:, None]))
+    if act:
+        x = x * 0.5 * (1 + (erf(x / 2**0.5) if act == 1 else np.tanh((2 / np.pi)**0.5 * (x + 0.044715 * x**3))))
+        bound = 1.13 * bound + 1e-6 * (1 + np.abs(x))
+    assert (np.abs(got - (x + r)) <= bound + 2.0**-23 * np.abs(r)).all()
+
+
 # the block list of the float32 tile kernel: one block and several per workgroup (more than two per compute unit of 256), remainders of rows, columns and of the
 # four K shares (equal and not), as few slices as the ring has and more, one problem and several
 @pytest.mark.parametrize("G,M,N,K", [(1, 33, 36, 256), (1, 64, 96, 320), (3, 97, 100, 448), (1, 3, 36, 256), (8, 20, 100, 416), (1, 1500, 1028, 256), (8, 130, 516, 320), (2, 700, 800, 768), (5, 40, 64, 3072)])
