@@ -118,8 +118,9 @@ struct TCfg {
     static constexpr int LDS = S * STAGE + XCHG;
     // loads younger than the activation slice that must have landed at a slice's barrier, on every path (see below)
     static constexpr int STEPS = F8 ? 2 : 4;                            // matrix steps of a slice
-    // A tall tile has one wavefront per SIMD: its loads go one by one between the matrix instructions (slice_spread).
-    static constexpr bool SPREAD = TMI >= 5;
+    // A tall tile has one wavefront per SIMD: from 7 panels on its loads go one by one between the matrix instructions (slice_spread has the figures).
+    static constexpr bool SPREAD = TMI >= 7;
+    static_assert(!SPREAD || (!F8 && KW == 1), "slice_spread loads bfloat16 weights in four steps");
     static constexpr int WAIT = (S - 2) * AL + 8 - 8 / STEPS + 8 * (NB < S - 2 ? NB : S - 2) - (SPREAD && NB >= S - 2 ? 8 - 8 / STEPS : 0);
     // activation fragments of two steps, or (where the registers of two workgroups do not hold two) each reloaded behind its last use
     static constexpr bool IN_PLACE = F8 && KW == 1 && TMI == 4;
@@ -351,9 +352,10 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         ++kt;
     };
     // The same with the loads spread: a wavefront whose load waits for the load path issues no matrix instruction either, and a tall tile's compute unit
-    // has no other.  18.6 k rows x 768 x 3072 78.5 -> 75.8 us, 8 problems of 20 k rows x 1024 x 4096 1130 -> 1070.  (Where two workgroups share a compute
-    // unit, and with K halved between wavefronts, it was level to 14 % slower.)  A step has its share of the activation slice (the last one none) and the
-    // weight registers that the step before has used.
+    // has no other.  18.6 k rows x 768 x 3072 78.5 -> 75.8 us (7 panels), 8 problems of 20 k rows x 1024 x 4096 1130 -> 1070.  Passes of 1 to 8 problems of 1 to 19 k
+    // rows: tiles of 7 and 8 panels 0.94 to 0.99 of the time, of 5 and 6, with fewer matrix instructions to hide behind, 0.97 to 1.06.  (Where two
+    // workgroups share a compute unit, and with K halved between wavefronts, it was level to 14 % slower.)  A step has its share of the activation slice (the
+    // last one none) and the weight registers that the step before has used.
     [[maybe_unused]] auto slice_spread = [&](auto bufc) {
         constexpr int buf = decltype(bufc)::value;
         const int ka = kt + S - 1, kw = kt + NB, kp = kw - 1;
