@@ -871,12 +871,14 @@ int choose_form(const TiledShape& s)
         // rows x 768 x 3072.)
         return slices < 5 || blocks <= (s.G > 1 ? 1536 : s.K < 1024 ? 3072 : 2304) ? TILED_ROWS_1X1 : TILED_PAIR;
     }
-    // Contexts (parts of 64 columns): one block per workgroup reads its rows twice.  8 problems of 12 heads x 768, 32 / 64 / 128 / 256 rows, 192 to 1536 blocks:
-    // 1x1 5.4, 7.5, 13.3, 18.2 us, 2x1 5.5, 6.0, 11.1, 18.8, 2x2 6.3, 7.0, 8.1, 15.9; 11 problems, 272 rows 25.9, 26.7, 22.9.
-    if (s.n_sub > 1) return blocks <= 288 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
+    // Contexts (parts of 64 columns): one block per workgroup reads its rows twice.  Two by two pays where K is long and there are workgroups enough.  12 heads x
+    // 768, 8 problems of 64 / 96 / 128 / 256 rows, 384 to 1536 blocks: 1x1 5.9, 10.7, 13.1, 17.9 us, 2x1 4.6, 9.3, 10.8, 18.6, 2x2 5.1, 6.1, 6.6, 15.5; but 1 of
+    // 512 rows, 384 blocks, 4.4, 4.4, 5.1 and 2 of 200, 336, 4.3, 4.8, 5.1.  8 heads x 512, 4 of 256 rows, 512 blocks, 3.8, 3.8, 4.4, 11 of 512, 2816, 18.5,
+    // 18.9, 20.4.
+    if (s.n_sub > 1 && s.K >= 768 && blocks > 400) return TILED_ROWS_2X2;
     // Poolers: the few-row forms at any size.  PAIR would be faster from 3072 blocks on (21 problems of 272 rows x 768 x 1536 32 us, 2x1 44) but adds K up in
     // one run instead of four quarters: error against float64 2.2e-7 instead of 1.1e-7 there, 2.4e-7 and 1.2e-7 for 24 of 128 rows x 1024 x 2048.
-    if (s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
+    if (s.n_sub > 1 || s.act == ACT_TANH) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X1;
     const bool k2_ok = s.K % (128 * s.splits) == 0 && slices / 2 >= 5, tile_ok = slices >= 5;
     if (!tile_ok) return blocks <= 1152 ? TILED_ROWS_1X1 : TILED_ROWS_2X2;
     const long most_rows = !k2_ok || pn > 32 ? 3072 : s.K < 2048 ? 2047 : plan > 1 || pm >= 64 ? 1152 : 3072;

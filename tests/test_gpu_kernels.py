@@ -365,7 +365,7 @@ def test_panel_linear_transposed_columns(form, height, M, K):
     assert np.array_equal(rows_of(moved), transposed_columns(rows_of(plain), first))
 
 
-@pytest.mark.parametrize("heads,B", [(3, 37), (12, 200)])               # one block per workgroup, and two by two
+@pytest.mark.parametrize("heads,B", [(3, 37), (12, 200), (12, 257), (8, 1200)])               # one block per workgroup, two by two, two by one
 def test_panel_linear_parts(heads, B):
     """Problems of equal parts with operands of their own, as the contexts of the heads, over 2 problems."""
     print(f"panel linear, parts: {heads} heads, {B} rows", flush=True)
