@@ -456,9 +456,13 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
     return (size_t)(p - p0);
 }
 
-// Calls of up to so many positions read weights ahead (AheadQueue): beyond, contractions wait for other things than their weights (BERT-large 8 x 100 tokens
-// 1599 -> 1615 us with it).
+// Calls of up to so many positions read weights ahead (AheadQueue): beyond, contractions wait for other things than their weights (gain at 64 to 512 positions 1 to 3
+// %, at 640 to 1024 0.2 to 1.5 %; 13 x 128 tokens 847 -> 856 us with it, BERT-large 6 x 200 1736 -> 1753).
 constexpr int kAheadRows = 512;
+// ... and of more bytes of layers than that: fewer stay in the last-level cache (256 MB) from call to call, and reading them ahead only lengthens the launches that
+// do it.  BERT-base, 8 layers and 1 to 8 tasks of 2, 1 x 20 tokens, 142, 170, 198, 227, 255, 283, 311, 340 MB: without 254, 262, 268, 278, 302, 323, 332, 343 us, with
+// 256, 266, 271, 280, 297, 317, 324, 331; 4 x 128 without 407, 413, 423, 445, 455, 477, 487, 499, with 412, 418, 427, 446, 455, 474, 484, 495.
+constexpr size_t kAheadBytesFrom = 240000000;
 
 size_t layer_floats(size_t H, size_t F) { return 4 * (H * H + H) + 2 * H + (F * H + F) + (H * F + H) + 2 * H; }
 
@@ -1735,8 +1739,10 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
     // (routed: the trunk has its launches to itself, and a group of tasks goes by its own number)
     const bool planned = !h_route;
     AheadQueue queue;
-    if (m->tiled && !m->fp8_attn && trunk && B * S <= kAheadRows) {
-        const size_t HH = (size_t)H * H * 2, HF = (size_t)H * m->cfg.ffn * 2;
+    const size_t HH = (size_t)H * H * 2, HF = (size_t)H * m->cfg.ffn * 2;
+    size_t layers = depth;
+    for (int t : enabled) layers += m->tasks[t].n_layers;
+    if (m->tiled && !m->fp8_attn && trunk && B * S <= kAheadRows && layers * (4 * HH + 2 * HF) > kAheadBytesFrom) {
         auto add = [&](size_t at, size_t bytes) { queue.piece.push_back({units(at), (uint32_t)bytes}); };
         queue.base = m->d_w;
         for (int step = 0; step < n_steps; ++step) {
