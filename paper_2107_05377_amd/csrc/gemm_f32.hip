@@ -6,7 +6,7 @@
 //                         32 floats = 128 bytes per row: buffer loads to LDS of 16-byte chunks, chunk c of row r in slot c ^ (r & 7).  A
 //                         lane reads 4 consecutive k of its row at once; since the order of k is free as long as both operands agree, MFMA i
 //                         of a step takes k = i from the lower and k = 4 + i from the upper half wavefront.
-//   gemm_f32_short_kernel short K (of 2, 4 or 6 slices, too few for four rings): all or most slices of a workgroup's operands in LDS at once.  Operands
+//   gemm_f32_short_kernel short K (of 2, 4 or 6 slices, too few for four rings; of 8 and 10 in large launches): all or most slices of a workgroup's operands in LDS at once.  Operands
 //                         straight from global memory to registers instead, 32 bytes of a row at a time: 2048 rows x 4 K columns, 8 problems,
 //                         K = 64 / 128 / 192 21, 51, 99 us, here 12, 31, 55.
 //   gemm_f32_any_kernel   any M, N, K and strides.
@@ -80,9 +80,11 @@ __device__ __forceinline__ void gemm_f32_tile_body(const GemmGroup& g, const Gem
     const uint32_t lda_b = (uint32_t)s.lda * 4, ldw_b = (uint32_t)(s.ldw ? s.ldw : s.K) * 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    // this wavefront's slices of 32 k: a quarter of them, the first wavefronts one more where four do not divide them
-    const int slices = s.K >> 5, KT = (slices >> 2) + (wave < (slices & 3) ? 1 : 0);
-    const int k0 = ((slices >> 2) * wave + min(wave, slices & 3)) * 128;
+    // this wavefront's slices of 32 k: a quarter of them, the first quarters one more where four do not divide them.  Of the two workgroups of a compute unit one
+    // has the longer quarters on its first two SIMDs and the other on its last two (8 problems of 1200 rows x 1728 x 576 198 -> 189 us).
+    const int share = (wave + (blockIdx.x >= gridDim.x / 2 ? 2 : 0)) & 3;
+    const int slices = s.K >> 5, KT = (slices >> 2) + (share < (slices & 3) ? 1 : 0);
+    const int k0 = ((slices >> 2) * share + min(share, slices & 3)) * 128;
 
     struct Ref {
         __amdgpu_buffer_rsrc_t A, W;                   // from the block's first row on; rows beyond the last one read as zero
@@ -142,7 +144,7 @@ __device__ __forceinline__ void gemm_f32_tile_body(const GemmGroup& g, const Gem
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<f32x4*>(part + ((wave * 4 + q) * 64 + lane) * 4) = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+            *reinterpret_cast<f32x4*>(part + ((share * 4 + q) * 64 + lane) * 4) = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
     };
     auto gather = [&]() {                                                // columns 8 wave .. + 7 of the block, added in a fixed order
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -265,7 +267,17 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tile_kernel(GemmGroup g, Gemm
     gemm_f32_tile_body(g, s, lds);
 }
 
-// K = 32 Q, Q = 2, 4 or 6: WM x WN wavefronts of 32 x 32 outputs, each with WK that share its K, slices of 32 k through a shared LDS ring.  Quarters of K are
+// The quarter of K = 32 Q that a step of 8 k belongs to: Q steps each, from 8 slices on whole slices, the first ones one more where four do not divide them (the
+// shares of gemm_f32_tile_kernel).
+template <int Q>
+constexpr int quarter_of(int step)
+{
+    if (Q < 8) return step / Q;
+    const int slice = step >> 2, longer = (Q / 4 + 1) * (Q % 4);
+    return slice < longer ? slice / (Q / 4 + 1) : Q % 4 + (slice - longer) / (Q / 4);
+}
+
+// K = 32 Q, Q = 2, 4, .. 10: WM x WN wavefronts of 32 x 32 outputs, each with WK that share its K, slices of 32 k through a shared LDS ring.  Quarters of K are
 // summed apart and added up in their order however many wavefronts they belong to: the same bits in every form.
 template <int Q, int WM, int WN, int WK>
 __global__ __launch_bounds__(256, 2) void gemm_f32_short_kernel(GemmGroup g, GemmShape s)
@@ -318,9 +330,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_short_kernel(GemmGroup g, Gem
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                constexpr int step0 = kt * 4;               // steps of 8 k, Q to a quarter
-                f32x16& q = acc[(step0 + c) / Q];
-                if ((step0 + c) % Q == 0) {
+                f32x16& q = acc[quarter_of<Q>(kt * 4 + c)];
+                if (kt + c == 0 || quarter_of<Q>(kt * 4 + c) != quarter_of<Q>(kt * 4 + c - 1)) {
 #pragma unroll
                     for (int e = 0; e < 16; ++e) q[e] = 0.f;
                 }
@@ -335,6 +346,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_short_kernel(GemmGroup g, Gem
     slice(std::integral_constant<int, 3>{});
     slice(std::integral_constant<int, 4>{});
     slice(std::integral_constant<int, 5>{});
+    slice(std::integral_constant<int, 6>{});
+    slice(std::integral_constant<int, 7>{});
+    slice(std::integral_constant<int, 8>{});
+    slice(std::integral_constant<int, 9>{});
+    static_assert(KT <= 10, "slices");
     if constexpr (WK > 1) {
         float* part = reinterpret_cast<float*>(lds) + (wm * WN + wn) * (WK - 1) * PART + lane;
         __syncthreads();
@@ -436,9 +452,12 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
     // Each wavefront's quarter has as many slices as the ring of the tile kernel; fewer: the short-K forms.  Up to 512 blocks (two for each compute unit; K = 192:
     // 1536) a launch is a chain of latencies, which K dealt out to wavefronts shortens (3 problems of 128 rows x 4 K columns, K = 128 / 192 4.8, 5.5 us, 64 x
     // 64 outputs 5.8, 7.0; 8 problems of 200 rows x 576 x 192 9.6 and 10.9).  Beyond, 64 x 64 outputs read the operands half as often (8 problems of 2048
-    // rows, K = 64 / 128 / 192 12, 31, 55 us, with K dealt out 14, 40, 62).
-    if (s.K < 4 * 32 * kRing) {
-        const bool few = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32) <= (s.K == 192 ? 1536 : 512);
+    // rows, K = 64 / 128 / 192 12, 31, 55 us, with K dealt out 14, 40, 62).  So they do in large launches of the shortest K of the tile kernel, whose blocks are
+    // mostly fill, exchange and uneven quarters there (8 problems of 2300 rows x 1024 x 256 / 1280 x 320 94, 141 us, the tile kernel 104, 161; of 750 rows x 768 x
+    // 256, 4608 blocks, 30 both).
+    const long blocks = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32);
+    if (s.K < 4 * 32 * kRing || (s.K <= 320 && blocks > 4700 && (s.M + 63) / 64 <= 65535)) {
+        const bool few = blocks <= (s.K == 192 ? 1536 : 512);
         auto launch = [&](auto kernel, int bm, int bn) {
             hipLaunchKernelGGL(kernel, dim3((s.N + bn - 1) / bn, (s.M + bm - 1) / bm, s.G), dim3(256), 0, stream, g, s);
             return hipGetLastError();
@@ -446,14 +465,15 @@ hipError_t launch_gemm_f32(const GemmGroup& g, const GemmShape& s, hipStream_t s
         switch (s.K) {
             case 64: return few ? launch(gemm_f32_short_kernel<2, 1, 2, 2>, 32, 64) : launch(gemm_f32_short_kernel<2, 2, 2, 1>, 64, 64);
             case 128: return few ? launch(gemm_f32_short_kernel<4, 1, 1, 4>, 32, 32) : launch(gemm_f32_short_kernel<4, 2, 2, 1>, 64, 64);
-            default: return few ? launch(gemm_f32_short_kernel<6, 1, 2, 2>, 32, 64) : launch(gemm_f32_short_kernel<6, 2, 2, 1>, 64, 64);
+            case 192: return few ? launch(gemm_f32_short_kernel<6, 1, 2, 2>, 32, 64) : launch(gemm_f32_short_kernel<6, 2, 2, 1>, 64, 64);
+            case 256: return launch(gemm_f32_short_kernel<8, 2, 2, 1>, 64, 64);
+            default: return launch(gemm_f32_short_kernel<10, 2, 2, 1>, 64, 64);
         }
     }
     static std::atomic<uint64_t> lds_raised{0};
     hipError_t e = ensure_dynamic_lds((const void*)gemm_f32_tile_kernel, kTileLds, lds_raised);
     if (e != hipSuccess) return e;
-    const long tiles = (long)s.G * ((s.M + 31) / 32) * ((s.N + 31) / 32);
-    hipLaunchKernelGGL(gemm_f32_tile_kernel, dim3((unsigned)std::min(tiles, 2l * device_cu_count())), dim3(256), kTileLds, stream, g, s);
+    hipLaunchKernelGGL(gemm_f32_tile_kernel, dim3((unsigned)std::min(blocks, 2l * device_cu_count())), dim3(256), kTileLds, stream, g, s);
     return hipGetLastError();
 }
 

@@ -42,9 +42,9 @@ def test_gemm_f32_tiles(M, N, K, act):
 
 # Short K: few blocks have K dealt out to wavefronts, many have not (the line is 512 blocks of 32 x 32, K = 192: 1536).  Quarters are added up in one order, so rows of a large launch
 # are the bits of a small one; remainders of rows and columns on both sides.
-@pytest.mark.parametrize("K", [64, 128, 192])
-@pytest.mark.parametrize("G,M,N,act", [(1, 1, 4, 0), (1, 33, 36, 1), (2, 300, 804, 0), (1, 993, 516, 1), (8, 130, 420, 2), (3, 650, 804, 0)])
-def test_gemm_f32_short_k(K, G, M, N, act):
+@pytest.mark.parametrize("G,M,N,K,act", [(g, m, n, k, a) for k in (64, 128, 192) for g, m, n, a in ((1, 1, 4, 0), (1, 33, 36, 1), (2, 300, 804, 0), (1, 993, 516, 1), (8, 130, 420, 2), (3, 650, 804, 0))] +
+                         [(8, 650, 900, 256, 1), (8, 650, 900, 320, 2)])      # K that takes this kernel beyond 4700 blocks only
+def test_gemm_f32_short_k(G, M, N, K, act):
     print(f"gemm_f32, short K, {G} x {M} x {N} x {K} act {act}", flush=True)
     from scipy.special import erf
     rng = np.random.default_rng(G + M + N + K)
@@ -60,8 +60,8 @@ def test_gemm_f32_short_k(K, G, M, N, act):
         one = mt.op_linear(mt.MT_FP32_CHECK, dev(A[i, -few:]), dev(W[i]), dev(b[i]), residual=dev(r[i, -few:]), act=act)
         assert np.array_equal(got[i, -few:], one.cpu().numpy()), i
     x = A.astype(np.float64) @ W.astype(np.float64).transpose(0, 2, 1) + b[:, None]
-    # as below; GELU: slope below 1.13, 1e-6 for erff and tanhf
-    bound = (K / 4 + 8) * 2.0**-24 * (np.abs(A) @ np.abs(W).transpose(0, 2, 1) + np.abs(b[:, None]))
+    # a quarter of K one after another, the four, the bias; GELU: slope below 1.13, 1e-6 for erff and tanhf
+    bound = ((K + 128) / 4 + 8) * 2.0**-24 * (np.abs(A) @ np.abs(W).transpose(0, 2, 1) + np.abs(b[:, None]))      # (a quarter is whole slices)
     if act:
         x = x * 0.5 * (1 + (erf(x / 2**0.5) if act == 1 else np.tanh((2 / np.pi)**0.5 * (x + 0.044715 * x**3))))
         bound = 1.13 * bound + 1e-6 * (1 + np.abs(x))
