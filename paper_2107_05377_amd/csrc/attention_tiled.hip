@@ -17,7 +17,7 @@
 // Bound by memory when the batch is large: 18.6 k rows of 12 heads are 114 MB in 29 us (staging keys and values in LDS 32, on 7
 // sequences of up to 509 tokens 23.5 instead of 10.1, on 128 of up to 256 with 16 heads 79 instead of 43), by the chain of its loads
 // when it is small (one sequence: 4.1 us, 6.3).  Loads run one block ahead: a block's keys are fetched after the scores of the one before, its values after the product, and
-// no wait is for what the next block needs (before: for all of it at every product; 32 x 128 tokens 9.4 -> 8.8 us a layer, 7 x 509 a pass 0.5 %).  The four
+// in large launches (DEEP) no wait is for what the next block needs (instead of for all of it at every product; 32 x 128 tokens 9.4 -> 8.8 us a layer).  The four
 // wavefronts of a workgroup take neighbouring query panels of a head, so that keys and values come from the first-level cache for
 // three of them; where that gives too few wavefronts (long sequences of a small batch), KS of them share a query panel and take
 // every KS-th key panel each, merged through LDS.
@@ -50,7 +50,7 @@ __device__ __forceinline__ u32x4 pack_chunks(const float (&v)[8])
 // nq: workgroups per (sequence, head).  pairs == 0: one each, grid (heads, sequences, problems).  Otherwise a flat grid in which an XCD
 // owns a contiguous range of (problem, head, sequence, workgroup), so that its second-level cache holds a sequence's keys and values,
 // and the panels that sequences share, once.
-template <int KS>
+template <int KS, bool DEEP>
 __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attention_tiled_kernel(const unsigned char* base_qkv, unsigned char* base_ctx,
                                                               const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len, int B, int S,
                                                               int A, int nq_nw, int pairs, int G, AttnTiledGroup g, ReadAhead ahead)
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
     const int p0 = row0 >> 5, p1 = (end + 31) >> 5;                          // panels of the sequence
     const int H = A * 64;
     const size_t pitch = (size_t)H * 192;                                    // bytes of a panel of projections
-    const unsigned char* qkv = base_qkv + (size_t)g.qkv[grp] * 256 + a * 4096;
+    const unsigned char* qkv = base_qkv + (size_t)g.qkv[grp] * 256 + a * 4096 + (DEEP ? 0 : lane * 16);
 
     for (int pb = p0 + qg * QW; pb < p1; pb += nq * QW) {
         const int qp = pb + qi;
@@ -94,38 +94,44 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
         const bool q_real = (unsigned)(qp * 32 + l32 - row0) < (unsigned)n;
         if (active && p0 + ks < p1) {
             bf16x8 qf[4], kf[4], vf[2][2];
-            // Behind the last block (not real) the loads are issued but read nothing: after a conditional fetch the compiler waits for everything under way
-            // before a block's values are used, the next block's keys included.
+            // After a conditional fetch the compiler waits for everything under way before a block's values are used, the next block's keys included.  DEEP: behind
+            // the last block (not real) the loads are issued too, but read nothing, and no wait is for what only the next block needs.
+            auto load = [&](bf16x8& to, const unsigned char* from, int at, bool real) {
+                if constexpr (DEEP)
+                    to = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(from), 0, real ? 4096 : 0, 0x00020000), lane * 16 + at, 0, 0));
+                else to = *reinterpret_cast<const bf16x8*>(from + at);
+            };
             auto load_k = [&](int kb, bool real) {
-                const auto kp = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(qkv + (size_t)kb * pitch + (size_t)H * 64), 0, real ? 4096 : 0, 0x00020000);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) kf[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kp, lane * 16 + kk * 1024, 0, 0));
+                for (int kk = 0; kk < 4; ++kk) load(kf[kk], qkv + (size_t)kb * pitch + (size_t)H * 64, kk * 1024, real);
             };
             auto load_v = [&](int kb, bool real) {
-                const auto vp = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(qkv + (size_t)kb * pitch + (size_t)H * 128), 0, real ? 4096 : 0, 0x00020000);
 #pragma unroll
                 for (int mf = 0; mf < 2; ++mf)
 #pragma unroll
-                    for (int dt = 0; dt < 2; ++dt)
-                        vf[mf][dt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vp, lane * 16 + dt * 2048 + mf * 1024, 0, 0));
+                    for (int dt = 0; dt < 2; ++dt) load(vf[mf][dt], qkv + (size_t)kb * pitch + (size_t)H * 128, dt * 2048 + mf * 1024, real);
             };
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qp * pitch + lane * 16 + kk * 1024);
+            for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)qp * pitch + (DEEP ? lane * 16 : 0) + kk * 1024);
             int kb = p0 + ks;
             load_k(kb, true);
             load_v(kb, true);
-            bool more;
-            do {
+            for (;;) {
                 f32x16 sc;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sc, 0, 0, 0);
                 const int kn = kb + KS;
-                more = kn < p1;
-                __builtin_amdgcn_sched_barrier(0);                           // (into the registers that the scores have used)
-                load_k(kn, more);
-                __builtin_amdgcn_sched_barrier(0);
+                const bool more = kn < p1;
+                if constexpr (DEEP) {
+                    __builtin_amdgcn_sched_barrier(0);                       // (into the registers that the scores have used)
+                    load_k(kn, more);
+                    __builtin_amdgcn_sched_barrier(0);
+                } else if (more) {
+                    load_k(kn, true);
+                }
                 if (kb * 32 < row0 || kb * 32 + 32 > end) {                  // a panel shared with a neighbour
                     const int r0 = kb * 32 + half * 4 - row0;
 #pragma unroll
@@ -170,10 +176,14 @@ __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attentio
 #pragma unroll
                     for (int dt = 0; dt < 2; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mf][dt], pf, o[dt], 0, 0, 0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (DEEP) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_v(kn, more);
+                }
+                if (!more) break;
                 kb = kn;
-                load_v(kb, more);
-            } while (more);
+                if constexpr (!DEEP) load_v(kb, true);
+            }
             l_run = lane_pair_sum<32>(l_run);
         }
         unsigned char* ctx = base_ctx + (size_t)g.ctx[grp] * 256 + (size_t)qp * H * 64 + a * 4096 + lane * 16;
@@ -261,8 +271,12 @@ hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t*
     const int pairs = flat ? groups : 0, nq_nw = nq | nw << 16;
     const unsigned char* q = static_cast<const unsigned char*>(g.base_qkv);
     unsigned char* c = static_cast<unsigned char*>(g.base_ctx);
-    if (ks == 2) hipLaunchKernelGGL(attention_tiled_kernel<2>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
-    else hipLaunchKernelGGL(attention_tiled_kernel<1>, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
+    // DEEP costs a block of loads that read nothing, and gains where wavefronts are many and loop: 32 / 64 / 256 x 128 tokens of 12 heads 8.2, 11.8, 29.3 us with 2 to 3 %
+    // less, 64 and 128 x 256, 16 x 512 3 to 7 %; 1 x 20 to 512, 4 x 100, 3 x 300, 32 x 40, 272 x 20, 512 x 32 1 to 4 % more, 7 x 509 level (16 heads 8.4 and
+    // 9.9).
+    const bool deep = S > 50 && (long)B * S >= 4096;
+    auto kfn = ks == 2 ? (deep ? attention_tiled_kernel<2, true> : attention_tiled_kernel<2, false>) : (deep ? attention_tiled_kernel<1, true> : attention_tiled_kernel<1, false>);
+    hipLaunchKernelGGL(kfn, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
     return hipGetLastError();
 }
 

@@ -406,6 +406,7 @@ def test_panel_linear_refuses(bad):
 @pytest.mark.parametrize("heads,lens,seq,late", [
     (1, [1, 2, 31, 32, 33], 33, False), (3, [64, 65, 63, 96], 96, True), (2, [128, 127, 97, 3], 128, True), (16, [128] + [97, 128, 66] * 21, 128, True),
     (2, [200, 161, 5], 200, True), (5, [289, 288, 257, 4], 289, True), (1, [512, 509, 1], 512, False), (16, [289, 270, 33] * 4, 289, True), (2, [70, 64], 40, False),
+    (2, [289, 1, 257, 33, 64] * 3, 289, True), (3, [51, 32, 1, 50, 33] * 17, 51, True), (3, [50, 32, 1, 49, 33] * 17, 50, False),      # many sequences: one wavefront a query panel and two, on both sides of the rule
 ])
 def test_attention_panels(heads, lens, seq, late):
     print(f"attention: {heads} heads, {len(lens)} sequences of up to {max(lens)}, bound {seq}, late {late}", flush=True)
