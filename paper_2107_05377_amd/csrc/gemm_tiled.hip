@@ -107,7 +107,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t t_rsrc(const void* base, uint3
 
 // Ring depth and weight prefetch distance by tile height: as deep as two (KW = 1, TMI <= 4: 80 KB of LDS and 256 registers each)
 // or one workgroup per compute unit allow, and within the 63 loads that a wait can count.
-template <int TMI, int KW, bool F8>
+template <int TMI, int KW, bool F8, bool SPREAD_ = (TMI >= 7)>
 struct TCfg {
     static constexpr int WN = 4 / KW;                                   // wavefronts along N
     static constexpr int AL = KW * TMI;                                 // activation loads per wavefront and slice
@@ -118,8 +118,7 @@ struct TCfg {
     static constexpr int LDS = S * STAGE + XCHG;
     // loads younger than the activation slice that must have landed at a slice's barrier, on every path (see below)
     static constexpr int STEPS = F8 ? 2 : 4;                            // matrix steps of a slice
-    // A tall tile has one wavefront per SIMD: from 7 panels on its loads go one by one between the matrix instructions (slice_spread has the figures).
-    static constexpr bool SPREAD = TMI >= 7;
+    static constexpr bool SPREAD = SPREAD_;                             // loads one by one between the matrix instructions (slice_spread)
     static_assert(!SPREAD || (!F8 && KW == 1), "slice_spread loads bfloat16 weights in four steps");
     static constexpr int WAIT = (S - 2) * AL + 8 - 8 / STEPS + 8 * (NB < S - 2 ? NB : S - 2) - (SPREAD && NB >= S - 2 ? 8 - 8 / STEPS : 0);
     // activation fragments of two steps, or (where the registers of two workgroups do not hold two) each reloaded behind its last use
@@ -127,10 +126,10 @@ struct TCfg {
     static_assert(WAIT <= 63 && LDS <= 160 * 1024, "ring");
 };
 
-template <int TMI, int KW, int OUT, int ACT, bool F8>
+template <int TMI, int KW, int OUT, int ACT, bool F8, bool SPREAD = (TMI >= 7)>
 __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const TiledShape& s, unsigned char* lds, int panels_m)
 {
-    using Cfg = TCfg<TMI, KW, F8>;
+    using Cfg = TCfg<TMI, KW, F8, SPREAD>;
     static_assert(!F8 || KW == 1, "");
     constexpr int S = Cfg::S, NB = Cfg::NB, WN = Cfg::WN, AL = Cfg::AL, STAGE = Cfg::STAGE, STEPS = Cfg::STEPS, STEP_BYTES = 4096 / STEPS;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -352,10 +351,9 @@ __device__ __forceinline__ void gemm_tiled_body(const TiledGroup& g, const Tiled
         ++kt;
     };
     // The same with the loads spread: a wavefront whose load waits for the load path issues no matrix instruction either, and a tall tile's compute unit
-    // has no other.  18.6 k rows x 768 x 3072 78.5 -> 75.8 us (7 panels), 8 problems of 20 k rows x 1024 x 4096 1130 -> 1070.  Passes of 1 to 8 problems of 1 to 19 k
-    // rows: tiles of 7 and 8 panels 0.94 to 0.99 of the time, of 5 and 6, with fewer matrix instructions to hide behind, 0.97 to 1.06.  (Where two
-    // workgroups share a compute unit, and with K halved between wavefronts, it was level to 14 % slower.)  A step has its share of the activation slice (the
-    // last one none) and the weight registers that the step before has used.
+    // has no other.  18.6 k rows x 768 x 3072 78.5 -> 75.8 us (7 panels), 20.5 k x 1024 x 4096 159 -> 154 (5), 8 problems of 20 k 1130 -> 1070 (7).  (Where
+    // two workgroups share a compute unit, and with K halved between wavefronts, it was level to 14 % slower.)  A step has its share of the activation slice
+    // (the last one none) and the weight registers that the step before has used.
     [[maybe_unused]] auto slice_spread = [&](auto bufc) {
         constexpr int buf = decltype(bufc)::value;
         const int ka = kt + S - 1, kw = kt + NB, kp = kw - 1;
@@ -520,11 +518,21 @@ __global__ __launch_bounds__(256, (MAXT <= 4 && KW == 1) ? 2 : 1) void gemm_tile
     const int slices = s.K / (64 * KW) / s.splits;
     const int per_row = ((s.N >> 5) + 8 / KW - 1) / (8 / KW) * s.G * s.splits;
     if constexpr (MAXT == 8) {
+        // Tall tiles spread their loads.  With 5 and 6 panels there are fewer matrix instructions to hide them behind: one and two problems 0.97 to 1.00 of the
+        // time (4.9 and 5.7 k rows x 1024 x 4096, 2 problems, 74.9, 84.1 -> 72.8, 82.2 us), four 0.99 to 1.06 (140.8 -> 145.4; 5.7 k x 768 x 3072 106.7 ->
+        // 113.5), eight 0.97 to 1.02.
+        const bool spread = s.G <= 2;
         switch (force ? force : pick_height<5, 8, F8>(panels_m, per_row, n_cu, slices)) {
             case 8: gemm_tiled_body<8, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
             case 7: gemm_tiled_body<7, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
-            case 6: gemm_tiled_body<6, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
-            default: gemm_tiled_body<5, KW, OUT, ACT, F8>(g, s, lds, panels_m); break;
+            case 6:
+                if (spread) gemm_tiled_body<6, KW, OUT, ACT, F8, true>(g, s, lds, panels_m);
+                else gemm_tiled_body<6, KW, OUT, ACT, F8>(g, s, lds, panels_m);
+                break;
+            default:
+                if (spread) gemm_tiled_body<5, KW, OUT, ACT, F8, true>(g, s, lds, panels_m);
+                else gemm_tiled_body<5, KW, OUT, ACT, F8>(g, s, lds, panels_m);
+                break;
         }
     } else {
         switch (force ? force : pick_height<1, MAXT, F8>(panels_m, per_row, n_cu, slices)) {
