@@ -490,7 +490,7 @@ def main():
     flops, main_flops, gemm_ms, gemm_ms_raw, gemm_launches = gemm_summary(spec, B, rows, prof, dur, kernels, args.steps, peak)
     gemm_tflops = main_flops / (gemm_ms * 1e-3) / 1e12
     kname = ("gemm_tiled_kernel" if rows * sv.R > 256 else "gemm_tiled_rows_kernel") if bf16 else \
-        ("gemm_f32_mfma_kernel" if rows * sv.R > 32 else "gemm_f32_rows_kernel")
+        ("gemm_f32_tile_kernel" if spec.hidden >= 256 else "gemm_f32_short_kernel")
     traffic = stored_traffic(spec.name, sv.R) if (bf16 and B == spec.batch and rows * sv.R > 256) else None
     measured_peak = mt.mfma_peak() if bf16 else None
     # per LAUNCH: a launch serves the rows of all request batches of its call

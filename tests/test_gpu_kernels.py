@@ -22,8 +22,8 @@ def dev(x, dtype=None):
     return t if dtype is None else t.to(dtype)
 
 
-# one row, full and one-over row blocks of the few-row kernel, of each tile of the matrix-core kernel (fewer K slices than ring stages, odd numbers of
-# them, and more), on both sides of the rule's lines
+# one row, full and one-over row blocks, remainders of columns; K of the short-K kernel's forms and, from 256 on, of the block list, with as many slices as its
+# rings hold and more, equal quarters and not
 @pytest.mark.parametrize("M,N,K", [(1, 4, 64), (32, 100, 192), (33, 68, 64), (65, 64, 128), (31, 32, 832), (2113, 2052, 64), (70, 100, 128), (161, 228, 640),
                                    (385, 1056, 128), (700, 1000, 192)])
 @pytest.mark.parametrize("act", [0, 1])
@@ -70,19 +70,30 @@ def test_gemm_f32_short_k(G, M, N, K, act):
 
 # the block list of the float32 tile kernel: one block and several per workgroup (more than two per compute unit of 256), remainders of rows, columns and of the
 # four K shares (equal and not), as few slices as the ring has and more, one problem and several
-@pytest.mark.parametrize("G,M,N,K", [(1, 33, 36, 256), (1, 64, 96, 320), (3, 97, 100, 448), (1, 3, 36, 256), (8, 20, 100, 416), (1, 1500, 1028, 256), (8, 130, 516, 320), (2, 700, 800, 768), (5, 40, 64, 3072)])
-def test_gemm_f32_block_list(G, M, N, K):
-    print(f"gemm_f32, {G} x {M} x {N} x {K}", flush=True)
+@pytest.mark.parametrize("G,M,N,K,act", [(1, 33, 36, 256, 0), (1, 64, 96, 320, 0), (3, 97, 100, 448, 0), (1, 3, 36, 256, 0), (8, 20, 100, 416, 0), (1, 1500, 1028, 256, 0), (8, 130, 516, 320, 0),
+                                         (2, 700, 800, 768, 0), (5, 40, 64, 3072, 0), (1, 40, 64, 448, 3), (1, 1500, 1028, 256, 1), (8, 130, 516, 320, 2), (2, 700, 800, 768, 3)])
+def test_gemm_f32_block_list(G, M, N, K, act):
+    """With an activation also a residual: both wait, with the block's sums, for the second slice of the next block or, of a workgroup's last block, for the end."""
+    print(f"gemm_f32, {G} x {M} x {N} x {K} act {act}", flush=True)
+    from scipy.special import erf
     rng = np.random.default_rng(G + M + N + K)
     A, W = rng.standard_normal((G, M, K)).astype(np.float32), rng.standard_normal((G, N, K)).astype(np.float32)
     b = rng.standard_normal((G, N)).astype(np.float32)
+    r = rng.standard_normal((G, M, N)).astype(np.float32) if act else np.zeros((G, M, N), np.float32)
     out = torch.full((G * M + 1, N), 7.0, dtype=torch.float32, device="cuda")
-    mt.op_linear_batched(mt.MT_FP32_CHECK, dev(A), dev(W), dev(b), out=out[:G * M].view(G, M, N))
-    ref = A.astype(np.float64) @ W.astype(np.float64).transpose(0, 2, 1) + b[:, None]
+    mt.op_linear_batched(mt.MT_FP32_CHECK, dev(A), dev(W), dev(b), residual=dev(r) if act else None, act=act, out=out[:G * M].view(G, M, N))
+    x = A.astype(np.float64) @ W.astype(np.float64).transpose(0, 2, 1) + b[:, None]
     # a quarter of K one after another, the four shares, the bias: each addition rounds at most by 2^-24 of the sum of magnitudes
     bound = (K / 4 + 8) * 2.0**-24 * (np.abs(A) @ np.abs(W).transpose(0, 2, 1) + np.abs(b[:, None]))
+    if act in (1, 2):                                    # slope below 1.13, 1e-6 for erff and tanhf
+        x = x * 0.5 * (1 + (erf(x / 2**0.5) if act == 1 else np.tanh((2 / np.pi)**0.5 * (x + 0.044715 * x**3))))
+        bound = 1.13 * bound + 1e-6 * (1 + np.abs(x))
+    elif act == 3:                                       # slope 1, 2^-21 for tanhf
+        x, bound = np.tanh(x), bound + 2.0**-21
+    if act:
+        bound = bound + 2.0**-23 * np.abs(r)             # the last addition, of the residual
     got = out.cpu().numpy()
-    assert (np.abs(got[:G * M].reshape(G, M, N) - ref) <= bound).all()
+    assert (np.abs(got[:G * M].reshape(G, M, N) - (x + r)) <= bound).all()
     assert (got[G * M:] == 7.0).all()                    # nothing beyond the last row
 
 
@@ -300,7 +311,7 @@ ROWS_1X1, ROWS_2X1, ROWS_2X2, K2, PAIR, TALL = 1, 2, 3, 4, 5, 6
     (PAIR, 1, 2, 65, 33, 288, 320, 2, 0, 1), (PAIR, 2, 1, 97, 97, 544, 448, 0, 1, 1), (PAIR, 3, 2, 200, 193, 96, 320, 1, 0, 1), (PAIR, 4, 1, 290, 257, 288, 384, 0, 0, 1),
     (PAIR, 4, 1, 130, 130, 288, 1536, 0, 1, 4), (PAIR, 1, 10, 1024, 1001, 512, 320, 1, 0, 1),
     (TALL, 5, 1, 170, 161, 288, 384, 0, 1, 1), (TALL, 6, 2, 390, 353, 96, 512, 0, 0, 1), (TALL, 7, 1, 230, 225, 288, 384, 0, 1, 1), (TALL, 8, 1, 300, 257, 544, 640, 0, 0, 1),
-    (TALL, 5, 8, 1312, 1300, 1024, 384, 0, 1, 1),
+    (TALL, 5, 8, 1312, 1300, 1024, 384, 0, 1, 1), (TALL, 5, 3, 170, 161, 288, 384, 0, 1, 1), (TALL, 6, 3, 390, 353, 96, 640, 0, 1, 1), (TALL, 6, 1, 200, 190, 544, 384, 0, 0, 1),
     (0, 0, 3, 512, 290, 768, 3072, 0, 1, 1), (0, 0, 3, 384, 290, 768, 3072, 0, 1, 1), (0, 0, 2, 1376, 700, 768, 768, 0, 1, 1), (0, 0, 1, 2016, 1100, 768, 3072, 0, 1, 1),
     (0, 0, 12, 270, 257, 1024, 448, 3, 1, 1), (0, 0, 12, 288, 33, 1024, 256, 3, 1, 1), (0, 0, 1, 300, 171, 768, 768, 0, 0, 1), (0, 0, 8, 300, 171, 768, 768, 0, 1, 1), (0, 0, 1, 2080, 1900, 2304, 768, 1, 0, 1),
 ])

@@ -562,8 +562,8 @@ def test_bf16_logits_do_not_depend_on_the_enabled_tasks_when_they_share_the_trun
 
 @pytest.mark.parametrize("batch,seq,n_tasks", [(1, 33, 8), (1, 128, 8), (3, 50, 8), (5, 64, 8), (40, 2, 26)])
 def test_fp32_logits_of_small_calls_do_not_depend_on_the_enabled_tasks(batch, seq, n_tasks):
-    """One task alone has a fraction of the output blocks, in the layers and (more than 32 sequences) in the poolers: the number of K shares goes by
-    those of all tasks."""
+    """One task alone has a fraction of the output blocks, so other workgroups and forms of a kernel take them: K is added up in the same four quarters in all of
+    them, in the layers and in the poolers."""
     spec = ms.MTSpec("f32_masks", vocab=300, hidden=256, heads=4, ffn=512, max_pos=128, n_trunk_layers=2,
                      tasks=tuple(ms.TaskSpec(2, 2 if n_tasks == 8 else 1, 2 + t % 5) for t in range(n_tasks)), precision="fp32", batch=batch, seq=seq,
                      len_lo=max(1, seq // 2), len_hi=seq, input_seed=5)
