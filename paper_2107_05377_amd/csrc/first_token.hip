@@ -6,7 +6,7 @@
 //                        bytes of a line at a time, every head's workgroup paid for them, 19.5 us for 8 tasks x 32 sequences; of up to kInPlace
 //                        sequences that costs less than the launch), then q~, the 64 columns between them staying in LDS.  A chain of latencies: 10 us
 //                        for the first panel, 3 for each further one (a workgroup per panel, each with weights to load: 10 and 11 tasks x 272
-//                        sequences 43 + 52 us, now 25 + 33, 8 tasks x 256 35, 19).
+//                        sequences 43 + 52 us, now 23 + 32, 8 tasks x 256 35, 21).
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
 //                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
 //                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509); bound by reading the rows.
@@ -306,8 +306,9 @@ hipError_t launch_first_query(const FirstTokenGroup& g, int G, int B, int H, int
 {
     if (G <= 0 || B <= 0) return hipSuccess;
     if (G > kMaxGroup || H != A * 64 || A > kHeadsPad) return hipErrorInvalidValue;
-    // One workgroup fills a compute unit's registers: as many per (task, head) as there are compute units for (8 tasks x 256 sequences, 96 pairs, 1 to 5:
-    // 36, 26, 34, 32, 31 us; 11 tasks x 272, 132 pairs: 42, 49, 39, 48, 43).
+    // One workgroup fills a compute unit's registers: as many per (task, head) as there are compute units for.  1 to 5 of them, launches inside passes: 8 tasks x
+    // 256 sequences, 96 pairs, 31, 21, 29, 26, 26 us; 10 and 11 tasks x 272, 120 pairs 32, 23, 31, 30, 33, 132 pairs 32, 40, 31, 42, 36 (one leaves 124 compute
+    // units idle, three are two uneven rounds: the pass is level); x 104, 4 panels, 19, 15, 20, 18 and 19, 25, 21, 26.
     const int nb = (B + 31) / 32, pairs = A * G, gy = std::max(1, std::min(nb, device_cu_count() / pairs));
     const dim3 grid((pairs + 7) / 8 * 8 * gy);
 #define MT_QUERY(NS)                                                                                                                          \
