@@ -251,8 +251,9 @@ int mt_forward_tokens(mt_model* m, const int32_t* d_input_ids, const int32_t* d_
  * written to d_out_logits[b][mt_logit_offset(t)..]; all other entries are left untouched.  batch <= 1024.
  * d_token_type_ids may be NULL.  Errors as mt_forward; NULL when a wanted task has a token-level head (that needs
  * mt_forward_routed_tokens).  After this call mt_read_hidden serves trunk taps only.
- * With more than one group the groups run side by side on hip_stream and up to three streams that the model owns (default
- * priority; the first routed call creates them and their events, mt_destroy releases them): those wait for the
+ * With more than one group the groups run side by side on hip_stream and up to three more streams (default priority; one set
+ * for all models of a device, created by the first routed call and released by mt_destroy of the last model that made one; a
+ * call that is captured takes streams of the model's own): those wait for the
  * trunk on hip_stream through an event and hip_stream waits for them before the call's work counts as done, so
  * for the caller everything is still ordered on hip_stream and the call only enqueues.
  */

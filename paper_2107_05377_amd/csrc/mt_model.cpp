@@ -151,9 +151,10 @@ struct mt_model {
     bool profiling = false;
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> event_pool;
-    // per-sequence routing: groups of tasks run side by side on streams of the model's own (default priority),
-    // forked from and joined back into the caller's stream with events; created by the first routed forward
-    std::vector<hipStream_t> aux_streams;
+    // per-sequence routing: groups of tasks run side by side on streams beside the caller's (default priority), forked from and
+    // joined back into it with events; got by the first routed forward.  Of the device's (SideStreams), in calls that are captured of the model's own.
+    std::vector<hipStream_t> shared_streams, own_streams;
+    int shared_device = 0;
     std::vector<hipEvent_t> aux_join;
     hipEvent_t aux_fork = nullptr;
 
@@ -454,6 +455,68 @@ size_t stage_layer(const mt_model* m, LayerW& L, const float* p, unsigned char* 
     memcpy(at(L.ln2g), p, H * 4); p += H;
     memcpy(at(L.ln2b), p, H * 4); p += H;
     return (size_t)(p - p0);
+}
+
+// Streams beside the caller's for the groups of routed calls, one set per device for all its models, from the first routed call of the first of them to the
+// destruction of the last.  With the caller's they are as many as a process has hardware queues by default.  Where every model had three of its own, which are
+// given queues in turn, one of them shared the caller's from the third model on (models one after another, 32 x 128 tokens with three task sets: the fourth
+// and fifth took 2185, 3745 us, 2057, 3226 so; a third one's 12 x 50 tokens 874, 794).
+constexpr int kSideStreams = 3;
+
+bool create_side_streams(std::vector<hipStream_t>& to)
+{
+    for (int j = 0; j < kSideStreams; ++j) {
+        hipStream_t s = nullptr;
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {      // default priority
+            (void)hipGetLastError();
+            for (auto t : to) (void)hipStreamDestroy(t);
+            to.clear();
+            return false;
+        }
+        to.push_back(s);
+    }
+    return true;
+}
+
+struct SideStreams {
+    int device, users;
+    std::vector<hipStream_t> streams;
+};
+std::mutex side_mutex;
+std::vector<SideStreams>& side_sets()
+{
+    static auto* sets = new std::vector<SideStreams>;       // (never destroyed: no order among what runs at the process's end)
+    return *sets;
+}
+
+bool acquire_side_streams(std::vector<hipStream_t>& to, int& device)
+{
+    if (hipGetDevice(&device) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    std::lock_guard<std::mutex> lock(side_mutex);
+    for (auto& s : side_sets())
+        if (s.device == device) {
+            ++s.users;
+            to = s.streams;
+            return true;
+        }
+    if (!create_side_streams(to)) return false;
+    side_sets().push_back({device, 1, to});
+    return true;
+}
+
+void release_side_streams(int device)
+{
+    std::lock_guard<std::mutex> lock(side_mutex);
+    auto& sets = side_sets();
+    for (size_t i = 0; i < sets.size(); ++i)
+        if (sets[i].device == device && --sets[i].users == 0) {
+            for (auto t : sets[i].streams) (void)hipStreamDestroy(t);
+            sets.erase(sets.begin() + i);
+            return;
+        }
 }
 
 // Calls of up to so many positions read weights ahead (AheadQueue): beyond, contractions wait for other things than their weights (gain at 64 to 512 positions 1 to 3
@@ -1411,7 +1474,8 @@ void mt_destroy(mt_model* m)
         (void)hipEventDestroy(r.t1);
     }
     for (auto e : m->event_pool) (void)hipEventDestroy(e);
-    for (auto st : m->aux_streams) (void)hipStreamDestroy(st);
+    if (!m->shared_streams.empty()) release_side_streams(m->shared_device);
+    for (auto st : m->own_streams) (void)hipStreamDestroy(st);
     for (auto e : m->aux_join) (void)hipEventDestroy(e);
     if (m->aux_fork) (void)hipEventDestroy(m->aux_fork);
     delete m;
@@ -1600,34 +1664,30 @@ int mt_load_weights(mt_model* m, int32_t scope, const void* h_blob, size_t nbyte
 
 // The forward pass.  h_route == NULL: every enabled task (h_task_mask) runs on every sequence, branches interleaved
 // with the trunk.  h_route [batch][n_tasks]: per-sequence routing, a task runs on the sequences that ask for it.
-// Streams and events for running routed groups side by side; false (and nothing kept) if the runtime refuses.
-static bool ensure_aux_streams(mt_model* m)
+// Streams (of either kind) and events for running routed groups side by side; nullptr (and nothing kept) if the runtime refuses.
+static const std::vector<hipStream_t>* ensure_side_streams(mt_model* m, hipStream_t caller)
 {
-    constexpr int kAux = 3;              // with the caller's stream as many as a process has hardware queues by default: a fifth would share one
-    if (!m->aux_streams.empty()) return true;
-    std::vector<hipStream_t> st;
-    std::vector<hipEvent_t> ev;
-    hipEvent_t fork = nullptr;
-    bool ok = hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
-    for (int j = 0; ok && j < kAux; ++j) {
-        hipStream_t s = nullptr;
-        hipEvent_t e = nullptr;
-        ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;      // default priority
-        if (ok) st.push_back(s);
-        ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-        if (ok) ev.push_back(e);
+    if (m->aux_join.empty()) {
+        std::vector<hipEvent_t> ev(kSideStreams + 1, nullptr);
+        bool ok = true;
+        for (auto& e : ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            for (auto e : ev)
+                if (e) (void)hipEventDestroy(e);
+            return nullptr;
+        }
+        m->aux_fork = ev.back();
+        ev.pop_back();
+        m->aux_join = ev;
     }
-    if (!ok) {
+    // what joins a capture takes no one else's work, and would be refused it
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(caller, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
-        for (auto s : st) (void)hipStreamDestroy(s);
-        for (auto e : ev) (void)hipEventDestroy(e);
-        if (fork) (void)hipEventDestroy(fork);
-        return false;
+        return m->own_streams.empty() && !create_side_streams(m->own_streams) ? nullptr : &m->own_streams;
     }
-    m->aux_streams = st;
-    m->aux_join = ev;
-    m->aux_fork = fork;
-    return true;
+    return m->shared_streams.empty() && !acquire_side_streams(m->shared_streams, m->shared_device) ? nullptr : &m->shared_streams;
 }
 
 static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* d_token_type_ids, const int32_t* d_attn_mask,
@@ -1956,13 +2016,17 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
             groups.push_back(std::move(grp));
         }
         // Groups touch disjoint scratch (per task) and disjoint logits, and only read the trunk's taps and the batch's
-        // row map: with more than one group they are dealt out to the caller's stream and the model's own streams, which wait for
+        // row map: with more than one group they are dealt out to the caller's stream and the side streams, which wait for
         // the trunk through one event and are joined back into the caller's stream at the end: the costliest groups first, each to the stream
-        // with the least so far (five groups of 8 tasks x 32 sequences; round-robin over four own streams, two of which shared a hardware queue
-        // while the caller's was idle: 1557 -> 1485 us).  A group costs a chain of launches per layer, and its rows.  Per-launch timing
-        // (mt_profile_enable) keeps everything on the caller's stream.
-        const bool side = groups.size() > 1 && !m->profiling && ensure_aux_streams(m);
-        const int n_side = side ? (int)std::min(groups.size() - 1, m->aux_streams.size()) : 0;
+        // with the least so far.  (Against round-robin over four streams beside the caller's, which lay idle: five groups of 8 tasks x 32 sequences of 128 tokens 0.5 to
+        // 4 % faster by which of the four shared a hardware queue, 4 x 64 tokens 4 to 15 %, 8 tasks of 1 to 3 layers x 8 sequences 21 %; none of 25 calls slower.  Two or four calls in flight
+        // together: 32 x 128 tokens 3 to 16 % faster, 12 x 50 level, 4 x 64, whose launches take the host as long, 5 to 13 % slower.)
+        // A group costs a chain of launches per layer, and its rows.  The weight of a layer matters where few sequences ask for the deep tasks: 30, 120,
+        // 480 and 2000 are level in 27 calls but for one at 30, 3 % faster, and 0 takes 1660 instead of 1506 us (8 tasks of 1 to 6 layers x 32 sequences) or 798
+        // instead of 875 (other groups); groups all taken as equal 8 % less to 25 % more.  How long the sequences are is known on the device only.
+        // Per-launch timing (mt_profile_enable) keeps everything on the caller's stream.
+        const std::vector<hipStream_t>* side = groups.size() > 1 && !m->profiling ? ensure_side_streams(m, L.st) : nullptr;
+        const int n_side = side ? (int)std::min(groups.size() - 1, side->size()) : 0;
         auto cost = [&](const Group& g) {
             long rows = 0, depth = 0, n = 0;
             for (int b = 0; b < B; ++b) rows += h_route[(size_t)b * T + g.t0] != 0;
@@ -1976,14 +2040,14 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         if (side) std::stable_sort(groups.begin(), groups.end(), [&](const Group& a, const Group& b) { return cost(a) > cost(b); });
         if (side) {
             L.check(hipEventRecord(m->aux_fork, L.st));
-            for (int j = 0; j < n_side; ++j) L.check(hipStreamWaitEvent(m->aux_streams[j], m->aux_fork, 0));
+            for (int j = 0; j < n_side; ++j) L.check(hipStreamWaitEvent((*side)[j], m->aux_fork, 0));
         }
         for (size_t gi = 0; gi < groups.size(); ++gi) {
             const std::vector<int>& grp_tasks = groups[gi].tasks;
             const int t0 = groups[gi].t0;
             const size_t lane = std::min_element(load.begin(), load.end()) - load.begin();
             load[lane] += cost(groups[gi]);
-            Launcher LS{m, lane ? m->aux_streams[lane - 1] : L.st};
+            Launcher LS{m, lane ? (*side)[lane - 1] : L.st};
             Launcher& GL = side ? LS : L;
             RouteIdx idx;
             int nb = 0;
@@ -2061,7 +2125,7 @@ static int forward_impl(mt_model* m, const int32_t* d_input_ids, const int32_t* 
         }
         if (side) {
             for (int j = 0; j < n_side; ++j) {
-                L.check(hipEventRecord(m->aux_join[j], m->aux_streams[j]));
+                L.check(hipEventRecord(m->aux_join[j], (*side)[j]));
                 L.check(hipStreamWaitEvent(L.st, m->aux_join[j], 0));
             }
         }

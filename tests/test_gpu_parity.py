@@ -1147,6 +1147,63 @@ def test_token_heads_under_per_sequence_routing(which):
     model.close()
 
 
+def test_routed_calls_of_several_models_share_streams_and_captured_ones_do_not():
+    """Groups of routed calls run on streams that all models of a device share.  Calls of two models from two threads, a call that is captured while another
+    model's is made, and calls after the first model is gone: all equal the same call made alone, bit for bit."""
+    import threading
+    specs = [SMALL, dataclasses.replace(SMALL, weights_seed=77)]
+    models, args, want = [], [], []
+    for k, spec in enumerate(specs):
+        tr, tri, tps = _params(spec, True, 0.05)
+        models.append(_load(spec, tr, tri, tps))
+        ids, mask, _ = ms.make_inputs(spec, batch_index=k)
+        route = (np.arange(spec.n_tasks)[None, :] + np.arange(spec.batch)[:, None]) % (spec.n_tasks + 1) != 0      # every task another row set
+        args.append((dev(ids), dev(mask), route))
+        out = torch.full((spec.batch, models[k].n_logits), 9.0, device="cuda")
+        want.append(models[k].forward_routed(*args[k], out).clone())
+    assert specs[0].n_tasks > 1 and (want[0] != 9.0).any()
+
+    def call(k, times, outs, stream):
+        with torch.cuda.stream(stream):
+            for i in range(times):
+                models[k].forward_routed(*args[k], outs[i])
+
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [[torch.full_like(want[k], 9.0) for _ in range(20)] for k in (0, 1)]
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=call, args=(k, 20, outs[k], streams[k])) for k in (0, 1)]
+    for th in threads: th.start()
+    for th in threads: th.join()
+    torch.cuda.synchronize()
+    for k in (0, 1):
+        assert all(torch.equal(o, want[k]) for o in outs[k]), k
+
+    out_g, out_e = torch.full_like(want[0], 9.0), torch.full_like(want[1], 9.0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        models[0].forward_routed(*args[0], out_g)
+        th = threading.Thread(target=call, args=(1, 1, [out_e], streams[1]))      # launched, not captured
+        th.start()
+        th.join()
+        models[0].forward_routed(*args[0], out_g)
+    torch.cuda.synchronize()
+    assert torch.equal(out_e, want[1]) and (out_g == 9.0).all()
+    for rep in range(3):
+        out_g.fill_(9.0)
+        out_e.fill_(9.0)
+        graph.replay()
+        models[1].forward_routed(*args[1], out_e)
+        torch.cuda.synchronize()
+        assert torch.equal(out_g, want[0]) and torch.equal(out_e, want[1]), f"replay {rep}"
+    del graph
+    models[0].close()
+    out_e.fill_(9.0)
+    models[1].forward_routed(*args[1], out_e)
+    torch.cuda.synchronize()
+    assert torch.equal(out_e, want[1])
+    models[1].close()
+
+
 def test_mask_precondition_is_checkable():
     """Position 0 of every sequence must be real: mt_check_mask counts the sequences that break it; a sequence that
     does is served from its first real token (pinned here against the oracle run on the shifted sequence)."""
