@@ -10,7 +10,7 @@
 //   first_attend_kernel  one workgroup per (task, sequence): scores, softmax and weighted row sums in one pass over the sequence's rows, a panel
 //                        of 32 keys at a time, both products on the matrix cores (with the sums as 2 H FMAs per key and head on the vector
 //                        units 8 tasks took 190 us for 256 sequences of up to 128 tokens and 72 for 7 of up to 509); bound by reading the rows.
-//                        Four wavefronts: six of 128 columns, placed 2, 2, 1, 1 on the SIMDs, left no room for a second workgroup of theirs at 168
+//                        Four wavefronts (narrow models in large launches: one): six of 128 columns, placed 2, 2, 1, 1 on the SIMDs, left no room for a second workgroup of theirs at 168
 //                        registers (200 workgroups in flight, now 450), and a compute unit stood still while its one waited for rows or stored.
 //                        21 tasks x 272 short sequences 62 + 77 -> 41 + 52 us, 8 tasks x 256 112 -> 73, x 7 of up to 509 tokens 33 -> 26.
 // Scores and sums were two kernels that read the rows once each (85 + 107 us for 8 tasks x 256 sequences).
@@ -196,16 +196,25 @@ __global__ __launch_bounds__(NW * 64, 2) void first_attend_kernel(const int32_t*
         for (int h = 0; h < 2; ++h) {
             sc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < STEPS; ++k) sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], sc[h], 0, 0, 0);    // row: key, column: head
-            *reinterpret_cast<f32x4*>(part[buf][wave][h][lane]) = sc[h];
+            for (int k = 0; k < STEPS; ++k) {                                // row: key, column: head
+                if constexpr (NW == 1) {                                     // the shares of four wavefronts of a step each, added in their order: the same bits
+                    const f32x4 share = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    sc[h] = k ? sc[h] + share : share;
+                } else {
+                    sc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[h][k], qf[k], sc[h], 0, 0, 0);
+                }
+            }
+            if constexpr (NW > 1) *reinterpret_cast<f32x4*>(part[buf][wave][h][lane]) = sc[h];
         }
-        __syncthreads();
+        if constexpr (NW > 1) {
+            __syncthreads();
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            sc[h] = *reinterpret_cast<const f32x4*>(part[buf][0][h][lane]);
+            for (int h = 0; h < 2; ++h) {
+                sc[h] = *reinterpret_cast<const f32x4*>(part[buf][0][h][lane]);
 #pragma unroll
-            for (int w = 1; w < NW; ++w) sc[h] += *reinterpret_cast<const f32x4*>(part[buf][w][h][lane]);
-            if constexpr (NW > 4) __builtin_amdgcn_sched_barrier(0);         // (fewer of the shares in registers at a time)
+                for (int w = 1; w < NW; ++w) sc[h] += *reinterpret_cast<const f32x4*>(part[buf][w][h][lane]);
+                if constexpr (NW > 4) __builtin_amdgcn_sched_barrier(0);     // (fewer of the shares in registers at a time)
+            }
         }
         // keys 16 h + 4 l4 + e of this panel; what belongs to a neighbouring sequence counts as nothing, whatever it is
         const bool edge = kb * 32 < row0 || kb * 32 + 32 > end;
@@ -347,7 +356,12 @@ hipError_t launch_first_attend(const FirstTokenGroup& g, int G, const int32_t* s
     }                                                                                                                                         \
     break
     switch ((H + 127) / 128) {
-        case 1: MT_ATTEND(4, 1);
+        // One block of columns: four wavefronts shorten a panel's chain of latencies, one leaves room for the other sequences where there are more than
+        // two workgroups for each compute unit.  1 and 2 heads, up to 60 tokens, 272 / 512 / 600 / 900 / 2200 sequences: four 4.5, 4.9, 5.5, 6.3, 10.1 us, one
+        // 4.7, 4.8, 4.9, 4.9, 7.9.  (3 heads, 96 columns of 2 wavefronts: level at 900 to 4000.)
+        case 1:
+            if ((long)B * G > 2l * device_cu_count()) { MT_ATTEND(1, 4); }
+            MT_ATTEND(4, 1);
         case 2: MT_ATTEND(4, 2);
         case 3: MT_ATTEND(4, 3);
         case 4: MT_ATTEND(4, 4);

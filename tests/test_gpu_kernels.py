@@ -238,6 +238,30 @@ def test_first_token_panels(heads, lens, late):
     assert worst <= 1.0
 
 
+# Narrow models have one wavefront a sequence in large launches (the line is two sequences for each of 256 compute units) and four in small ones: the same bits.
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("heads,B", [(1, 513), (2, 700)])
+def test_first_token_panels_of_many_sequences(heads, B, fp8):
+    print(f"first token, {B} sequences: {heads} heads, fp8 {fp8}", flush=True)
+    H, rng = 64 * heads, np.random.default_rng(B)
+    lens = rng.integers(1, 100, B).astype(np.int32)
+    row0, rows = ragged_rows(lens, 5, rng)
+    x = np.full((rows, H), np.nan)
+    for b, n in enumerate(lens): x[row0[b]:row0[b] + n] = bf16(rng.standard_normal((n, H)))
+    px, qt = mt.to_panels(torch.from_numpy(x).cuda(), torch.bfloat16), bf16(rng.standard_normal((B, 16, H)) * 8 / H**0.5)
+    call = lambda lo, hi: mt.op_panel_first_attend(px, dev(qt[lo:hi], torch.bfloat16), dev(row0[lo:hi]), dev(lens[lo:hi]), hi - lo, 99, heads, fp8=fp8)
+    many = call(0, B)
+    assert not torch.isnan(many).any()
+    for lo, hi in ((0, 37), (200, 512), (B - 64, B)):
+        assert torch.equal(many[lo:hi], call(lo, hi)), (lo, hi)
+    for b in (0, 31, 32, B // 2, B - 1):
+        xb = x[row0[b]:row0[b] + lens[b]]
+        s = qt[b, :heads] @ xb.T / 8
+        p = np.exp(s - s.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        assert (np.abs(many[b].double().cpu().numpy() - p @ xb) <= 1.01 * 2.0**-8 * np.abs(p @ xb) + 2.0**-14 * (p @ np.abs(xb))).all(), b
+
+
 # Row sums that cancel to 2^-18 of their terms show the bits of the weights: two keys of every sequence are chosen, column by column, against the
 # sum of the others under one head's weights.  Weights of 24 bits from an exponential good to 2^-23 leave at most 2^-23 of sum p |x| (rms over the
 # columns, independent from key to key); weights of 16 bits leave 2^-22 to 2^-20.  Scores come from one column alone, exactly.
