@@ -50,14 +50,16 @@ __device__ __forceinline__ u32x4 pack_chunks(const float (&v)[8])
 // nq: workgroups per (sequence, head).  pairs == 0: one each, grid (heads, sequences, problems).  Otherwise a flat grid in which an XCD
 // owns a contiguous range of (problem, head, sequence, workgroup), so that its second-level cache holds a sequence's keys and values,
 // and the panels that sequences share, once.
-template <int KS, bool DEEP>
+template <int KS, bool DEEP, class Ahead>
 __global__ __launch_bounds__(KS == 1 ? 512 : 256, KS == 1 ? 4 : 3) void attention_tiled_kernel(const unsigned char* base_qkv, unsigned char* base_ctx,
                                                               const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len, int B, int S,
-                                                              int A, int nq_nw, int pairs, int G, AttnTiledGroup g, ReadAhead ahead)
+                                                              int A, int nq_nw, int pairs, int G, AttnTiledGroup g, Ahead ahead)
 {
-    if (!pairs && (int)blockIdx.z >= G) {
-        read_ahead(ahead, ((blockIdx.z - G) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
-        return;
+    if constexpr (Ahead::kAny) {
+        if ((int)blockIdx.z >= G) {
+            read_ahead(ahead, ((blockIdx.z - G) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+            return;
+        }
     }
     const int nq = nq_nw & 0xFFFF, QW = KS == 1 ? nq_nw >> 16 : 4 / KS;      // query panels of a workgroup at a time
     constexpr float kScale = 0.125f * 1.4426950408889634f;                   // exponents of two
@@ -275,8 +277,10 @@ hipError_t launch_attention_tiled(const AttnTiledGroup& g, int G, const int32_t*
     // less, 64 and 128 x 256, 16 x 512 3 to 7 %; 1 x 20 to 512, 4 x 100, 3 x 300, 32 x 40, 272 x 20, 512 x 32 1 to 4 % more, 7 x 509 level (16 heads 8.4 and
     // 9.9).
     const bool deep = S > 50 && (long)B * S >= 4096;
-    auto kfn = ks == 2 ? (deep ? attention_tiled_kernel<2, true> : attention_tiled_kernel<2, false>) : (deep ? attention_tiled_kernel<1, true> : attention_tiled_kernel<1, false>);
-    hipLaunchKernelGGL(kfn, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, ahead);
+    auto launch = [&](auto kfn, auto a) { hipLaunchKernelGGL(kfn, grid, block, 0, stream, q, c, seq_start, seq_len, B, S, A, nq_nw, pairs, G, g, a); };
+    if (ahead.blocks()) ks == 2 ? launch(attention_tiled_kernel<2, false, ReadAhead>, ahead) : launch(attention_tiled_kernel<1, false, ReadAhead>, ahead);
+    else if (deep) ks == 2 ? launch(attention_tiled_kernel<2, true, NoAhead>, NoAhead{}) : launch(attention_tiled_kernel<1, true, NoAhead>, NoAhead{});
+    else ks == 2 ? launch(attention_tiled_kernel<2, false, NoAhead>, NoAhead{}) : launch(attention_tiled_kernel<1, false, NoAhead>, NoAhead{});
     return hipGetLastError();
 }
 

@@ -81,6 +81,7 @@ __host__ __device__ inline size_t tiled_offset(size_t row, size_t col, size_t wi
 // four pieces (offsets from base in 256 bytes).
 constexpr uint32_t kAheadBlock = 32768;
 struct ReadAhead {
+    static constexpr bool kAny = true;
     const void* base = nullptr;
     uint32_t at[4] = {}, bytes[4] = {};
     int blocks() const
@@ -89,6 +90,11 @@ struct ReadAhead {
         for (int i = 0; i < 4; ++i) n += (int)((bytes[i] + kAheadBlock - 1) / kAheadBlock);
         return n;
     }
+};
+// Launches that read nothing ahead have kernels without it: its registers and arguments cost them (32 x 37 tokens of 8 tasks 705 -> 695 us a pass, 22 x 58 711 ->
+// 702, 13 x 58 602 -> 597).
+struct NoAhead {
+    static constexpr bool kAny = false;
 };
 // ... in the order of their use.  A launch takes kAheadBytes: two MB more or less are level, 8 MB and what contractions of few rows could carry lengthen
 // the launches by as much as the later ones gain (one request, 0 / 4 / 8 MB by each: 312, 305, 308 us; with 4 MB by each contraction as well 320).

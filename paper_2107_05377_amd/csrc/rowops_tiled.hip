@@ -232,13 +232,15 @@ __device__ __forceinline__ void layernorm_tiled_body(const float* x, const float
     finish_row<NI, SPLIT, !SPLIT, SUMS>(v[0], gamma, beta, row, wave, row < M, eps, out);
 }
 
-template <int NI, int NP>
+template <int NI, int NP, class Ahead>
 __global__ __launch_bounds__(kRowWaves * 64) void layernorm_tiled_kernel(const float* x, const float* res, const int32_t* d_M, const float* gamma,
-                                                              const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps, int groups, ReadAhead ahead)
+                                                              const float* beta, float* of, __bf16* ob, int M, int64_t part_stride, float eps, int groups, Ahead ahead)
 {
-    if ((int)blockIdx.x >= groups) {
-        read_ahead(ahead, blockIdx.x - groups);
-        return;
+    if constexpr (Ahead::kAny) {
+        if ((int)blockIdx.x >= groups) {
+            read_ahead(ahead, blockIdx.x - groups);
+            return;
+        }
     }
     layernorm_tiled_body<NI, NP, true, true, ROW_SHARES>(x, res, gamma, beta, RowOut{of, ob, nullptr, 0, false}, d_M, M, part_stride, nullptr, 0, eps);
 }
@@ -455,10 +457,14 @@ void ln_launch(const TiledLnGroup& g, const TiledLnShape& s, hipStream_t stream,
     }
     if (s.G == 1 && !s.res_row && !s.split && few && (s.want_b & 1) && !(s.want_q & 1)) {
         const ReadAhead ahead = queue ? queue->take() : ReadAhead{};
-        hipLaunchKernelGGL((layernorm_tiled_kernel<NI, NP>), dim3(grid.x + ahead.blocks()), block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
-                           (const float*)(ws + (size_t)g.res[0] * 256), s.d_M, (const float*)(wt + (size_t)g.gamma[0] * 256),
-                           (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
-                           s.M, s.part_stride, s.eps, (int)grid.x, ahead);
+        auto launch = [&](auto kfn, auto a) {
+            hipLaunchKernelGGL(kfn, dim3(grid.x + ahead.blocks()), block, 0, stream, (const float*)(ws + (size_t)g.x[0] * 256),
+                               (const float*)(ws + (size_t)g.res[0] * 256), s.d_M, (const float*)(wt + (size_t)g.gamma[0] * 256),
+                               (const float*)(wt + (size_t)g.beta[0] * 256), (float*)(ws + (size_t)g.out_f[0] * 256), (__bf16*)(ws + (size_t)g.out_b[0] * 256),
+                               s.M, s.part_stride, s.eps, (int)grid.x, a);
+        };
+        if (ahead.blocks()) launch(layernorm_tiled_kernel<NI, NP, ReadAhead>, ahead);
+        else launch(layernorm_tiled_kernel<NI, NP, NoAhead>, NoAhead{});
     } else if (few)
         hipLaunchKernelGGL((layernorm_tiled_group_kernel<NI, NP, true, true, ROW_SHARES>), grid, block, 0, stream, g, s);
     else if (split)
