@@ -1195,7 +1195,16 @@ def test_routed_calls_of_several_models_share_streams_and_captured_ones_do_not()
         models[1].forward_routed(*args[1], out_e)
         torch.cuda.synchronize()
         assert torch.equal(out_g, want[0]) and torch.equal(out_e, want[1]), f"replay {rep}"
-    del graph
+    graph_1 = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph_1):                      # the model's own streams are created inside a capture of the default mode
+        models[1].forward_routed(*args[1], out_e)
+    for rep in range(3):
+        out_e.fill_(9.0)
+        graph_1.replay()
+        models[0].forward_routed(*args[0], out_g)
+        torch.cuda.synchronize()
+        assert torch.equal(out_e, want[1]), f"replay {rep}"
+    del graph, graph_1
     models[0].close()
     out_e.fill_(9.0)
     models[1].forward_routed(*args[1], out_e)
